@@ -555,7 +555,7 @@ int env_pow2(const char* name, int dflt, int lo, int hi) {
   return dflt;
 }
 // Window length of the ring in steps.
-int ring_window_steps() { return env_pow2("ADSEQ_RING_WINDOW", 16, 2, 64); }
+int ring_window_steps() { return env_pow2("ADSEQ_RING_WINDOW", 16, 2, kMaxWindow); }
 
 // Resident step kernels (ring_resident.h): up to 32 blocks of 512 threads (up to 128 over several
 // XCDs by ADSEQ_RING_RESIDENT_BLOCKS), one or two groups of four neurons per thread, B N a
@@ -965,13 +965,22 @@ void flush_admit(adseq* h, hipStream_t st) {
 void mark(adseq* h, hipStream_t st, int kind, int count = 1);
 void close_group(adseq* h, hipStream_t st, int kind);
 
+// RING: zeroes the spike words of steps [n, n + count), count <= R.
+void clear_spike_rows(adseq* h, hipStream_t st, long long n, int count) {
+  const Dev& d = h->dev;
+  const int slot = (int)(n % d.R), head = slot + count <= d.R ? count : d.R - slot;
+  fill_u32(st, d.spike_bits + (size_t)slot * d.words, 0u, (size_t)head * d.words * 2);
+  if (count > head) fill_u32(st, d.spike_bits, 0u, (size_t)(count - head) * d.words * 2);
+}
+
 // RING: called before step k0 is popped when k0 opens a window (k0 mod W = 0): expands the
 // events of the spikes of the last d_max steps that arrive in the window (staging pass, then
 // per-part accumulation; without staging room the first pass scatters with atomics and the
 // second is skipped).  The staging pass also counts the spikes not counted yet, and their
 // events, into the device counters.
 // Expansion of the events of the spikes of steps [n_lo, n_hi) that arrive in window [k0, k0 + W) on `st`.
-void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, long long n_hi, long long count_from) {
+// clear: spike words of that many steps from k0 on to zero along the way (see k_win_acc).
+void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, long long n_hi, long long count_from, int clear = 0) {
   const Dev& d = h->dev;
   // staging mode: 0 none (atomics), 1 one store per event, 2 ordered by part in LDS first
   static const int sort_stage = env_pow2("ADSEQ_RING_SORTSTAGE", 1, 0, 1);
@@ -980,7 +989,9 @@ void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, lo
                      stage, count_from, h->res_P > 0 ? 1 : 0);
   if (d.cap > 0) {
     const int parts = d.P < kMaxParts ? d.P : kMaxParts;
-    hipLaunchKernelGGL(k_win_acc, dim3((unsigned)parts), dim3(kRingThreads), 0, st, d, k0, 0);
+    hipLaunchKernelGGL(k_win_acc, dim3((unsigned)parts), dim3(kRingThreads), 0, st, d, k0, 0, clear);
+  } else if (clear > 0) {
+    clear_spike_rows(h, st, k0, clear);
   }
 }
 
@@ -989,9 +1000,10 @@ void join_ahead(adseq* h, hipStream_t st) {
   if (h->ahead_for >= 0 && h->ev_ahead) (void)hipStreamWaitEvent(st, h->ev_ahead, 0);
 }
 
-void ring_open_window(adseq* h, hipStream_t st, long long k0) {
+// clear: see launch_expansion.  Returns whether there was a window to open.
+bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0) {
   const Dev& d = h->dev;
-  if ((k0 & (long long)(d.W - 1)) != 0 || k0 <= 0) return;
+  if ((k0 & (long long)(d.W - 1)) != 0 || k0 <= 0) return false;
   close_group(h, st, 1);
   mark(h, st, -1);
 #ifdef ADSEQ_PHASE_CLOCK
@@ -1012,7 +1024,7 @@ void ring_open_window(adseq* h, hipStream_t st, long long k0) {
     else join_ahead(h, st);
     h->ahead_for = -1;
   }
-  launch_expansion(h, st, k0, n_lo, k0, h->fold_upto);
+  launch_expansion(h, st, k0, n_lo, k0, h->fold_upto, clear);
   h->fold_upto = k0;
   if (ahead && h->aux) {
     // the next window's events from the spikes before this boundary: on the other stream, beside the steps of this window
@@ -1027,6 +1039,7 @@ void ring_open_window(adseq* h, hipStream_t st, long long k0) {
     }
   }
   mark(h, st, 0);
+  return true;
 }
 
 // Records an event that closes a launch of class `kind` (and opens the next one).
@@ -1696,21 +1709,37 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
   if (!h || !spike_ids || !spike_offsets || !n_spikes || !I_out || n_steps < 0 || I_stride < 0)
     return h ? fail(h, ADSEQ_E_INVALID_ARG, "adseq_run_open: null or negative argument") : ADSEQ_E_INVALID_ARG;
   if (h->dev.kind == ADSEQ_RING) {
-    // pop and enqueue of a step in one launch (k_open_step_win)
     const Dev& d = h->dev;
     hipStream_t st = (hipStream_t)stream;
-    for (int64_t k = 0; k < n_steps; ++k) {
+    if (n_steps > 0 && step0 != h->next_step)
+      return fail(h, ADSEQ_E_ORDER, "adseq_run_open: got step %lld, expected %lld", (long long)step0, h->next_step);
+    for (int64_t k = 0; k < n_steps;) {
       const long long step = step0 + k;
-      if (step != h->next_step)
-        return fail(h, ADSEQ_E_ORDER, "adseq_run_open: got step %lld, expected %lld", step, h->next_step);
-      ring_open_window(h, st, step);
-      if (h->bits_clear_for != step)
-        fill_u32(st, d.spike_bits + (size_t)(step % d.R) * d.words, 0u, (size_t)d.words * 2);
-      hipLaunchKernelGGL(k_open_step_win, dim3((unsigned)d.nblk), dim3(kBlock), 0, st, d, step,
-                         spike_ids + spike_offsets[k], n_spikes + k, I_out + k * I_stride);
-      h->bits_clear_for = step + 1;
-      h->next_step = step + 1;
-      h->enq_calls += 1;
+      const long long in_win = (long long)d.W - (step & (long long)(d.W - 1));
+      int cnt = (int)(n_steps - k < in_win ? n_steps - k : in_win);
+      // A stretch of three steps or more goes by two launches and one that clears its spike words (which rides on the
+      // window's expansion where there is one); a shorter one, or output rows that overlap (the later step's values
+      // stay), by a launch per step.
+      if (cnt >= 3 && (I_stride == 0 || I_stride >= d.BN)) {
+        if (!ring_open_window(h, st, step, cnt)) clear_spike_rows(h, st, step, cnt);
+        OpenOffsets o;
+        for (int j = 0; j < cnt; ++j) o.off[j] = spike_offsets[k + j];
+        const int gx = d.nblk < 16 ? 4 : (d.nblk < 256 ? d.nblk / 4 : 64);
+        hipLaunchKernelGGL(k_open_mark, dim3((unsigned)gx, (unsigned)cnt), dim3(kBlock), 0, st, d, step, spike_ids, n_spikes + k, o);
+        hipLaunchKernelGGL(k_open_pop, dim3((unsigned)d.nblk, (unsigned)cnt), dim3(kBlock), 0, st, d, step,
+                           I_out + k * I_stride, (long long)I_stride);
+        h->bits_clear_for = -1;
+      } else {
+        cnt = 1;
+        ring_open_window(h, st, step);
+        if (h->bits_clear_for != step) clear_spike_rows(h, st, step, 1);
+        hipLaunchKernelGGL(k_open_step_win, dim3((unsigned)d.nblk), dim3(kBlock), 0, st, d, step,
+                           spike_ids + spike_offsets[k], n_spikes + k, I_out + k * I_stride);
+        h->bits_clear_for = step + 1;
+      }
+      k += cnt;
+      h->next_step = step + cnt;
+      h->enq_calls += cnt;
       h->tape_ok = false;
     }
     HIP_TRY(h, hipGetLastError());

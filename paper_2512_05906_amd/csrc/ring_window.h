@@ -328,25 +328,27 @@ __global__ __launch_bounds__(kBlock) void k_deliver_win(Dev d, long long n, floa
     d.spike_bits[(size_t)(n % d.R) * d.words + (size_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)] = 0ull;
 }
 
-// Open-loop enqueue of the listed spikes at step n: one wavefront per spike sets its bit and
-// scatters its in-window events; everything else stays implicit until its window begins.
-__global__ __launch_bounds__(kBlock) void k_enqueue_win(Dev d, long long n, const int* __restrict__ spk,
-                                                        const int* __restrict__ n_spk_ptr) {
-  int nspk = *n_spk_ptr;
+// Open-loop enqueue of the listed spikes at step n: one wavefront per spike (wavefront `wave` of `nwaves`) sets its
+// bit and scatters its in-window events; everything else stays implicit until its window begins.
+__device__ __forceinline__ void open_enqueue(const Dev& d, long long n, const int* __restrict__ spk, int nspk, int wave, int nwaves) {
   nspk = nspk < 0 ? 0 : (nspk > d.BN ? d.BN : nspk);
   const int phi = (int)(n & (long long)(d.W - 1));
   int near_h = d.W - 1 - phi;
   if (near_h > d.d_max) near_h = d.d_max;
   const int lane = threadIdx.x & 63;
-  const int wave = (blockIdx.x * kBlock + threadIdx.x) >> 6, nwaves = (gridDim.x * kBlock) >> 6;
+  int* __restrict__ win = win_of(d, n);
   for (int e = wave; e < nspk; e += nwaves) {
     const int g = spk[e];
     if ((unsigned)g >= (unsigned)d.BN) continue;  // uniform over the wavefront
     const int b = trial_of(d, g), i = g - b * d.N;
     if (lane == 0) atomicOr(&d.spike_bits[(size_t)(n % d.R) * d.words + (g >> 6)], 1ull << (g & 63));
     if (near_h >= 1)
-      near_scatter(d, win_of(d, n), phi, d.row_ptr[i], d.nearcnt[(size_t)near_h * d.N + i], b * d.N);
+      near_scatter(d, win, phi, d.row_ptr[i], d.nearcnt[(size_t)near_h * d.N + i], b * d.N);
   }
+}
+__global__ __launch_bounds__(kBlock) void k_enqueue_win(Dev d, long long n, const int* __restrict__ spk,
+                                                        const int* __restrict__ n_spk_ptr) {
+  open_enqueue(d, n, spk, *n_spk_ptr, (int)(blockIdx.x * kBlock + threadIdx.x) >> 6, (int)(gridDim.x * kBlock) >> 6);
 }
 
 // Open loop, pop and enqueue of one step in ONE launch (adseq_run_open knows both): block b pops
@@ -358,8 +360,7 @@ __global__ __launch_bounds__(kBlock) void k_enqueue_win(Dev d, long long n, cons
 __global__ __launch_bounds__(kBlock) void k_open_step_win(Dev d, long long n, const int* __restrict__ spk,
                                                           const int* __restrict__ n_spk_ptr,
                                                           float* __restrict__ I_out) {
-  int nspk = *n_spk_ptr;
-  nspk = nspk < 0 ? 0 : (nspk > d.BN ? d.BN : nspk);
+  const int nspk = *n_spk_ptr;
   const int g0 = blockIdx.x * kBlock + threadIdx.x;
   const int phi = (int)(n & (long long)(d.W - 1));
   int* __restrict__ win = win_of(d, n);
@@ -374,18 +375,31 @@ __global__ __launch_bounds__(kBlock) void k_open_step_win(Dev d, long long n, co
   if (d.count_pop) count_popped(d, popped);
   if ((threadIdx.x & 63) == 0 && blockIdx.x < d.nblk)
     d.spike_bits[(size_t)((n + 1) % d.R) * d.words + (size_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)] = 0ull;
-  int near_h = d.W - 1 - phi;
-  if (near_h > d.d_max) near_h = d.d_max;
-  const int lane = threadIdx.x & 63;
-  const int wave = (blockIdx.x * kBlock + threadIdx.x) >> 6, nwaves = (gridDim.x * kBlock) >> 6;
-  for (int e = wave; e < nspk; e += nwaves) {
-    const int g = spk[e];
-    if ((unsigned)g >= (unsigned)d.BN) continue;  // uniform over the wavefront
-    const int b = trial_of(d, g), i = g - b * d.N;
-    if (lane == 0) atomicOr(&d.spike_bits[(size_t)(n % d.R) * d.words + (g >> 6)], 1ull << (g & 63));
-    if (near_h >= 1)
-      near_scatter(d, win, phi, d.row_ptr[i], d.nearcnt[(size_t)near_h * d.N + i], b * d.N);
+  open_enqueue(d, n, spk, nspk, (int)(blockIdx.x * kBlock + threadIdx.x) >> 6, (int)(gridDim.x * kBlock) >> 6);
+}
+
+// Open loop, a stretch of steps inside one window in TWO launches: nothing that is enqueued depends on what is popped,
+// so the spikes of all the steps are enqueued first (k_open_mark: a grid row per step; their in-window events go to later
+// rows of the window), then all the rows are popped (k_open_pop).  A launch per step is bound by the launch itself, not
+// by its work: 10,000 neurons x 1,000 synapses, 20 spikes per step, 5.0 us per step with a launch each, 1.5 us so.
+constexpr int kMaxWindow = 64;   // steps of the longest window
+struct OpenOffsets { long long off[kMaxWindow]; };   // first spike of every step in the caller's list
+__global__ __launch_bounds__(kBlock) void k_open_mark(Dev d, long long n0, const int* __restrict__ spk,
+                                                      const int* __restrict__ n_spk, OpenOffsets o) {
+  const int k = blockIdx.y;
+  open_enqueue(d, n0 + k, spk + o.off[k], n_spk[k], (int)(blockIdx.x * kBlock + threadIdx.x) >> 6, (int)(gridDim.x * kBlock) >> 6);
+}
+// I_stride = 0: the rows share one buffer, which the last of them keeps.
+__global__ __launch_bounds__(kBlock) void k_open_pop(Dev d, long long n0, float* __restrict__ I_out, long long I_stride) {
+  const int k = blockIdx.y, g = blockIdx.x * kBlock + threadIdx.x;
+  int popped = 0;
+  if (g < d.BN) {
+    int* cell = &win_of(d, n0)[(size_t)((int)(n0 & (long long)(d.W - 1)) + k) * d.BN + g];
+    popped = *cell;
+    if (popped != 0) *cell = 0;
+    if (I_stride != 0 || k + 1 == (int)gridDim.y) __builtin_nontemporal_store((float)popped * 0x1p-24f, &I_out[k * I_stride + g]);
   }
+  if (d.count_pop) count_popped(d, popped);
 }
 
 // ---------------------------------------------------------------- forward: window expansion
@@ -890,9 +904,16 @@ __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, l
     for (size_t x = (hi4 < hi ? hi4 : hi) + threadIdx.x; x < hi; x += kRingThreads) other[x] = 0;
   }
 }
-__global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, int p0) {
+// clear > 0: the launch also zeroes the spike words of steps k0 .. k0 + clear - 1 (at most R), which the staging pass
+// before it was the last to read as those of the steps R before (open loop: the next launch sets their bits).
+__global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, int p0, int clear) {
   __shared__ int tile[kMaxTileCells];
   XPH_SPAN(1, 0)
+  if (clear > 0) {
+    const long long first = (k0 % d.R) * d.words, all = (long long)d.R * d.words, cnt = (long long)clear * d.words;
+    for (long long x = (long long)blockIdx.x * kRingThreads + threadIdx.x; x < cnt; x += (long long)gridDim.x * kRingThreads)
+      d.spike_bits[first + x < all ? first + x : first + x - all] = 0ull;
+  }
   role_acc(d, tile, k0, p0 + (int)blockIdx.x);
   XPH_SPAN(1, 1)
 }

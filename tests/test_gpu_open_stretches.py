@@ -1,0 +1,56 @@
+"""Open-loop stretches of the ring (adseq_run_open: all the steps of a window enqueued in one launch and popped in
+another) against the oracle, bit for bit: calls cut so that stretches start and end anywhere in a window, mixed with
+single deliver / enqueue calls; output rows that are apart, that share one buffer and that overlap."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(wl, B, T, seed, rate):
+    rng = np.random.default_rng(seed)
+    forced = (rng.random((T, B * wl.n_neurons)) < rate).astype(np.uint8)
+    forced[5] = 0
+    lists = [np.flatnonzero(forced[n]).astype(np.int32) for n in range(T)]
+    return forced.reshape(T, B, wl.n_neurons), lists
+
+
+@pytest.mark.parametrize("n,fan,b,d_max,window", [(301, 40, 3, 37, 16), (1, 5, 1, 3, 16), (70000, 6, 1, 20, 16), (500, 30, 2, 70, 64), (130, 20, 1, 9, 4)])
+@pytest.mark.parametrize("stride", ["apart", "wide", "one", "overlap"])
+def test_open_stretches(n, fan, b, d_max, window, stride, monkeypatch):
+    monkeypatch.setenv("ADSEQ_RING_WINDOW", str(window))
+    T = 150
+    wl = synth.ragged_network(n, fan, d_max, seed=n + b, rate_hz=0.0, t=T, b=b, w_mean=0.01, w_std=0.02)
+    bn = b * n
+    forced, lists = _lists(wl, b, T, seed=3, rate=0.02 if n < 10000 else 0.002)
+    ref = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=b, forced_spikes=forced, keep_currents=True)
+    want = ref.Iq.reshape(T, bn).astype(np.float32) * np.float32(2.0 ** -24)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b)
+    counts = torch.tensor([len(x) for x in lists], dtype=torch.int32, device=sim.dev)
+    offs = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    ids = torch.from_numpy(np.concatenate(lists + [np.zeros(1, np.int32)])).to(sim.dev)
+    step = {"apart": bn, "wide": bn + 5, "one": 0, "overlap": max(1, bn - 1)}[stride]
+    s = 0
+    for piece in (1, 2, 3, 20, "d", 30, 64, 29):
+        if piece == "d":
+            out = torch.zeros(bn, dtype=torch.float32, device=sim.dev)
+            sim.deliver(s, out); sim.enqueue(s, ids[int(offs[s]):], counts[s:])
+            np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want[s].view(np.uint32))
+            s += 1
+            continue
+        buf = torch.zeros((piece - 1) * step + bn, dtype=torch.float32, device=sim.dev)
+        sim.run_open(s, piece, ids, offs[s:s + piece], counts[s:], buf, step)
+        exp = np.zeros((piece - 1) * step + bn, np.float32)
+        for k in range(piece):
+            exp[k * step:k * step + bn] = want[s + k]
+        np.testing.assert_array_equal(buf.cpu().numpy().view(np.uint32), exp.view(np.uint32))
+        s += piece
+    assert s == T
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    sim.close()
