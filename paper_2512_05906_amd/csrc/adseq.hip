@@ -580,15 +580,18 @@ ResidentPlan resident_plan(long long BN) {
 }
 // Resident reverse and forward kernels (ring_flow_reverse.h, ring_resident_reverse.h, ring_resident_forward.h): up
 // to 256 blocks of 512 worker threads with one, four or -- not the reverse kernel with a grid barrier -- eight
-// consecutive neurons each (at most 4,096 neurons per block), B N a multiple of 4; delta synapse only.
+// consecutive neurons each (at most 4,096 neurons per block), B N a multiple of 4 unless the blocks own one neuron per
+// thread (B N up to 131,072: 4-byte accesses need no alignment).  Synaptic current states: the forward kernel holds both,
+// the reverse kernel without a grid barrier the slow one (two adjoint windows would have to be waited for), the reverse
+// kernel with a barrier none.
 // ADSEQ_RING_RESIDENT_REVERSE = 0: never, 1 (default): whenever the layout allows; ADSEQ_RING_REVERSE_BLOCKS:
 // taking-part blocks (8 .. 256, default 128).
 ResidentPlan reverse_plan(long long BN, bool forward = false) {
   ResidentPlan r;
   // (forward: 0 never, 1 wherever the layout fits, default from 2,048 state cells on: below that one XCD's blocks, whose
-  // barrier is shorter, are faster -- 100 cells 2.4 against 2.9 us per step)
+  // barrier is shorter, are faster -- 100 cells 2.4 against 2.9 us per step --, where their 16-byte accesses fit)
   const int fwd = env_pow2("ADSEQ_RING_FORWARD_CHIP", 2, 0, 2);
-  const int on = forward ? ((fwd == 1 || (fwd == 2 && BN >= 2048)) ? 1 : 0) : env_pow2("ADSEQ_RING_RESIDENT_REVERSE", 1, 0, 1);
+  const int on = forward ? ((fwd == 1 || (fwd == 2 && (BN >= 2048 || BN % 4 != 0))) ? 1 : 0) : env_pow2("ADSEQ_RING_RESIDENT_REVERSE", 1, 0, 1);
   // (reverse: 256 blocks for the kernel without a grid barrier, 128 for the one with: its barrier costs more with more blocks)
   const int blocks = forward ? env_pow2("ADSEQ_RING_FORWARD_BLOCKS", 256, 8, 256)
                              : env_pow2("ADSEQ_RING_REVERSE_BLOCKS", env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) ? 256 : 128, 8, 256);
@@ -596,7 +599,7 @@ ResidentPlan reverse_plan(long long BN, bool forward = false) {
   chunk = (chunk + 255) / 256 * 256;
   // (the forward kernel and the reverse kernel without a grid barrier also take eight neurons per thread: a million state cells)
   const int per_thread = (forward || env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1)) ? 8 : 4;
-  if (on && chunk <= per_thread * kResThreads && BN % 4 == 0) {
+  if (on && chunk <= per_thread * kResThreads && (BN % 4 == 0 || chunk <= kResThreads)) {
     r.chunk = (int)chunk;
     r.P = (int)((BN + chunk - 1) / chunk);
     r.npt = 1;
@@ -621,16 +624,36 @@ const void* run_xcd_kernel_of(int syn, int npt) {
   if (npt == 1) return syn == 0 ? (const void*)k_run_xcd<RECORD, 0, 1> : (syn == 1 ? (const void*)k_run_xcd<RECORD, 1, 1> : (const void*)k_run_xcd<RECORD, 2, 1>);
   return syn == 0 ? (const void*)k_run_xcd<RECORD, 0, 2> : (syn == 1 ? (const void*)k_run_xcd<RECORD, 1, 2> : (const void*)k_run_xcd<RECORD, 2, 2>);
 }
-template <bool DU, int NPT>
-const void* flow_kernel_of(int surrogate) {
-  if (surrogate == ADSEQ_SURR_SUPERSPIKE) return (const void*)k_bwd_flow<DU, ADSEQ_SURR_SUPERSPIKE, NPT>;
-  if (surrogate == ADSEQ_GRAD_SPIKE_TIME) return (const void*)k_bwd_flow<DU, ADSEQ_GRAD_SPIKE_TIME, NPT>;
-  return (const void*)k_bwd_flow<DU, ADSEQ_SURR_OFF, NPT>;
+// The instances of the reverse kernel without a grid barrier and of the forward kernel over the whole chip: one neuron per
+// thread where a block owns no more neurons than it has worker threads, else four, else eight.
+typedef void (*FlowKernel)(long long, int, long long, int, int, int, int, const float*, const float*, Dev);
+template <bool DU, int SYN, int NPT>
+FlowKernel flow_kernel_of(int surrogate) {
+  if (surrogate == ADSEQ_SURR_SUPERSPIKE) return k_bwd_flow<DU, ADSEQ_SURR_SUPERSPIKE, NPT, SYN>;
+  if (surrogate == ADSEQ_GRAD_SPIKE_TIME) return k_bwd_flow<DU, ADSEQ_GRAD_SPIKE_TIME, NPT, SYN>;
+  return k_bwd_flow<DU, ADSEQ_SURR_OFF, NPT, SYN>;
 }
-const void* flow_kernel(bool du, int surrogate, int chunk) {
-  if (chunk <= kResThreads) return du ? flow_kernel_of<true, 1>(surrogate) : flow_kernel_of<false, 1>(surrogate);
-  if (chunk <= 4 * kResThreads) return du ? flow_kernel_of<true, 4>(surrogate) : flow_kernel_of<false, 4>(surrogate);
-  return du ? flow_kernel_of<true, 8>(surrogate) : flow_kernel_of<false, 8>(surrogate);
+template <bool DU, int SYN>
+FlowKernel flow_kernel_npt(int surrogate, int chunk) {
+  if (chunk <= kResThreads) return flow_kernel_of<DU, SYN, 1>(surrogate);
+  if (chunk <= 4 * kResThreads) return flow_kernel_of<DU, SYN, 4>(surrogate);
+  return flow_kernel_of<DU, SYN, 8>(surrogate);
+}
+FlowKernel flow_kernel(bool du, int syn, int surrogate, int chunk) {
+  if (syn) return du ? flow_kernel_npt<true, 1>(surrogate, chunk) : flow_kernel_npt<false, 1>(surrogate, chunk);
+  return du ? flow_kernel_npt<true, 0>(surrogate, chunk) : flow_kernel_npt<false, 0>(surrogate, chunk);
+}
+typedef void (*ChipKernel)(long long, int, unsigned, int, int, int, float, Dev);
+template <bool RECORD, int SYN>
+ChipKernel chip_kernel_of(int chunk) {
+  if (chunk <= kResThreads) return k_fwd_chip<RECORD, 1, SYN>;
+  if (chunk <= 4 * kResThreads) return k_fwd_chip<RECORD, 4, SYN>;
+  return k_fwd_chip<RECORD, 8, SYN>;
+}
+ChipKernel chip_kernel(bool record, int syn, int chunk) {
+  if (syn == 2) return record ? chip_kernel_of<true, 2>(chunk) : chip_kernel_of<false, 2>(chunk);
+  if (syn == 1) return record ? chip_kernel_of<true, 1>(chunk) : chip_kernel_of<false, 1>(chunk);
+  return record ? chip_kernel_of<true, 0>(chunk) : chip_kernel_of<false, 0>(chunk);
 }
 const void* run_xcd_kernel(bool record, int syn, int npt) {
   return record ? run_xcd_kernel_of<true>(syn, npt) : run_xcd_kernel_of<false>(syn, npt);
@@ -1162,6 +1185,7 @@ void ring_run_resident(adseq* h, hipStream_t st, long long step0, long long n_st
 // RING: steps step0 .. step0 + n_steps - 1 with one launch per window over the whole chip (ring_resident_forward.h).
 void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps) {
   const Dev& d = h->dev;
+  const int syn = d.alpha_r > 0.0f ? 2 : (d.alpha_s > 0.0f ? 1 : 0);
   long long n = step0;
   const long long end = step0 + n_steps;
   int stride = env_pow2("ADSEQ_RING_RESIDENT_STRIDE", kResStride, 1, 8);
@@ -1176,12 +1200,7 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
     const bool record = d.record && h->tape_ok && n < d.max_steps;
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
     if (d.record && n >= d.max_steps) h->tape_ok = false;
-    // (one neuron per thread where a block owns no more neurons than it has worker threads, else four)
-#define ADSEQ_FWD(REC, NPT) hipLaunchKernelGGL((k_fwd_chip<REC, NPT>), grid, block, 0, st, n, cnt, h->rev_base, h->fwd_P, h->fwd_chunk, stride, h->fwd_margin, d)
-    if (h->fwd_chunk <= kResThreads) { if (record) ADSEQ_FWD(true, 1); else ADSEQ_FWD(false, 1); }
-    else if (h->fwd_chunk <= 4 * kResThreads) { if (record) ADSEQ_FWD(true, 4); else ADSEQ_FWD(false, 4); }
-    else { if (record) ADSEQ_FWD(true, 8); else ADSEQ_FWD(false, 8); }
-#undef ADSEQ_FWD
+    hipLaunchKernelGGL(chip_kernel(record, syn, h->fwd_chunk), grid, block, 0, st, n, cnt, h->rev_base, h->fwd_P, h->fwd_chunk, stride, h->fwd_margin, d);
     h->rev_base += (unsigned)(cnt - 1) * (unsigned)h->fwd_P;
     h->grp_count += 1;   // (launches of the group)
     h->enq_calls += cnt;
@@ -1304,14 +1323,8 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
           const int buf = (int)((k0 >> d.wshift) & 1);
           if (flow_filled != buf) fill_u32(st, d.gwin + (size_t)buf * d.W * d.BN, kFlowSentinel, (size_t)d.W * d.BN);
           const int fill_other = (counts == nullptr && k0 > 0) ? 1 : 0;
-          // (one neuron per thread where a block owns no more than it has threads, else four)
-#define ADSEQ_FLOW3(DU, SURR, NPT) hipLaunchKernelGGL((k_bwd_flow<DU, SURR, NPT>), rg, dim3(kResThreads), 0, st, k1, nsteps, T, h->rev_P, h->rev_chunk, stride, fill_other, dL_dcount, dL_dU, d)
-#define ADSEQ_FLOW(DU, SURR) do { if (h->rev_chunk <= kResThreads) ADSEQ_FLOW3(DU, SURR, 1); else if (h->rev_chunk <= 4 * kResThreads) ADSEQ_FLOW3(DU, SURR, 4); else ADSEQ_FLOW3(DU, SURR, 8); } while (0)
-          if (d.surrogate == ADSEQ_SURR_SUPERSPIKE) { if (dL_dU) ADSEQ_FLOW(true, ADSEQ_SURR_SUPERSPIKE); else ADSEQ_FLOW(false, ADSEQ_SURR_SUPERSPIKE); }
-          else if (d.surrogate == ADSEQ_GRAD_SPIKE_TIME) { if (dL_dU) ADSEQ_FLOW(true, ADSEQ_GRAD_SPIKE_TIME); else ADSEQ_FLOW(false, ADSEQ_GRAD_SPIKE_TIME); }
-          else { if (dL_dU) ADSEQ_FLOW(true, ADSEQ_SURR_OFF); else ADSEQ_FLOW(false, ADSEQ_SURR_OFF); }
-#undef ADSEQ_FLOW
-#undef ADSEQ_FLOW3
+          hipLaunchKernelGGL(flow_kernel(dL_dU != nullptr, d.alpha_s > 0.0f ? 1 : 0, d.surrogate, h->rev_chunk), rg, dim3(kResThreads), 0, st, k1, nsteps, T,
+                             h->rev_P, h->rev_chunk, stride, fill_other, dL_dcount, dL_dU, d);
           flow_filled = fill_other ? 1 - buf : -1;
         } else {
         if (dL_dU) hipLaunchKernelGGL((k_bwd_xcd<true>), rg, rb, 0, st, k1, nsteps, T, h->rev_base, h->rev_P, h->rev_chunk, stride, dL_dcount, dL_dU, d);
@@ -1543,29 +1556,25 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
     ResidentPlan rp = resident_plan((long long)d.BN);
     if (rp.P > 0 && !(resident_fits(run_xcd_kernel(true, syn, rp.npt)) && resident_fits(run_xcd_kernel(false, syn, rp.npt)))) rp = ResidentPlan();
     h->res_chunk = rp.chunk; h->res_P = rp.P; h->res_npt = rp.npt;
-    if (!(d.alpha_s > 0.0f)) {
-      ResidentPlan vp = reverse_plan((long long)d.BN);
-      if (vp.P > 0 && vp.chunk <= 4 * kResThreads && !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))) vp = ResidentPlan();
-      h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
-      // the same layout without a grid barrier: the blocks wait for the cells they gather (ring_flow_reverse.h);
-      // ADSEQ_RING_REVERSE_FLOW = 0: the kernel with a barrier per step
-      h->rev_flow = vp.P > 0 && env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) &&
-                    resident_fits(flow_kernel(true, d.surrogate, vp.chunk), kResThreads) && resident_fits(flow_kernel(false, d.surrogate, vp.chunk), kResThreads);
-      if (!h->rev_flow && vp.chunk > 4 * kResThreads) { h->rev_chunk = 0; h->rev_P = 0; h->rev_npt = 0; }   // (the kernel with a barrier holds four neurons per thread)
-      // forward kernel over the whole chip with the candidates' rows requested ahead (ring_resident_forward.h): the
-      // reverse kernel's layout (ADSEQ_RING_FORWARD_BLOCKS taking-part blocks, default 256).  ADSEQ_RING_FORWARD_CHIP:
-      // see reverse_plan; ADSEQ_RING_FORWARD_MARGIN: candidate margin in thousandths of the membrane unit (default 5).
-      ResidentPlan fp = reverse_plan((long long)d.BN, true);
-      if (fp.P > 0 && !(fp.chunk <= kResThreads
-                            ? resident_fits((const void*)k_fwd_chip<true, 1>) && resident_fits((const void*)k_fwd_chip<false, 1>)
-                            : fp.chunk <= 4 * kResThreads
-                            ? resident_fits((const void*)k_fwd_chip<true, 4>) && resident_fits((const void*)k_fwd_chip<false, 4>)
-                            : resident_fits((const void*)k_fwd_chip<true, 8>) && resident_fits((const void*)k_fwd_chip<false, 8>)))
-        fp = ResidentPlan();
-      if (fp.P > 0 && !d.count_pop) {
-        h->fwd_P = fp.P; h->fwd_chunk = fp.chunk; h->res_P = 0;
-        if (const char* e = getenv("ADSEQ_RING_FORWARD_MARGIN")) { const int v = atoi(e); if (v >= 0 && v <= 100000) h->fwd_margin = (float)v * 1e-3f; }
-      }
+    ResidentPlan vp = syn < 2 ? reverse_plan((long long)d.BN) : ResidentPlan();
+    // without a grid barrier: the blocks wait for the cells they gather (ring_flow_reverse.h); ADSEQ_RING_REVERSE_FLOW = 0:
+    // the kernel with a barrier per step, which holds four neurons per thread and no synaptic state
+    h->rev_flow = vp.P > 0 && env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) &&
+                  resident_fits((const void*)flow_kernel(true, syn, d.surrogate, vp.chunk), kResThreads) &&
+                  resident_fits((const void*)flow_kernel(false, syn, d.surrogate, vp.chunk), kResThreads);
+    if (vp.P > 0 && !h->rev_flow &&
+        (syn || d.BN % 4 != 0 || vp.chunk > 4 * kResThreads || !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))))
+      vp = ResidentPlan();
+    h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
+    // forward kernel over the whole chip with the candidates' rows requested ahead (ring_resident_forward.h): the
+    // reverse kernel's layout (ADSEQ_RING_FORWARD_BLOCKS taking-part blocks, default 256).  ADSEQ_RING_FORWARD_CHIP:
+    // see reverse_plan; ADSEQ_RING_FORWARD_MARGIN: candidate margin in thousandths of the membrane unit (default 5).
+    ResidentPlan fp = reverse_plan((long long)d.BN, true);
+    if (fp.P > 0 && !(resident_fits((const void*)chip_kernel(true, syn, fp.chunk)) && resident_fits((const void*)chip_kernel(false, syn, fp.chunk))))
+      fp = ResidentPlan();
+    if (fp.P > 0 && !d.count_pop) {
+      h->fwd_P = fp.P; h->fwd_chunk = fp.chunk; h->res_P = 0;
+      if (const char* e = getenv("ADSEQ_RING_FORWARD_MARGIN")) { const int v = atoi(e); if (v >= 0 && v <= 100000) h->fwd_margin = (float)v * 1e-3f; }
     }
     // chained step launches (ring_chain.h; experimental, off by default: measured slower than a launch per step on
     // one stream): delta synapse, and two launches' blocks must fit the chip side by side (512 blocks each at

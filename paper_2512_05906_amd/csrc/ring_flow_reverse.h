@@ -1,5 +1,5 @@
 // Ring queue, reverse sweep: the steps of one window in ONE launch with NO grid barrier -- the blocks
-// wait for the very cells they gather (delta synapse).  Included by adseq.hip after
+// wait for the very cells they gather (delta synapse, or one synaptic current state).  Included by adseq.hip after
 // ring_resident_reverse.h, whose layout (P taking-part blocks, consecutive neurons per thread -- here
 // one, four or eight --, spikes listed a step ahead, the leading 64 entries of their rows requested
 // ahead) it shares.
@@ -126,6 +126,7 @@ __device__ __forceinline__ FlowVec<NPT> flow_splat(float a) {
 template <int NPT>
 struct FlowState {
   float carry[NPT], dLc[NPT];        // its neurons: carry of the adjoint, dL/dcount
+  float cj[NPT];                     // SYN: the current state's adjoint dL/dJ of the step after the one being run
   long long r0[NPT]; int rlen[NPT];  // bounds of their sorted rows
   unsigned actmask;                  // bit c: neuron c exists
   FlowVec<NPT> Ua, Ub, Uc;           // tape values of the step being run, of the one after it, of the one after that
@@ -141,7 +142,7 @@ struct FlowState {
   int g0, hi;
 };
 
-template <bool HAS_DU, int SURR, int NPT>
+template <bool HAS_DU, int SURR, int NPT, int SYN>
 __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const int PAR, RevBatch& cur, RevBatch& nxt, bool last,
                                           int* s_dead, int* s_nspk, RevSpike (*s_spk)[kRevList], float (*s_G2)[(NPT < 4 ? 4 : NPT) * kResThreads],
                                           float* fill_row, int& cnt_base0, int& cnt_base1) {
@@ -180,6 +181,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
     for (int c = 0; c < NPT; ++c) {
       float gu;
       S.carry[c] = bwd_update_as<SURR>(d, n, U[c], 0.0f, (smask >> c) & 1u, S.carry[c], S.dLc[c], Gf[c], dU[c], &gu);
+      if (SYN && !((smask >> c) & 1u)) { S.cj[c] = __fmaf_rn(d.alpha_s, S.cj[c], gu); gu = S.cj[c]; }   // (what a gather takes, see bwd_receiver)
       gu4.v[c] = ((smask >> c) & 1u) ? __uint_as_float(kFlowSentinel) : gu;
     }
     const __amdgpu_buffer_rsrc_t row = res_rows(gwin, hi * 4), far = res_rows(d.Gacc + (size_t)S.slot * d.BN, hi * 4);
@@ -316,6 +318,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
       if (near_h >= 1 && S.rlen[c] > 0 && !((S.ovf_cur >> c) & 1u)) G += s_G[NPT * (int)threadIdx.x + c];
       float gu;
       S.carry[c] = bwd_update_as<SURR>(d, n, U[c], S.Ub.v[c], true, 0.0f, S.dLc[c], G, dU[c], &gu);
+      if (SYN) { S.cj[c] = __fmaf_rn(d.alpha_s, S.cj[c], gu); gu = S.cj[c]; }
       if (!d.flow_hold) st_agent(&gwin[g0 + c], gu);   // (withheld only by the test of the waits' failure path)
     }
   }
@@ -336,11 +339,12 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
 // Reverse steps n_hi - 1, n_hi - 2, ..., n_hi - nsteps, all inside one window whose buffer the host
 // has filled with the sentinel.  P taking-part blocks (every stride-th block of the grid), each
 // owning `chunk` <= NPT * 512 neurons, NPT consecutive ones per thread (NPT = 4 or, for state arrays beyond
-// 256 x 2,048 cells, 8: 16-byte accesses, B N a multiple of 4; NPT = 1 where the blocks own 512 neurons at most: the
+// 256 x 2,048 cells, 8: 16-byte accesses, B N a multiple of 4; NPT = 1, any B N, where the blocks own 512 neurons at most: the
 // dense part of a step then spreads over all the block's wavefronts).  HAS_DU: a cotangent on the membrane values comes with the call; SURR: the gradient mode.
 // fill_other: the launch also fills the OTHER window buffer (the one the next launch sweeps) with the sentinel, every
 // block the cells of its own neurons, a row per step and what is left when the steps are done.
-template <bool HAS_DU, int SURR, int NPT>
+// SYN = 1: a synaptic current state; its adjoint stays in registers like the carry, and is what the cells hold.
+template <bool HAS_DU, int SURR, int NPT, int SYN>
 __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int nsteps, long long T, int P, int chunk, int stride,
                                                           int fill_other, const float* __restrict__ dL_dcount,
                                                           const float* __restrict__ dL_dU, Dev d) {
@@ -361,13 +365,14 @@ __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int ns
 #pragma unroll
   for (int c = 0; c < NPT; ++c) {
     const int g = S.g0 + c;
-    S.rlen[c] = 0; S.r0[c] = 0; S.carry[c] = 0.0f; S.dLc[c] = 0.0f;
+    S.rlen[c] = 0; S.r0[c] = 0; S.carry[c] = 0.0f; S.dLc[c] = 0.0f; S.cj[c] = 0.0f;
     if (g < S.hi) {
       S.actmask |= 1u << c;
       const int i = g - trial_of(d, g) * d.N;
       S.r0[c] = d.row_ptr[i];
       S.rlen[c] = (int)(d.row_ptr[i + 1] - S.r0[c]);
       S.carry[c] = d.bwd_carry[g];
+      if (SYN) S.cj[c] = d.bwd_carryJ[g];
       if (dL_dcount) S.dLc[c] = dL_dcount[g];
     }
   }
@@ -395,7 +400,7 @@ __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int ns
   float* const other = gwin_of(d, n_hi - 1 + d.W);   // (the buffers take turns window by window)
   int cnt_base0 = 0, cnt_base1 = 0;   // what the counters of list 0 and list 1 held when their last list was complete
   for (int k = 0; k < nsteps; ++k) {
-    flow_step<HAS_DU, SURR, NPT>(d, S, k & 1, A, B, k + 1 == nsteps, &s_dead, s_nspk, s_spk, s_G,
+    flow_step<HAS_DU, SURR, NPT, SYN>(d, S, k & 1, A, B, k + 1 == nsteps, &s_dead, s_nspk, s_spk, s_G,
                       fill_other ? other + (size_t)(phi0 - k) * d.BN : nullptr, cnt_base0, cnt_base1);
     A = B;
   }
@@ -407,5 +412,8 @@ __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int ns
   }
 #pragma unroll
   for (int c = 0; c < NPT; ++c)
-    if ((S.actmask >> c) & 1u) d.bwd_carry[S.g0 + c] = S.carry[c];
+    if ((S.actmask >> c) & 1u) {
+      d.bwd_carry[S.g0 + c] = S.carry[c];
+      if (SYN) d.bwd_carryJ[S.g0 + c] = S.cj[c];
+    }
 }

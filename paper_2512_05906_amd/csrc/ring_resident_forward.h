@@ -1,5 +1,5 @@
 // Ring queue, forward: the steps of one window in ONE launch over the whole chip, with the rows of
-// the neurons that are ABOUT to spike requested ahead (delta synapse).  Included by adseq.hip after
+// the neurons that are ABOUT to spike requested ahead.  Included by adseq.hip after
 // ring_resident_reverse.h, whose barrier (rev_wait / rev_arrive: kArriveLines arrival counters, a
 // wavefront per block that only synchronises, bounded waits) and list entries it shares.
 //
@@ -25,6 +25,7 @@ constexpr int kFwdCand = 32;   // candidates per block and step whose rows are r
 template <int NPT>
 struct FwdState {
   float V[NPT];
+  float J[NPT], Jf[NPT];         // synaptic current states (SYN; the fast one with SYN = 2)
   long long r0[NPT]; int rlen[NPT];
   unsigned long long zg[NPT];    // mix64(seed + G (g + 1)): the neuron's half of the drive's hash
   unsigned actmask;
@@ -52,9 +53,11 @@ __device__ __forceinline__ void fwd_row_tail(const Dev& d, int* __restrict__ win
 // Steps n0 .. n0 + nsteps - 1, all inside one window.  P taking-part blocks (every stride-th block of
 // the grid), each owning `chunk` <= NPT * 512 neurons, NPT consecutive ones per thread (four; eight for state arrays
 // beyond 256 x 2,048 cells; one where a block owns no more neurons than it has threads: a step's instructions then
-// spread over all its wavefronts); B N a multiple of 4.  bar_base: sum of the arrival counters when the launch begins.  margin: how far below the
+// spread over all its wavefronts); B N a multiple of 4 unless NPT = 1 (whose accesses are of 4 bytes).  SYN: synaptic
+// current states, as in k_step_win; they stay in registers too.  (9,973 neurons x 2 trials with a current state, 1,000
+// steps with the reverse sweep: 8.4 ms by a launch per step, 5.1 ms so.)  bar_base: sum of the arrival counters when the launch begins.  margin: how far below the
 // threshold the early value of a candidate may lie.
-template <bool RECORD, int NPT>
+template <bool RECORD, int NPT, int SYN>
 __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nsteps, unsigned bar_base, int P, int chunk,
                                                           int stride, float margin, Dev d) {
   __shared__ int s_dead, s_ncand, s_nslow;
@@ -88,13 +91,15 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
 #pragma unroll
   for (int c = 0; c < NPT; ++c) {
     const int g = S.g0 + c;
-    S.V[c] = 0.0f; S.r0[c] = 0; S.rlen[c] = 0; S.zg[c] = 0ull;
+    S.V[c] = 0.0f; S.J[c] = 0.0f; S.Jf[c] = 0.0f; S.r0[c] = 0; S.rlen[c] = 0; S.zg[c] = 0ull;
     if (g < S.hi) {
       S.actmask |= 1u << c;
       const int i = g - trial_of(d, g) * d.N;
       S.r0[c] = d.row_ptr[i];
       S.rlen[c] = (int)(d.row_ptr[i + 1] - S.r0[c]);
       S.V[c] = d.V[g];
+      if (SYN) S.J[c] = d.J[g];
+      if (SYN == 2) S.Jf[c] = d.J[(size_t)d.BN + g];
       S.zg[c] = mix64(d.seed + G64 * ((unsigned long long)g + 1ull));
     }
   }
@@ -126,6 +131,11 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
 #pragma unroll
       for (int c = 0; c < NPT; ++c) {
         float I = (float)__float_as_int(early.v[c]) * 0x1p-24f;
+        if (SYN) {
+          const float jump = I;
+          I = __fmaf_rn(d.alpha_s, S.J[c], jump);
+          if (SYN == 2) I = I - __fmaf_rn(d.alpha_r, S.Jf[c], jump);
+        }
         if (d.p_thresh) I = I + (((xi >> c) & 1u) ? d.ext_w : 0.0f);
         cmask |= __fmaf_rn(d.alpha, S.V[c], I) >= cand_theta ? 1u << c : 0u;
       }
@@ -197,6 +207,16 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
 #pragma unroll
       for (int c = 0; c < NPT; ++c) {
         float I = (float)__float_as_int(acc.v[c]) * 0x1p-24f;
+        if (SYN) {   // the jumps go into the synaptic current state(s)
+          const float jump = I;
+          I = __fmaf_rn(d.alpha_s, S.J[c], jump);
+          S.J[c] = I;
+          if (SYN == 2) {
+            const float fast = __fmaf_rn(d.alpha_r, S.Jf[c], jump);
+            S.Jf[c] = fast;
+            I = I - fast;
+          }
+        }
         if (d.p_thresh) I = I + (((xi >> c) & 1u) ? d.ext_w : 0.0f);
         U[c] = __fmaf_rn(d.alpha, S.V[c], I);
         const bool s = U[c] >= d.theta;
@@ -307,5 +327,9 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
   }
 #pragma unroll
   for (int c = 0; c < NPT; ++c)
-    if ((S.actmask >> c) & 1u) d.V[g0 + c] = S.V[c];
+    if ((S.actmask >> c) & 1u) {
+      d.V[g0 + c] = S.V[c];
+      if (SYN) d.J[g0 + c] = S.J[c];
+      if (SYN == 2) d.J[(size_t)d.BN + g0 + c] = S.Jf[c];
+    }
 }
