@@ -307,7 +307,8 @@ int adseq_spike_counts(adseq_t *h, int32_t *counts, void *stream);
  * synchronises `stream` and returns, per kernel class, the summed time in ms and the number of
  * launches since the last read, then forgets them.  Classes for FIFO / SORTED (an event after
  * every launch): [0] fan-out + contender registration, [1] admission + pop + drive + LIF,
- * [2] backward queue term + gradients, [3] backward neuron update.  Classes for RING: [0] the
+ * [2] backward queue term + gradients, [3] backward neuron update (where the reverse sweep goes window
+ * by window, the far gather of a window and its reverse steps, as for RING; [3] counts the steps).  Classes for RING: [0] the
  * expansion of one window (staging pass + accumulation pass, timed as a pair and counted as one
  * launch), [1] forward step kernel, [2] backward far gather of one window, [3] backward step
  * kernel (where the reverse steps of a window run in one launch, that launch); the step kernels are timed in groups (all the step launches between two window

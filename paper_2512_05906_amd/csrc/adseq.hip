@@ -20,8 +20,9 @@
 //                                           for the forward pass, {packed, fp32 amplitude} for the reverse
 //   amp, fdec    fp32  [S]                  continuous delays: a = w f (FIFO/SORTED) and f
 //   tape_*                                  membrane tape, spike list, admission flags
-//   bwd_*                                   FIFO/SORTED: adjoint delay line [R][BN], carry, queue term
-//   gwin, Gacc, gsum                        RING: adjoint rows of the window, far queue terms, per-synapse sums
+//   gwin, Gacc, gsum                        reverse sweep: adjoint rows of the window, far queue terms, per-synapse sums
+//   adm_base, adm_bits                      bounded kinds, reverse sweep: admission flags of the sorted rows, one bit each
+//   bwd_ring, bwd_G, tape_row               bounded kinds whose workspace must stay below 32 MB: adjoint delay line [R][BN], queue terms
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -167,6 +168,9 @@ struct Dev {
   Counters* ctr;
   BlkCtr* blk;   // FIFO / SORTED: [nblk + kFanoutBlocks]
   // (what was added later stays behind what the per-step kernels read, whose place in the argument block is tuned)
+  int sorted_rev;       // bounded kinds with tape: the reverse sweep runs on rows sorted by arrival offset (the ring's kernels)
+  unsigned* adm_base;   // bounded kinds: [T][words] first word in adm_bits of the spikes of a (step, spike word)
+  unsigned long long* adm_bits;  // bounded kinds: admission flags of every spike's sorted row, one bit each (k_adm_bits)
   long long* insum;     // [N] create only: sum of |Q8.24 amplitude| over every target's incoming synapses
   int flow_hold;        // RING, reverse kernel without a grid barrier: 1 = spiking neurons never store their final adjoints (ADSEQ_RING_FLOW_WITHHOLD: drives the waits' failure path from the host)
   int res_spins;        // RING, resident kernels: polls of one wait before it gives up (kResMaxSpins; ADSEQ_RING_RESIDENT_SPINS lowers it to test the failure path)
@@ -337,7 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Dev d, ExpCoef ec) {
     q = q > 2147483647LL ? 2147483647LL : (q < -2147483648LL ? -2147483648LL : q);
     d.a_q[p] = (int)q;
     d.packed[p] = ((unsigned)c << d.dbits) | (unsigned)D;
-    if (d.continuous) { d.amp[p] = (float)a; d.fdec[p] = (float)f; }
+    if (d.amp) { d.amp[p] = (float)a; d.fdec[p] = (float)f; }
     if (err) atomicOr(&d.ctr->err, err);
   }
   // row_ptr: starts at 0, ends at S, never decreases, rows shorter than 2^31
@@ -392,6 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 
 // ---------------------------------------------------------------- backward (FIFO / SORTED)
 
+// These two run where the workspace has no room for the sorted rows (see make_layout).
 // Queue term of the reverse sweep at step n for the bounded kinds: fsplit blocks per recorded
 // spike (b, i, n), the spikes being tape entries [off, off + gridDim.x / fsplit).  Block (e, c)
 // takes share c of the row (entries c * 256 .. + 255 of every fsplit * 256), four entries per
@@ -537,12 +542,13 @@ namespace {
 struct Layout {
   size_t V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
-      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
+      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
       total;
   long long spike_cap, event_cap, pool_cap;
   int R, dbits, nblk, words;
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
+  bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
 
 // A power of two in [lo, hi] from the environment, else the default (tuning knobs of the ring:
@@ -627,21 +633,25 @@ const void* run_xcd_kernel_of(int syn, int npt) {
 // The instances of the reverse kernel without a grid barrier and of the forward kernel over the whole chip: one neuron per
 // thread where a block owns no more neurons than it has worker threads, else four, else eight.
 typedef void (*FlowKernel)(long long, int, long long, int, int, int, int, const float*, const float*, Dev);
-template <bool DU, int SYN, int NPT>
+template <bool ADM, bool DU, int SYN, int NPT>
 FlowKernel flow_kernel_of(int surrogate) {
-  if (surrogate == ADSEQ_SURR_SUPERSPIKE) return k_bwd_flow<DU, ADSEQ_SURR_SUPERSPIKE, NPT, SYN>;
-  if (surrogate == ADSEQ_GRAD_SPIKE_TIME) return k_bwd_flow<DU, ADSEQ_GRAD_SPIKE_TIME, NPT, SYN>;
-  return k_bwd_flow<DU, ADSEQ_SURR_OFF, NPT, SYN>;
+  if (surrogate == ADSEQ_SURR_SUPERSPIKE) return k_bwd_flow<DU, ADSEQ_SURR_SUPERSPIKE, NPT, SYN, ADM>;
+  if (surrogate == ADSEQ_GRAD_SPIKE_TIME) return k_bwd_flow<DU, ADSEQ_GRAD_SPIKE_TIME, NPT, SYN, ADM>;
+  return k_bwd_flow<DU, ADSEQ_SURR_OFF, NPT, SYN, ADM>;
 }
-template <bool DU, int SYN>
+template <bool ADM, bool DU, int SYN>
 FlowKernel flow_kernel_npt(int surrogate, int chunk) {
-  if (chunk <= kResThreads) return flow_kernel_of<DU, SYN, 1>(surrogate);
-  if (chunk <= 4 * kResThreads) return flow_kernel_of<DU, SYN, 4>(surrogate);
-  return flow_kernel_of<DU, SYN, 8>(surrogate);
+  if (chunk <= kResThreads) return flow_kernel_of<ADM, DU, SYN, 1>(surrogate);
+  if (chunk <= 4 * kResThreads) return flow_kernel_of<ADM, DU, SYN, 4>(surrogate);
+  return flow_kernel_of<ADM, DU, SYN, 8>(surrogate);
 }
-FlowKernel flow_kernel(bool du, int syn, int surrogate, int chunk) {
-  if (syn) return du ? flow_kernel_npt<true, 1>(surrogate, chunk) : flow_kernel_npt<false, 1>(surrogate, chunk);
-  return du ? flow_kernel_npt<true, 0>(surrogate, chunk) : flow_kernel_npt<false, 0>(surrogate, chunk);
+template <bool ADM>
+FlowKernel flow_kernel_adm(bool du, int syn, int surrogate, int chunk) {
+  if (syn) return du ? flow_kernel_npt<ADM, true, 1>(surrogate, chunk) : flow_kernel_npt<ADM, false, 1>(surrogate, chunk);
+  return du ? flow_kernel_npt<ADM, true, 0>(surrogate, chunk) : flow_kernel_npt<ADM, false, 0>(surrogate, chunk);
+}
+FlowKernel flow_kernel(bool adm, bool du, int syn, int surrogate, int chunk) {
+  return adm ? flow_kernel_adm<true>(du, syn, surrogate, chunk) : flow_kernel_adm<false>(du, syn, surrogate, chunk);
 }
 typedef void (*ChipKernel)(long long, int, unsigned, int, int, int, float, Dev);
 template <bool RECORD, int SYN>
@@ -693,8 +703,11 @@ bool host_validate(const adseq_config* c) {
   return true;
 }
 
-bool make_layout(const adseq_config* c, Layout* L) {
+// sorted_rev: bounded kinds with tape get what the ring's reverse kernels need (rows sorted by arrival offset, window
+// buffers, admission bits) instead of an adjoint delay line.
+bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev) {
   if (!host_validate(c)) return false;
+  if (c->kind == ADSEQ_RING || !c->record_tape) sorted_rev = false;
   const size_t BN = (size_t)c->n_neurons * c->batch;
   const size_t S = (size_t)c->n_synapses;
   const bool bounded = c->kind != ADSEQ_RING;
@@ -730,6 +743,13 @@ bool make_layout(const adseq_config* c, Layout* L) {
   L->words = L->nblk * (kBlock / 64);
   L->W = L->wshift = L->tp_shift = L->P = L->NB = L->cap = L->wgroups = 0;
   size_t stage_parts = 0;
+  L->sorted_rev = sorted_rev;
+  if (sorted_rev) {
+    L->W = ring_window_steps();
+    while (L->W > c->d_max_steps) L->W >>= 1;
+    L->wshift = bit_width((unsigned)L->W) - 1;
+    L->wgroups = (L->words + 7) / 8;
+  }
   if (!bounded) {
     // the window is no longer than the largest delay (so that a window boundary comes before
     // any spike word is overwritten)
@@ -802,35 +822,41 @@ bool make_layout(const adseq_config* c, Layout* L) {
   L->packed = take(bounded ? S * 4 : 0);
   L->a_q = take(bounded ? S * 4 : 0);
   L->synf = take(bounded ? 0 : S * 8);
-  L->synb = take(bounded ? 0 : S * 8);
-  L->dstart = take(bounded ? 0 : (size_t)c->n_neurons * (c->d_max_steps + 2) * 4);
-  L->nearcnt = take(bounded ? 0 : (size_t)(L->W + 1) * c->n_neurons * 4);
-  L->perm = take(bounded ? 0 : S * 4);
+  const bool windows = !bounded || sorted_rev;
+  L->synb = take(windows ? S * 8 : 0);
+  L->dstart = take(windows ? (size_t)c->n_neurons * (c->d_max_steps + 2) * 4 : 0);
+  L->nearcnt = take(windows ? (size_t)(L->W + 1) * c->n_neurons * 4 : 0);
+  L->perm = take(windows ? S * 4 : 0);
   L->rowsum = take((size_t)c->n_neurons * 8);
   L->insum = take((size_t)c->n_neurons * 8);
   L->rowlen = take(bounded ? (size_t)c->n_neurons * 4 : 0);
   L->ebuf = take(bounded ? 0 : stage_parts * L->NB * (size_t)L->cap * 8);
   L->ecnt = take(bounded ? 0 : stage_parts * L->NB * 4);
-  L->amp = take(cont && bounded ? S * 4 : 0);
+  L->amp = take(cont && !windows ? S * 4 : 0);
   L->fdec = take(cont ? S * 4 : 0);
   const size_t T = c->record_tape ? (size_t)c->max_steps : 0;
   L->tapeU = take(T * BN * 4);
-  L->tape_bits = take(bounded ? 0 : T * L->words * 8);
+  L->tape_bits = take(windows ? T * L->words * 8 : 0);
   L->spk_count = take(c->record_tape ? BN * 4 : 0);
   L->step_off = take(c->record_tape ? (T + 1) * 8 : 0);
   L->step_evoff = take(c->record_tape && bounded ? (T + 1) * 8 : 0);
   L->tape_spk = take(bounded ? (size_t)L->spike_cap * 4 : 0);
   L->tape_evb = take(bounded ? (size_t)L->spike_cap * 8 : 0);
-  L->tape_row = take(bounded ? (size_t)L->spike_cap * sizeof(RowSpan) : 0);
+  L->tape_row = take(!windows ? (size_t)L->spike_cap * sizeof(RowSpan) : 0);
   L->tape_adm = take((size_t)L->event_cap);
   const bool tape = c->record_tape != 0;
-  L->bwd_ring = take(tape && bounded ? nstates * (size_t)L->R * BN * 4 : 0);
+  L->bwd_ring = take(tape && !windows ? nstates * (size_t)L->R * BN * 4 : 0);
   L->bwd_carry = take(tape ? BN * 4 : 0);
   L->bwd_carryJ = take(tape && c->tau_syn_ms > 0.0f ? nstates * BN * 4 : 0);
-  L->bwd_G = take(tape && bounded ? (size_t)kFanSplitMax * BN * 4 : 0);
-  L->gwin = take(tape && !bounded ? nstates * 2 * (size_t)L->W * BN * 4 : 0);
-  L->Gacc = take(tape && !bounded ? (size_t)L->R * BN * 4 : 0);
-  L->gsum = take(tape && !bounded ? nstates * S * 4 : 0);
+  L->bwd_G = take(tape && !windows ? (size_t)kFanSplitMax * BN * 4 : 0);
+  L->gwin = take(tape && windows ? nstates * 2 * (size_t)L->W * BN * 4 : 0);
+  L->Gacc = take(tape && windows ? (size_t)L->R * BN * 4 : 0);
+  L->gsum = take(tape && windows ? nstates * S * 4 : 0);
+  // (the words of a spike's bits: see k_adm_bits)
+  const long long adm_words = sorted_rev ? (L->event_cap >> 6) + L->spike_cap + 1 : 0;
+  if (adm_words > 0xffffffffLL) return false;   // their indices are 32-bit
+  L->adm_base = take(sorted_rev ? T * L->words * 4 : 0);
+  L->adm_bits = take((size_t)adm_words * 8);
   {
     // reverse sweep by windows (delta synapse only): staging of a window's near events, 4 per state
     // cell and step, between 4,096 and 262,144
@@ -846,6 +872,19 @@ bool make_layout(const adseq_config* c, Layout* L) {
   }
   L->total = o;
   return true;
+}
+// The bounded kinds' reverse sweep takes the ring's kernels (a window of steps per launch; 16 x 1,000 neurons, FIFO[32]:
+// 2,000 steps forward and back 40.6 -> 27.7 ms) wherever their rows sorted by arrival offset fit: not where 2^32 words of admission
+// bits are too few, and not where only the smaller layout -- an adjoint delay line, two launches per step -- stays within
+// the workspace that adseq_create_static has.
+bool make_layout(const adseq_config* c, Layout* L) {
+  const int off = env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 0;
+  if (!off && layout_as(c, L, true)) {
+    if (!L->sorted_rev || L->total <= (size_t)ADSEQ_STATIC_WORKSPACE_BYTES) return true;
+    Layout small;
+    if (!layout_as(c, &small, false) || small.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES) return true;
+  }
+  return layout_as(c, L, false);
 }
 
 int fail(adseq* h, int code, const char* fmt, ...) {
@@ -1271,7 +1310,7 @@ int gather_blocks(const Dev& d, long long n_lo, long long n_hi) {
   return env_pow2("ADSEQ_RING_GATHERBLOCKS", (int)(g < 1 ? 1 : (g > 256 ? 256 : g)), 1, 2048);
 }
 
-// RING: the whole reverse sweep on `st`.  A window is swept as a whole (ring_reverse.h: one dense
+// The whole reverse sweep on `st` (RING, and the bounded kinds with sorted rows: only admitted events, adm).  A window is swept as a whole (ring_reverse.h: one dense
 // pass, the near corrections step by step inside one workgroup, then the far gather) when
 // `counts` (spikes and near events of every step, from k_bwd_near_counts; null: never) says that
 // its staging fits; otherwise with one launch per reverse step (k_bwd_step_win).  Either way, when
@@ -1282,6 +1321,15 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
   const Dev& d = h->dev;
   const dim3 block(kBlock), gn((unsigned)d.nblk);
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
+  const bool adm = d.kind != ADSEQ_RING;
+  if (adm && T > 0) {
+    fill_u32(st, d.tape_bits, 0u, (size_t)T * d.words * 2);
+    const unsigned steps = (unsigned)(T < 65536 ? T : 65536);
+    // (about 4,096 blocks; one row of the grid per step where there are many)
+    const unsigned shares = steps >= 4096 ? 1 : (4096 + steps - 1) / steps;
+    hipLaunchKernelGGL(k_tape_words, dim3(steps), block, 0, st, d, T);
+    hipLaunchKernelGGL(k_adm_bits, dim3(steps, shares), block, 0, st, d, T);
+  }
   fill_u32(st, d.bwd_carry, 0u, (size_t)d.BN);
   if (d.alpha_s > 0.0f) fill_u32(st, d.bwd_carryJ, 0u, nst * (size_t)d.BN);
   fill_u32(st, d.gsum, 0u, nst * (size_t)d.S);
@@ -1323,7 +1371,7 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
           const int buf = (int)((k0 >> d.wshift) & 1);
           if (flow_filled != buf) fill_u32(st, d.gwin + (size_t)buf * d.W * d.BN, kFlowSentinel, (size_t)d.W * d.BN);
           const int fill_other = (counts == nullptr && k0 > 0) ? 1 : 0;
-          hipLaunchKernelGGL(flow_kernel(dL_dU != nullptr, d.alpha_s > 0.0f ? 1 : 0, d.surrogate, h->rev_chunk), rg, dim3(kResThreads), 0, st, k1, nsteps, T,
+          hipLaunchKernelGGL(flow_kernel(adm, dL_dU != nullptr, d.alpha_s > 0.0f ? 1 : 0, d.surrogate, h->rev_chunk), rg, dim3(kResThreads), 0, st, k1, nsteps, T,
                              h->rev_P, h->rev_chunk, stride, fill_other, dL_dcount, dL_dU, d);
           flow_filled = fill_other ? 1 - buf : -1;
         } else {
@@ -1346,13 +1394,17 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
         chain_join(h, st);
       } else
       for (long long n = k1 - 1; n >= k0; --n) {
-        if (d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<2, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
-        else if (d.alpha_s > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<1, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
-        else if (d.lazy_rows) hipLaunchKernelGGL((k_bwd_step_win<0, true>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
-        else hipLaunchKernelGGL((k_bwd_step_win<0, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        if (adm && d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<2, false, true>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else if (adm && d.alpha_s > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<1, false, true>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else if (adm) hipLaunchKernelGGL((k_bwd_step_win<0, false, true>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else if (d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<2, false, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else if (d.alpha_s > 0.0f) hipLaunchKernelGGL((k_bwd_step_win<1, false, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else if (d.lazy_rows) hipLaunchKernelGGL((k_bwd_step_win<0, true, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
+        else hipLaunchKernelGGL((k_bwd_step_win<0, false, false>), gn, block, 0, st, n, T, dL_dcount, dL_dU, d);
       }
     }
-    h->grp_count += (!whole && h->rev_P > 0) ? 1 : nsteps;   // launches of the group: the resident reverse kernel takes the window in one
+    // launches of the group: the resident reverse kernel takes the window in one (the bounded kinds count reverse steps)
+    h->grp_count += (!whole && h->rev_P > 0 && !adm) ? 1 : nsteps;
     // far gather into the window (and, after a sweep of the whole window, the per-synapse sums of
     // its own near events): spikes of steps [lo, hi)
     const long long lo = k0 - d.d_max > 0 ? k0 - d.d_max : 0;
@@ -1361,8 +1413,11 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
       close_group(h, st, 3);
       mark(h, st, -1);
       const int nvb = gather_blocks(d, lo, hi);
-      if (d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_win<true>), dim3((unsigned)nvb), dim3(kRingThreads), 0, st, d, k0, lo, hi, T, 0, nvb);
-      else hipLaunchKernelGGL((k_bwd_win<false>), dim3((unsigned)nvb), dim3(kRingThreads), 0, st, d, k0, lo, hi, T, 0, nvb);
+      const dim3 gb((unsigned)nvb), gt(kRingThreads);
+      if (adm && d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_win<true, true>), gb, gt, 0, st, d, k0, lo, hi, T, 0, nvb);
+      else if (adm) hipLaunchKernelGGL((k_bwd_win<false, true>), gb, gt, 0, st, d, k0, lo, hi, T, 0, nvb);
+      else if (d.alpha_r > 0.0f) hipLaunchKernelGGL((k_bwd_win<true, false>), gb, gt, 0, st, d, k0, lo, hi, T, 0, nvb);
+      else hipLaunchKernelGGL((k_bwd_win<false, false>), gb, gt, 0, st, d, k0, lo, hi, T, 0, nvb);
       mark(h, st, 2);
     }
   }
@@ -1515,6 +1570,8 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
   d.ebuf = (uint2*)(ws + L.ebuf); d.ecnt = (int*)(ws + L.ecnt);
   d.tape_bits = (unsigned long long*)(ws + L.tape_bits);
   d.spk_count = (int*)(ws + L.spk_count);
+  d.sorted_rev = L.sorted_rev ? 1 : 0;
+  d.adm_base = (unsigned*)(ws + L.adm_base); d.adm_bits = (unsigned long long*)(ws + L.adm_bits);
   d.gwin = (float*)(ws + L.gwin); d.Gacc = (float*)(ws + L.Gacc); d.gsum = (float*)(ws + L.gsum);
   d.wspk = (unsigned long long*)(ws + L.wspk); d.near_nspk = (int*)(ws + L.near_cnt); d.near_nev = d.near_nspk + 64;
   d.near_ev = (uint4*)(ws + L.near_ev); d.near_spk = (int*)(ws + L.near_spk); d.near_counts = (int*)(ws + L.near_counts);
@@ -1540,7 +1597,7 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
   d.sq_flag = (long long*)(ws + L.sq_flag);
   d.I_acc = (int*)(ws + L.I_acc); d.last_evb = (long long*)(ws + L.last_evb); d.blk_pop = L.nblk + (int)fan_slots(L.nblk);
   d.packed = (unsigned*)(ws + L.packed); d.a_q = (int*)(ws + L.a_q);
-  d.amp = (d.continuous && d.kind != ADSEQ_RING) ? (float*)(ws + L.amp) : nullptr;
+  d.amp = (d.continuous && d.kind != ADSEQ_RING && !L.sorted_rev) ? (float*)(ws + L.amp) : nullptr;
   d.synf = (uint2*)(ws + L.synf); d.synb = (uint2*)(ws + L.synb);
   d.fdec = d.continuous ? (float*)(ws + L.fdec) : nullptr;
   d.tapeU = (float*)(ws + L.tapeU); d.step_off = (long long*)(ws + L.step_off);
@@ -1551,21 +1608,24 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
   d.bwd_ring = (float*)(ws + L.bwd_ring); d.bwd_carry = (float*)(ws + L.bwd_carry);
   d.bwd_G = (float*)(ws + L.bwd_G);
 
+  const int syn = d.alpha_r > 0.0f ? 2 : (d.alpha_s > 0.0f ? 1 : 0);
+  if (d.kind == ADSEQ_RING || d.sorted_rev) {
+    ResidentPlan vp = syn < 2 ? reverse_plan((long long)d.BN) : ResidentPlan();
+    // without a grid barrier: the blocks wait for the cells they gather (ring_flow_reverse.h); ADSEQ_RING_REVERSE_FLOW = 0:
+    // the kernel with a barrier per step, which holds four neurons per thread, no synaptic state and no admission bits
+    const bool adm = d.kind != ADSEQ_RING;
+    h->rev_flow = vp.P > 0 && env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) &&
+                  resident_fits((const void*)flow_kernel(adm, true, syn, d.surrogate, vp.chunk), kResThreads) &&
+                  resident_fits((const void*)flow_kernel(adm, false, syn, d.surrogate, vp.chunk), kResThreads);
+    if (vp.P > 0 && !h->rev_flow &&
+        (adm || syn || d.BN % 4 != 0 || vp.chunk > 4 * kResThreads || !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))))
+      vp = ResidentPlan();
+    h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
+  }
   if (d.kind == ADSEQ_RING) {
-    const int syn = d.alpha_r > 0.0f ? 2 : (d.alpha_s > 0.0f ? 1 : 0);
     ResidentPlan rp = resident_plan((long long)d.BN);
     if (rp.P > 0 && !(resident_fits(run_xcd_kernel(true, syn, rp.npt)) && resident_fits(run_xcd_kernel(false, syn, rp.npt)))) rp = ResidentPlan();
     h->res_chunk = rp.chunk; h->res_P = rp.P; h->res_npt = rp.npt;
-    ResidentPlan vp = syn < 2 ? reverse_plan((long long)d.BN) : ResidentPlan();
-    // without a grid barrier: the blocks wait for the cells they gather (ring_flow_reverse.h); ADSEQ_RING_REVERSE_FLOW = 0:
-    // the kernel with a barrier per step, which holds four neurons per thread and no synaptic state
-    h->rev_flow = vp.P > 0 && env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) &&
-                  resident_fits((const void*)flow_kernel(true, syn, d.surrogate, vp.chunk), kResThreads) &&
-                  resident_fits((const void*)flow_kernel(false, syn, d.surrogate, vp.chunk), kResThreads);
-    if (vp.P > 0 && !h->rev_flow &&
-        (syn || d.BN % 4 != 0 || vp.chunk > 4 * kResThreads || !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))))
-      vp = ResidentPlan();
-    h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
     // forward kernel over the whole chip with the candidates' rows requested ahead (ring_resident_forward.h): the
     // reverse kernel's layout (ADSEQ_RING_FORWARD_BLOCKS taking-part blocks, default 256).  ADSEQ_RING_FORWARD_CHIP:
     // see reverse_plan; ADSEQ_RING_FORWARD_MARGIN: candidate margin in thousandths of the membrane unit (default 5).
@@ -1620,6 +1680,7 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
     if (e == hipSuccess && !err) {
       const unsigned gr = (unsigned)((d.N + 3) / 4 < 8192 ? (d.N + 3) / 4 : 8192);
       hipLaunchKernelGGL(k_row_sums, dim3(gr), dim3(kBlock), 0, st, d);
+      if (d.sorted_rev) hipLaunchKernelGGL(k_sort_rows, dim3((unsigned)(d.N < 262144 ? d.N : 262144)), dim3(kBlock), 0, st, d, ec);
     }
   }
   if (e == hipSuccess && !(err & (ERR_GRAPH | ERR_DELAY)) && d.S > 0) {
@@ -1830,7 +1891,7 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   const dim3 block(kBlock), gn(grid_for((size_t)d.BN));
   const bool bounded = d.kind != ADSEQ_RING;
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
-  if (!bounded) {
+  if (!bounded || d.sorted_rev) {
     ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr);
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;

@@ -670,8 +670,10 @@ __global__ __launch_bounds__(kBlock) void k_fanout_step(Dev d, long long n, int 
             if (c == 0 && threadIdx.x == 0) {
               if (fits) {
                 d.tape_spk[pre_s + rank0 + j] = gs[j]; d.tape_evb[pre_s + rank0 + j] = evb;
-                RowSpan rsn; rsn.r0 = rr[j].r0; rsn.r1 = rr[j].r1;
-                d.tape_row[pre_s + rank0 + j] = rsn;
+                if (!d.sorted_rev) {
+                  RowSpan rsn; rsn.r0 = rr[j].r0; rsn.r1 = rr[j].r1;
+                  d.tape_row[pre_s + rank0 + j] = rsn;
+                }
               }
               else atomicOr(&d.ctr->err, ERR_TAPE_SPIKES);
               if (!ev_fits) atomicOr(&d.ctr->err, ERR_TAPE_EVENTS);

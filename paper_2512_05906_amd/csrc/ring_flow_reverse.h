@@ -47,8 +47,10 @@ __device__ __forceinline__ float flow_settle(const Dev& d, const float* p, bool 
 // Entries [q0, len) of a spike's sorted row, 64 at a time while they arrive inside the window (the
 // rows ascend in the arrival offset): gathers the adjoints, waiting for those that are not there
 // yet, adds them to gsum, and returns the wavefront's sum of amplitude * adjoint.
+// ADM (bounded queue kinds): admitted entries only; adm: first word of the row's admission bits.
+template <bool ADM>
 __device__ __forceinline__ float flow_row_tail(const Dev& d, const float* __restrict__ gwin, int near_h, long long r0,
-                                               int len, int base, int q0, bool more, int* s_dead) {
+                                               int len, int base, int q0, bool more, int* s_dead, unsigned adm) {
   const int lane = threadIdx.x & 63;
   float part = 0.0f;
   for (; (__ballot(more) >> 63) && q0 < len; q0 += 64) {
@@ -58,9 +60,11 @@ __device__ __forceinline__ float flow_row_tail(const Dev& d, const float* __rest
     unsigned amp = 0u;
     if (q0 + lane < len) {
       const uint2 e = load_stream(&d.synb[r0 + q0 + lane]);
+      const unsigned long long bits = ADM ? d.adm_bits[adm + (unsigned)(q0 >> 6)] : ~0ull;
       const int D = (int)(e.x & d.dmask);
       if (D <= near_h) {
-        want = true;
+        more = true;
+        want = (bits >> lane) & 1ull;
         amp = e.y;
         p = &gwin[(size_t)D * d.BN + (size_t)base + (e.x >> d.dbits)];
       }
@@ -72,7 +76,6 @@ __device__ __forceinline__ float flow_row_tail(const Dev& d, const float* __rest
     if (want) {
       unsafeAtomicAdd(&d.gsum[r0 + q0 + lane], gv);
       t = __uint_as_float(amp) * gv;
-      more = true;
     }
     part += wave_sum_f(t);
   }
@@ -132,6 +135,8 @@ struct FlowState {
   FlowVec<NPT> Ua, Ub, Uc;           // tape values of the step being run, of the one after it, of the one after that
   FlowVec<NPT> Ga, Gb, dUa, dUb;     // far queue terms and dL/dU of the step being run and of the next
   unsigned ovf_cur;                  // bit c: neuron c spiked in the step being run and did not fit the list
+  unsigned Ab, adm[NPT];             // ADM: adm_base of the thread's spike word for the step after the one being run; first words of the admission bits of the spikes of the step being run
+  const unsigned* abase2;            // ADM: adm_base of step n - 2 (of step 0 below that), at the thread's spike word
   int nspk_cur;                      // listed spikes of the step being run
   // the same in every lane
   long long n;                       // step being run
@@ -142,9 +147,11 @@ struct FlowState {
   int g0, hi;
 };
 
-template <bool HAS_DU, int SURR, int NPT, int SYN>
-__device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const int PAR, RevBatch& cur, RevBatch& nxt, bool last,
-                                          int* s_dead, int* s_nspk, RevSpike (*s_spk)[kRevList], float (*s_G2)[(NPT < 4 ? 4 : NPT) * kResThreads],
+// ADM (bounded queue kinds): the batch carries the admission bits of its rows' leading 64 entries too.
+struct FlowBatch : RevBatch { unsigned inw; unsigned adm[4]; unsigned long long bits[4]; };
+template <bool HAS_DU, int SURR, int NPT, int SYN, bool ADM>
+__device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const int PAR, FlowBatch& cur, FlowBatch& nxt, bool last,
+                                          int* s_dead, int* s_nspk, RevSpike (*s_spk)[kRevList], unsigned (*s_adm)[ADM ? kRevList : 1], float (*s_G2)[(NPT < 4 ? 4 : NPT) * kResThreads],
                                           float* fill_row, int& cnt_base0, int& cnt_base1) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int kWaves = kResThreads / 64;
@@ -166,11 +173,13 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
   // ---- requested first, so that they are there when the step ends (the values move up a place then, and a move of a
   // register that a load has not filled yet waits for the load): tape values of step n - 2, far queue terms and dL/dU
   // of step n - 1 (below step 0 the rows are step 0's again and are never used)
+  unsigned Ac = 0u;
   const int slot1 = n >= 1 ? (S.slot == 0 ? d.R - 1 : S.slot - 1) : 0;   // (n - 1) mod R
   {
     const __amdgpu_buffer_rsrc_t t2 = res_rows(S.tape2, hi * 4), f1 = res_rows(d.Gacc + (size_t)slot1 * d.BN, hi * 4);
     S.Uc = flow_load<NPT, kBufNonTemporal>(t2, g0 * 4);
     S.Gb = flow_load<NPT, kBufNonTemporal>(f1, g0 * 4);
+    if (ADM) Ac = *S.abase2;
     if (HAS_DU) S.dUb = flow_load<NPT, kBufNonTemporal>(res_rows(S.du1, hi * 4), g0 * 4);
   }
   // ---- the row of this step, as early as can be (others may be waiting for it): final for every neuron that does not
@@ -194,13 +203,15 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
   // ---- this step's gathers (rows requested a step ago): every entry of the leading 64 that arrives inside the window
   float gv[4];
   const float* gp[4];
-  cur.ok = 0u;
+  cur.ok = 0u; cur.inw = 0u;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     gv[u] = 0.0f; gp[u] = gwin;
     if (cur.len[u] > 0) {   // (the same in every lane)
       const int D = (int)(cur.e[u].x & d.dmask);
-      const bool ok = lane < cur.len[u] && D <= near_h;
+      const bool inw = lane < cur.len[u] && D <= near_h;
+      const bool ok = inw && (!ADM || ((cur.bits[u] >> lane) & 1ull));
+      cur.inw |= inw ? 1u << u : 0u;
       cur.ok |= ok ? 1u << u : 0u;
       if (ok) {
         gp[u] = &gwin[(size_t)D * d.BN + (size_t)cur.base[u] + (cur.e[u].x >> d.dbits)];
@@ -212,9 +223,22 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
   int nspk_nxt = 0;
   unsigned ovf_nxt = 0;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) { nxt.e[u] = make_uint2(0u, 0u); nxt.r0[u] = 0; nxt.len[u] = 0; nxt.base[u] = 0; nxt.loc[u] = 0; }
+  for (int u = 0; u < 4; ++u) { nxt.e[u] = make_uint2(0u, 0u); nxt.r0[u] = 0; nxt.len[u] = 0; nxt.base[u] = 0; nxt.loc[u] = 0; nxt.adm[u] = 0u; nxt.bits[u] = 0ull; }
+  unsigned adm1[NPT];
+#pragma unroll
+  for (int c = 0; c < NPT; ++c) adm1[c] = 0u;
   if (near1 >= 1) {
     if (__ballot(s1 != 0u) != 0ull) {
+      if (ADM) {
+        // where the spikes' admission bits begin: the words of the spikes before them in the same spike word are left out
+        int words = 0;
+#pragma unroll
+        for (int c = 0; c < NPT; ++c) { adm1[c] = (unsigned)words; words += ((s1 >> c) & 1u) ? (S.rlen[c] + 63) >> 6 : 0; }
+        const int excl = dpp_scan_add(words) - words;
+        const int first = __shfl(excl, lane & ~(64 / NPT - 1), 64);   // (64 / NPT lanes hold a spike word)
+#pragma unroll
+        for (int c = 0; c < NPT; ++c) adm1[c] += S.Ab + (unsigned)(excl - first);
+      }
       unsigned long long m[NPT];
       int total = 0;
 #pragma unroll
@@ -234,6 +258,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
             r.r0 = S.r0[c]; r.len = S.rlen[c];
             r.pk = (NPT * (int)threadIdx.x + c) | (trial_of(d, g0 + c) << kRevLocBits);
             s_spk[PAR ^ 1][idx] = r;
+            if (ADM) s_adm[PAR ^ 1][idx] = adm1[c];
           } else {
             ovf_nxt |= 1u << c;
           }
@@ -262,6 +287,10 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
         const __amdgpu_buffer_rsrc_t rs = res_rows(d.synb + nxt.r0[u], shown * 8);
         const unsigned long long ev = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(rs, lane * 8, 0, 0));
         nxt.e[u] = make_uint2((unsigned)ev, (unsigned)(ev >> 32));
+        if (ADM) {
+          nxt.adm[u] = (unsigned)__builtin_amdgcn_readfirstlane((int)s_adm[PAR ^ 1][x]);
+          nxt.bits[u] = d.adm_bits[nxt.adm[u]];
+        }
       }
     }
   }
@@ -276,7 +305,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
       const bool ok = (cur.ok >> u) & 1u;
       cur.gv[u] = flow_settle(d, gp[u], ok, gv[u], s_dead);
       float part = wave_sum_f(ok ? __uint_as_float(cur.e[u].y) * cur.gv[u] : 0.0f);
-      part += flow_row_tail(d, gwin, near_h, cur.r0[u], cur.len[u], cur.base[u], 64, ok, s_dead);
+      part += flow_row_tail<ADM>(d, gwin, near_h, cur.r0[u], cur.len[u], cur.base[u], 64, (cur.inw >> u) & 1u, s_dead, cur.adm[u]);
       if (lane == 0) s_G[cur.loc[u]] = part;
     }
     // more than 32 listed spikes in the block: the rest one at a time
@@ -284,7 +313,8 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
       const RevSpike r = s_spk[PAR][x];
       const long long rr0 = uniform_of(r.r0);
       const int len = __builtin_amdgcn_readfirstlane(r.len), pk = __builtin_amdgcn_readfirstlane(r.pk);
-      const float part = flow_row_tail(d, gwin, near_h, rr0, len, (pk >> kRevLocBits) * d.N, 0, true, s_dead);
+      const unsigned adm = ADM ? (unsigned)__builtin_amdgcn_readfirstlane((int)s_adm[PAR][x]) : 0u;
+      const float part = flow_row_tail<ADM>(d, gwin, near_h, rr0, len, (pk >> kRevLocBits) * d.N, 0, true, s_dead, adm);
       if (lane == 0) s_G[pk & ((1 << kRevLocBits) - 1)] = part;
     }
     // more spikes than the list holds: the owner's wavefront takes them one by one
@@ -298,7 +328,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
           const long long rr0 = lane_get(S.r0[c], L);
           const int len = lane_get(S.rlen[c], L);
           const int base = trial_of(d, lane_get(g0, L) + c) * d.N;
-          const float part = flow_row_tail(d, gwin, near_h, rr0, len, base, 0, true, s_dead);
+          const float part = flow_row_tail<ADM>(d, gwin, near_h, rr0, len, base, 0, true, s_dead, ADM ? lane_get(S.adm[c], L) : 0u);
           if (lane == L) Gx[c] = part;
         }
       }
@@ -330,6 +360,12 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
   S.nspk_cur = nspk_nxt; S.ovf_cur = ovf_nxt;
   S.Ua = S.Ub; S.Ub = S.Uc; S.Ga = S.Gb; S.dUa = S.dUb;
   S.slot = slot1;
+  if (ADM) {
+    S.Ab = Ac;
+#pragma unroll
+    for (int c = 0; c < NPT; ++c) S.adm[c] = adm1[c];
+    if (n >= 3) S.abase2 -= d.words;
+  }
   if (n >= 3) S.tape2 -= d.BN;
   if (HAS_DU && n >= 2) S.du1 -= d.BN;
   S.gwin -= d.BN;
@@ -344,11 +380,13 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
 // fill_other: the launch also fills the OTHER window buffer (the one the next launch sweeps) with the sentinel, every
 // block the cells of its own neurons, a row per step and what is left when the steps are done.
 // SYN = 1: a synaptic current state; its adjoint stays in registers like the carry, and is what the cells hold.
-template <bool HAS_DU, int SURR, int NPT, int SYN>
+// ADM: bounded queue kinds (admission bits, see k_adm_bits).
+template <bool HAS_DU, int SURR, int NPT, int SYN, bool ADM>
 __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int nsteps, long long T, int P, int chunk, int stride,
                                                           int fill_other, const float* __restrict__ dL_dcount,
                                                           const float* __restrict__ dL_dU, Dev d) {
   __shared__ int s_dead, s_nspk[2];
+  __shared__ unsigned s_adm[2][ADM ? kRevList : 1];   // ADM: first word of their admission bits
   __shared__ RevSpike s_spk[2][kRevList];     // the block's spikes of the step being run and of the step being prepared
   __shared__ float s_G[2][(NPT < 4 ? 4 : NPT) * kResThreads];   // near part of the queue term of every listed spike, by its neuron's place (two steps' worth in turn)
   if (blockIdx.x % stride) return;
@@ -388,19 +426,27 @@ __global__ __launch_bounds__(kResThreads) void k_bwd_flow(long long n_hi, int ns
   S.Uc = zero4;
   S.Ga = load_row(d.Gacc + (size_t)S.slot * d.BN); S.Gb = zero4;
   S.dUa = HAS_DU ? load_row(dL_dU + (size_t)(n_hi - 1) * d.BN) : zero4; S.dUb = zero4;
+  S.Ab = 0u;
+#pragma unroll
+  for (int c = 0; c < NPT; ++c) S.adm[c] = 0u;
+  if (ADM) {
+    const int word = S.g0 >> 6 < d.words ? S.g0 >> 6 : 0;   // (a thread past the last neuron has no spike)
+    S.abase2 = d.adm_base + (size_t)(n_hi >= 3 ? n_hi - 3 : 0) * d.words + word;
+    if (n_hi >= 2) S.Ab = d.adm_base[(size_t)(n_hi - 2) * d.words + word];
+  }
   S.nspk_cur = 0; S.ovf_cur = 0;   // (the launch's first step has no listed spike: nothing arrives after it inside the window)
-  RevBatch A, B;
+  FlowBatch A, B;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     A.e[u] = make_uint2(0u, 0u); A.gv[u] = 0.0f; A.r0[u] = 0; A.len[u] = 0; A.base[u] = 0; A.loc[u] = 0;
     B.e[u] = make_uint2(0u, 0u); B.gv[u] = 0.0f; B.r0[u] = 0; B.len[u] = 0; B.base[u] = 0; B.loc[u] = 0;
   }
-  A.ok = 0u; B.ok = 0u;
+  A.ok = 0u; B.ok = 0u; A.inw = 0u; B.inw = 0u;
   __syncthreads();
   float* const other = gwin_of(d, n_hi - 1 + d.W);   // (the buffers take turns window by window)
   int cnt_base0 = 0, cnt_base1 = 0;   // what the counters of list 0 and list 1 held when their last list was complete
   for (int k = 0; k < nsteps; ++k) {
-    flow_step<HAS_DU, SURR, NPT, SYN>(d, S, k & 1, A, B, k + 1 == nsteps, &s_dead, s_nspk, s_spk, s_G,
+    flow_step<HAS_DU, SURR, NPT, SYN, ADM>(d, S, k & 1, A, B, k + 1 == nsteps, &s_dead, s_nspk, s_spk, s_adm, s_G,
                       fill_other ? other + (size_t)(phi0 - k) * d.BN : nullptr, cnt_base0, cnt_base1);
     A = B;
   }

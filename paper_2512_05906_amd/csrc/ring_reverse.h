@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kRingThreads) void k_bwd_near_stage(Dev d, long lon
     }
   };
   long long cnt[3] = {0, 0, 0};
-  walk_segments(d, L, d.tape_bits, false, k0, k0, k1, T, (int)blockIdx.x, nvb, k1, cnt, stage);
+  walk_segments<false>(d, L, d.tape_bits, false, k0, k0, k1, T, (int)blockIdx.x, nvb, k1, cnt, stage);
   const int qn = L.qn < kSegQueue ? L.qn : kSegQueue;
   for (int t = threadIdx.x >> 6; t < qn; t += kRingWaves) stage(L.q[t]);
 }

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_rows(Dev d, ExpCoef ec) {
       if (c < 0 || c >= d.N) c = 0;
       const long long q = r0 + atomicAdd(&s_hist[s.D], 1u);
       const unsigned pk = ((unsigned)c << d.dbits) | (unsigned)s.D;
-      d.synf[q] = make_uint2(pk, (unsigned)s.a_q);
+      if (d.kind == ADSEQ_RING) d.synf[q] = make_uint2(pk, (unsigned)s.a_q);
       d.synb[q] = make_uint2(pk, __float_as_uint(s.amp));
       if (d.continuous) d.fdec[q] = s.f;
       d.perm[q] = (unsigned)(p - r0);
@@ -434,7 +434,9 @@ __device__ __forceinline__ uint2 load_stream(const uint2* p) {
 }
 
 // The piece of one spike's sorted row that lands in the window being expanded.
-struct Seg { long long p0; int len; int base; int dlo; int slot; long long g; };
+// (slot: in its lower half the row of the circular arrays that belongs to the spike's step, in the upper half the
+// place of the piece's first entry in its 64-entry group; adm: index of that group's word in adm_bits, bounded kinds)
+struct Seg { long long p0; int len; int base; int dlo; int slot; int g; unsigned adm; };
 constexpr int kSegQueue = 768;   // queue entries per block (32 B each)
 
 // LDS of a block of an expansion / gather role.
@@ -486,7 +488,8 @@ __device__ __forceinline__ void walk_advance(WalkPos& p, long long dq, int dr, i
 // whose piece is the front of its row) and appends it to the block's LDS queue;
 // handle(seg) is called instead when the queue is full.  Spikes of steps >= count_from are
 // counted into cnt[3] (spikes, their events, Q8.24 sum of those).  Ends with a block barrier.
-template <class Direct>
+// ADM: the pieces are to be taken with their admission bits (see k_adm_bits).
+template <bool ADM, class Direct>
 __device__ __forceinline__ void walk_segments(const Dev& d, ExpandLds& L, const unsigned long long* __restrict__ words,
                                               bool circular, long long k0, long long n_lo, long long n_hi,
                                               long long T, int vb, int nvb, long long count_from,
@@ -512,17 +515,20 @@ __device__ __forceinline__ void walk_segments(const Dev& d, ExpandLds& L, const 
   const int slot_lo = (int)(n_lo % d.R);
   // four trips' words are requested before the first is looked at
   for (long long c00 = gw; c00 < nlines; c00 += stride * 4) {
-    unsigned long long bw[4]; long long nn[4]; int ww[4], sl[4];
+    unsigned long long bw[4]; long long nn[4]; int ww[4], sl[4]; unsigned aw[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      bw[j] = 0ull; nn[j] = n_lo; ww[j] = 0; sl[j] = slot_lo;
+      bw[j] = 0ull; nn[j] = n_lo; ww[j] = 0; sl[j] = slot_lo; aw[j] = 0u;
       if (pos.si < nsteps) {   // (a trip past the end gives no word)
         nn[j] = n_lo + pos.si;
         ww[j] = pos.rem * 8 + (lane & 7);
         int slot = slot_lo + (int)pos.si;
         while (slot >= d.R) slot -= d.R;   // (a walk may span up to d_max + W steps)
         sl[j] = slot;
-        if (ww[j] < d.words) bw[j] = words[(size_t)(circular ? (long long)slot : nn[j]) * d.words + ww[j]];
+        if (ww[j] < d.words) {
+          bw[j] = words[(size_t)(circular ? (long long)slot : nn[j]) * d.words + ww[j]];
+          if (ADM) aw[j] = d.adm_base[(size_t)nn[j] * d.words + ww[j]];
+        }
       }
       walk_advance(pos, dq, dr, lps);
     }
@@ -540,7 +546,7 @@ __device__ __forceinline__ void walk_segments(const Dev& d, ExpandLds& L, const 
       const bool counted = n >= count_from;
       while (__ballot(bits != 0ull)) {
         // every lane that still has a spike takes its lowest one
-        Seg sg; sg.p0 = 0; sg.len = 0; sg.base = 0; sg.dlo = dlo; sg.slot = sl[j]; sg.g = 0;
+        Seg sg; sg.p0 = 0; sg.len = 0; sg.base = 0; sg.dlo = dlo; sg.slot = sl[j]; sg.g = 0; sg.adm = 0u;
         if (bits) {
           const int bit = __ffsll((long long)bits) - 1;
           bits &= bits - 1;
@@ -554,7 +560,11 @@ __device__ __forceinline__ void walk_segments(const Dev& d, ExpandLds& L, const 
             // (the row's length and sum are loaded for every spike, counted or not: under a branch
             // of their own they would be a second round trip to memory)
             const long long r1 = d.row_ptr[i + 1], rs = d.rowsum[i];
-            sg.p0 = r0 + q0; sg.len = (int)(q1 - q0); sg.base = b * d.N; sg.g = g;
+            sg.p0 = r0 + q0; sg.len = (int)(q1 - q0); sg.base = b * d.N; sg.g = (int)g;
+            if (ADM) {
+              sg.slot |= (int)(q0 & 63u) << 16; sg.adm = aw[j] + (q0 >> 6);
+              aw[j] += (unsigned)((r1 - r0 + 63) >> 6);
+            }
             cnt[0] += counted ? 1 : 0; cnt[1] += counted ? r1 - r0 : 0; cnt[2] += counted ? rs : 0;
           }
         }
@@ -572,6 +582,7 @@ __device__ __forceinline__ void walk_segments(const Dev& d, ExpandLds& L, const 
             Seg o;
             o.p0 = __shfl(sg.p0, src, 64); o.len = __shfl(sg.len, src, 64); o.base = __shfl(sg.base, src, 64);
             o.dlo = __shfl(sg.dlo, src, 64); o.slot = __shfl(sg.slot, src, 64); o.g = __shfl(sg.g, src, 64);
+            o.adm = __shfl(sg.adm, src, 64);
             handle(o);
           }
         }
@@ -757,7 +768,7 @@ __device__ __forceinline__ void role_bin(const Dev& d, ExpandLds& L, SortLds& S,
     }
   };
   long long cnt[3] = {0, 0, 0};
-  walk_segments(d, L, d.spike_bits, true, k0, n_lo, n_hi, -1, vb, nvb, count_from, cnt, one);
+  walk_segments<false>(d, L, d.spike_bits, true, k0, n_lo, n_hi, -1, vb, nvb, count_from, cnt, one);
   XPH(0)
   // counters first: their atomics complete while the events are staged
   if (count_from < n_hi) fold_counts(d, L, cnt, vb);
@@ -1046,16 +1057,17 @@ __device__ __forceinline__ float queue_term_of(const Dev& d, float x, float y) {
 // Gathers the adjoint at the arrival cell of the entries [0, cnt) of the sorted row at pr0
 // (a spike at step n, window phase phi; arrivals inside the same window), adds it to gsum and
 // returns the wavefront's sum of amplitude * adjoint in every lane.
-template <bool DEXP>
+// ADM (bounded kinds): only admitted entries; adm: word of the row's 64-entry group that pr0 begins.
+template <bool DEXP, bool ADM>
 __device__ __forceinline__ float near_gather(const Dev& d, const float* __restrict__ gwin, long long n,
-                                             long long T, int phi, long long pr0, unsigned cnt, int base) {
+                                             long long T, int phi, long long pr0, unsigned cnt, int base, unsigned adm) {
   const int lane = threadIdx.x & 63;
   const size_t second = 2 * (size_t)d.W * d.BN;   // the Y rows lie behind the two window buffers of X
   float G = 0.0f;
   for (unsigned q = lane; q < cnt; q += 64) {
     const uint2 e = d.synb[pr0 + q];
     const int D = (int)(e.x & d.dmask);
-    if (n + D < T) {
+    if (n + D < T && (!ADM || ((d.adm_bits[adm + (q >> 6)] >> lane) & 1ull))) {
       const size_t cell = (size_t)(phi + D) * d.BN + (size_t)base + (e.x >> d.dbits);
       const float gv = gwin[cell];
       unsafeAtomicAdd(&d.gsum[pr0 + q], gv);
@@ -1081,7 +1093,8 @@ __device__ __forceinline__ float near_gather(const Dev& d, const float* __restri
 // takes two adjoints, X for the weight and Y for the delay (see bwd_receiver)
 // LAZY: row start, in-window count and far queue term are fetched by the spiking lanes only (16
 // bytes per neuron less HBM traffic, one more memory round trip before the gathers)
-template <int SYN, bool LAZY>
+// ADM: bounded queue kinds, only the admitted events of a spike's row take part (admission bits, see k_adm_bits)
+template <int SYN, bool LAZY, bool ADM>
 __global__ __launch_bounds__(kBlock) void k_bwd_step_win(long long n, long long T,
                                                          const float* __restrict__ dL_dcount,
                                                          const float* __restrict__ dL_dU, Dev d) {
@@ -1098,6 +1111,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step_win(long long n, long long 
   int b = 0;
   long long r0 = 0;
   unsigned ncnt = 0;
+  unsigned adm = 0;   // first word of the neuron's admission bits (ADM, spiking neurons)
   float* __restrict__ gwin = gwin_of(d, n);
   constexpr bool DEXP = SYN == 2;
   const size_t second = 2 * (size_t)d.W * d.BN;   // the Y rows lie behind the two window buffers of X
@@ -1129,30 +1143,39 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step_win(long long n, long long 
   // loads, then adjoint gathers, each for all four before the next stage)
   unsigned long long m = __ballot(s && ncnt > 0);
   const int lane = threadIdx.x & 63;
+  if (ADM && m) {   // (uniform; the wavefront's neurons are one spike word)
+    const int words = s ? (int)((d.row_ptr[g - b * d.N + 1] - r0 + 63) >> 6) : 0;
+    adm = d.adm_base[(size_t)n * d.words + ((blockIdx.x * kBlock + threadIdx.x) >> 6)] + (unsigned)(dpp_scan_add(words) - words);
+  }
   while (m) {
-    long long pr[4]; unsigned cn[4]; int bs[4], Ls[4];
+    long long pr[4]; unsigned cn[4]; int bs[4], Ls[4]; unsigned ab[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      pr[j] = 0; cn[j] = 0; bs[j] = 0; Ls[j] = -1;
+      pr[j] = 0; cn[j] = 0; bs[j] = 0; Ls[j] = -1; ab[j] = 0;
       if (m) {
         const int L = __ffsll((long long)m) - 1;
         m &= m - 1;
         Ls[j] = L;
+        if (ADM) ab[j] = lane_get(adm, L);
         pr[j] = lane_get(r0, L); cn[j] = lane_get(ncnt, L); bs[j] = lane_get(b, L) * d.N;
       }
     }
     uint2 e[4];
+    unsigned long long am[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      e[j] = make_uint2(0u, 0u);
-      if ((unsigned)lane < cn[j]) e[j] = d.synb[pr[j] + lane];
+      e[j] = make_uint2(0u, 0u); am[j] = ~0ull;
+      if ((unsigned)lane < cn[j]) {
+        e[j] = d.synb[pr[j] + lane];
+        if (ADM) am[j] = d.adm_bits[ab[j]];
+      }
     }
     float gv[4], gy[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       gv[j] = 0.0f; gy[j] = 0.0f;
       const int D = (int)(e[j].x & d.dmask);
-      if ((unsigned)lane < cn[j] && n + D < T) {
+      if ((unsigned)lane < cn[j] && n + D < T && ((am[j] >> lane) & 1ull)) {
         const size_t cell = (size_t)(phi + D) * d.BN + (size_t)bs[j] + (e[j].x >> d.dbits);
         gv[j] = gwin[cell];
         if (DEXP) gy[j] = gwin[second + cell];
@@ -1163,13 +1186,13 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step_win(long long n, long long 
       if (Ls[j] < 0) continue;    // uniform
       const int D = (int)(e[j].x & d.dmask);
       float part = 0.0f;
-      if ((unsigned)lane < cn[j] && n + D < T) {
+      if ((unsigned)lane < cn[j] && n + D < T && ((am[j] >> lane) & 1ull)) {
         part = __uint_as_float(e[j].y) * (DEXP ? queue_term_of(d, gv[j], gy[j]) : gv[j]);
         unsafeAtomicAdd(&d.gsum[pr[j] + lane], gv[j]);
         if (DEXP) unsafeAtomicAdd(&d.gsum[(size_t)d.S + pr[j] + lane], gy[j]);
       }
       part = wave_sum_f(part);
-      if (cn[j] > 64u) part += near_gather<DEXP>(d, gwin, n, T, phi, pr[j] + 64, cn[j] - 64u, bs[j]);
+      if (cn[j] > 64u) part += near_gather<DEXP, ADM>(d, gwin, n, T, phi, pr[j] + 64, cn[j] - 64u, bs[j], ab[j] + 1u);
       if (lane == Ls[j]) G += part;
     }
   }
@@ -1190,7 +1213,8 @@ __global__ __launch_bounds__(kBlock) void k_bwd_step_win(long long n, long long 
 // wavefront's sum of amplitude * adjoint is added to Gacc[n mod R][g] (one wavefront per piece,
 // one piece per spike and window).
 // DEXP (double-exponential synapse): two adjoints per arrival cell, X and Y (see bwd_receiver).
-template <bool DEXP>
+// ADM (bounded kinds): admitted entries only; their bits are loaded beside the entries.
+template <bool DEXP, bool ADM>
 __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long long k0, long long n_lo, long long n_hi,
                                             long long T, int vb, int nvb) {
   XPH_BEGIN
@@ -1218,20 +1242,27 @@ __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long lon
     if (lane == 0) {
       // one wavefront per piece, one piece per spike and window: the add has no competitor; an
       // atomic without return value so that the wavefront does not wait for a load
-      unsafeAtomicAdd(&d.Gacc[(size_t)o.slot * d.BN + o.g], G);
+      unsafeAtomicAdd(&d.Gacc[(size_t)(o.slot & 0xffff) * d.BN + o.g], G);
     }
+  };
+  // admission bit of entry q of a piece
+  auto admitted = [&](const Seg& o, int q) -> bool {
+    if (!ADM) return true;
+    const int x = (int)((unsigned)o.slot >> 16) + q;
+    return (d.adm_bits[o.adm + (unsigned)(x >> 6)] >> (x & 63)) & 1ull;
   };
   auto one = [&](const Seg& o) {
     float G = 0.0f;
     for (int q = lane; q < o.len; q += 64) {
       const uint2 e = d.synb[o.p0 + q];
+      if (!admitted(o, q)) continue;
       const size_t cell = (size_t)((int)(e.x & d.dmask) - o.dlo) * d.BN + (size_t)o.base + (e.x >> d.dbits);
       G += take(e.y, cell, o.p0 + q, gwin[cell]);
     }
     finish(o, G);
   };
   long long cnt[3] = {0, 0, 0};
-  walk_segments(d, L, d.tape_bits, false, k0, n_lo, n_hi, T, vb, nvb, n_hi, cnt, one);
+  walk_segments<ADM>(d, L, d.tape_bits, false, k0, n_lo, n_hi, T, vb, nvb, n_hi, cnt, one);
   XPH(16)
   const int qn = L.qn < kSegQueue ? L.qn : kSegQueue;
   for (;;) {
@@ -1241,14 +1272,18 @@ __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long lon
     if (t >= qn) break;
     Seg o[4];
     uint2 ev[4][2];
+    bool use[4][2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       o[j].len = 0;
       if (t + j < qn) o[j] = L.q[t + j];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        ev[j][h] = make_uint2(0u, 0u);
-        if (lane + 64 * h < o[j].len) ev[j][h] = load_stream(&d.synb[o[j].p0 + lane + 64 * h]);
+        ev[j][h] = make_uint2(0u, 0u); use[j][h] = false;
+        if (lane + 64 * h < o[j].len) {
+          ev[j][h] = load_stream(&d.synb[o[j].p0 + lane + 64 * h]);
+          use[j][h] = admitted(o[j], lane + 64 * h);
+        }
       }
     }
     float gv[4][2];
@@ -1259,7 +1294,7 @@ __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long lon
       for (int h = 0; h < 2; ++h) {
         gv[j][h] = 0.0f;
         cell[j][h] = (size_t)((int)(ev[j][h].x & d.dmask) - o[j].dlo) * d.BN + (size_t)o[j].base + (ev[j][h].x >> d.dbits);
-        if (lane + 64 * h < o[j].len) gv[j][h] = gwin[cell[j][h]];
+        if (use[j][h]) gv[j][h] = gwin[cell[j][h]];
       }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1267,9 +1302,10 @@ __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long lon
       float G = 0.0f;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        if (lane + 64 * h < o[j].len) G += take(ev[j][h].y, cell[j][h], o[j].p0 + lane + 64 * h, gv[j][h]);
+        if (use[j][h]) G += take(ev[j][h].y, cell[j][h], o[j].p0 + lane + 64 * h, gv[j][h]);
       for (int q = 128 + lane; q < o[j].len; q += 64) {
         const uint2 e = d.synb[o[j].p0 + q];
+        if (!admitted(o[j], q)) continue;
         const size_t c = (size_t)((int)(e.x & d.dmask) - o[j].dlo) * d.BN + (size_t)o[j].base + (e.x >> d.dbits);
         G += take(e.y, c, o[j].p0 + q, gwin[c]);
       }
@@ -1286,11 +1322,69 @@ __device__ __forceinline__ void role_gather(const Dev& d, ExpandLds& L, long lon
 #endif
 }
 
-template <bool DEXP>
+template <bool DEXP, bool ADM>
 __global__ __launch_bounds__(kRingThreads) void k_bwd_win(Dev d, long long k0, long long n_lo, long long n_hi,
                                                           long long T, int vb0, int nvb) {
   __shared__ ExpandLds L;
-  role_gather<DEXP>(d, L, k0, n_lo, n_hi, T, vb0 + (int)blockIdx.x, nvb);
+  role_gather<DEXP, ADM>(d, L, k0, n_lo, n_hi, T, vb0 + (int)blockIdx.x, nvb);
+}
+
+// ---------------------------------------------------------------- reverse sweep: the tape of the bounded kinds
+
+// The bounded kinds (FIFO, SORTED, per synapse) are swept by the same kernels as the ring, over rows sorted by arrival
+// offset, with one difference: only the events that the queues admitted take part.  Their tape holds a spike list and an
+// admission flag (a byte) per emitted event in the caller's order; before a sweep these two kernels make of it what the
+// reverse kernels read: the spike words tape_bits, and per spike the flags of its SORTED row as one bit each, 64 to a
+// word, so that a wavefront takes 64 entries with one word.  Where a spike's words begin needs no lookup per spike: the
+// words of the spikes of one (step, 64-neuron word) follow one another in ascending order of the neuron, ceil(row length /
+// 64) each, from adm_base[step][word] = (index of the first one's first flag) / 64 + (its number on the tape), so
+// that the ranges never overlap (sum of ceil(len / 64) <= (sum of len) / 64 + number of rows).
+// A wavefront takes a row 256 entries at a time: positions in the caller's row, then the flags there.
+__global__ __launch_bounds__(kBlock) void k_tape_words(Dev d, long long T) {
+  for (long long n = blockIdx.x; n < T; n += gridDim.x) {
+    const long long lo = d.step_off[n], hi = d.step_off[n + 1];
+    for (long long e = lo + threadIdx.x; e < hi; e += kBlock) {
+      const int g = d.tape_spk[e], word = g >> 6;     // (ascending within a step: see k_fanout_step)
+      atomicOr(&d.tape_bits[(size_t)n * d.words + word], 1ull << (g & 63));
+      if (e == lo || (d.tape_spk[e - 1] >> 6) != word)
+        d.adm_base[(size_t)n * d.words + word] = (unsigned)((d.tape_evb[e] >> 6) + e);
+    }
+  }
+}
+// One wavefront per spike; blockIdx.y: share of a step's spikes.
+__global__ __launch_bounds__(kBlock) void k_adm_bits(Dev d, long long T) {
+  const int lane = threadIdx.x & 63;
+  const int wave = (int)(blockIdx.y * (kBlock / 64)) + (threadIdx.x >> 6), nwaves = (int)gridDim.y * (kBlock / 64);
+  for (long long n = blockIdx.x; n < T; n += gridDim.x) {
+    const long long lo = d.step_off[n], hi = d.step_off[n + 1];
+    for (long long e = lo + wave; e < hi; e += nwaves) {
+      const int g = d.tape_spk[e];
+      const long long evb = d.tape_evb[e];
+      // the spikes before this one in the same word (at most 63, right before it on the tape)
+      int before = -1;
+      if (lane < 63 && e - 1 - lane >= lo) before = d.tape_spk[e - 1 - lane];
+      const bool same = before >= 0 && (before >> 6) == (g >> 6);
+      int words = 0;
+      if (same) { const int i = before - trial_of(d, before) * d.N; words = (int)((d.row_ptr[i + 1] - d.row_ptr[i] + 63) >> 6); }
+      const unsigned skip = (unsigned)__builtin_amdgcn_readlane(dpp_scan_add(words), 63);
+      const int i = g - trial_of(d, g) * d.N;
+      const long long r0 = d.row_ptr[i], len = d.row_ptr[i + 1] - r0;
+      unsigned long long* out = d.adm_bits + (size_t)d.adm_base[(size_t)n * d.words + (g >> 6)] + skip;
+      const unsigned char* flag = d.tape_adm + evb;
+      for (long long q0 = 0; q0 < len; q0 += 256) {
+        unsigned at[4]; unsigned char f[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const long long q = q0 + 64 * j + lane; at[j] = q < len ? d.perm[r0 + q] : 0u; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const long long q = q0 + 64 * j + lane; f[j] = q < len ? flag[at[j]] : (unsigned char)0; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const unsigned long long m = __ballot(f[j] != 0);
+          if (lane == j && q0 + 64 * j < len) out[(q0 >> 6) + j] = m;
+        }
+      }
+    }
+  }
 }
 
 // grad_w[p] = f_p * gsum, grad_d[p] = a_p * dscale * gsum, back in the caller's synapse order.

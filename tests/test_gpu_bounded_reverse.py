@@ -1,0 +1,72 @@
+"""Reverse sweep of the bounded queue kinds on rows sorted by arrival offset, only admitted events taking part
+(k_tape_words, k_adm_bits and the reverse kernels' ADM instances), against the oracle: queues that drop and replace,
+several spikes per 64-neuron word, rows of no, few and more than 64 in-window entries, odd sizes, synaptic states, one
+launch per window and per step; and the smaller layout with its adjoint delay line."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+KINDS = [(adseq.FIFO, 3), (adseq.SORTED, 2), (adseq.SYN_FIFO, 1), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 2)]
+
+
+@pytest.mark.parametrize("kind,cap", KINDS)
+@pytest.mark.parametrize("n,b,T,d_max,fan,rate,tau_syn,tau_rise,continuous,surrogate,env", [
+    (700, 3, 90, 40, 200, 900.0, 0.0, 0.0, False, adseq.SURR_SUPERSPIKE, {}),
+    (701, 1, 75, 2, 300, 900.0, 0.0, 0.0, False, adseq.GRAD_SPIKE_TIME, {}),
+    (1500, 2, 70, 30, 120, 900.0, 0.0, 0.0, True, adseq.SURR_SUPERSPIKE, {"ADSEQ_RING_REVERSE_BLOCKS": "8"}),
+    (2050, 4, 50, 30, 60, 900.0, 0.0, 0.0, False, adseq.GRAD_SPIKE_TIME, {"ADSEQ_RING_REVERSE_BLOCKS": "8"}),
+    (9000, 2, 40, 20, 40, 2500.0, 0.0, 0.0, False, adseq.SURR_SUPERSPIKE, {"ADSEQ_RING_REVERSE_BLOCKS": "8"}),
+    (501, 2, 70, 30, 150, 900.0, 5.0, 0.0, False, adseq.GRAD_SPIKE_TIME, {}),
+    (500, 2, 70, 30, 150, 900.0, 5.0, 1.0, False, adseq.SURR_SUPERSPIKE, {}),
+    (600, 2, 70, 30, 150, 900.0, 5.0, 0.0, True, adseq.SURR_SUPERSPIKE, {"ADSEQ_RING_RESIDENT_REVERSE": "0"}),
+    (600, 2, 70, 30, 150, 900.0, 0.0, 0.0, False, adseq.SURR_SUPERSPIKE, {"ADSEQ_RING_RESIDENT_REVERSE": "0", "ADSEQ_RING_WINDOW": "64"}),
+    (400, 2, 60, 30, 150, 900.0, 5.0, 1.0, False, adseq.GRAD_SPIKE_TIME, {"ADSEQ_SORTED_REVERSE": "0"}),
+    (400, 2, 60, 30, 150, 900.0, 0.0, 0.0, True, adseq.SURR_SUPERSPIKE, {"ADSEQ_SORTED_REVERSE": "0"})])
+def test_bounded_reverse(kind, cap, n, b, T, d_max, fan, rate, tau_syn, tau_rise, continuous, surrogate, env, monkeypatch):
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=0.6 / fan, w_std=0.6 / fan, continuous=continuous)
+    wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, surrogate=surrogate, n_threads=8)
+    assert ref.spikes.sum() > 100
+    if kind in (adseq.FIFO, adseq.SORTED):   # (a queue per synapse loses events only where its source spikes again in time)
+        assert ref.counters()["dropped"] > 0
+    rng = np.random.default_rng(n)
+    dc = rng.normal(0, 1e-3, (b, n)).astype(np.float32)
+    dU = rng.normal(0, 1e-4, (T, b, n)).astype(np.float32)
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T + 3, surrogate=surrogate,
+                      tape_spike_capacity=T * b * n // 2, tape_event_capacity=T * b * wl.n_synapses // 2)
+    for du in (dU, None):   # (the second time after a reset: tape and bits of the run before are not there any more)
+        gw, gd = ref.backward(dc, du)
+        sim.run(0, T)
+        g_w, g_d = (torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2))
+        sim.backward(torch.from_numpy(dc).to(sim.dev), None if du is None else torch.from_numpy(du).to(sim.dev), g_w, g_d)
+        torch.cuda.synchronize()
+        assert sim.counters()["error_bits"] == 0
+        H.grad_close(g_w.cpu().numpy(), gw)
+        H.grad_close(g_d.cpu().numpy(), gd)
+        sim.reset()
+    sim.close()
+
+
+def test_small_layout_is_kept_for_the_static_workspace():
+    """A configuration that only the smaller layout brings below the static workspace's 32 MB is still accepted there."""
+    wl = synth.ragged_network(14000, 10, 250, seed=5, rate_hz=500.0, t=40, b=1, w_mean=0.05, w_std=0.05)
+    ref = oracle.Run(wl, adseq.FIFO, 2, n_steps=40, n_threads=8)
+    sim = adseq.Adseq(wl, adseq.FIFO, 2, record_tape=True, max_steps=40, static_workspace=True)
+    assert 16 << 20 < sim.workspace_bytes <= adseq.STATIC_WORKSPACE_BYTES
+    dc = np.random.default_rng(1).normal(0, 1e-3, (1, 14000)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    sim.run(0, 40)
+    g_w, g_d = (torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2))
+    sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+    torch.cuda.synchronize()
+    H.grad_close(g_w.cpu().numpy(), gw)
+    H.grad_close(g_d.cpu().numpy(), gd)
+    sim.close()
