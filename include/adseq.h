@@ -151,7 +151,8 @@ typedef struct {
                                   (tape_spike_capacity * ceil(S / N))                         */
   int64_t step_event_capacity; /* FIFO/SORTED: events per step that may wait in the overflow
                                   list of their target (more than 8 contenders for one target
-                                  in one step); 0 = default min(B * S, 2^24).  RING: events
+                                  in one step); 0 = default min(B * S, 2^24), without a tape up
+                                  to 2^27 for open-loop stretches of several steps.  RING: events
                                   the staging buffer of a window holds (the rest takes a slower
                                   route, same result); 0 = default                            */
   void *workspace;             /* device memory, 256-byte aligned                             */
@@ -178,7 +179,9 @@ int adseq_create(const adseq_config *cfg, adseq_t **out);
  * ADSEQ_E_WORKSPACE if adseq_workspace_bytes(cfg) exceeds the limit, or if the device's static
  * workspace already holds a live handle (one at a time per device: two would share the memory
  * and race); adseq_destroy releases it.  The workspace keeps the last handle's contents;
- * everything a new handle needs to start from zero is cleared here. */
+ * everything a new handle needs to start from zero is cleared here.  The bounded kinds come with a
+ * smaller state if need be (slower reverse sweeps and open-loop runs, same results): then the limit
+ * is on that. */
 #define ADSEQ_STATIC_WORKSPACE_BYTES (32u << 20)
 int adseq_create_static(const adseq_config *cfg, adseq_t **out);
 

@@ -22,7 +22,7 @@
 //   tape_*                                  membrane tape, spike list, admission flags
 //   gwin, Gacc, gsum                        reverse sweep: adjoint rows of the window, far queue terms, per-synapse sums
 //   adm_base, adm_bits                      bounded kinds, reverse sweep: admission flags of the sorted rows, one bit each
-//   bwd_ring, bwd_G, tape_row               bounded kinds whose workspace must stay below 32 MB: adjoint delay line [R][BN], queue terms
+//   bwd_ring, bwd_G, tape_row               bounded kinds in the static workspace that have no room for those: adjoint delay line [R][BN], queue terms
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -137,12 +137,13 @@ struct Dev {
   int prefetch;         // FIFO/SORTED: 1 = few targets (B N <= 2^18): the step kernel loads keys and row lengths up front
   int fsplit;           // FIFO/SORTED: blocks per neuron block of the closed-loop fan-out (1 .. kFanSplitMax)
   int nw, cpad;         // FIFO: mask words per target = ceil(C / 32); C rounded up to a multiple of 8
+  int qsteps;           // FIFO/SORTED: contender buffers (1, or as many as an open-loop stretch has steps)
   int* occ;
   int* head;
   unsigned* min_k;      // FIFO/SORTED: earliest stored arrival step per target (0xffffffff: none)
-  int* cnt;             // contenders registered per target since its last admission
-  uint4* cont;          // [kCont][BN] contender records (see bounded_queues.h)
-  int* c_head;          // overflow list head per target (-1: empty)
+  int* cnt;             // [qsteps][BN] contenders registered per target since its last admission
+  uint4* cont;          // [qsteps][kCont][BN] contender records (see bounded_queues.h)
+  int* c_head;          // [qsteps][BN] overflow list head per target (-1: empty)
   long long* pool_p;
   long long* pool_t;
   int* pool_next;
@@ -548,6 +549,7 @@ struct Layout {
   int R, dbits, nblk, words;
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
+  int qsteps;           // FIFO / SORTED: contender buffers
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
 
@@ -705,7 +707,9 @@ bool host_validate(const adseq_config* c) {
 
 // sorted_rev: bounded kinds with tape get what the ring's reverse kernels need (rows sorted by arrival offset, window
 // buffers, admission bits) instead of an adjoint delay line.
-bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev) {
+// qsteps: steps of an open-loop stretch that FIFO and SORTED register at once; fewer where their buffers, or the overflow
+// entries that their worst case needs (every synapse of every trial in every step), would be out of proportion.
+bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   if (!host_validate(c)) return false;
   if (c->kind == ADSEQ_RING || !c->record_tape) sorted_rev = false;
   const size_t BN = (size_t)c->n_neurons * c->batch;
@@ -727,11 +731,16 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev) {
       if (L->event_cap >= (1LL << 40) - 1) return false;   // admission-flag indices are packed into 40 bits
     }
   }
+  L->qsteps = 1;
   if (ptq) {
+    const double bs = (double)c->batch * (double)S;
+    while (qsteps > 1 && ((double)qsteps * BN * (kCont * 16 + 8) > 1073741824.0 ||
+                          (double)qsteps * bs > (c->step_event_capacity ? (double)c->step_event_capacity : 134217728.0))) qsteps >>= 1;
+    L->qsteps = qsteps;
     long long cap = c->step_event_capacity;
     if (!cap) {
-      const double bs = (double)c->batch * (double)S;
       cap = bs < 16777216.0 ? (long long)bs : 16777216LL;
+      if (qsteps > 1) cap = (long long)(qsteps * bs);
       if (cap < 1) cap = 1;
     }
     if (cap > 0x7fffffffLL) cap = 0x7fffffffLL;
@@ -799,9 +808,9 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev) {
   L->occ = take(ptq ? BN * 4 : 0);
   L->head = take(ptq ? BN * 4 : 0);
   L->min_k = take(ptq ? BN * 4 : 0);
-  L->cnt = take(ptq ? BN * 4 : 0);
-  L->cont = take(ptq ? (size_t)kCont * BN * 16 : 0);
-  L->c_head = take(ptq ? BN * 4 : 0);
+  L->cnt = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
+  L->cont = take(ptq ? (size_t)L->qsteps * kCont * BN * 16 : 0);
+  L->c_head = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
   L->pool_p = take((size_t)L->pool_cap * 8);
   L->pool_t = take((size_t)L->pool_cap * 8);
   L->pool_next = take((size_t)L->pool_cap * 4);
@@ -874,17 +883,14 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev) {
   return true;
 }
 // The bounded kinds' reverse sweep takes the ring's kernels (a window of steps per launch; 16 x 1,000 neurons, FIFO[32]:
-// 2,000 steps forward and back 40.6 -> 27.7 ms) wherever their rows sorted by arrival offset fit: not where 2^32 words of admission
-// bits are too few, and not where only the smaller layout -- an adjoint delay line, two launches per step -- stays within
-// the workspace that adseq_create_static has.
-bool make_layout(const adseq_config* c, Layout* L) {
-  const int off = env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 0;
-  if (!off && layout_as(c, L, true)) {
-    if (!L->sorted_rev || L->total <= (size_t)ADSEQ_STATIC_WORKSPACE_BYTES) return true;
-    Layout small;
-    if (!layout_as(c, &small, false) || small.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES) return true;
-  }
-  return layout_as(c, L, false);
+// 2,000 steps forward and back 40.6 -> 27.7 ms) wherever 2^32 words of admission bits are enough for the tape, and a handle
+// without a tape, which may run open loop, gets the buffers of a whole stretch (k_queue_steps).  small: neither -- an
+// adjoint delay line and two launches per reverse step, a stretch of one step -- for what only so fits the static workspace.
+bool make_layout(const adseq_config* c, Layout* L, bool small = false) {
+  if (!c) return false;
+  if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
+      layout_as(c, L, true, c->record_tape ? 1 : env_pow2("ADSEQ_QUEUE_STEPS", kQueueSteps, 1, kQueueSteps))) return true;
+  return layout_as(c, L, false, 1);
 }
 
 int fail(adseq* h, int code, const char* fmt, ...) {
@@ -947,10 +953,10 @@ void launch_reset(adseq* h, hipStream_t st) {
   } else {
     fill_u32(st, d.occ, 0u, BN);
     fill_u32(st, d.head, 0u, BN);
-    fill_u32(st, d.c_head, 0xffffffffu, BN);
+    fill_u32(st, d.c_head, 0xffffffffu, (size_t)d.qsteps * BN);
     fill_u32(st, d.min_k, 0xffffffffu, BN);
     if (d.kind == ADSEQ_FIFO) fill_u32(st, d.vmask, 0u, (size_t)d.nw * BN);
-    fill_u32(st, d.cnt, 0u, BN);
+    fill_u32(st, d.cnt, 0u, (size_t)d.qsteps * BN);
     fill_u32(st, d.blk, 0u, ((size_t)d.nblk + fan_slots(d.nblk)) * sizeof(BlkCtr) / 4);
     h->pending_admit = false;
   }
@@ -1454,7 +1460,7 @@ void* static_workspace(int* dev_out) {
   return g_scratch_ptr[dev];
 }
 
-int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, adseq* storage, adseq_t** out);
+int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t workspace_bytes, adseq* storage, adseq_t** out);
 
 }  // namespace
 
@@ -1468,19 +1474,22 @@ size_t adseq_workspace_bytes(const adseq_config* cfg) {
 
 int adseq_create(const adseq_config* cfg, adseq_t** out) {
   if (!cfg || !out) return ADSEQ_E_INVALID_ARG;
-  return create_in(cfg, cfg->workspace, cfg->workspace_bytes, nullptr, out);
+  Layout L;
+  if (!make_layout(cfg, &L)) return ADSEQ_E_INVALID_ARG;
+  return create_in(cfg, L, cfg->workspace, cfg->workspace_bytes, nullptr, out);
 }
 
 int adseq_create_static(const adseq_config* cfg, adseq_t** out) {
   if (!cfg || !out) return ADSEQ_E_INVALID_ARG;
   Layout L;
   if (!make_layout(cfg, &L)) return ADSEQ_E_INVALID_ARG;
-  if (L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES) return ADSEQ_E_WORKSPACE;   // does not fit the static workspace
+  if (L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES && (!make_layout(cfg, &L, true) || L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES))
+    return ADSEQ_E_WORKSPACE;   // does not fit the static workspace
   int dev = -1;
   void* ws = static_workspace(&dev);
   if (!ws) return ADSEQ_E_HIP;
   if (g_static_busy[dev]) return ADSEQ_E_WORKSPACE;   // this device's static workspace already holds a live handle
-  const int rc = create_in(cfg, ws, (size_t)ADSEQ_STATIC_WORKSPACE_BYTES, &g_static_handle[dev], out);
+  const int rc = create_in(cfg, L, ws, (size_t)ADSEQ_STATIC_WORKSPACE_BYTES, &g_static_handle[dev], out);
   if (rc == ADSEQ_OK) g_static_busy[dev] = true;
   return rc;
 }
@@ -1491,9 +1500,7 @@ namespace {
 
 // Body of adseq_create / adseq_create_static: the handle lives in `storage` if given (nothing is
 // allocated then), else on the heap.
-int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, adseq* storage, adseq_t** out) {
-  Layout L;
-  if (!make_layout(cfg, &L)) return ADSEQ_E_INVALID_ARG;
+int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t workspace_bytes, adseq* storage, adseq_t** out) {
   if (!cfg->row_ptr) return ADSEQ_E_INVALID_ARG;
   if (cfg->n_synapses > 0) {   // a network without synapses needs none of the per-synapse arrays
     if (!cfg->weight || !cfg->col) return ADSEQ_E_INVALID_ARG;
@@ -1571,6 +1578,7 @@ int create_in(const adseq_config* cfg, void* workspace, size_t workspace_bytes, 
   d.tape_bits = (unsigned long long*)(ws + L.tape_bits);
   d.spk_count = (int*)(ws + L.spk_count);
   d.sorted_rev = L.sorted_rev ? 1 : 0;
+  d.qsteps = L.qsteps;
   d.adm_base = (unsigned*)(ws + L.adm_base); d.adm_bits = (unsigned long long*)(ws + L.adm_bits);
   d.gwin = (float*)(ws + L.gwin); d.Gacc = (float*)(ws + L.Gacc); d.gsum = (float*)(ws + L.gsum);
   d.wspk = (unsigned long long*)(ws + L.wspk); d.near_nspk = (int*)(ws + L.near_cnt); d.near_nev = d.near_nspk + 64;
@@ -1815,7 +1823,35 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }
-  for (int64_t k = 0; k < n_steps; ++k) {
+  int64_t done = 0;
+  if (h->dev.qsteps > 1 && n_steps >= 4 && (I_stride == 0 || I_stride >= h->dev.BN) && step0 == h->next_step) {
+    // FIFO / SORTED: stretches of steps (k_fanout_steps, k_queue_steps) for all steps but the last, whose events stay
+    // pending: an adseq_enqueue for the same step may add to them.  Output rows that overlap, where the later step's
+    // values stay, go step by step.
+    const Dev& d = h->dev;
+    hipStream_t st = (hipStream_t)stream;
+    flush_admit(h, st);
+    for (int64_t k = 0; k < n_steps - 1;) {
+      const int cnt = (int)(n_steps - 1 - k < d.qsteps ? n_steps - 1 - k : d.qsteps);
+      QueueOffsets o;
+      for (int j = 0; j < cnt; ++j) o.off[j] = spike_offsets[k + j];
+      const dim3 fan(kFanoutBlocks / kQueueSteps, (unsigned)cnt), fb(kBlock), own((unsigned)((d.BN + 63) / 64)), ob(64);
+      if (d.kind == ADSEQ_FIFO) {
+        hipLaunchKernelGGL((k_fanout_steps<ADSEQ_FIFO>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
+        hipLaunchKernelGGL((k_queue_steps<ADSEQ_FIFO>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
+      } else {
+        hipLaunchKernelGGL((k_fanout_steps<ADSEQ_SORTED>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
+        hipLaunchKernelGGL((k_queue_steps<ADSEQ_SORTED>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
+      }
+      k += cnt;
+      h->next_step = step0 + k;
+      h->enq_calls += cnt;
+      h->tape_ok = false;
+      done = k;
+    }
+    HIP_TRY(h, hipGetLastError());
+  }
+  for (int64_t k = done; k < n_steps; ++k) {
     int rc = adseq_deliver(h, step0 + k, I_out + k * I_stride, stream);
     if (rc == ADSEQ_OK) rc = adseq_enqueue(h, step0 + k, spike_ids + spike_offsets[k], n_spikes + k, stream);
     if (rc != ADSEQ_OK) return rc;

@@ -71,8 +71,19 @@ __device__ __forceinline__ unsigned cont_arrival(const uint4& c, unsigned kn) {
 }
 
 // Queue state of one target in registers: stored events, earliest stored arrival step
-// (0xffffffff: none; SORTED only), index of the front (SORTED), first mask word (FIFO).
+// (0xffffffff: none; FIFO: only where several steps run in one launch), index of the front (SORTED), first mask word (FIFO).
 struct QState { int occ; unsigned mn; int hd; unsigned m0; };
+
+// Where the contenders of one step are registered: ticket counters [BN], contender records [kCont][BN], overflow list
+// heads [BN].  (There are Dev::qsteps of each; a step of its own launches uses the first.)
+struct QBuf { int* cnt; uint4* cont; int* head; };
+__device__ __forceinline__ QBuf queue_buf(const Dev& d, int j) {
+  QBuf b;
+  b.cnt = d.cnt + (size_t)j * d.BN;
+  b.cont = d.cont + (size_t)j * kCont * d.BN;
+  b.head = d.c_head + (size_t)j * d.BN;
+  return b;
+}
 
 // FIFO: stores an admitted event in the first free slot of target g.
 __device__ __forceinline__ void fifo_insert(const Dev& d, int g, QState& q, unsigned k, int a) {
@@ -150,18 +161,19 @@ __device__ __forceinline__ void take_event(const Dev& d, int g, unsigned kn, QSt
     return;
   }
   if (KIND == ADSEQ_FIFO) fifo_insert(d, g, q, k, a);
-  else { sorted_insert(d, g, q, k, a); q.mn = k < q.mn ? k : q.mn; }
+  else sorted_insert(d, g, q, k, a);
+  q.mn = k < q.mn ? k : q.mn;
   q.occ += 1;
 }
 
 // The rare case: more than kCont contenders for one target in one step, the later ones in the
 // overflow list.  Same rule, general selection.
 template <int KIND, int MODE>
-__device__ __forceinline__ void admit_overflowed(const Dev& d, int g, int K, int take, unsigned kn,
+__device__ __forceinline__ void admit_overflowed(const Dev& d, const QBuf& qb, int g, int K, int take, unsigned kn,
                                               QState& q, StepAcc& r, const uint4* cc) {
   const int nc = kCont;                // the contender slots are all taken
-  const int ovf_head = d.c_head[g];    // the others: overflow list
-  d.c_head[g] = -1;
+  const int ovf_head = qb.head[g];     // the others: overflow list
+  qb.head[g] = -1;
   if (take == K) {
     // room for all: any order
 #pragma unroll
@@ -214,9 +226,9 @@ __device__ __forceinline__ void admit_overflowed(const Dev& d, int g, int K, int
 // (number of records with a smaller synapse index) decides, and is only computed when there are
 // more contenders than free slots.
 template <int KIND, int MODE>
-__device__ __forceinline__ void admit_contenders(const Dev& d, int g, int K, int free_slots, unsigned kn,
+__device__ __forceinline__ void admit_contenders(const Dev& d, const QBuf& qb, int g, int K, int free_slots, unsigned kn,
                                                  QState& q, StepAcc& r, const uint4* cc) {
-  d.cnt[g] = 0;
+  qb.cnt[g] = 0;
   const int take = K < free_slots ? K : free_slots;
   if (K <= kCont) {
     int rank[kCont];
@@ -250,7 +262,80 @@ __device__ __forceinline__ void admit_contenders(const Dev& d, int g, int K, int
     }
     return;
   }
-  admit_overflowed<KIND, MODE>(d, g, K, take, kn, q, r, cc);
+  admit_overflowed<KIND, MODE>(d, qb, g, K, take, kn, q, r, cc);
+}
+
+// Takes what is due at step kn from the front of the circular array (SORTED), four slots loaded at a time.
+__device__ __forceinline__ void sorted_pop(const Dev& d, int g, unsigned kn, QState& q, StepAcc& r) {
+  const uint2* __restrict__ sl = d.slot + (size_t)g * d.C;
+  int occ = q.occ, hd = q.hd;
+  unsigned front = q.mn;
+  while (occ > 0 && front == kn) {
+    uint2 e[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      e[j] = make_uint2(0xffffffffu, 0u);
+      if (j < occ) { int ph = hd + j; if (ph >= d.C) ph -= d.C; e[j] = sl[ph]; }
+    }
+    int took = 0;
+    unsigned next = kn;     // four taken and more stored: the next trip looks at the new front
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (took == j && j < occ && e[j].x == kn) { r.acc = wrap_add(r.acc, (int)e[j].y); ++took; }
+      else if (took == j) next = e[j].x;   // first slot not taken (0xffffffff past the end)
+    }
+    hd += took; if (hd >= d.C) hd -= d.C;
+    occ -= took;
+    r.popped += took;
+    front = occ > 0 ? next : 0xffffffffu;
+  }
+  q.occ = occ; q.hd = hd; q.mn = occ > 0 ? front : 0xffffffffu;
+}
+
+// Looks at all keys of target g (FIFO): takes the events due at step kn (TAKE) and leaves in q.mn the earliest arrival of
+// those that stay.
+template <bool TAKE>
+__device__ __forceinline__ void fifo_scan(const Dev& d, int g, unsigned kn, QState& q, StepAcc& r) {
+  unsigned nearest = 0xffffffffu;   // steps from kn to the earliest that stays
+  for (int w = 0; w < d.nw; ++w) {
+    unsigned m = w == 0 ? q.m0 : d.vmask[(size_t)g * d.nw + w];
+    if (!m) continue;
+    const uint4* kp = reinterpret_cast<const uint4*>(d.fkey + (size_t)g * d.cpad + 32 * w);
+    uint4 kq[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { kq[c] = make_uint4(0u, 0u, 0u, 0u); if (32 * w + 8 * c < d.cpad) kq[c] = kp[c]; }
+    unsigned due = 0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const unsigned wd[4] = {kq[c].x, kq[c].y, kq[c].z, kq[c].w};
+#pragma unroll
+      for (int h = 0; h < 8; ++h) {
+        const unsigned away = ((h & 1 ? wd[h >> 1] >> 16 : wd[h >> 1]) - kn) & 0xffffu;
+        const bool here = (m >> (8 * c + h)) & 1u;
+        if (TAKE && here && away == 0u) due |= 1u << (8 * c + h);
+        else if (here && away < nearest) nearest = away;
+      }
+    }
+    if (TAKE && due) {
+      m &= ~due;
+      const int nd = __popc(due);
+      if (w == 0) q.m0 = m; else d.vmask[(size_t)g * d.nw + w] = m;
+      const int* __restrict__ ap = d.famp + (size_t)g * d.C + 32 * w;
+      while (due) {
+        // up to four amplitude loads in flight
+        int j[4], av[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) { j[x] = due ? __ffs((int)due) - 1 : -1; due &= due - 1u; }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) av[x] = j[x] >= 0 ? ap[j[x]] : 0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) r.acc = wrap_add(r.acc, av[x]);
+      }
+      r.popped += nd;
+      q.occ -= nd;
+    }
+  }
+  q.mn = nearest == 0xffffffffu ? 0xffffffffu : kn + nearest;
 }
 
 // Block-level event counters in LDS: [0] offered, [1] admitted, [2] delivered, [3..5] the same as
@@ -311,7 +396,8 @@ __global__ __launch_bounds__(kBlock) void k_neurons(Dev d, long long n, int pari
     }
   } else if (act) {
     // everything the thread needs first, loaded together
-    const int K = d.cnt[g];
+    const QBuf qb = queue_buf(d, 0);
+    const int K = qb.cnt[g];
     QState q;
     q.mn = KIND == ADSEQ_SORTED ? d.min_k[g] : 0u;
     q.hd = KIND == ADSEQ_SORTED ? d.head[g] : 0;
@@ -392,36 +478,12 @@ __global__ __launch_bounds__(kBlock) void k_neurons(Dev d, long long n, int pari
         r.popped += ndue;
         q.occ -= ndue;
       }
-      if (K > 0) admit_contenders<KIND, MODE>(d, g, K, d.C - q0.occ, kn, q, r, cc);
+      if (K > 0) admit_contenders<KIND, MODE>(d, qb, g, K, d.C - q0.occ, kn, q, r, cc);
     } else {
       // ordered by arrival: admission first (an insert may land at the front), then everything
       // due now is taken from the front of the circular array, four slots loaded at a time
-      if (K > 0) admit_contenders<KIND, MODE>(d, g, K, d.C - q0.occ, kn, q, r, cc);
-      if (MODE != 0) {
-        const uint2* __restrict__ sl = d.slot + (size_t)g * d.C;
-        int occ = q.occ, hd = q.hd;
-        unsigned front = q.mn;
-        while (occ > 0 && front == kn) {
-          uint2 e[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            e[j] = make_uint2(0xffffffffu, 0u);
-            if (j < occ) { int ph = hd + j; if (ph >= d.C) ph -= d.C; e[j] = sl[ph]; }
-          }
-          int took = 0;
-          unsigned next = kn;     // four taken and more stored: the next trip looks at the new front
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (took == j && j < occ && e[j].x == kn) { r.acc = wrap_add(r.acc, (int)e[j].y); ++took; }
-            else if (took == j) next = e[j].x;   // first slot not taken (0xffffffff past the end)
-          }
-          hd += took; if (hd >= d.C) hd -= d.C;
-          occ -= took;
-          r.popped += took;
-          front = occ > 0 ? next : 0xffffffffu;
-        }
-        q.occ = occ; q.hd = hd; q.mn = occ > 0 ? front : 0xffffffffu;
-      }
+      if (K > 0) admit_contenders<KIND, MODE>(d, qb, g, K, d.C - q0.occ, kn, q, r, cc);
+      if (MODE != 0) sorted_pop(d, g, kn, q, r);
     }
     if (q.occ != q0.occ) d.occ[g] = q.occ;
     if (KIND == ADSEQ_SORTED && q.mn != q0.mn) d.min_k[g] = q.mn;
@@ -501,12 +563,15 @@ __device__ __forceinline__ void push_rows_latest(const Dev& d, long long n, cons
 __device__ __forceinline__ void push_rows_bins(const Dev& d, long long n, const RowRef* rr, int nrows,
                                                long long stride, int& c_adm, long long& s_adm);
 
+// EARLY: the occupancy at the end of step n is known: an event whose target is full is dropped here.  Otherwise (several
+// steps' spikes registered in one launch) every event is a contender, and the owner's selection drops it.
 // Offers, for each of up to four row shares of step n, the entries r0 + first + threadIdx.x +
 // t * stride (t = 0, 1, ...) to their targets.  An event whose target is already full
 // is dropped here; the others register as contenders (see the header of this file).  Each stage is
 // done for all four rows before the next, so that the loads, the occupancy gathers and the ticket
 // atomics are in flight together.  The whole block must call it together.
-__device__ __forceinline__ void offer_rows(const Dev& d, long long n, const RowRef* rr, int nrows,
+template <bool EARLY>
+__device__ __forceinline__ void offer_rows(const Dev& d, const QBuf& qb, long long n, const RowRef* rr, int nrows,
                                            long long stride) {
   const int lane = threadIdx.x & 63;
   const size_t BN = (size_t)d.BN;
@@ -527,12 +592,12 @@ __device__ __forceinline__ void offer_rows(const Dev& d, long long n, const RowR
     for (int j = 0; j < 4; ++j) {
       gt[j] = rr[j].b * d.N + (int)(pk[j] >> d.dbits);
       contend[j] = false;
-      if (valid[j]) contend[j] = d.occ[gt[j]] < d.C;
+      if (valid[j]) contend[j] = !EARLY || d.occ[gt[j]] < d.C;
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       tk[j] = -1;
-      if (contend[j]) tk[j] = atomicAdd(&d.cnt[gt[j]], 1);
+      if (contend[j]) tk[j] = atomicAdd(&qb.cnt[gt[j]], 1);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -540,7 +605,7 @@ __device__ __forceinline__ void offer_rows(const Dev& d, long long n, const RowR
       const long long tidx = (valid[j] && rr[j].tbase >= 0) ? rr[j].tbase + (p[j] - rr[j].r0) : -1;
       if (tidx >= 0) d.tape_adm[tidx] = contend[j] ? 1 : 0;
       if (contend[j] && tk[j] < kCont)
-        d.cont[(size_t)tk[j] * BN + gt[j]] = cont_pack(p[j], tidx, (unsigned)(n + D) & 0xffffu, a[j]);
+        qb.cont[(size_t)tk[j] * BN + gt[j]] = cont_pack(p[j], tidx, (unsigned)(n + D) & 0xffffu, a[j]);
       // the others: wavefront-aggregated claim of pool entries, pushed on the target's list
       const bool over = contend[j] && tk[j] >= kCont;
       const unsigned long long cm = __ballot(over);
@@ -553,12 +618,12 @@ __device__ __forceinline__ void offer_rows(const Dev& d, long long n, const RowR
           if (x >= d.pool_cap) {
             // no room to remember it: it can only be dropped, and the run is flagged as invalid
             atomicOr(&d.ctr->err, ERR_POOL);
-            atomicSub(&d.cnt[gt[j]], 1);
+            atomicSub(&qb.cnt[gt[j]], 1);
             if (tidx >= 0) d.tape_adm[tidx] = 0;
           } else {
             d.pool_p[x] = p[j]; d.pool_t[x] = tidx;
             d.pool_k[x] = (unsigned)(n + D); d.pool_a[x] = a[j];
-            d.pool_next[x] = atomicExch(&d.c_head[gt[j]], x);
+            d.pool_next[x] = atomicExch(&qb.head[gt[j]], x);
           }
         }
       }
@@ -692,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void k_fanout_step(Dev d, long long n, int 
       if (KIND == ADSEQ_SYN_FIFO) push_rows(d, n, rr, nrows, (long long)d.fsplit * kBlock, c_adm, s_adm);
       else if (KIND == ADSEQ_SYN_LATEST) push_rows_latest(d, n, rr, nrows, (long long)d.fsplit * kBlock, c_adm, s_adm);
       else if (KIND == ADSEQ_SYN_BINS) push_rows_bins(d, n, rr, nrows, (long long)d.fsplit * kBlock, c_adm, s_adm);
-      else offer_rows(d, n, rr, nrows, (long long)d.fsplit * kBlock);
+      else offer_rows<true>(d, queue_buf(d, 0), n, rr, nrows, (long long)d.fsplit * kBlock);
     }
   }
   if (per_synapse_kind(KIND)) push_counts_flush(d, c_adm, s_adm, d.blk[d.nblk + blockIdx.x]);
@@ -705,17 +770,15 @@ __global__ __launch_bounds__(kBlock) void k_fanout_step(Dev d, long long n, int 
 
 #undef ADSEQ_LOAD_GROUP
 
-// Open-loop fan-out: the spikes come as the caller's list of flat neuron indices; one block per
-// spike (grid-stride over the list).
-template <int KIND>
-__global__ __launch_bounds__(kBlock) void k_fanout_list(Dev d, long long n, const int* __restrict__ spk,
-                                                        const int* __restrict__ n_spk_ptr) {
-  int nspk = *n_spk_ptr;
+// Open-loop fan-out: the spikes come as the caller's list of flat neuron indices; one block (bx of nbx) per
+// spike (stride nbx over the list).  EARLY, qb: see offer_rows (per-target kinds).
+template <int KIND, bool EARLY>
+__device__ __forceinline__ void fanout_list(const Dev& d, const QBuf& qb, long long n, const int* __restrict__ spk, int nspk, int bx, int nbx, BlkCtr& bc) {
   nspk = nspk < 0 ? 0 : (nspk > d.BN ? d.BN : nspk);
   long long c_off = 0, s_off = 0;
   int c_adm = 0;
   long long s_adm = 0;
-  for (int e = blockIdx.x; e < nspk; e += gridDim.x) {
+  for (int e = bx; e < nspk; e += nbx) {
     const int g = spk[e];
     if ((unsigned)g >= (unsigned)d.BN) continue;  // uniform over the block
     const int b = trial_of(d, g), i = g - b * d.N;
@@ -727,13 +790,109 @@ __global__ __launch_bounds__(kBlock) void k_fanout_list(Dev d, long long n, cons
     if (KIND == ADSEQ_SYN_FIFO) push_rows(d, n, rr, 4, 4LL * kBlock, c_adm, s_adm);
     else if (KIND == ADSEQ_SYN_LATEST) push_rows_latest(d, n, rr, 4, 4LL * kBlock, c_adm, s_adm);
     else if (KIND == ADSEQ_SYN_BINS) push_rows_bins(d, n, rr, 4, 4LL * kBlock, c_adm, s_adm);
-    else offer_rows(d, n, rr, 4, 4LL * kBlock);
+    else offer_rows<EARLY>(d, qb, n, rr, 4, 4LL * kBlock);
   }
-  if (per_synapse_kind(KIND)) push_counts_flush(d, c_adm, s_adm, d.blk[d.nblk + blockIdx.x]);
-  if (threadIdx.x == 0 && c_off) {
-    BlkCtr& bc = d.blk[d.nblk + blockIdx.x];   // private to this block
-    atomicAdd(&bc.offered, (unsigned long long)c_off);   // atomics without return value: nobody waits for a load
+  if (per_synapse_kind(KIND)) push_counts_flush(d, c_adm, s_adm, bc);
+  if (threadIdx.x == 0 && c_off) {   // (atomics without return value: nobody waits for a load)
+    atomicAdd(&bc.offered, (unsigned long long)c_off);
     atomicAdd((unsigned long long*)&bc.sum_offered, (unsigned long long)s_off);
+  }
+}
+template <int KIND>
+__global__ __launch_bounds__(kBlock) void k_fanout_list(Dev d, long long n, const int* __restrict__ spk,
+                                                        const int* __restrict__ n_spk_ptr) {
+  fanout_list<KIND, true>(d, queue_buf(d, 0), n, spk, *n_spk_ptr, (int)blockIdx.x, (int)gridDim.x, d.blk[d.nblk + blockIdx.x]);
+}
+
+// Open loop, FIFO and SORTED: a stretch of up to qsteps steps in TWO launches.  What the spikes of a step offer does not
+// depend on the queues, and what a queue does depends on nothing but its own events: so the rows of the spikes of all the
+// steps are registered first, every step in contender buffers of its own (k_fanout_steps: a grid row per step), and then the
+// thread that owns a target takes it through all the steps by itself (k_queue_steps): admission and pop as in
+// k_neurons, the events of the stretch's last step admitted at its end.  Nothing binds the targets of a wavefront to the
+// same step: each goes from one step in which something is due or was offered to its next one (the earliest stored
+// arrival is kept in a register, the steps with contenders in a bit mask), so the chains of dependent accesses -- what
+// this kernel is bound by -- are as many as one target has such steps, not as many as the wavefront has.  The currents
+// are gathered in LDS and stored row by row.
+// 10,000 independent FIFO[4] queues, 2.5 spikes per step: 8.7 us per step by two launches per step, 0.41 us so.
+constexpr int kQueueSteps = 64;   // steps of the longest stretch
+struct QueueOffsets { long long off[kQueueSteps]; };   // first spike of every step in the caller's list
+template <int KIND>
+__global__ __launch_bounds__(kBlock) void k_fanout_steps(Dev d, long long n0, const int* __restrict__ spk,
+                                                         const int* __restrict__ n_spk, QueueOffsets o) {
+  const int k = blockIdx.y;
+  fanout_list<KIND, false>(d, queue_buf(d, k), n0 + k, spk + o.off[k], n_spk[k], (int)blockIdx.x, (int)gridDim.x,
+                           d.blk[d.nblk + (blockIdx.x + blockIdx.y * gridDim.x) % kFanoutBlocks]);
+}
+template <int KIND>
+__global__ __launch_bounds__(64) void k_queue_steps(Dev d, long long n0, int cnt, float* __restrict__ I_out, long long I_stride) {
+  __shared__ int s_K[kQueueSteps][64];   // contenders of the lane's target in every step
+  __shared__ int s_I[kQueueSteps][64];   // what it delivers
+  const int lane = threadIdx.x, g = blockIdx.x * 64 + lane;
+  const size_t BN = (size_t)d.BN;
+  StepAcc r; r.acc = 0; r.popped = 0; r.c_adm = 0; r.s_adm = 0;
+  long long s_del = 0;   // Q8.24 sum of what was delivered
+  if (blockIdx.x == 0 && lane == 0) d.ctr->pool_n[0] = 0;   // the overflow pool is consumed by this launch
+  if (g < d.BN) {
+    unsigned long long offered = 0ull;   // bit j: step n0 + j has contenders
+    QState q;
+    q.hd = KIND == ADSEQ_SORTED ? d.head[g] : 0;
+    q.m0 = KIND == ADSEQ_FIFO ? d.vmask[(size_t)g * d.nw] : 0u;
+    q.occ = d.occ[g];
+    q.mn = KIND == ADSEQ_SORTED ? d.min_k[g] : 0xffffffffu;
+#pragma unroll 8
+    for (int j = 0; j < cnt; ++j) {
+      const int K = d.cnt[(size_t)j * BN + g];
+      s_K[j][lane] = K; s_I[j][lane] = 0;
+      offered |= K > 0 ? 1ull << j : 0ull;
+    }
+    const QState q0 = q;
+    if (KIND == ADSEQ_FIFO && q.occ > 0) fifo_scan<false>(d, g, (unsigned)n0, q, r);
+    for (;;) {
+      // the next step in which something is due, or after which something was offered
+      const int jk = offered ? __ffsll((long long)offered) : cnt + 1;
+      const unsigned away = q.mn - (unsigned)n0;
+      const int jd = q.mn != 0xffffffffu && away < (unsigned)cnt ? (int)away : cnt + 1;
+      const int j = jk < jd ? jk : jd;
+      if (j > cnt) break;
+      const unsigned kn = (unsigned)n0 + (unsigned)j;
+      int K = 0;
+      uint4 cc[kCont];
+#pragma unroll
+      for (int x = 0; x < kCont; ++x) cc[x] = make_uint4(0u, 0u, 0u, 0u);
+      const QBuf qb = queue_buf(d, j > 0 ? j - 1 : 0);
+      if (jk == j) {
+        offered &= offered - 1ull;
+        K = s_K[j - 1][lane];
+#pragma unroll
+        for (int x = 0; x < kCont; ++x) if (x < K) cc[x] = qb.cont[(size_t)x * BN + g];
+      }
+      const int room = d.C - q.occ;     // what the contenders found when they were emitted
+      r.acc = 0;
+      if (j < cnt) {
+        if (jd == j) {
+          if (KIND == ADSEQ_FIFO) fifo_scan<true>(d, g, kn, q, r); else sorted_pop(d, g, kn, q, r);
+        }
+        if (K > 0) admit_contenders<KIND, 1>(d, qb, g, K, room, kn, q, r, cc);
+        s_I[j][lane] = r.acc;
+        s_del += r.acc;
+      } else if (K > 0) {
+        admit_contenders<KIND, 0>(d, qb, g, K, room, kn, q, r, cc);
+      }
+    }
+    for (int j = I_stride != 0 ? 0 : cnt - 1; j < cnt; ++j)
+      __builtin_nontemporal_store((float)s_I[j][lane] * 0x1p-24f, &I_out[j * I_stride + g]);
+    if (KIND == ADSEQ_SORTED) { if (q.mn != q0.mn) d.min_k[g] = q.mn; if (q.hd != q0.hd) d.head[g] = q.hd; }
+    if (KIND == ADSEQ_FIFO && q.m0 != q0.m0) d.vmask[(size_t)g * d.nw] = q.m0;
+    if (q.occ != q0.occ) d.occ[g] = q.occ;
+  }
+  if (__ballot(r.popped != 0 || r.c_adm != 0)) {
+    const long long t_pop = wave_total(r.popped), t_adm = wave_total(r.c_adm), t_sadm = wave_total64(r.s_adm), t_del = wave_total64(s_del);
+    if (lane == 0) {
+      BlkCtr& bc = d.blk[blockIdx.x % d.nblk];   // (atomics without return value)
+      atomicAdd(&bc.delivered, (unsigned long long)t_pop); atomicAdd(&bc.admitted, (unsigned long long)t_adm);
+      atomicAdd((unsigned long long*)&bc.sum_admitted, (unsigned long long)t_sadm);
+      atomicAdd((unsigned long long*)&bc.sum_delivered, (unsigned long long)t_del);
+    }
   }
 }
 

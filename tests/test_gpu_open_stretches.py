@@ -54,3 +54,43 @@ def test_open_stretches(n, fan, b, d_max, window, stride, monkeypatch):
     for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
         assert c[key] == rc[key], key
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 1), (adseq.FIFO, 5), (adseq.FIFO, 40), (adseq.SORTED, 1), (adseq.SORTED, 7)])
+@pytest.mark.parametrize("n,fan,b,d_max,rate,steps", [(301, 200, 2, 37, 0.05, "16"), (1, 5, 1, 3, 0.5, "16"), (3000, 8, 1, 1, 0.02, "16"), (130, 40, 3, 20, 0.1, "2")])
+@pytest.mark.parametrize("stride", ["apart", "one", "overlap"])
+def test_open_stretches_bounded(kind, cap, n, fan, b, d_max, rate, steps, stride, monkeypatch):
+    """FIFO and SORTED: the steps of a stretch registered in one launch and taken through by the targets' owners in another
+    (k_fanout_steps, k_queue_steps); queues that overflow, more contenders in a step than record slots (301 x 200), delays of
+    one step only; a second enqueue for the last step of a stretch, whose events are admitted together with the first's."""
+    monkeypatch.setenv("ADSEQ_QUEUE_STEPS", steps)
+    T = 120
+    wl = synth.ragged_network(n, fan, d_max, seed=n + b, rate_hz=0.0, t=T, b=b, w_mean=0.01, w_std=0.02)
+    bn = b * n
+    forced, lists = _lists(wl, b, T, seed=4, rate=rate)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, forced_spikes=forced, keep_currents=True)
+    want = ref.Iq.reshape(T, bn).astype(np.float32) * np.float32(2.0 ** -24)
+    sim = adseq.Adseq(wl, kind, cap, batch=b)
+    step = {"apart": bn, "one": 0, "overlap": max(1, bn - 1)}[stride]
+    half = [len(x) // 2 for x in lists]
+    s = 0
+    for piece in (1, 3, 4, 20, 33, 2, 57):
+        # (the last step's list in two parts: the second part comes by an enqueue of its own)
+        lens = [len(x) for x in lists[s:s + piece]]
+        lens[-1] = half[s + piece - 1]
+        ids = torch.from_numpy(np.concatenate(lists[s:s + piece] + [np.zeros(1, np.int32)])).to(sim.dev)
+        offs = np.concatenate([[0], np.cumsum([len(x) for x in lists[s:s + piece]])]).astype(np.int64)
+        counts = torch.tensor(lens + [len(lists[s + piece - 1]) - lens[-1]], dtype=torch.int32, device=sim.dev)
+        buf = torch.zeros((piece - 1) * step + bn, dtype=torch.float32, device=sim.dev)
+        sim.run_open(s, piece, ids, offs[:piece], counts, buf, step)
+        sim.enqueue(s + piece - 1, ids[int(offs[piece - 1]) + lens[-1]:], counts[piece:])
+        exp = np.zeros((piece - 1) * step + bn, np.float32)
+        for k in range(piece):
+            exp[k * step:k * step + bn] = want[s + k]
+        np.testing.assert_array_equal(buf.cpu().numpy().view(np.uint32), exp.view(np.uint32))
+        s += piece
+    assert s == T
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    sim.close()
