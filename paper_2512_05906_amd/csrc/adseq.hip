@@ -143,6 +143,7 @@ struct Dev {
   unsigned* min_k;      // FIFO/SORTED: earliest stored arrival step per target (0xffffffff: none)
   int* cnt;             // [qsteps][BN] contenders registered per target since its last admission
   uint4* cont;          // [qsteps][kCont][BN] contender records (see bounded_queues.h)
+  unsigned long long* full_bits;  // k_queue_run: [2][words] targets that stay full in the next step
   int* c_head;          // [qsteps][BN] overflow list head per target (-1: empty)
   long long* pool_p;
   long long* pool_t;
@@ -158,6 +159,7 @@ struct Dev {
   int blk_pop;             // SYN_FIFO: index of the first counter line of k_synq_pop's blocks in blk
   unsigned long long* spk_words;  // FIFO/SORTED: [2][words] ballot words of the step launch, by step parity
   long long* stepcnt;   // FIFO/SORTED: [2][nblk][2] spikes and emitted events of every neuron block, by step parity
+  unsigned long long* claims;  // FIFO/SORTED with tape: [T + 1] spikes << 40 | events that the blocks of a resident launch have claimed in a step
   long long* step_off;
   long long* step_evoff;  // FIFO/SORTED: events emitted before step n (index of its first admission flag)
   int* tape_spk;
@@ -394,6 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 #include "ring_flow_reverse.h"
 #include "ring_resident_forward.h"
 #include "ring_chain.h"
+#include "queue_resident.h"
 
 // ---------------------------------------------------------------- backward (FIFO / SORTED)
 
@@ -522,6 +525,7 @@ struct adseq {
   int rev_P = 0, rev_chunk = 0, rev_npt = 0;   // RING, reverse sweep: the same for the resident reverse kernel (0: one launch per step)
   bool rev_flow = false;                      // RING: the resident reverse kernel without a grid barrier (ring_flow_reverse.h)
   int fwd_P = 0, fwd_chunk = 0;                // RING: the same for the forward kernel over the whole chip (ring_resident_forward.h; 0: not used)
+  int q_P = 0, q_chunk = 0;                    // FIFO / SORTED: the same for k_queue_run (0: two launches per step)
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
   hipStream_t aux = nullptr;
@@ -541,7 +545,7 @@ struct adseq {
 namespace {
 
 struct Layout {
-  size_t V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
+  size_t claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
       tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
       total;
@@ -626,6 +630,32 @@ bool resident_fits(const void* f, int threads = kResLaunch) {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, threads, 0) != hipSuccess) { (void)hipGetLastError(); return false; }
   if (const char* e = getenv("ADSEQ_RING_ASSUME_CUS")) { const int v = atoi(e); if (v >= 1 && v <= 4096) cus = v; }
   return (long long)cus * per >= 256;
+}
+// k_queue_run: the same layout for any B N up to 256 x 4,096 targets.
+ResidentPlan queue_plan(long long BN) {
+  ResidentPlan r;
+  const int blocks = env_pow2("ADSEQ_QUEUE_BLOCKS", 256, 8, 256);
+  long long chunk = (BN + blocks - 1) / blocks;
+  chunk = (chunk + 255) / 256 * 256;
+  if (env_pow2("ADSEQ_QUEUE_RESIDENT", 1, 0, 1) && chunk <= 8 * kResThreads) {
+    r.chunk = (int)chunk;
+    r.P = (int)((BN + chunk - 1) / chunk);
+    r.npt = 1;
+  }
+  return r;
+}
+typedef void (*QueueKernel)(long long, int, unsigned, int, int, int, unsigned long long*, Dev);
+template <int KIND, bool RECORD>
+QueueKernel queue_kernel_of(int chunk) {
+  if (chunk <= kResThreads) return k_queue_run<KIND, RECORD, 1, false>;
+  if (chunk <= 4 * kResThreads) return k_queue_run<KIND, RECORD, 4, false>;
+  return k_queue_run<KIND, RECORD, 8, false>;
+}
+QueueKernel queue_kernel(int kind, bool record, int chunk, int capacity) {
+  if (kind == ADSEQ_FIFO && chunk <= kResThreads && capacity <= 32)   // (the slots in LDS)
+    return record ? k_queue_run<ADSEQ_FIFO, true, 1, true> : k_queue_run<ADSEQ_FIFO, false, 1, true>;
+  if (kind == ADSEQ_FIFO) return record ? queue_kernel_of<ADSEQ_FIFO, true>(chunk) : queue_kernel_of<ADSEQ_FIFO, false>(chunk);
+  return record ? queue_kernel_of<ADSEQ_SORTED, true>(chunk) : queue_kernel_of<ADSEQ_SORTED, false>(chunk);
 }
 template <bool RECORD>
 const void* run_xcd_kernel_of(int syn, int npt) {
@@ -734,8 +764,13 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   L->qsteps = 1;
   if (ptq) {
     const double bs = (double)c->batch * (double)S;
-    while (qsteps > 1 && ((double)qsteps * BN * (kCont * 16 + 8) > 1073741824.0 ||
-                          (double)qsteps * bs > (c->step_event_capacity ? (double)c->step_event_capacity : 134217728.0))) qsteps >>= 1;
+    // (two of them, what k_queue_run takes, are worth four times the room)
+    auto too_much = [&](int q) {
+      const double room = q > 2 ? 1.0 : 4.0;
+      return (double)q * BN * (kCont * 16 + 8) > room * 1073741824.0 ||
+             (double)q * bs > (c->step_event_capacity ? (double)c->step_event_capacity : room * 134217728.0);
+    };
+    while (qsteps > 1 && too_much(qsteps)) qsteps >>= 1;
     L->qsteps = qsteps;
     long long cap = c->step_event_capacity;
     if (!cap) {
@@ -809,6 +844,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   L->head = take(ptq ? BN * 4 : 0);
   L->min_k = take(ptq ? BN * 4 : 0);
   L->cnt = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
+  L->full_bits = take(ptq && L->qsteps >= 2 ? 2 * (size_t)L->words * 8 : 0);
   L->cont = take(ptq ? (size_t)L->qsteps * kCont * BN * 16 : 0);
   L->c_head = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
   L->pool_p = take((size_t)L->pool_cap * 8);
@@ -848,6 +884,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   L->tape_bits = take(windows ? T * L->words * 8 : 0);
   L->spk_count = take(c->record_tape ? BN * 4 : 0);
   L->step_off = take(c->record_tape ? (T + 1) * 8 : 0);
+  L->claims = take(c->record_tape && ptq && L->qsteps >= 2 ? (T + 1) * 8 : 0);
   L->step_evoff = take(c->record_tape && bounded ? (T + 1) * 8 : 0);
   L->tape_spk = take(bounded ? (size_t)L->spike_cap * 4 : 0);
   L->tape_evb = take(bounded ? (size_t)L->spike_cap * 8 : 0);
@@ -883,13 +920,14 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   return true;
 }
 // The bounded kinds' reverse sweep takes the ring's kernels (a window of steps per launch; 16 x 1,000 neurons, FIFO[32]:
-// 2,000 steps forward and back 40.6 -> 27.7 ms) wherever 2^32 words of admission bits are enough for the tape, and a handle
-// without a tape, which may run open loop, gets the buffers of a whole stretch (k_queue_steps).  small: neither -- an
+// 2,000 steps forward and back 40.6 -> 27.7 ms) wherever 2^32 words of admission bits are enough for the tape; FIFO and SORTED
+// get the two contender buffers of k_queue_run, without a tape, where they may run open loop, those of a whole stretch
+// (k_queue_steps).  small: neither -- an
 // adjoint delay line and two launches per reverse step, a stretch of one step -- for what only so fits the static workspace.
 bool make_layout(const adseq_config* c, Layout* L, bool small = false) {
   if (!c) return false;
   if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
-      layout_as(c, L, true, c->record_tape ? 1 : env_pow2("ADSEQ_QUEUE_STEPS", kQueueSteps, 1, kQueueSteps))) return true;
+      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps))) return true;
   return layout_as(c, L, false, 1);
 }
 
@@ -963,6 +1001,7 @@ void launch_reset(adseq* h, hipStream_t st) {
   if (d.record) {
     fill_u32(st, d.step_off, 0u, 2);  // step_off[0] = 0 (int64)
     if (d.kind != ADSEQ_RING) fill_u32(st, d.step_evoff, 0u, 2);
+    if (d.qsteps >= 2) fill_u32(st, d.claims, 0u, ((size_t)d.max_steps + 1) * 2);
     fill_u32(st, d.spk_count, 0u, BN);
   }
   h->next_step = 0;
@@ -1252,6 +1291,31 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
     n += cnt;
     h->next_step = n;
   }
+}
+
+// FIFO / SORTED: steps step0 .. step0 + n_steps - 1 by k_queue_run, up to 1,024 of them in one launch.
+void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_steps) {
+  const Dev& d = h->dev;
+  long long n = step0;
+  const long long end = step0 + n_steps;
+  int stride = env_pow2("ADSEQ_RING_RESIDENT_STRIDE", kResStride, 1, 8);
+  while (stride > 1 && (long long)h->q_P * stride > 32 * 8) stride >>= 1;
+  flush_admit(h, st);
+  while (n < end) {
+    int cnt = (int)(end - n < 1024 ? end - n : 1024);
+    // a launch either records all its steps or none: it ends where the tape ends
+    const bool record = d.record && h->tape_ok && n < d.max_steps;
+    if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
+    if (d.record && n >= d.max_steps) h->tape_ok = false;
+    hipLaunchKernelGGL(queue_kernel(d.kind, record, h->q_chunk, d.C), dim3((unsigned)(h->q_P * stride)), dim3(kResLaunch), 0, st, n, cnt, h->rev_base,
+                       h->q_P, h->q_chunk, stride, d.claims, d);
+    h->rev_base += (unsigned)cnt * (unsigned)h->q_P;
+    h->enq_calls += cnt;
+    n += cnt;
+    h->next_step = n;
+  }
+  hipLaunchKernelGGL(k_queue_settle, dim3(256), dim3(kBlock), 0, st, d);
+  h->last_stream = st;
 }
 
 // RING, chained step launches (ring_chain.h): the step launches go to the caller's stream and to a
@@ -1608,6 +1672,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.amp = (d.continuous && d.kind != ADSEQ_RING && !L.sorted_rev) ? (float*)(ws + L.amp) : nullptr;
   d.synf = (uint2*)(ws + L.synf); d.synb = (uint2*)(ws + L.synb);
   d.fdec = d.continuous ? (float*)(ws + L.fdec) : nullptr;
+  d.claims = (unsigned long long*)(ws + L.claims); d.full_bits = (unsigned long long*)(ws + L.full_bits);
   d.tapeU = (float*)(ws + L.tapeU); d.step_off = (long long*)(ws + L.step_off);
   d.step_evoff = (long long*)(ws + L.step_evoff);
   d.tape_spk = (int*)(ws + L.tape_spk); d.tape_evb = (long long*)(ws + L.tape_evb);
@@ -1629,6 +1694,13 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
         (adm || syn || d.BN % 4 != 0 || vp.chunk > 4 * kResThreads || !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))))
       vp = ResidentPlan();
     h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
+  }
+  if ((d.kind == ADSEQ_FIFO || d.kind == ADSEQ_SORTED) && d.qsteps >= 2 && (double)d.B * (double)d.S * 2.0 <= (double)d.pool_cap) {
+    // (half of the overflow pool has room for every synapse of every trial)
+    ResidentPlan qp = queue_plan((long long)d.BN);
+    if (qp.P > 0 && resident_fits((const void*)queue_kernel(d.kind, true, qp.chunk, d.C)) && resident_fits((const void*)queue_kernel(d.kind, false, qp.chunk, d.C))) {
+      h->q_P = qp.P; h->q_chunk = qp.chunk;
+    }
   }
   if (d.kind == ADSEQ_RING) {
     ResidentPlan rp = resident_plan((long long)d.BN);
@@ -1876,7 +1948,11 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   } else if (h->dev.kind == ADSEQ_RING && h->chain && n_steps >= 2 && chain_ready(h)) {
     ring_run_chain(h, (hipStream_t)stream, step0, n_steps);
   } else {
-    for (int64_t n = 0; n < n_steps; ++n) {
+    // (the last step goes by its own two launches: its events stay pending, to be admitted with what an adseq_enqueue may
+    // add; so does everything while kernels are timed, class by class)
+    const int64_t ahead = h->q_P > 0 && n_steps >= 4 && !h->prof ? n_steps - 1 : 0;
+    if (ahead) queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+    for (int64_t n = ahead; n < n_steps; ++n) {
       const int rc = step_impl(h, step0 + n, nullptr, nullptr, (hipStream_t)stream);
       if (rc != ADSEQ_OK) return rc;
     }

@@ -75,18 +75,35 @@ __device__ __forceinline__ unsigned cont_arrival(const uint4& c, unsigned kn) {
 struct QState { int occ; unsigned mn; int hd; unsigned m0; };
 
 // Where the contenders of one step are registered: ticket counters [BN], contender records [kCont][BN], overflow list
-// heads [BN].  (There are Dev::qsteps of each; a step of its own launches uses the first.)
-struct QBuf { int* cnt; uint4* cont; int* head; };
+// heads [BN], and the part of the overflow pool that the entries come from.  (There are Dev::qsteps of each buffer; a step
+// of its own launches uses the first.)
+struct QBuf { int* cnt; uint4* cont; int* head; int* pool_n; int pool0, pool_cap; };
 __device__ __forceinline__ QBuf queue_buf(const Dev& d, int j) {
   QBuf b;
   b.cnt = d.cnt + (size_t)j * d.BN;
   b.cont = d.cont + (size_t)j * kCont * d.BN;
   b.head = d.c_head + (size_t)j * d.BN;
+  b.pool_n = &d.ctr->pool_n[0]; b.pool0 = 0; b.pool_cap = d.pool_cap;
   return b;
 }
+// Buffer j of the two that k_queue_run fills in turn: half of the pool each.
+__device__ __forceinline__ QBuf queue_buf_half(const Dev& d, int j) {
+  QBuf b = queue_buf(d, j);
+  b.pool_cap = d.pool_cap / 2; b.pool0 = j ? b.pool_cap : 0; b.pool_n = &d.ctr->pool_n[j];
+  return b;
+}
+// Accesses to what other blocks of the same launch write or read (RES): agent scope.
+template <bool RES, class T> __device__ __forceinline__ T q_load(const T* p) {
+  if (RES) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return *p;
+}
+template <bool RES, class T> __device__ __forceinline__ void q_store(T* p, T v) {
+  if (RES) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
 
-// FIFO: stores an admitted event in the first free slot of target g.
-__device__ __forceinline__ void fifo_insert(const Dev& d, int g, QState& q, unsigned k, int a) {
+// FIFO: stores an admitted event in the first free slot of target g, whose keys and amplitudes are at `keys` and `amps`.
+__device__ __forceinline__ void fifo_insert(const Dev& d, int g, unsigned short* keys, int* amps, QState& q, unsigned k, int a) {
   const unsigned lim0 = d.C >= 32 ? 0xffffffffu : ((1u << d.C) - 1u);
   const unsigned free0 = ~q.m0 & lim0;
   int slot = -1;
@@ -109,8 +126,11 @@ __device__ __forceinline__ void fifo_insert(const Dev& d, int g, QState& q, unsi
     }
   }
   if (slot < 0) return;   // not reached: the caller admits no more events than there are free slots
-  d.fkey[(size_t)g * d.cpad + slot] = (unsigned short)k;
-  d.famp[(size_t)g * d.C + slot] = a;
+  keys[slot] = (unsigned short)k;
+  amps[slot] = a;
+}
+__device__ __forceinline__ void fifo_insert(const Dev& d, int g, QState& q, unsigned k, int a) {
+  fifo_insert(d, g, d.fkey + (size_t)g * d.cpad, d.famp + (size_t)g * d.C, q, k, a);
 }
 
 // SORTED: stores an admitted event at its place in the circular array ordered by arrival step
@@ -292,21 +312,22 @@ __device__ __forceinline__ void sorted_pop(const Dev& d, int g, unsigned kn, QSt
   q.occ = occ; q.hd = hd; q.mn = occ > 0 ? front : 0xffffffffu;
 }
 
-// Looks at all keys of target g (FIFO): takes the events due at step kn (TAKE) and leaves in q.mn the earliest arrival of
+// Looks at all keys of target g (FIFO; keys and amplitudes at `keys` and `amps`): takes the events due at step kn (TAKE) and leaves in q.mn the earliest arrival of
 // those that stay.
 template <bool TAKE>
-__device__ __forceinline__ void fifo_scan(const Dev& d, int g, unsigned kn, QState& q, StepAcc& r) {
+__device__ __forceinline__ void fifo_scan(const Dev& d, int g, const unsigned short* keys, const int* amps, unsigned kn, QState& q, StepAcc& r) {
   unsigned nearest = 0xffffffffu;   // steps from kn to the earliest that stays
   for (int w = 0; w < d.nw; ++w) {
     unsigned m = w == 0 ? q.m0 : d.vmask[(size_t)g * d.nw + w];
     if (!m) continue;
-    const uint4* kp = reinterpret_cast<const uint4*>(d.fkey + (size_t)g * d.cpad + 32 * w);
+    const uint4* kp = reinterpret_cast<const uint4*>(keys + 32 * w);
     uint4 kq[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) { kq[c] = make_uint4(0u, 0u, 0u, 0u); if (32 * w + 8 * c < d.cpad) kq[c] = kp[c]; }
+    for (int c = 0; c < 4; ++c) { kq[c] = make_uint4(0u, 0u, 0u, 0u); if ((m >> (8 * c)) & 0xffu) kq[c] = kp[c]; }
     unsigned due = 0u;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
+      if (!((m >> (8 * c)) & 0xffu)) continue;   // (the first free slot is filled first: the groups behind are mostly empty)
       const unsigned wd[4] = {kq[c].x, kq[c].y, kq[c].z, kq[c].w};
 #pragma unroll
       for (int h = 0; h < 8; ++h) {
@@ -320,7 +341,7 @@ __device__ __forceinline__ void fifo_scan(const Dev& d, int g, unsigned kn, QSta
       m &= ~due;
       const int nd = __popc(due);
       if (w == 0) q.m0 = m; else d.vmask[(size_t)g * d.nw + w] = m;
-      const int* __restrict__ ap = d.famp + (size_t)g * d.C + 32 * w;
+      const int* ap = amps + 32 * w;
       while (due) {
         // up to four amplitude loads in flight
         int j[4], av[4];
@@ -336,6 +357,10 @@ __device__ __forceinline__ void fifo_scan(const Dev& d, int g, unsigned kn, QSta
     }
   }
   q.mn = nearest == 0xffffffffu ? 0xffffffffu : kn + nearest;
+}
+template <bool TAKE>
+__device__ __forceinline__ void fifo_scan(const Dev& d, int g, unsigned kn, QState& q, StepAcc& r) {
+  fifo_scan<TAKE>(d, g, d.fkey + (size_t)g * d.cpad, d.famp + (size_t)g * d.C, kn, q, r);
 }
 
 // Block-level event counters in LDS: [0] offered, [1] admitted, [2] delivered, [3..5] the same as
@@ -563,6 +588,30 @@ __device__ __forceinline__ void push_rows_latest(const Dev& d, long long n, cons
 __device__ __forceinline__ void push_rows_bins(const Dev& d, long long n, const RowRef* rr, int nrows,
                                                long long stride, int& c_adm, long long& s_adm);
 
+// Contenders beyond the record slots (`over`, any lanes of the wavefront, which all call it): wavefront-aggregated claim of
+// pool entries, pushed on their targets' lists.
+template <bool RES>
+__device__ __forceinline__ void overflow_push(const Dev& d, const QBuf& qb, bool over, int gt, long long p, long long flag, unsigned k, int a) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long cm = __ballot(over);
+  int base = 0;
+  if (lane == __ffsll((long long)cm) - 1) base = atomicAdd(qb.pool_n, __popcll(cm));
+  base = lane_get(base, __ffsll((long long)cm) - 1);
+  if (!over) return;
+  const int at = base + __popcll(cm & ((1ull << lane) - 1ull));
+  if (at >= qb.pool_cap) {
+    // no room to remember it: it can only be dropped, and the run is flagged as invalid
+    atomicOr(&d.ctr->err, ERR_POOL);
+    atomicSub(&qb.cnt[gt], 1);
+    if (flag >= 0) d.tape_adm[flag] = 0;
+  } else {
+    const int x = qb.pool0 + at;
+    q_store<RES>(&d.pool_p[x], p); q_store<RES>(&d.pool_t[x], flag);
+    q_store<RES>(&d.pool_k[x], k); q_store<RES>(&d.pool_a[x], a);
+    q_store<RES>(&d.pool_next[x], atomicExch(&qb.head[gt], x));
+  }
+}
+
 // EARLY: the occupancy at the end of step n is known: an event whose target is full is dropped here.  Otherwise (several
 // steps' spikes registered in one launch) every event is a contender, and the owner's selection drops it.
 // Offers, for each of up to four row shares of step n, the entries r0 + first + threadIdx.x +
@@ -573,7 +622,6 @@ __device__ __forceinline__ void push_rows_bins(const Dev& d, long long n, const 
 template <bool EARLY>
 __device__ __forceinline__ void offer_rows(const Dev& d, const QBuf& qb, long long n, const RowRef* rr, int nrows,
                                            long long stride) {
-  const int lane = threadIdx.x & 63;
   const size_t BN = (size_t)d.BN;
   long long longest = 0;
 #pragma unroll
@@ -606,27 +654,8 @@ __device__ __forceinline__ void offer_rows(const Dev& d, const QBuf& qb, long lo
       if (tidx >= 0) d.tape_adm[tidx] = contend[j] ? 1 : 0;
       if (contend[j] && tk[j] < kCont)
         qb.cont[(size_t)tk[j] * BN + gt[j]] = cont_pack(p[j], tidx, (unsigned)(n + D) & 0xffffu, a[j]);
-      // the others: wavefront-aggregated claim of pool entries, pushed on the target's list
       const bool over = contend[j] && tk[j] >= kCont;
-      const unsigned long long cm = __ballot(over);
-      if (cm) {
-        int base = 0;
-        if (lane == __ffsll((long long)cm) - 1) base = atomicAdd(&d.ctr->pool_n[0], __popcll(cm));
-        base = lane_get(base, __ffsll((long long)cm) - 1);
-        if (over) {
-          const int x = base + __popcll(cm & ((1ull << lane) - 1ull));
-          if (x >= d.pool_cap) {
-            // no room to remember it: it can only be dropped, and the run is flagged as invalid
-            atomicOr(&d.ctr->err, ERR_POOL);
-            atomicSub(&qb.cnt[gt[j]], 1);
-            if (tidx >= 0) d.tape_adm[tidx] = 0;
-          } else {
-            d.pool_p[x] = p[j]; d.pool_t[x] = tidx;
-            d.pool_k[x] = (unsigned)(n + D); d.pool_a[x] = a[j];
-            d.pool_next[x] = atomicExch(&qb.head[gt[j]], x);
-          }
-        }
-      }
+      if (__ballot(over)) overflow_push<false>(d, qb, over, gt[j], p[j], tidx, (unsigned)(n + D), a[j]);
     }
   }
 }

@@ -1,0 +1,96 @@
+"""FIFO and SORTED, closed loop, many steps in one launch (k_queue_run) against the oracle: trace bit for bit, counters,
+which events were admitted and dropped, gradients; one, four and eight targets per thread, one block and many, odd sizes,
+queues that overflow, more contenders for a target than record slots, rows and bursts of more pieces than are shared out at
+once, synaptic states, runs cut into pieces and mixed with single steps, and agreement with two launches per step."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(wl, kind, cap, T, b, pieces, record=True, **kw):
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=record, max_steps=T, **kw)
+    n = 0
+    for p in pieces:
+        if p == "s":
+            sim.step(n); n += 1
+        else:
+            sim.run(n, p); n += p
+    assert n == T
+    torch.cuda.synchronize()
+    return sim
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 1), (adseq.FIFO, 6), (adseq.FIFO, 40), (adseq.SORTED, 1), (adseq.SORTED, 9)])
+@pytest.mark.parametrize("n,b,T,d_max,fan,rate,tau_syn,tau_rise,continuous,blocks", [
+    (701, 3, 80, 40, 200, 900.0, 0.0, 0.0, False, ""), (100, 1, 60, 1, 60, 900.0, 0.0, 0.0, False, ""),
+    (1501, 4, 50, 30, 90, 900.0, 5.0, 0.0, True, "8"), (4100, 4, 40, 20, 40, 900.0, 5.0, 1.0, False, "8"),
+    (1100, 8, 24, 12, 2500, 1500.0, 0.0, 0.0, False, "8")])
+def test_queue_resident(kind, cap, n, b, T, d_max, fan, rate, tau_syn, tau_rise, continuous, blocks, monkeypatch):
+    if blocks:   # (few blocks: four and eight targets per thread)
+        monkeypatch.setenv("ADSEQ_QUEUE_BLOCKS", blocks)
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=0.6 / fan, w_std=0.6 / fan, continuous=continuous)
+    wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, n_threads=8)
+    assert ref.spikes.sum() > 50
+    kw = dict(tape_spike_capacity=T * b * n // 2, tape_event_capacity=T * b * wl.n_synapses // 4)
+    rc = ref.counters()
+    dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    for resident, pieces, record in (("1", [T], True), ("1", [3, 9, "s", T - 13], True), ("1", [T], False), ("0", [T], True)):
+        monkeypatch.setenv("ADSEQ_QUEUE_RESIDENT", resident)
+        sim = _run(wl, kind, cap, T, b, pieces, record, **(kw if record else {}))
+        c = sim.counters()
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], key
+        assert c["error_bits"] & ~64 == 0
+        if record:
+            np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+            cnt = torch.empty(b * n, dtype=torch.int32, device=sim.dev)
+            sim.spike_counts(cnt)
+            np.testing.assert_array_equal(cnt.cpu().numpy().reshape(b, -1), ref.spikes.sum(axis=0))
+            g_w, g_d = (torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2))
+            sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+            torch.cuda.synchronize()
+            H.grad_close(g_w.cpu().numpy(), gw)
+            H.grad_close(g_d.cpu().numpy(), gd)
+        sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 2), (adseq.SORTED, 3)])
+def test_queue_resident_admission_flags_and_reset(kind, cap):
+    """Every recorded spike once, every event with its own flag; the same after a reset."""
+    T, b = 50, 2
+    wl = synth.ragged_network(300, 80, 20, seed=5, rate_hz=900.0, t=T, b=b, w_mean=0.01, w_std=0.01)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, log_events=True)
+    sim = _run(wl, kind, cap, T, b, [T])
+    for _ in range(2):
+        tp = sim.tape()
+        out = {k: tp[k].cpu().numpy() for k in ("step_offset", "spike_id", "event_base")}
+        np.testing.assert_array_equal(H.spikes_from_tape(out, wl, b), ref.spikes)
+        admitted, dropped = H.gpu_dropped_set(sim, out, wl)
+        delivered, want_dropped = H.oracle_sets(ref)
+        assert dropped == want_dropped and len(dropped) > 0 and delivered <= admitted
+        sim.reset()
+        sim.run(0, T)
+        torch.cuda.synchronize()
+    sim.close()
+
+
+def test_queue_resident_wait_that_runs_out_is_reported(monkeypatch):
+    """Failure path of the bounded waits, forced from the host (one poll per wait): the kernel runs to its end, the error
+    word carries bit 32, a reset clears it."""
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    wl = synth.ragged_network(40000, 30, 20, seed=45, rate_hz=700.0, t=60, b=1, w_mean=0.02, w_std=0.01)
+    sim = _run(wl, adseq.FIFO, 4, 60, 1, [60])
+    assert sim.counters()["error_bits"] & 32
+    with pytest.raises(adseq.AdseqError):
+        sim.drop_count()
+    sim.reset()
+    assert sim.counters()["error_bits"] == 0
+    sim.close()
