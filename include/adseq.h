@@ -151,8 +151,9 @@ typedef struct {
                                   (tape_spike_capacity * ceil(S / N))                         */
   int64_t step_event_capacity; /* FIFO/SORTED: events per step that may wait in the overflow
                                   list of their target (more than 8 contenders for one target
-                                  in one step); 0 = default min(B * S, 2^24), without a tape up
-                                  to 2^27 for open-loop stretches of several steps.  RING: events
+                                  in one step); 0 = default: twice B * S up to 2^29 for runs in
+                                  one kernel, without a tape 64 times that up to 2^27 for
+                                  open-loop stretches; else min(B * S, 2^24).  RING: events
                                   the staging buffer of a window holds (the rest takes a slower
                                   route, same result); 0 = default                            */
   void *workspace;             /* device memory, 256-byte aligned                             */
@@ -221,7 +222,9 @@ int adseq_run_open(adseq_t *h, int64_t step0, int64_t n_steps, const int32_t *sp
 int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out, void *stream);
 
 /* n_steps closed-loop steps starting at `step0` (same results as calling adseq_step in a loop with
- * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries in ONE kernel
+ * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries, and
+ * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (where half the overflow list has room for every
+ * synapse of every trial, and kernels are not being timed: adseq_profile), in ONE kernel
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
  * launch needs the device free enough for all its blocks to run at the same time.  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
@@ -309,7 +312,7 @@ int adseq_spike_counts(adseq_t *h, int32_t *counts, void *stream);
  * are created by the library on first use and destroyed with the handle).  adseq_profile_read
  * synchronises `stream` and returns, per kernel class, the summed time in ms and the number of
  * launches since the last read, then forgets them.  Classes for FIFO / SORTED (an event after
- * every launch): [0] fan-out + contender registration, [1] admission + pop + drive + LIF,
+ * every launch; while timing is on every step goes by its own launches): [0] fan-out + contender registration, [1] admission + pop + drive + LIF,
  * [2] backward queue term + gradients, [3] backward neuron update (where the reverse sweep goes window
  * by window, the far gather of a window and its reverse steps, as for RING; [3] counts the steps).  Classes for RING: [0] the
  * expansion of one window (staging pass + accumulation pass, timed as a pair and counted as one
