@@ -53,6 +53,8 @@ struct Counters {
   long long tape_spikes, tape_events;
   unsigned err;
   int pool_n[2];
+  unsigned dense[2];                // RING: the window's expansion takes the dense way (by window parity)
+  long long pieces;                 // RING: row pieces of the last expansion, estimated from its first block
   unsigned long long in_flight[2];  // scratch of k_ring_in_flight: events, Q8.24 sum
   unsigned long long fold[3];       // scratch of k_count_spikes: spikes, events, Q8.24 sum
   alignas(128) unsigned bar[32];    // bar[0]: arrivals at the barriers of the resident step kernels (a line of its own)
@@ -170,6 +172,7 @@ struct Dev {
   float* bwd_G;         // FIFO/SORTED: [fsplit][BN] partial queue terms of the spikes of the step being swept
   Counters* ctr;
   BlkCtr* blk;   // FIFO / SORTED: [nblk + kFanoutBlocks]
+  int dense_rows, dense_G, dense_K; // RING, dense windows: rows of a tile, row groups, shares of the spikes (0: never)
   // (what was added later stays behind what the per-step kernels read, whose place in the argument block is tuned)
   int sorted_rev;       // bounded kinds with tape: the reverse sweep runs on rows sorted by arrival offset (the ring's kernels)
   unsigned* adm_base;   // bounded kinds: [T][words] first word in adm_bits of the spikes of a (step, spike word)
@@ -598,7 +601,11 @@ ResidentPlan resident_plan(long long BN) {
 // kernel with a barrier none.
 // ADSEQ_RING_RESIDENT_REVERSE = 0: never, 1 (default): whenever the layout allows; ADSEQ_RING_REVERSE_BLOCKS:
 // taking-part blocks (8 .. 256, default 128).
-ResidentPlan reverse_plan(long long BN, bool forward = false) {
+// row: average row length (forward).  Where the rows are long, the forward kernel's blocks own multiples of 64 neurons
+// instead of 256: more blocks share the adds of a step's spikes (10,000 neurons x 1,000 synapses, 157 blocks instead of 40: 31.9 ->
+// 31.1 ms per 10,000 steps at 20 spikes per step, 263 -> 209 ms at 4,800); with short ones the barrier over more blocks costs
+// more than that gives (16,000 neurons x 100, 250 instead of 63: 8.57 -> 8.68 ms per 2,000 steps forward and back).
+ResidentPlan reverse_plan(long long BN, bool forward = false, long long row = 0) {
   ResidentPlan r;
   // (forward: 0 never, 1 wherever the layout fits, default from 2,048 state cells on: below that one XCD's blocks, whose
   // barrier is shorter, are faster -- 100 cells 2.4 against 2.9 us per step --, where their 16-byte accesses fit)
@@ -609,6 +616,7 @@ ResidentPlan reverse_plan(long long BN, bool forward = false) {
                              : env_pow2("ADSEQ_RING_REVERSE_BLOCKS", env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1) ? 256 : 128, 8, 256);
   long long chunk = (BN + blocks - 1) / blocks;
   chunk = (chunk + 255) / 256 * 256;
+  if (forward && row >= 128 && chunk <= kResThreads) chunk = ((BN + blocks - 1) / blocks + 63) / 64 * 64;
   // (the forward kernel and the reverse kernel without a grid barrier also take eight neurons per thread: a million state cells)
   const int per_thread = (forward || env_pow2("ADSEQ_RING_REVERSE_FLOW", 1, 0, 1)) ? 8 : 4;
   if (on && chunk <= per_thread * kResThreads && (BN % 4 == 0 || chunk <= kResThreads)) {
@@ -1634,6 +1642,17 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.flow_hold = env_pow2("ADSEQ_RING_FLOW_WITHHOLD", 0, 0, 1);
   d.W = L.W; d.wshift = L.wshift; d.tp_shift = L.tp_shift; d.P = L.P; d.NB = L.NB; d.cap = L.cap;
   d.wgroups = L.wgroups;
+  static_assert(sizeof(uint2) == 2 * sizeof(int), "tiles of a dense window are laid over the staging buffer");
+  if (d.kind == ADSEQ_RING && L.cap > 0 && d.N <= kDenseCells && env_pow2("ADSEQ_RING_DENSE", 1, 0, 1) && !env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1)) {
+    // rows of the window that a tile of all targets holds; as many shares of the spikes as blocks and staging buffer allow, a
+    // block for every trial and row group at least eight times over
+    const int most = kDenseCells / d.N < L.W ? kDenseCells / d.N : L.W;
+    const int G = (L.W + most - 1) / most, rows = (L.W + G - 1) / G;
+    const double ebuf = 8.0 * (L.P < kMaxParts ? L.P : kMaxParts) * L.NB * L.cap, tile = 4.0 * rows * d.N;
+    const long long K1 = L.NB / ((long long)d.B * G), K2 = (long long)(ebuf / (tile * d.B * G));
+    const long long K = K1 < K2 ? K1 : K2;
+    if (K >= 8) { d.dense_rows = rows; d.dense_G = G; d.dense_K = (int)K; }
+  }
   d.win = (int*)(ws + L.win);
   d.dstart = (unsigned*)(ws + L.dstart); d.nearcnt = (unsigned*)(ws + L.nearcnt);
   d.perm = (unsigned*)(ws + L.perm); d.rowsum = (long long*)(ws + L.rowsum); d.rowlen = (int*)(ws + L.rowlen);
@@ -1709,7 +1728,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     // forward kernel over the whole chip with the candidates' rows requested ahead (ring_resident_forward.h): the
     // reverse kernel's layout (ADSEQ_RING_FORWARD_BLOCKS taking-part blocks, default 256).  ADSEQ_RING_FORWARD_CHIP:
     // see reverse_plan; ADSEQ_RING_FORWARD_MARGIN: candidate margin in thousandths of the membrane unit (default 5).
-    ResidentPlan fp = reverse_plan((long long)d.BN, true);
+    ResidentPlan fp = reverse_plan((long long)d.BN, true, d.S / d.N);
     if (fp.P > 0 && !(resident_fits((const void*)chip_kernel(true, syn, fp.chunk)) && resident_fits((const void*)chip_kernel(false, syn, fp.chunk))))
       fp = ResidentPlan();
     if (fp.P > 0 && !d.count_pop) {

@@ -273,10 +273,30 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
     }
     // the others: row entries loaded now
     const int nslow = s_nslow;
-    for (int x = wave; x < nslow; x += kWaves) {
-      const RevSpike r = s_slow[x];
-      const int pk = __builtin_amdgcn_readfirstlane(r.pk);
-      fwd_row_tail(d, win, near_h, uniform_of(r.r0), __builtin_amdgcn_readfirstlane(r.len), (pk >> kRevLocBits) * d.N, 0, true);
+    // (four spikes at a time, the leading entries of all four requested before the first add: where many neurons spike at
+    // once -- 10,000 neurons, 5,000 spikes per step -- most are in this list: 31 -> 28 us per step)
+    for (int x0 = wave; x0 < nslow; x0 += 4 * kWaves) {
+      long long sr0[4]; int slen[4], sbase[4]; uint2 se[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int x = x0 + u * kWaves;
+        sr0[u] = 0; slen[u] = 0; sbase[u] = 0; se[u] = make_uint2(0u, 0u);
+        if (x < nslow) {   // (the same in every lane)
+          const RevSpike r = s_slow[x];
+          sr0[u] = uniform_of(r.r0);
+          slen[u] = __builtin_amdgcn_readfirstlane(r.len);
+          sbase[u] = (__builtin_amdgcn_readfirstlane(r.pk) >> kRevLocBits) * d.N;
+          if (lane < slen[u]) se[u] = load_stream(&d.synf[sr0[u] + lane]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (slen[u] == 0) continue;   // uniform
+        const int D = (int)(se[u].x & d.dmask);
+        const bool ok = lane < slen[u] && D <= near_h;
+        if (ok) atomicAdd(&win[(size_t)D * d.BN + (size_t)sbase[u] + (se[u].x >> d.dbits)], (int)se[u].y);
+        fwd_row_tail(d, win, near_h, sr0[u], slen[u], sbase[u], 64, ok);
+      }
     }
     rev_arrive(d, k + 1 < nsteps, rank);   // (adds acknowledged; every wavefront has read the lists)
     if (threadIdx.x == 0) s_nslow = 0;   // (the next step's slow spikes are counted behind its first block barrier)

@@ -422,6 +422,37 @@ __global__ __launch_bounds__(kBlock) void k_open_pop(Dev d, long long n0, float*
 #define XPH_SPAN(k, e) {}
 #endif
 
+// ---- dense windows.  Where half the network spikes at once a window holds tens of millions of events, and staging
+// them costs an 8-byte store each, or -- the staging regions being full -- a global atomic each (10,000 neurons x 1,000
+// synapses, 5,000 spikes per step, 80 million events per window: 2.8 ms).  Then the events are summed where they are read:
+// a block takes one trial, a few rows of the window and one share of the spikes, and adds its events to a tile of all N targets
+// in LDS; the tiles go to the staging buffer with plain stores and the second pass adds them up (80 million events: 2.8 -> 0.4 ms).
+// A tile costs its zeroing and its trip through memory whatever the number of events, hence only from as many row pieces on
+// as the blocks' queues hold (kSegQueue each): below that the ordered staging is the faster one.  How many there are in a window
+// is known when its first pass is over, and neighbouring windows are alike: the pass of one window decides for the next
+// (block 0's pieces stand for all: lines are dealt out round-robin).  The sums are integers, so that results do not depend on it.
+constexpr int kDenseCells = 40000;   // cells of a tile: 160,000 bytes of LDS
+__device__ __forceinline__ bool dense_window(const Dev& d, long long k0) { return d.dense_K > 0 && d.ctr->dense[(k0 >> d.wshift) & 1] != 0; }
+
+// Pass 1 for block x: trial, row group and share from x; spikes of steps [n_lo, n_hi).
+__device__ __forceinline__ void role_dense(const Dev& d, int* tile, int* s_pieces, long long k0, long long n_lo, long long n_hi, int x, long long count_from);
+// Pass 2: the cells of all trials and rows, spread over the blocks of the launch.
+__device__ __forceinline__ void role_dense_sum(const Dev& d, long long k0) {
+  const int* parts = reinterpret_cast<const int*>(d.ebuf);
+  int* __restrict__ win = win_of(d, k0);
+  const long long cells = (long long)d.W * d.BN;
+  for (long long c = (long long)blockIdx.x * kRingThreads + threadIdx.x; c < cells; c += (long long)gridDim.x * kRingThreads) {
+    const int r = (int)(c / d.BN), g = (int)(c - (long long)r * d.BN);
+    const int b = trial_of(d, g), j = g - b * d.N, rg = r / d.dense_rows;
+    const size_t tile = (size_t)d.dense_rows * d.N;
+    const int* p = parts + (size_t)((b * d.dense_G + rg) * d.dense_K) * tile + (size_t)(r - rg * d.dense_rows) * d.N + j;
+    int sum = 0;
+#pragma unroll 8
+    for (int s = 0; s < d.dense_K; ++s) sum = wrap_add(sum, p[(size_t)s * tile]);
+    if (sum != 0) atomicAdd(&win[c], sum);
+  }
+}
+
 // Streaming loads of the expansion and gather passes (row pieces and staged events are read
 // once per pass): non-temporal, so that they do not push the window out of the L2.  (The staging
 // stores stay ordinary: as non-temporal 8-byte stores they reach memory one by one, 2.6x slower.)
@@ -440,7 +471,7 @@ struct Seg { long long p0; int len; int base; int dlo; int slot; int g; unsigned
 constexpr int kSegQueue = 768;   // queue entries per block (32 B each)
 
 // LDS of a block of an expansion / gather role.
-struct ExpandLds {
+struct alignas(16) ExpandLds {
   int cur[kMaxParts];        // staging cursors of k_win_bin's parts
   Seg q[kSegQueue];          // segments found by the walk, shared out among the wavefronts
   int qn, qhead, qlen;       // queued pieces, next to hand out, events in the queued pieces
@@ -888,14 +919,112 @@ __device__ __forceinline__ void role_acc(const Dev& d, int* tile, long long k0, 
 #endif
 }
 
+__device__ __forceinline__ void role_dense(const Dev& d, int* tile, int* s_pieces, long long k0, long long n_lo, long long n_hi, int x, long long count_from) {
+  if (x >= d.B * d.dense_G * d.dense_K) return;   // uniform over the block
+  const int share = x % d.dense_K, rg = (x / d.dense_K) % d.dense_G, b = x / (d.dense_K * d.dense_G);
+  const int ra = rg * d.dense_rows, rb = ra + d.dense_rows < d.W ? ra + d.dense_rows : d.W;
+  const int cells = (rb - ra) * d.N;
+  for (int c = threadIdx.x; c < cells; c += kRingThreads) tile[c] = 0;
+  if (threadIdx.x == 0) *s_pieces = 0;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, sub = lane & 15, grp = lane >> 4;
+  const int nb = d.d_max + 2;
+  const int g_lo = b * d.N, g_hi = g_lo + d.N;               // the trial's state indices
+  const int w_lo = g_lo >> 6, words = ((g_hi - 1) >> 6) - w_lo + 1;
+  const long long items = (n_hi - n_lo) * words;
+  const long long nwaves = (long long)d.dense_K * kRingWaves;
+  const int slot_lo = (int)(n_lo % d.R);
+  long long cnt[3] = {0, 0, 0};
+  int pieces = 0;
+  // a wavefront takes 64 spike words at a time (dealt out round-robin), a lane its word's spikes one by one
+  for (long long it0 = ((long long)(threadIdx.x >> 6) * d.dense_K + share) * 64; it0 < items; it0 += nwaves * 64) {
+    const long long it = it0 + lane;
+    unsigned long long bits = 0ull;
+    long long n = n_lo;
+    int g0 = 0;
+    if (it < items) {
+      const int si = (int)(it / words), w = w_lo + (int)(it - (long long)si * words);
+      n = n_lo + si;
+      int slot = slot_lo + si;
+      if (slot >= d.R) slot -= d.R;
+      g0 = w * 64;
+      bits = d.spike_bits[(size_t)slot * d.words + w];
+      if (g0 < g_lo) bits &= ~0ull << (g_lo - g0);
+      if (g0 + 64 > g_hi) bits &= ~0ull >> (g0 + 64 - g_hi);
+    }
+    const int dlo = (int)(k0 - n);                           // offset that arrives in row 0
+    const int q_lo = dlo + ra < nb - 1 ? dlo + ra : nb - 1, q_hi = dlo + rb < nb - 1 ? dlo + rb : nb - 1;
+    const bool counted = rg == 0 && n >= count_from;
+    while (__ballot(bits != 0ull)) {
+      long long p0 = 0;
+      int len = 0;
+      if (bits) {
+        const int i = g0 + __ffsll((long long)bits) - 1 - g_lo;
+        bits &= bits - 1;
+        const unsigned* ds = d.dstart + (size_t)i * nb;
+        const unsigned q0 = ds[q_lo], q1 = ds[q_hi];
+        const long long r0 = d.row_ptr[i];
+        p0 = r0 + q0; len = (int)(q1 - q0);
+        pieces += 1;
+        if (counted) { cnt[0] += 1; cnt[1] += d.row_ptr[i + 1] - r0; cnt[2] += d.rowsum[i]; }
+      }
+      // 16 lanes to a piece, four pieces per instruction, four instructions (twice 16 entries each) in flight
+      for (int j0 = 0; j0 < 16; j0 += 4) {
+        long long pp[4]; int ln[4], dl[4]; uint2 e[4][2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int src = 4 * (j0 + u) + grp;
+          pp[u] = __shfl(p0, src, 64); ln[u] = __shfl(len, src, 64); dl[u] = __shfl(dlo, src, 64) + ra;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            e[u][h] = make_uint2(0u, 0u);
+            if (sub + 16 * h < ln[u]) e[u][h] = d.synf[pp[u] + sub + 16 * h];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            if (sub + 16 * h < ln[u]) atomicAdd(&tile[((int)(e[u][h].x & d.dmask) - dl[u]) * d.N + (int)(e[u][h].x >> d.dbits)], (int)e[u][h].y);
+          for (int q = 32 + sub; q < ln[u]; q += 16) {
+            const uint2 x = d.synf[pp[u] + q];
+            atomicAdd(&tile[((int)(x.x & d.dmask) - dl[u]) * d.N + (int)(x.x >> d.dbits)], (int)x.y);
+          }
+        }
+      }
+    }
+  }
+  for (int k = 0; k < 3; ++k) {   // spikes of the window just finished, their events and amplitudes
+    const long long v = wave_total64(cnt[k]);
+    if (lane == 0 && v) {
+      BlkCtr& bc = d.blk[x & (kMaxBinBlocks - 1)];
+      atomicAdd(k == 0 ? (unsigned long long*)&bc.pad[0] : k == 1 ? &bc.offered : (unsigned long long*)&bc.sum_offered, (unsigned long long)v);
+    }
+  }
+  const long long mine = wave_total(pieces);
+  if (lane == 0) atomicAdd(s_pieces, (int)mine);
+  __syncthreads();
+  if (x == 0 && threadIdx.x == 0) d.ctr->pieces = (long long)*s_pieces * d.dense_K * d.B;
+  int* out = reinterpret_cast<int*>(d.ebuf) + (size_t)x * d.dense_rows * d.N;
+  for (int c = threadIdx.x; c < cells; c += kRingThreads) out[c] = tile[c];
+}
+
 // The two passes of the expansion as kernels.
 // The same roles as launches of their own (window boundaries, catching up, open loop).
 __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, long long n_lo, long long n_hi,
                                                           int vb0, int nvb, int stage, long long count_from, int clear_other) {
-  __shared__ ExpandLds L;
-  __shared__ SortLds S;
+  // (the roles share the LDS: queues and ordering buffers of the staging, or a tile of a dense window)
+  constexpr size_t kStageBytes = sizeof(ExpandLds) + sizeof(SortLds), kTileBytes = (size_t)kDenseCells * 4;
+  __shared__ __align__(16) unsigned char lds[kStageBytes > kTileBytes ? kStageBytes : kTileBytes];
+  __shared__ int s_pieces;
+  static_assert(sizeof(ExpandLds) % 16 == 0, "the second buffer begins on 16 bytes");
   XPH_SPAN(0, 0)
-  role_bin(d, L, S, k0, n_lo, n_hi, vb0 + (int)blockIdx.x, nvb, stage, count_from);
+  if (stage && dense_window(d, k0)) role_dense(d, reinterpret_cast<int*>(lds), &s_pieces, k0, n_lo, n_hi, vb0 + (int)blockIdx.x, count_from);
+  else {
+    ExpandLds& L = *reinterpret_cast<ExpandLds*>(lds);
+    role_bin(d, L, *reinterpret_cast<SortLds*>(lds + sizeof(ExpandLds)), k0, n_lo, n_hi, vb0 + (int)blockIdx.x, nvb, stage, count_from);
+    if (d.dense_K > 0 && vb0 + (int)blockIdx.x == 0 && threadIdx.x == 0) d.ctr->pieces = (long long)L.qn * nvb;
+  }
   XPH_SPAN(0, 1)
   // The other window buffer -- the one the steps before k0 have just used up -- is zeroed here, a
   // slice per block, for the expansion that fills it next: the resident step kernels do not clear
@@ -925,7 +1054,11 @@ __global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, i
     for (long long x = (long long)blockIdx.x * kRingThreads + threadIdx.x; x < cnt; x += (long long)gridDim.x * kRingThreads)
       d.spike_bits[first + x < all ? first + x : first + x - all] = 0ull;
   }
-  role_acc(d, tile, k0, p0 + (int)blockIdx.x);
+  if (dense_window(d, k0)) role_dense_sum(d, k0);
+  else role_acc(d, tile, k0, p0 + (int)blockIdx.x);
+  // which way the next window goes
+  if (d.dense_K > 0 && blockIdx.x == 0 && threadIdx.x == 0)
+    d.ctr->dense[((k0 >> d.wshift) + 1) & 1] = d.ctr->pieces > (long long)kSegQueue * d.NB ? 1u : 0u;
   XPH_SPAN(1, 1)
 }
 
