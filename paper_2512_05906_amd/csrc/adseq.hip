@@ -569,8 +569,27 @@ int env_pow2(const char* name, int dflt, int lo, int hi) {
   }
   return dflt;
 }
-// Window length of the ring in steps.
-int ring_window_steps() { return env_pow2("ADSEQ_RING_WINDOW", 16, 2, kMaxWindow); }
+// Window length of the ring in steps.  A window costs its expansion (and far gather) once, some 10 us each even when there is
+// little to expand, so longer windows are cheaper -- until the entries that a spike's row holds inside the window, which
+// the step kernels handle one step at a time, outweigh that.  While they are no more than the 64 that the resident kernels
+// request with one load (row length x W / d_max) the longest window is the fastest; beyond that what counts is how many they
+// are in a step, which goes with B S W / d_max: up to 4 million 32 steps are still faster than 16.
+// Measured at 16 / 32 / 64 steps, ms per run: 16 x 1,000 neurons x 100 synapses, d_max 50: 8.57 / 7.20 / -; 60,000 x 100, 200:
+// 3.34 / 2.84 / 2.57; 250,000 x 60, 100: 3.27 / 2.87 / 2.70; 9,973 x 2 trials x 150 with a current state, 150: 5.07 / 4.31 / 3.98;
+// 10,000 x 1,000, 200: 31.1 / 27.9 / 30.9; 100,000 x 1,000, 250: 9.7 / 11.2 / 13.0.
+// No window of more than 16 steps is longer than four fifths of the largest delay, beyond which hardly an event is left for
+// the expansion (a cautious bound: at d_max = 40 a window of 32 steps would still win, 7.4 against 8.6 ms).
+// small: 16 steps at most (two buffers of W rows each).
+int ring_window_steps(const adseq_config* c, bool small) {
+  int W = 16;
+  const double row = (double)c->n_synapses / (double)c->n_neurons / (double)c->d_max_steps;      // entries of a row per step of the window
+  const double load = (double)c->batch * (double)c->n_synapses / (double)c->d_max_steps;   // the same for all rows
+  if (!small && (row * 32.0 <= 64.0 || load * 32.0 <= 4e6) && 5 * 32 < 4 * c->d_max_steps) W = 32;
+  if (!small && row * 64.0 <= 64.0 && 5 * 64 < 4 * c->d_max_steps) W = 64;
+  W = env_pow2("ADSEQ_RING_WINDOW", W, 2, kMaxWindow);
+  while (W > c->d_max_steps) W >>= 1;
+  return W;
+}
 
 // Resident step kernels (ring_resident.h): up to 32 blocks of 512 threads (up to 128 over several
 // XCDs by ADSEQ_RING_RESIDENT_BLOCKS), one or two groups of four neurons per thread, B N a
@@ -747,7 +766,7 @@ bool host_validate(const adseq_config* c) {
 // buffers, admission bits) instead of an adjoint delay line.
 // qsteps: steps of an open-loop stretch that FIFO and SORTED register at once; fewer where their buffers, or the overflow
 // entries that their worst case needs (every synapse of every trial in every step), would be out of proportion.
-bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
+bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bool small) {
   if (!host_validate(c)) return false;
   if (c->kind == ADSEQ_RING || !c->record_tape) sorted_rev = false;
   const size_t BN = (size_t)c->n_neurons * c->batch;
@@ -797,16 +816,14 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
   size_t stage_parts = 0;
   L->sorted_rev = sorted_rev;
   if (sorted_rev) {
-    L->W = ring_window_steps();
-    while (L->W > c->d_max_steps) L->W >>= 1;
+    L->W = ring_window_steps(c, small);
     L->wshift = bit_width((unsigned)L->W) - 1;
     L->wgroups = (L->words + 7) / 8;
   }
   if (!bounded) {
     // the window is no longer than the largest delay (so that a window boundary comes before
     // any spike word is overwritten)
-    L->W = ring_window_steps();
-    while (L->W > c->d_max_steps) L->W >>= 1;
+    L->W = ring_window_steps(c, small);
     L->wshift = bit_width((unsigned)L->W) - 1;
     // LDS tile of the accumulation pass: by default 4,096 cells, fewer (down to 1,024) where the state array would
     // otherwise give fewer than 256 target parts, one workgroup each (cfg2, 10,000 targets: 40 parts of 256 targets
@@ -814,6 +831,13 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
     int cells = ring_tile_cells();
     if (!getenv("ADSEQ_RING_TILE"))
       while (cells > 1024 && cells > 2 * L->W && (long long)BN * L->W / cells < 256) cells >>= 1;
+    // ... and more (up to 16,384) where the ordered staging, which handles kSortParts parts, then reaches the whole array,
+    // or where the staging would not
+    if (!getenv("ADSEQ_RING_TILE")) {
+      const long long all = (long long)BN * L->W;
+      while (all / cells >= kSortParts && all / kMaxTileCells < kSortParts) cells <<= 1;
+      while (all / cells > kMaxParts && cells < kMaxTileCells) cells <<= 1;
+    }
     if (cells < L->W) cells = L->W;
     L->tp_shift = bit_width((unsigned)cells) - 1 - L->wshift;
     L->P = (int)((BN + ((size_t)1 << L->tp_shift) - 1) >> L->tp_shift);
@@ -931,12 +955,13 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps) {
 // 2,000 steps forward and back 40.6 -> 27.7 ms) wherever 2^32 words of admission bits are enough for the tape; FIFO and SORTED
 // get the two contender buffers of k_queue_run, without a tape, where they may run open loop, those of a whole stretch
 // (k_queue_steps).  small: neither -- an
-// adjoint delay line and two launches per reverse step, a stretch of one step -- for what only so fits the static workspace.
+// adjoint delay line and two launches per reverse step, a stretch of one step, and windows of 16 steps -- for what only so
+// fits the static workspace.
 bool make_layout(const adseq_config* c, Layout* L, bool small = false) {
   if (!c) return false;
   if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
-      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps))) return true;
-  return layout_as(c, L, false, 1);
+      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps), false)) return true;
+  return layout_as(c, L, false, 1, small);
 }
 
 int fail(adseq* h, int code, const char* fmt, ...) {
