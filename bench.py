@@ -199,8 +199,8 @@ def main():
         label = {"fan_out": "k_fanout_step (CSR fan-out, full-target drops, contender registration)",
                  "lif": ("k_synq_pop + k_neurons (look at every queue, then drive + LIF + spike words)"
                          if args.queue in ("syn", "latest", "bins") else "k_neurons (admission + pop + drive + LIF + spike words)"),
-                 "bwd_gather": "k_bwd_rows (adjoint gathers and gradient sums of the step's recorded spikes)",
-                 "bwd_neurons": "k_bwd_neurons (adjoint update)"}
+                 "bwd_gather": "k_bwd_win (far queue terms and gradient sums of one window, admitted events)",
+                 "bwd_neurons": "k_bwd_flow (the reverse steps of one window in one launch, admitted events; counted by step)"}
     if args.queue == "ring" and prof.get("bwd_neurons", {}).get("launches", T) < T:
         # fewer launches than steps: the reverse steps of a window ran in one launch each (resident reverse kernel)
         label["bwd_neurons"] = ("k_bwd_xcd (the reverse steps of one window in one launch: adjoint update + in-window gather, a grid barrier per step)"
