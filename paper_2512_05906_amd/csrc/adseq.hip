@@ -30,6 +30,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -1326,6 +1327,41 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
   }
 }
 
+// The blocks of a resident launch over the whole chip wait for one another, so two such launches on different streams must
+// not be dealt out side by side: each could hold half of the chip and wait for the other half until its waits run out.  A call
+// that makes such launches therefore waits, on its stream, for the last such call of the process on another stream of the
+// device (one event per device), and holds the lock while it launches.  Not under capture, where an event of another
+// stream may not be waited for, and not for the static handle, which creates nothing.
+constexpr int kChipDevices = 64;
+std::mutex g_chip_lock;
+hipEvent_t g_chip_event[kChipDevices];
+hipStream_t g_chip_stream[kChipDevices];
+struct WholeChipCall {
+  bool on = false;
+  int dev = -1;
+  hipStream_t st;
+  WholeChipCall(const adseq* h, hipStream_t stream, bool wanted) : st(stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!wanted || h->in_static || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kChipDevices) return;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return; }
+    if (cap != hipStreamCaptureStatusNone) return;
+    g_chip_lock.lock();
+    on = true;
+    if (!g_chip_event[dev]) {
+      if (hipEventCreateWithFlags(&g_chip_event[dev], hipEventDisableTiming) != hipSuccess) g_chip_event[dev] = nullptr;
+    } else if (g_chip_stream[dev] != st) {
+      (void)hipStreamWaitEvent(st, g_chip_event[dev], 0);
+    }
+  }
+  ~WholeChipCall() {
+    if (!on) return;
+    if (g_chip_event[dev]) { (void)hipEventRecord(g_chip_event[dev], st); g_chip_stream[dev] = st; }
+    g_chip_lock.unlock();
+  }
+  WholeChipCall(const WholeChipCall&) = delete;
+  WholeChipCall& operator=(const WholeChipCall&) = delete;
+};
+
 // FIFO / SORTED: steps step0 .. step0 + n_steps - 1 by k_queue_run, up to 1,024 of them in one launch.
 void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_steps) {
   const Dev& d = h->dev;
@@ -1986,6 +2022,7 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   if (step0 != h->next_step)
     return fail(h, ADSEQ_E_ORDER, "adseq_run: got step %lld, expected %lld", (long long)step0, h->next_step);
   if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
+    WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);
     ring_run_chip(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->res_P > 0) {
     ring_run_resident(h, (hipStream_t)stream, step0, n_steps);
@@ -1995,7 +2032,10 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
     // (the last step goes by its own two launches: its events stay pending, to be admitted with what an adseq_enqueue may
     // add; so does everything while kernels are timed, class by class)
     const int64_t ahead = h->q_P > 0 && n_steps >= 4 && !h->prof ? n_steps - 1 : 0;
-    if (ahead) queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+    if (ahead) {
+      WholeChipCall turn(h, (hipStream_t)stream, true);
+      queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+    }
     for (int64_t n = ahead; n < n_steps; ++n) {
       const int rc = step_impl(h, step0 + n, nullptr, nullptr, (hipStream_t)stream);
       if (rc != ADSEQ_OK) return rc;
@@ -2048,6 +2088,7 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   const bool bounded = d.kind != ADSEQ_RING;
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
   if (!bounded || d.sorted_rev) {
+    WholeChipCall turn(h, st, h->rev_P > 0 && T > 0);
     ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr);
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
