@@ -1327,9 +1327,9 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
   }
 }
 
-// The blocks of a resident launch over the whole chip wait for one another, so two such launches on different streams must
-// not be dealt out side by side: each could hold half of the chip and wait for the other half until its waits run out.  A call
-// that makes such launches therefore waits, on its stream, for the last such call of the process on another stream of the
+// The blocks of a resident launch wait for one another, so two such launches on different streams must not be dealt out side
+// by side: each could hold half of the chip -- or, the one-XCD kernels and those whose blocks fall on few XCDs, of one XCD --
+// and wait for the other half until its waits run out.  A call that makes such launches therefore waits, on its stream, for the last such call of the process on another stream of the
 // device (one event per device), and holds the lock while it launches.  Not under capture, where an event of another
 // stream may not be waited for, and not for the static handle, which creates nothing.
 constexpr int kChipDevices = 64;
@@ -2025,8 +2025,10 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
     WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);
     ring_run_chip(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->res_P > 0) {
+    WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0 && h->res_P > 1);   // (one block waits for nobody)
     ring_run_resident(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->chain && n_steps >= 2 && chain_ready(h)) {
+    WholeChipCall turn(h, (hipStream_t)stream, true);
     ring_run_chain(h, (hipStream_t)stream, step0, n_steps);
   } else {
     // (the last step goes by its own two launches: its events stay pending, to be admitted with what an adseq_enqueue may
@@ -2088,7 +2090,7 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   const bool bounded = d.kind != ADSEQ_RING;
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
   if (!bounded || d.sorted_rev) {
-    WholeChipCall turn(h, st, h->rev_P > 0 && T > 0);
+    WholeChipCall turn(h, st, (h->rev_P > 0 || h->chain) && T > 0);
     ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr);
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;

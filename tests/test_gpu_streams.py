@@ -49,3 +49,32 @@ def test_two_streams(kinds):
         H.grad_close(grads[j][0].cpu().numpy(), want[j][0])
         H.grad_close(grads[j][1].cpu().numpy(), want[j][1])
         sims[j].close()
+
+
+@pytest.mark.parametrize("n_ring", [1996, 40000])
+def test_ring_waits_for_fifo(n_ring):
+    """A FIFO run of 16,000 targets (63 blocks that nearly fill two XCDs), and while it runs a ring of n_ring cells on
+    another stream: the ring's run ends after the FIFO's, and both results are the oracle's.  (1,996 cells: the ring's
+    kernel on the blocks of one XCD; 40,000: the one over the whole chip.)"""
+    T, n = 1500, 16000
+    wl = synth.ragged_network(n, 12, 20, seed=9, rate_hz=400.0, t=T, b=1, w_mean=0.04, w_std=0.04)
+    small = synth.ragged_network(n_ring, 60, 20, seed=4, rate_hz=400.0, t=T, b=1, w_mean=0.01, w_std=0.01)
+    refs = [oracle.Run(wl, adseq.FIFO, 4, n_steps=T, n_threads=8), oracle.Run(small, oracle.RING, 0, n_steps=T, n_threads=8)]
+    sims = [adseq.Adseq(wl, adseq.FIFO, 4, record_tape=True, max_steps=T),
+            adseq.Adseq(small, adseq.RING, 0, record_tape=True, max_steps=T)]
+    streams = [torch.cuda.Stream() for _ in sims]
+    ends = [torch.cuda.Event(enable_timing=True) for _ in sims]
+    torch.cuda.synchronize()
+    for sim, st, end, steps in zip(sims, streams, ends, (T, 40)):
+        with torch.cuda.stream(st):
+            sim.run(0, steps)
+            end.record(st)
+    torch.cuda.synchronize()
+    assert ends[0].elapsed_time(ends[1]) > 0.0
+    with torch.cuda.stream(streams[1]):
+        sims[1].run(40, T - 40)
+    torch.cuda.synchronize()
+    for sim, ref in zip(sims, refs):
+        assert sim.counters()["error_bits"] & 32 == 0
+        np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+        sim.close()
