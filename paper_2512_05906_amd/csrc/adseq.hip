@@ -1329,13 +1329,13 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
 
 // The blocks of a resident launch wait for one another, so two such launches on different streams must not be dealt out side
 // by side: each could hold half of the chip -- or, the one-XCD kernels and those whose blocks fall on few XCDs, of one XCD --
-// and wait for the other half until its waits run out.  A call that makes such launches therefore waits, on its stream, for the last such call of the process on another stream of the
-// device (one event per device), and holds the lock while it launches.  Not under capture, where an event of another
+// and wait for the other half until its waits run out.  A call that makes such launches therefore waits, on its stream, for the last such call of the process on the device (one event per
+// device, whichever stream it was recorded on: equal handles need not be one stream -- hipStreamPerThread is one value for all
+// threads, and that of a destroyed stream may come back), and holds the lock while it launches.  Not under capture, where an event of another
 // stream may not be waited for, and not for the static handle, which creates nothing.
 constexpr int kChipDevices = 64;
 std::mutex g_chip_lock;
 hipEvent_t g_chip_event[kChipDevices];
-hipStream_t g_chip_stream[kChipDevices];
 struct WholeChipCall {
   bool on = false;
   int dev = -1;
@@ -1349,13 +1349,13 @@ struct WholeChipCall {
     on = true;
     if (!g_chip_event[dev]) {
       if (hipEventCreateWithFlags(&g_chip_event[dev], hipEventDisableTiming) != hipSuccess) g_chip_event[dev] = nullptr;
-    } else if (g_chip_stream[dev] != st) {
+    } else {
       (void)hipStreamWaitEvent(st, g_chip_event[dev], 0);
     }
   }
   ~WholeChipCall() {
     if (!on) return;
-    if (g_chip_event[dev]) { (void)hipEventRecord(g_chip_event[dev], st); g_chip_stream[dev] = st; }
+    if (g_chip_event[dev]) (void)hipEventRecord(g_chip_event[dev], st);
     g_chip_lock.unlock();
   }
   WholeChipCall(const WholeChipCall&) = delete;

@@ -78,3 +78,43 @@ def test_ring_waits_for_fifo(n_ring):
         assert sim.counters()["error_bits"] & 32 == 0
         np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
         sim.close()
+
+
+def test_one_handle_value_two_streams():
+    """hipStreamPerThread is one handle value and a stream of its own in every thread: a run on the second thread's still
+    waits for the one on the first's."""
+    per_thread = torch.cuda.ExternalStream(2)
+    T = 1500
+    wl = synth.ragged_network(16000, 12, 20, seed=9, rate_hz=400.0, t=T, b=1, w_mean=0.04, w_std=0.04)
+    sims = [adseq.Adseq(wl, adseq.FIFO, 4, record_tape=True, max_steps=T) for _ in range(2)]
+    ends = [torch.cuda.Event(enable_timing=True) for _ in sims]
+    torch.cuda.synchronize()
+    failed, issued, done = [], threading.Event(), threading.Event()
+
+    def work(j, steps):
+        try:
+            with torch.cuda.stream(per_thread):
+                sims[j].run(0, steps)
+                ends[j].record(per_thread)
+        except Exception as e:
+            failed.append(e)
+        issued.set()
+        done.wait(60)   # (its stream goes with the thread)
+
+    threads = []
+    for j, steps in ((0, T), (1, 40)):
+        issued.clear()
+        threads.append(threading.Thread(target=work, args=(j, steps)))
+        threads[j].start()
+        issued.wait(60)
+    torch.cuda.synchronize()
+    assert not failed
+    assert ends[0].elapsed_time(ends[1]) > 0.0
+    done.set()
+    for t in threads:
+        t.join()
+    U = [s.tape()["U"].cpu().numpy().view(np.uint32) for s in sims]
+    np.testing.assert_array_equal(U[1], U[0][:40])
+    for s in sims:
+        assert s.counters()["error_bits"] & 32 == 0
+        s.close()
