@@ -1329,10 +1329,12 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
 
 // The blocks of a resident launch wait for one another, so two such launches on different streams must not be dealt out side
 // by side: each could hold half of the chip -- or, the one-XCD kernels and those whose blocks fall on few XCDs, of one XCD --
-// and wait for the other half until its waits run out.  A call that makes such launches therefore waits, on its stream, for the last such call of the process on the device (one event per
-// device, whichever stream it was recorded on: equal handles need not be one stream -- hipStreamPerThread is one value for all
-// threads, and that of a destroyed stream may come back), and holds the lock while it launches.  Not under capture, where an event of another
-// stream may not be waited for, and not for the static handle, which creates nothing.
+// and wait for the other half until its waits run out.  A call that makes such launches therefore waits, on its stream, for
+// the last such call of the process on the device (one event per device, whichever stream it was recorded on: equal handles
+// need not be one stream -- hipStreamPerThread is one value for all threads, and that of a destroyed stream may come back),
+// and holds the lock while it launches.  on: the call has its turn.  There is none under capture, where an event of another
+// stream may not be waited for, and none for the static handle, which creates nothing: there the bounded kinds keep to
+// launches whose blocks wait for nobody, and a ring's launches need what adseq.h says of them.
 constexpr int kChipDevices = 64;
 std::mutex g_chip_lock;
 hipEvent_t g_chip_event[kChipDevices];
@@ -1346,16 +1348,16 @@ struct WholeChipCall {
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return; }
     if (cap != hipStreamCaptureStatusNone) return;
     g_chip_lock.lock();
-    on = true;
-    if (!g_chip_event[dev]) {
-      if (hipEventCreateWithFlags(&g_chip_event[dev], hipEventDisableTiming) != hipSuccess) g_chip_event[dev] = nullptr;
-    } else {
-      (void)hipStreamWaitEvent(st, g_chip_event[dev], 0);
-    }
+    hipEvent_t& ev = g_chip_event[dev];
+    if (ev) on = hipStreamWaitEvent(st, ev, 0) == hipSuccess;
+    else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) on = true;
+    else ev = nullptr;
+    if (!on) { (void)hipGetLastError(); g_chip_lock.unlock(); }
   }
   ~WholeChipCall() {
     if (!on) return;
-    if (g_chip_event[dev]) (void)hipEventRecord(g_chip_event[dev], st);
+    // (a call that cannot leave its mark is over before the next one begins)
+    if (hipEventRecord(g_chip_event[dev], st) != hipSuccess) { (void)hipGetLastError(); (void)hipStreamSynchronize(st); }
     g_chip_lock.unlock();
   }
   WholeChipCall(const WholeChipCall&) = delete;
@@ -1452,11 +1454,11 @@ int gather_blocks(const Dev& d, long long n_lo, long long n_hi) {
 // The whole reverse sweep on `st` (RING, and the bounded kinds with sorted rows: only admitted events, adm).  A window is swept as a whole (ring_reverse.h: one dense
 // pass, the near corrections step by step inside one workgroup, then the far gather) when
 // `counts` (spikes and near events of every step, from k_bwd_near_counts; null: never) says that
-// its staging fits; otherwise with one launch per reverse step (k_bwd_step_win).  Either way, when
+// its staging fits; otherwise in one launch (resident) or with one per reverse step (k_bwd_step_win).  Either way, when
 // a window is complete the far queue terms of all earlier spikes that arrive in it are gathered in
 // one pass.
 void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, const float* dL_dcount,
-                          const float* dL_dU, float* grad_w, float* grad_d, const int* counts) {
+                          const float* dL_dU, float* grad_w, float* grad_d, const int* counts, bool resident) {
   const Dev& d = h->dev;
   const dim3 block(kBlock), gn((unsigned)d.nblk);
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
@@ -1498,7 +1500,7 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
         }
       }
     } else {
-      if (h->rev_P > 0) {
+      if (resident) {
         // the steps of the window in one launch on the blocks of one XCD (ring_resident_reverse.h)
         int stride = env_pow2("ADSEQ_RING_RESIDENT_STRIDE", kResStride, 1, 8);
         while (stride > 1 && (long long)h->rev_P * stride > 32 * 8) stride >>= 1;
@@ -1543,7 +1545,7 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
       }
     }
     // launches of the group: the resident reverse kernel takes the window in one (the bounded kinds count reverse steps)
-    h->grp_count += (!whole && h->rev_P > 0 && !adm) ? 1 : nsteps;
+    h->grp_count += (!whole && resident && !adm) ? 1 : nsteps;
     // far gather into the window (and, after a sweep of the whole window, the per-synapse sums of
     // its own near events): spikes of steps [lo, hi)
     const long long lo = k0 - d.d_max > 0 ? k0 - d.d_max : 0;
@@ -2032,11 +2034,14 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
     ring_run_chain(h, (hipStream_t)stream, step0, n_steps);
   } else {
     // (the last step goes by its own two launches: its events stay pending, to be admitted with what an adseq_enqueue may
-    // add; so does everything while kernels are timed, class by class)
-    const int64_t ahead = h->q_P > 0 && n_steps >= 4 && !h->prof ? n_steps - 1 : 0;
-    if (ahead) {
-      WholeChipCall turn(h, (hipStream_t)stream, true);
-      queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+    // add; so does everything while kernels are timed, class by class, and where the call has no turn)
+    int64_t ahead = 0;
+    {
+      WholeChipCall turn(h, (hipStream_t)stream, h->q_P > 0 && n_steps >= 4 && !h->prof);
+      if (turn.on) {
+        ahead = n_steps - 1;
+        queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+      }
     }
     for (int64_t n = ahead; n < n_steps; ++n) {
       const int rc = step_impl(h, step0 + n, nullptr, nullptr, (hipStream_t)stream);
@@ -2091,7 +2096,8 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
   if (!bounded || d.sorted_rev) {
     WholeChipCall turn(h, st, (h->rev_P > 0 || h->chain) && T > 0);
-    ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr);
+    ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr,
+                         h->rev_P > 0 && (!bounded || turn.on));
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }

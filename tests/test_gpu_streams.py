@@ -118,3 +118,54 @@ def test_one_handle_value_two_streams():
     for s in sims:
         assert s.counters()["error_bits"] & 32 == 0
         s.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 4), (adseq.SORTED, 3), (adseq.SYN_FIFO, 2)])
+def test_static_handle_waits_for_nobody(kind, cap, monkeypatch):
+    """The static handle takes no turn, so the bounded kinds' runs and reverse sweeps make no launch whose blocks wait for
+    one another: with a bound of one poll such a wait would run out (as it does with an ordinary handle)."""
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    T, n = 60, 3000
+    wl = synth.ragged_network(n, 12, 20, seed=9, rate_hz=900.0, t=T, b=1, w_mean=0.04, w_std=0.04)
+    dc = np.random.default_rng(1).normal(0, 1e-3, (1, n)).astype(np.float32)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, n_threads=8)
+    want = ref.backward(dc, None)
+    sim = adseq.Adseq(wl, kind, cap, record_tape=True, max_steps=T, static_workspace=True)
+    sim.run(0, T)
+    grads = [torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2)]
+    sim.backward(torch.from_numpy(dc).to(sim.dev), None, *grads)
+    torch.cuda.synchronize()
+    assert sim.counters()["error_bits"] == 0
+    np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    H.grad_close(grads[0].cpu().numpy(), want[0])
+    H.grad_close(grads[1].cpu().numpy(), want[1])
+    sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 4), (adseq.SORTED, 3)])
+def test_captured_run_waits_for_nobody(kind, cap, monkeypatch):
+    """A captured run takes no turn either.  Every replay, with eager work of another handle in between, is the oracle's."""
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    T, n = 60, 3000
+    wl = synth.ragged_network(n, 12, 20, seed=9, rate_hz=900.0, t=T, b=1, w_mean=0.04, w_std=0.04)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, n_threads=8)
+    sim = adseq.Adseq(wl, kind, cap, record_tape=True, max_steps=T)
+    monkeypatch.delenv("ADSEQ_RING_RESIDENT_SPINS")
+    other = adseq.Adseq(wl, kind, cap, record_tape=True, max_steps=T)
+    U = sim.membrane_tape(T)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sim.reset()
+        sim.run(0, T)
+    for _ in range(3):
+        U.zero_()
+        other.reset()
+        other.run(0, T)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert sim.counters()["error_bits"] == 0
+        for u in (U, other.membrane_tape(T)):
+            np.testing.assert_array_equal(u.cpu().numpy().view(np.uint32).reshape(ref.U.shape), ref.U.view(np.uint32))
+    other.close()
+    sim.close()
