@@ -228,11 +228,10 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
  * launch needs the device free enough for all its blocks to run at the same time.  Calls that
  * make such launches (adseq_backward too) wait, on their stream, for the last such call of the
- * process on the device.  Under stream capture, and with the handle of adseq_create_static, they
- * cannot: there ADSEQ_FIFO, ADSEQ_SORTED and the reverse sweeps of all the bounded kinds keep to launches
- * whose blocks wait for nobody (one or two per step); a ring's launches stay what they are, and the
- * program keeps them apart from other such launches (same stream, or events of its own; the replays
- * of a graph likewise).  adseq_create
+ * process on the device.  Under stream capture they cannot: there, and with the handle of adseq_create_static,
+ * the bounded kinds keep to launches whose blocks wait for nobody, one or two per step; a captured ring's launches stay what they are, and
+ * the program keeps the graph's replays apart from other such launches (same stream, or events of
+ * its own).  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
  * launch per step (same results).  Every wait is
  * bounded: if one runs out, the kernels still run to their end, the run is void, and the error

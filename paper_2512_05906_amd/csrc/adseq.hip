@@ -1333,8 +1333,9 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
 // the last such call of the process on the device (one event per device, whichever stream it was recorded on: equal handles
 // need not be one stream -- hipStreamPerThread is one value for all threads, and that of a destroyed stream may come back),
 // and holds the lock while it launches.  on: the call has its turn.  There is none under capture, where an event of another
-// stream may not be waited for, and none for the static handle, which creates nothing: there the bounded kinds keep to
-// launches whose blocks wait for nobody, and a ring's launches need what adseq.h says of them.
+// stream may not be waited for: there the bounded kinds keep to launches whose blocks wait for nobody, and a ring's launches
+// need what adseq.h says of them.  The event is made with the device's first handle that may allocate.  The static handle makes
+// none: its ring takes turns from then on (until then nobody else is there), its bounded kinds keep to launches per step.
 constexpr int kChipDevices = 64;
 std::mutex g_chip_lock;
 hipEvent_t g_chip_event[kChipDevices];
@@ -1344,14 +1345,11 @@ struct WholeChipCall {
   hipStream_t st;
   WholeChipCall(const adseq* h, hipStream_t stream, bool wanted) : st(stream) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!wanted || h->in_static || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kChipDevices) return;
+    if (!wanted || (h->in_static && h->dev.kind != ADSEQ_RING) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kChipDevices) return;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return; }
     if (cap != hipStreamCaptureStatusNone) return;
     g_chip_lock.lock();
-    hipEvent_t& ev = g_chip_event[dev];
-    if (ev) on = hipStreamWaitEvent(st, ev, 0) == hipSuccess;
-    else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) on = true;
-    else ev = nullptr;
+    on = g_chip_event[dev] && hipStreamWaitEvent(st, g_chip_event[dev], 0) == hipSuccess;   // (not recorded yet: no wait)
     if (!on) { (void)hipGetLastError(); g_chip_lock.unlock(); }
   }
   ~WholeChipCall() {
@@ -1363,6 +1361,16 @@ struct WholeChipCall {
   WholeChipCall(const WholeChipCall&) = delete;
   WholeChipCall& operator=(const WholeChipCall&) = delete;
 };
+// Makes the event of the current device (at its first handle that may allocate).  unseen: the static handle is alive and may
+// have launches under way that left no mark.
+void chip_event_make(bool unseen) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kChipDevices) return;
+  std::lock_guard<std::mutex> hold(g_chip_lock);
+  if (g_chip_event[dev]) return;
+  if (hipEventCreateWithFlags(&g_chip_event[dev], hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); g_chip_event[dev] = nullptr; return; }
+  if (unseen) (void)hipDeviceSynchronize();
+}
 
 // FIFO / SORTED: steps step0 .. step0 + n_steps - 1 by k_queue_run, up to 1,024 of them in one launch.
 void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_steps) {
@@ -1809,6 +1817,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     d.chain_sleep = env_pow2("ADSEQ_RING_CHAIN_SLEEP", 1, 0, 64);
     d.rev_delay = env_pow2("ADSEQ_RING_REVERSE_DELAY", 0, 0, 16);
     d.res_wide = env_pow2("ADSEQ_RING_RESIDENT_WIDE", 0, 0, 1);
+  }
+  if (!storage) {
+    int dev = -1;
+    chip_event_make(hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && g_static_busy[dev]);
   }
   hipStream_t st = (hipStream_t)cfg->stream;
   launch_reset(h, st);

@@ -169,3 +169,28 @@ def test_captured_run_waits_for_nobody(kind, cap, monkeypatch):
             np.testing.assert_array_equal(u.cpu().numpy().view(np.uint32).reshape(ref.U.shape), ref.U.view(np.uint32))
     other.close()
     sim.close()
+
+
+def test_static_ring_takes_its_turn():
+    """The static handle's ring waits for the FIFO run of an ordinary handle on another stream, and the other way round."""
+    T = 1500
+    wl = synth.ragged_network(16000, 12, 20, seed=9, rate_hz=400.0, t=T, b=1, w_mean=0.04, w_std=0.04)
+    small = synth.ragged_network(1996, 60, 20, seed=4, rate_hz=400.0, t=T, b=1, w_mean=0.01, w_std=0.01)
+    fifo = adseq.Adseq(wl, adseq.FIFO, 4, record_tape=True, max_steps=T)
+    ring = adseq.Adseq(small, adseq.RING, 0, record_tape=True, max_steps=1000, static_workspace=True)
+    for order in (((fifo, T), (ring, 40)), ((ring, 1000), (fifo, 40))):
+        ends = [torch.cuda.Event(enable_timing=True) for _ in order]
+        fifo.reset(); ring.reset()
+        torch.cuda.synchronize()
+        for (sim, steps), end in zip(order, ends):
+            st = torch.cuda.Stream()
+            with torch.cuda.stream(st):
+                sim.run(0, steps)
+                end.record(st)
+        torch.cuda.synchronize()
+        assert ends[0].elapsed_time(ends[1]) > 0.0
+        assert fifo.counters()["error_bits"] == 0 and ring.counters()["error_bits"] == 0
+    ref = oracle.Run(small, oracle.RING, 0, n_steps=1000, n_threads=8)
+    np.testing.assert_array_equal(ring.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    ring.close()
+    fifo.close()
