@@ -234,7 +234,7 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * its own).  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
  * launch per step (same results).  Every wait is
- * bounded: if one runs out, the kernels still run to their end, the run is void, and the error
+ * bounded (tens of ms, with the bounded kinds a second and more): if one runs out, the kernels still run to their end, the run is void, and the error
  * word carries bit 32 (adseq_counters; adseq_drop_count and adseq_backward then return
  * ADSEQ_E_HIP until adseq_reset). */
 int adseq_run(adseq_t *h, int64_t step0, int64_t n_steps, void *stream);

@@ -180,7 +180,7 @@ struct Dev {
   unsigned long long* adm_bits;  // bounded kinds: admission flags of every spike's sorted row, one bit each (k_adm_bits)
   long long* insum;     // [N] create only: sum of |Q8.24 amplitude| over every target's incoming synapses
   int flow_hold;        // RING, reverse kernel without a grid barrier: 1 = spiking neurons never store their final adjoints (ADSEQ_RING_FLOW_WITHHOLD: drives the waits' failure path from the host)
-  int res_spins;        // RING, resident kernels: polls of one wait before it gives up (kResMaxSpins; ADSEQ_RING_RESIDENT_SPINS lowers it to test the failure path)
+  int res_spins;        // resident kernels: polls of one wait before it gives up (kResMaxSpins, bounded kinds kResMaxSpinsBounded; ADSEQ_RING_RESIDENT_SPINS lowers it to test the failure path)
   int lazy_rows;        // RING: the step kernels fetch row start, in-window count and far queue term for spiking lanes only (experiment)
   int count_pop;        // RING: the step kernels add up the Q8.24 sums they pop (checking aid, off by default)
   int chain_sleep;      // RING, chained step launches: pauses of 128 cycles between two polls of a wait
@@ -1709,7 +1709,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
 #endif
   d.count_pop = env_pow2("ADSEQ_RING_COUNT_POPPED", 0, 0, 1);
   d.lazy_rows = env_pow2("ADSEQ_RING_LAZY_ROWS", 0, 0, 1);
-  d.res_spins = env_pow2("ADSEQ_RING_RESIDENT_SPINS", kResMaxSpins, 1, kResMaxSpins);
+  {
+    const int most = d.kind == ADSEQ_RING ? kResMaxSpins : kResMaxSpinsBounded;
+    d.res_spins = env_pow2("ADSEQ_RING_RESIDENT_SPINS", most, 1, most);
+  }
   d.flow_hold = env_pow2("ADSEQ_RING_FLOW_WITHHOLD", 0, 0, 1);
   d.W = L.W; d.wshift = L.wshift; d.tp_shift = L.tp_shift; d.P = L.P; d.NB = L.NB; d.cap = L.cap;
   d.wgroups = L.wgroups;

@@ -24,6 +24,9 @@ constexpr int kResThreads = 512;      // two wavefronts per SIMD: a step is boun
 constexpr int kResBlocks = 32;        // taking-part blocks at most: the compute units of one XCD
 constexpr int kResStride = 8;         // XCDs: block b runs on XCD b mod 8
 constexpr int kResMaxSpins = 1 << 16;  // polls of one wait before it gives up (tens of ms; a step takes microseconds); Dev::res_spins, lowered only by tests of the failure path
+// The same for the bounded kinds (a second and more): their launches per step once ran beside kernels of any length, so blocks that are
+// on the chip wait for those whose compute units a foreign kernel holds for as long as that may take.
+constexpr int kResMaxSpinsBounded = 1 << 22;
 constexpr int kResLaunch = kResThreads + 64;   // one more wavefront per block that only synchronises: it
                                                // polls the barrier counter and adds the block's arrival, so that
                                                // a poll never waits behind the stores of a wavefront that has neurons

@@ -94,3 +94,21 @@ def test_queue_resident_wait_that_runs_out_is_reported(monkeypatch):
     sim.reset()
     assert sim.counters()["error_bits"] == 0
     sim.close()
+
+
+def test_waits_outlast_foreign_kernels(monkeypatch):
+    """The bounded kinds' waits last for a second and more, not tens of ms, before a run is void: a foreign kernel may hold compute
+    units that long.  (Cells withheld from the host: the reverse sweep's waits run out, its kernels end.)"""
+    monkeypatch.setenv("ADSEQ_RING_FLOW_WITHHOLD", "1")
+    T = 30
+    wl = synth.ragged_network(3000, 30, 20, seed=45, rate_hz=900.0, t=T, b=1, w_mean=0.02, w_std=0.01)
+    sim = _run(wl, adseq.FIFO, 4, T, 1, [T])
+    g = torch.empty(wl.n_synapses, device=sim.dev)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    sim.backward(torch.full((3000,), 1e-3, device=sim.dev), None, g, g.clone())
+    b.record()
+    torch.cuda.synchronize()
+    assert sim.counters()["error_bits"] & 32
+    assert 300.0 < a.elapsed_time(b) < 30000.0
+    sim.close()
