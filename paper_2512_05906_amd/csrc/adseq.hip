@@ -1992,38 +1992,46 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }
-  int64_t done = 0;
-  if (h->dev.qsteps > 1 && n_steps >= 4 && (I_stride == 0 || I_stride >= h->dev.BN) && step0 == h->next_step) {
-    // FIFO / SORTED: stretches of steps (k_fanout_steps, k_queue_steps) for all steps but the last, whose events stay
-    // pending: an adseq_enqueue for the same step may add to them.  Output rows that overlap, where the later step's
-    // values stay, go step by step.
-    const Dev& d = h->dev;
-    hipStream_t st = (hipStream_t)stream;
-    flush_admit(h, st);
-    for (int64_t k = 0; k < n_steps - 1;) {
-      const int cnt = (int)(n_steps - 1 - k < d.qsteps ? n_steps - 1 - k : d.qsteps);
-      QueueOffsets o;
-      for (int j = 0; j < cnt; ++j) o.off[j] = spike_offsets[k + j];
-      const dim3 fan(kFanoutBlocks / kQueueSteps, (unsigned)cnt), fb(kBlock), own((unsigned)((d.BN + 63) / 64)), ob(64);
-      if (d.kind == ADSEQ_FIFO) {
-        hipLaunchKernelGGL((k_fanout_steps<ADSEQ_FIFO>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
-        hipLaunchKernelGGL((k_queue_steps<ADSEQ_FIFO>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
-      } else {
-        hipLaunchKernelGGL((k_fanout_steps<ADSEQ_SORTED>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
-        hipLaunchKernelGGL((k_queue_steps<ADSEQ_SORTED>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
+  // FIFO / SORTED: stretches of steps (k_fanout_steps, k_queue_steps) for all steps but the last, whose events stay
+  // pending: an adseq_enqueue for the same step may add to them.  Output rows that overlap, where the later step's
+  // values stay, go step by step; so do two steps (three launches, two of them wide, against four), and crowded ones.  Within a
+  // stretch nothing is dropped where it is emitted, as a step's own fan-out does when the target is full, so every event
+  // costs a ticket and a record, and beyond kCont of one target and step a walk of a list.  How many there are is read off the
+  // caller's list positions.  Stretch against a launch pair per step, us per step: 32,000 events per step for 40,000 targets 6.9
+  // / 13.6, 64,000 for 16,000 12.3 / 20.4; 20,000 for 2,000 17.4 / 19.3; 60,000 for 2,000 54.8 / 42.3; 100,000 for 10,000 33.5 / 29.7; 200,000 for
+  // 100,000 30.0 / 20.8; 400,000 for 100,000 66.7 / 33.7.  In pairs of steps 11.8 / 13.6 at best, 19.6 / 18.4 in short calls.
+  const Dev& d = h->dev;
+  hipStream_t st = (hipStream_t)stream;
+  const bool stretches = d.qsteps > 1 && (I_stride == 0 || I_stride >= d.BN) && step0 == h->next_step;
+  for (int64_t k = 0; k < n_steps;) {
+    const int cnt = (int)(n_steps - 1 - k < d.qsteps ? n_steps - 1 - k : d.qsteps);
+    if (stretches && cnt >= 3) {
+      const double spikes = std::fabs((double)(spike_offsets[k + cnt - 1] - spike_offsets[k])) / (cnt - 1);
+      const double events = spikes * (double)d.S / (double)d.N;
+      if (events <= 65536.0 && events <= (double)kCont * (double)d.BN) {
+        flush_admit(h, st);
+        QueueOffsets o;
+        for (int j = 0; j < cnt; ++j) o.off[j] = spike_offsets[k + j];
+        const dim3 fan((unsigned)(kFanoutBlocks / cnt), (unsigned)cnt), fb(kBlock), own((unsigned)((d.BN + 63) / 64)), ob(64);
+        if (d.kind == ADSEQ_FIFO) {
+          hipLaunchKernelGGL((k_fanout_steps<ADSEQ_FIFO>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
+          hipLaunchKernelGGL((k_queue_steps<ADSEQ_FIFO>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
+        } else {
+          hipLaunchKernelGGL((k_fanout_steps<ADSEQ_SORTED>), fan, fb, 0, st, d, (long long)(step0 + k), spike_ids, n_spikes + k, o);
+          hipLaunchKernelGGL((k_queue_steps<ADSEQ_SORTED>), own, ob, 0, st, d, (long long)(step0 + k), cnt, I_out + k * I_stride, (long long)I_stride);
+        }
+        k += cnt;
+        h->next_step = step0 + k;
+        h->enq_calls += cnt;
+        h->tape_ok = false;
+        HIP_TRY(h, hipGetLastError());
+        continue;
       }
-      k += cnt;
-      h->next_step = step0 + k;
-      h->enq_calls += cnt;
-      h->tape_ok = false;
-      done = k;
     }
-    HIP_TRY(h, hipGetLastError());
-  }
-  for (int64_t k = done; k < n_steps; ++k) {
     int rc = adseq_deliver(h, step0 + k, I_out + k * I_stride, stream);
     if (rc == ADSEQ_OK) rc = adseq_enqueue(h, step0 + k, spike_ids + spike_offsets[k], n_spikes + k, stream);
     if (rc != ADSEQ_OK) return rc;
+    ++k;
   }
   return ADSEQ_OK;
 }

@@ -1,6 +1,8 @@
 """Open-loop stretches of the ring (adseq_run_open: all the steps of a window enqueued in one launch and popped in
 another) against the oracle, bit for bit: calls cut so that stretches start and end anywhere in a window, mixed with
 single deliver / enqueue calls; output rows that are apart, that share one buffer and that overlap."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -93,4 +95,44 @@ def test_open_stretches_bounded(kind, cap, n, fan, b, d_max, rate, steps, stride
     c, rc = sim.counters(), ref.counters()
     for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
         assert c[key] == rc[key], key
+    sim.close()
+
+
+def _launches(call):
+    """Kernels that a call launches: nodes of the graph that it is captured into."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    lib = [line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line][0]
+    n = C.c_size_t(0)
+    assert C.CDLL(lib).hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 2), (adseq.SORTED, 2)])
+@pytest.mark.parametrize("n,rate,crowded", [(5000, 0.2, True), (150, 0.6, True), (5000, 0.02, False)])
+def test_crowded_stretches_go_step_by_step(kind, cap, n, rate, crowded):
+    """More events in a step than 65,536, or than there are record slots: two launches per step; otherwise two per stretch,
+    the spikes' rows spread over as many blocks as a step's.  In between, calls of either sort in turn, against the oracle."""
+    T = 90
+    wl = synth.ragged_network(n, 150 if crowded else 30, 25, seed=n, rate_hz=0.0, t=T, b=1, w_mean=0.01, w_std=0.02)
+    rng = np.random.default_rng(2)
+    dense = (np.arange(T) // 30) != 1   # (30 crowded steps, 30 sparse ones, 30 crowded ones)
+    forced = (rng.random((T, n)) < np.where(dense, rate, 0.01)[:, None]).astype(np.uint8)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=1, forced_spikes=forced.reshape(T, 1, n), keep_currents=True)
+    sim = adseq.Adseq(wl, kind, cap)
+    counts = torch.from_numpy(forced.sum(axis=1).astype(np.int32)).to(sim.dev)
+    offs = np.concatenate([[0], np.cumsum(forced.sum(axis=1))]).astype(np.int64)
+    ids = torch.from_numpy(np.flatnonzero(forced).astype(np.int32) % n).to(sim.dev)
+    out = torch.zeros((T, n), dtype=torch.float32, device=sim.dev)
+    sim.run_open(0, T, ids, offs[:T], counts, out, n)
+    want = ref.Iq.reshape(T, n).astype(np.float32) * np.float32(2.0 ** -24)
+    np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    sim.reset()
+    torch.cuda.synchronize()
+    # (29 steps in stretches, the last one in two launches; or all 30 in two each)
+    assert _launches(lambda: sim.run_open(0, 30, ids, offs[:30], counts, out, n)) == (60 if crowded else 4)
     sim.close()
