@@ -101,8 +101,11 @@ __device__ __forceinline__ void pop_target(const Dev& d, QueueLds<NPT, LS>& L, i
 // records (the others are requested here, together).  deliver: an event that is due at step kn is delivered at once (false:
 // the launch ends, everything is stored).  The winners are a bit mask over the record slots, so that there is one copy of the
 // insertion and not one per slot: unrolled as in k_neurons this kernel spilled a hundred registers.  More contenders than
-// slots: the smallest synapse index is selected again and again, reading the records and the list anew.
-template <int KIND, int NPT, bool LS>
+// record slots: if there is room for all, the records and the overflow list are walked once; if not, the smallest synapse index is
+// selected as often as there is room.  (Selecting in either case, an entry and then the link to the next, took longer than
+// two launches per step: 16,000 targets, 25 contenders for each in every step, us per step: SORTED[128] with room for all 1,002 -> 176,
+// two launches 262; FIFO[32], one event in six dropped, 693 -> 496, two launches 530; 10 contenders 194 -> 60, two launches 103.)
+template <int KIND, bool RECORD, int NPT, bool LS>
 __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L, const QBuf& qb, int t, int g, int K, unsigned kn, bool deliver,
                                              const uint4& c0, const uint4& c1, StepAcc& r, long long& s_del) {
   QState q = qstate_of<KIND>(L, t);
@@ -128,7 +131,7 @@ __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L,
     for (int x = 2; x < kCont; ++x) { cc[x] = make_uint4(0u, 0u, 0u, 0u); if (x < K) cc[x] = cont_load(d, qb, x, g); }
     unsigned won = take ? (1u << K) - 1u : 0u;
     if (take > 0 && take < K) {
-      // a contender's rank among them decides (synapse indices below 2^28)
+      // a contender's rank among them decides (synapse indices below 2^30)
       int rank[kCont];
 #pragma unroll
       for (int x = 0; x < kCont; ++x) rank[x] = 0;
@@ -155,28 +158,49 @@ __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L,
   } else {
     const int head = q_load<true>(&qb.head[g]);   // beyond the record slots: overflow list
     q_store<true>(&qb.head[g], -1);
-    const int nrec = kCont;
+    const bool all = take == K;   // room for all of them: taken as they stand
+    int at = head;
     long long last = -1;
     for (int rnd = 0; rnd <= take; ++rnd) {   // (the last round clears the flags of those that are left)
       const bool clear = rnd == take;
       long long bp = 0x7fffffffffffffffLL, flag = -1;
       unsigned k = 0; int a = 0;
-      for (int x = 0; x < nrec; ++x) {
-        const uint4 c = cont_load(d, qb, x, g);
-        const long long p = cont_syn(c);
-        if (p <= last) continue;
-        if (clear) flag_it(cont_flag(c), 0);
-        else if (p < bp) { bp = p; k = cont_arrival(c, kn); a = (int)c.w; flag = cont_flag(c); }
+      if (clear && (all || !RECORD)) break;
+      if (all && rnd < kCont) {
+        const uint4 c = cont_load(d, qb, rnd, g);
+        k = cont_arrival(c, kn); a = (int)c.w; flag = cont_flag(c);
+      } else if (all) {
+        if (!linked(at)) break;
+        const int next = q_load<true>(&d.pool_next[at]);
+        k = q_load<true>(&d.pool_k[at]); a = q_load<true>(&d.pool_a[at]); flag = q_load<true>(&d.pool_t[at]);
+        at = next;
+      } else {
+        // (requested together where there are registers for it; so are an entry of the list and the link to the next)
+        constexpr int kAtOnce = NPT == 1 ? kCont : 1;
+#pragma unroll 1
+        for (int x0 = 0; x0 < kCont; x0 += kAtOnce) {
+          uint4 cc[kAtOnce];
+#pragma unroll
+          for (int x = 0; x < kAtOnce; ++x) cc[x] = cont_load(d, qb, x0 + x, g);
+#pragma unroll
+          for (int x = 0; x < kAtOnce; ++x) {
+            const long long p = cont_syn(cc[x]);
+            if (clear) { if (p > last) flag_it(cont_flag(cc[x]), 0); }
+            else if (p > last && p < bp) { bp = p; k = cont_arrival(cc[x], kn); a = (int)cc[x].w; flag = cont_flag(cc[x]); }
+          }
+        }
+        int y = head, best = -1;
+        for (int left = K - kCont; left > 0 && linked(y); --left) {
+          const int next = q_load<true>(&d.pool_next[y]);
+          const long long p = q_load<true>(&d.pool_p[y]);
+          if (clear) { if (p > last) flag_it(q_load<true>(&d.pool_t[y]), 0); }
+          else if (p > last && p < bp) { bp = p; best = y; }
+          y = next;
+        }
+        if (best >= 0) { k = q_load<true>(&d.pool_k[best]); a = q_load<true>(&d.pool_a[best]); flag = q_load<true>(&d.pool_t[best]); }
+        if (clear) break;
+        last = bp;
       }
-      int left = K - nrec;
-      for (int y = head; left > 0 && linked(y); y = q_load<true>(&d.pool_next[y]), --left) {
-        const long long p = q_load<true>(&d.pool_p[y]);
-        if (p <= last) continue;
-        if (clear) flag_it(q_load<true>(&d.pool_t[y]), 0);
-        else if (p < bp) { bp = p; k = q_load<true>(&d.pool_k[y]); a = q_load<true>(&d.pool_a[y]); flag = q_load<true>(&d.pool_t[y]); }
-      }
-      if (clear) break;
-      last = bp;
       take_in(k, a);
       flag_it(flag, 1);
     }
@@ -236,7 +260,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
   const bool syn = d.alpha_s > 0.0f, dexp = d.alpha_r > 0.0f;
   const unsigned long long G64 = 0x9E3779B97F4A7C15ull;
   float V[NPT];
-  int r0[NPT], rlen[NPT];   // (B S < 2^28)
+  int r0[NPT], rlen[NPT];   // (2 B S entries fit the overflow pool: B S < 2^30)
   unsigned long long zg[NPT];
   const int voff = (lo + tid) * 4;   // of the thread's first target in a row of 4-byte values; the others 2,048 bytes apart
   constexpr int kRow = kResThreads * 4;
@@ -324,7 +348,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
         const int K = ld_agent(&in.cnt[g]);
         // (the first two records are requested beside the count: most targets that have contenders have no more)
         const uint4 c0 = cont_load(d, in, 0, g), c1 = cont_load(d, in, 1, g);
-        if (K > 0) admit_target<KIND>(d, L, in, tid, g, K, kn, !last, c0, c1, r, s_del);
+        if (K > 0) admit_target<KIND, RECORD>(d, L, in, tid, g, K, kn, !last, c0, c1, r, s_del);
       }
 #pragma unroll
       for (int x = 0; x < 4; ++x) { const int w = tid + x * kResThreads; if (w < d.words && w < 2048) L.full[w] = stay[x]; }
@@ -341,7 +365,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       for (int x = tid; x < offered; x += kResThreads) {
         const int t = L.list[x].x, Kt = L.list[x].y, g = lo + t;
         const uint4 c0 = cont_load(d, in, 0, g), c1 = cont_load(d, in, 1, g);
-        admit_target<KIND>(d, L, in, t, g, Kt, kn, !last, c0, c1, r, s_del);
+        admit_target<KIND, RECORD>(d, L, in, t, g, Kt, kn, !last, c0, c1, r, s_del);
       }
     }
     if (rank == 0 && tid == 0) q_store<true>(in.pool_n, 0);   // (its entries are being consumed; the next ones come a barrier later)

@@ -112,3 +112,43 @@ def test_waits_outlast_foreign_kernels(monkeypatch):
     assert sim.counters()["error_bits"] & 32
     assert 300.0 < a.elapsed_time(b) < 30000.0
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap,n,b", [(adseq.SORTED, 128, 16000, 1), (adseq.FIFO, 32, 16000, 1), (adseq.FIFO, 128, 40000, 5),
+                                          (adseq.SORTED, 12, 40000, 15)])
+def test_bursts(kind, cap, n, b, monkeypatch):
+    """25 contenders per target in every step, room for all of them, for some and for none: same trace, counters and (through
+    the flags) gradients as a launch pair per step, and not slower by more than half where one target per thread is."""
+    T = 16
+    rng = np.random.default_rng(3)
+    fan = 100
+    wl = synth.Workload(name="bursts", n_neurons=n, fan_out=fan, n_steps=T, batch=b, d_max_steps=4, ext_rate_hz=2500.0,
+                        ext_weight=1.5, seed=3, row_ptr=np.arange(0, n * fan + 1, fan, dtype=np.int64),
+                        col=rng.integers(0, n, n * fan).astype(np.int32), weight=rng.normal(0, 1e-3, n * fan).astype(np.float32))
+    wl.delay_steps = rng.integers(1, 5, n * fan).astype(np.uint8)
+    dc = torch.full((b * n,), 1e-3, device="cuda:0")
+    got = []
+    for resident in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_QUEUE_RESIDENT", resident)
+        sim = adseq.Adseq(wl, kind, cap, record_tape=True, max_steps=T, tape_spike_capacity=b * n * T // 3)
+        a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        ms = []
+        for _ in range(3):
+            sim.reset()
+            torch.cuda.synchronize()
+            a.record()
+            sim.run(0, T)
+            e.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(e))
+        g = [torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2)]
+        sim.backward(dc, None, *g)
+        got.append((min(ms), sim.counters(), sim.tape()["U"].cpu().numpy().view(np.uint32).copy(), [x.cpu().numpy() for x in g]))
+        sim.close()
+    (ms1, c1, U1, g1), (ms0, c0, U0, g0) = got
+    assert c1 == c0 and c1["error_bits"] & ~64 == 0 and c1["tape_spikes"] > b * n * T // 5
+    assert (c1["dropped"] > 0) == (cap < 128)
+    np.testing.assert_array_equal(U1, U0)
+    for x, y in zip(g1, g0):
+        H.grad_close(x, y)
+    assert n * b > 16000 or ms1 < 1.5 * ms0
