@@ -134,35 +134,36 @@ __device__ __forceinline__ void fifo_insert(const Dev& d, int g, QState& q, unsi
 }
 
 // SORTED: stores an admitted event at its place in the circular array ordered by arrival step
-// (behind the stored events with the same step); the events behind it move up one slot, eight at
-// a time so that the loads of a group are in flight together.
+// (behind the stored events with the same step).  The events behind it move up one slot, eight at
+// a time from the last one on, so that the loads of a group are in flight together, until one is found
+// that stays: a binary search for the place first was as many dependent trips to memory again
+// (10,000 targets, SORTED[128], 60 events stored: 59.8 -> 36.4 us per step).
 __device__ __forceinline__ void sorted_insert(const Dev& d, int g, QState& q, unsigned k, int a) {
   uint2* __restrict__ sl = d.slot + (size_t)g * d.C;
-  const int occ = q.occ, hd = q.hd;
-  int lo = 0, hi = occ;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    int ph = hd + mid; if (ph >= d.C) ph -= d.C;
-    if (sl[ph].x <= k) lo = mid + 1; else hi = mid;
-  }
-  for (int top = occ; top > lo;) {
-    const int nmove = top - lo < 8 ? top - lo : 8;     // move entries [top - nmove, top) up by one
+  const int hd = q.hd;
+  int top = q.occ;                 // slots from here on are free or have been moved up
+  for (;;) {
     uint2 mv[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (j < nmove) {
+    for (int j = 0; j < 8; ++j) {
+      mv[j] = make_uint2(0u, 0u);
+      if (j < top) {
         int ph = hd + top - 1 - j; if (ph >= d.C) ph -= d.C;
         mv[j] = sl[ph];
       }
+    }
+    int moved = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (j < nmove) {
+      if (moved == j && j < top && mv[j].x > k) {
         int pd = hd + top - j; if (pd >= d.C) pd -= d.C;
         sl[pd] = mv[j];
+        moved = j + 1;
       }
-    top -= nmove;
+    top -= moved;
+    if (moved < 8) break;
   }
-  int pw = hd + lo; if (pw >= d.C) pw -= d.C;
+  int pw = hd + top; if (pw >= d.C) pw -= d.C;
   sl[pw] = make_uint2(k, (unsigned)a);
 }
 

@@ -152,3 +152,21 @@ def test_bursts(kind, cap, n, b, monkeypatch):
     for x, y in zip(g1, g0):
         H.grad_close(x, y)
     assert n * b > 16000 or ms1 < 1.5 * ms0
+
+
+@pytest.mark.parametrize("cap", [2, 7, 8, 9, 16, 17, 40])
+@pytest.mark.parametrize("resident", ["1", "0"])
+def test_sorted_insertion(cap, resident, monkeypatch):
+    """Ordered queues around the eight slots that an insertion moves at a time: front, middle and end, equal arrival steps,
+    full queues, the array's end anywhere (its front goes round many times)."""
+    monkeypatch.setenv("ADSEQ_QUEUE_RESIDENT", resident)
+    T, b = 300, 2
+    wl = synth.ragged_network(90, 60, 30, seed=cap, rate_hz=600.0, t=T, b=b, w_mean=0.004, w_std=0.01)
+    ref = oracle.Run(wl, adseq.SORTED, cap, n_steps=T, batch=b, n_threads=8)
+    sim = _run(wl, adseq.SORTED, cap, T, b, [T], tape_spike_capacity=T * b * 90 // 2)
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    assert rc["delivered"] > 5 * cap * b * 90 and (rc["dropped"] > 0) == (cap < 40)
+    np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    sim.close()
