@@ -106,7 +106,9 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
   const int g0 = S.g0, hi = S.hi;
   // the wavefront's NPT spike words: lane w < NPT stores word (first neuron of the wavefront) / 64 + w
   const int gw = __builtin_amdgcn_readfirstlane(g0);
-  const int my_word = (lane < NPT && gw < lo + chunk && (gw >> 6) + lane < d.words) ? (gw >> 6) + lane : -1;
+  // (blocks of 64 neurons and up: the last one's last wavefront writes the words that round the state array up to 256 neurons too)
+  const bool tail = NPT == 1 && rank == P - 1 && lane < 4 && gw + 64 == lo + chunk;
+  const int my_word = ((lane < NPT || tail) && gw < lo + chunk && (gw >> 6) + lane < d.words) ? (gw >> 6) + lane : -1;
   int slot = (int)(n0 % d.R);   // row of the circular spike words that holds step n0 (one division per launch)
   int phi = (int)(n0 & (long long)(d.W - 1));
   int* __restrict__ win = win_of(d, n0) + (size_t)phi * d.BN;   // row of the step being run
@@ -334,7 +336,8 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
           if (lane == w) wbits = b;
         }
       } else {
-        wbits = __ballot(smask & 1u);   // lane l holds neuron l of the wavefront's one word
+        const unsigned long long b = __ballot(smask & 1u);   // lane l holds neuron l of the wavefront's one word
+        if (lane == 0) wbits = b;
       }
     }
     if (my_word >= 0) {

@@ -408,3 +408,23 @@ def test_resident_wait_that_runs_out_is_reported(monkeypatch):
     monkeypatch.delenv("ADSEQ_RING_RESIDENT_SPINS")
     ref = _check(wl, 60, 20, [60])
     assert ref.spikes.sum() > 100
+
+
+@pytest.mark.parametrize("n,fan", [(10000, 300), (2049, 150), (40001, 200)])
+def test_every_spike_word_is_written(n, fan):
+    """The tape's spike words, which lie right behind the membrane tape: every word of every step is written, those that
+    round the state array up to 256 neurons included (rows of 128 and more: blocks of 64 neurons and up)."""
+    T = 50
+    wl = synth.ragged_network(n, 2 * fan, 40, seed=n, rate_hz=500.0, t=T, b=1, w_mean=0.6 / fan, w_std=0.4 / fan)
+    sim = adseq.Adseq(wl, adseq.RING, 0, record_tape=True, max_steps=T)
+    words = (n + 255) // 256 * 4
+    off = sim.membrane_tape(T).storage_offset() * 4 + (T * n * 4 + 255) // 256 * 256
+    bits = sim.workspace[off:off + T * words * 8]
+    bits.fill_(0xa5)
+    sim.run(0, T)
+    torch.cuda.synchronize()
+    spikes = np.zeros((T, words * 64), np.uint8)
+    spikes[:, :n] = (sim.tape()["U"].cpu().numpy().reshape(T, n) >= wl.v_thresh)
+    assert spikes.sum() > 1000
+    np.testing.assert_array_equal(np.unpackbits(bits.cpu().numpy().reshape(T, -1), axis=1, bitorder="little"), spikes)
+    sim.close()
