@@ -175,8 +175,9 @@ __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L,
         k = q_load<true>(&d.pool_k[at]); a = q_load<true>(&d.pool_a[at]); flag = q_load<true>(&d.pool_t[at]);
         at = next;
       } else {
-        // (requested together where there are registers for it; so are an entry of the list and the link to the next)
-        constexpr int kAtOnce = NPT == 1 ? kCont : 1;
+        // (requested together where there are registers for it -- four at a time: with all eight the FIFO[32] run of
+        // 100,000 neurons took 19.5 ms forward and back where it takes 18.5 --; so are an entry of the list and the link to the next)
+        constexpr int kAtOnce = NPT == 1 ? 4 : 1;
 #pragma unroll 1
         for (int x0 = 0; x0 < kCont; x0 += kAtOnce) {
           uint4 cc[kAtOnce];
