@@ -70,3 +70,22 @@ def test_small_layout_is_kept_for_the_static_workspace():
     H.grad_close(g_w.cpu().numpy(), gw)
     H.grad_close(g_d.cpu().numpy(), gd)
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 4), (adseq.SYN_FIFO, 2), (adseq.RING, 0)])
+@pytest.mark.parametrize("where", ["membrane", "count"])
+def test_nan_cotangents_propagate(kind, cap, where):
+    """Cotangents with the very bits that mark an adjoint cell as not written yet: gradients with NaN, no wait that runs out."""
+    T, n = 40, 3000
+    wl = synth.ragged_network(n, 30, 20, seed=45, rate_hz=900.0, t=T, b=1, w_mean=0.02, w_std=0.01)
+    sim = adseq.Adseq(wl, kind, cap, record_tape=True, max_steps=T)
+    sim.run(0, T)
+    dU = torch.zeros((T, n), device=sim.dev)
+    dc = torch.full((n,), 1e-3, device=sim.dev)
+    (dU[20:, :50] if where == "membrane" else dc[:50]).view(torch.int32).fill_(0x7fa5c3e1)
+    g = torch.empty(wl.n_synapses, device=sim.dev)
+    sim.backward(dc, dU, g, g.clone())
+    torch.cuda.synchronize()
+    assert sim.counters()["error_bits"] == 0
+    assert 0 < int(torch.isnan(g).sum()) < g.numel()
+    sim.close()

@@ -12,6 +12,13 @@ from paper_2512_05906_amd import adseq, synth
 pytestmark = pytest.mark.gpu
 
 
+def _went_dense(sim):
+    """Whether the last window was (and the next one will be) expanded the dense way: Counters::dense, at byte 76 of the
+    workspace, which begins with the counters."""
+    base = -sim.workspace.data_ptr() % 256
+    return sim.workspace[base + 76:base + 84].cpu().numpy().view(np.uint32).tolist()
+
+
 @pytest.mark.parametrize("dense", ["1", "0"])
 @pytest.mark.parametrize("n,b,fan,d_max,T,window,blocks", [(2000, 1, 100, 40, 130, 16, 16), (1501, 2, 90, 33, 110, 16, 16),
                                                            (6001, 1, 60, 50, 100, 16, 32), (900, 3, 120, 70, 200, 16, 32),
@@ -33,5 +40,6 @@ def test_dense_windows(n, b, fan, d_max, T, window, blocks, dense, monkeypatch):
         c, rc = sim.counters(), ref.counters()
         for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
             assert c[key] == rc[key], key
+        assert any(_went_dense(sim)) == (dense == "1")
         sim.reset()
     sim.close()

@@ -82,6 +82,22 @@ def test_queue_resident_admission_flags_and_reset(kind, cap):
     sim.close()
 
 
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 4), (adseq.FIFO, 40), (adseq.SORTED, 4)])
+@pytest.mark.parametrize("n,blocks", [(40000, "256"), (16000, "16"), (40000, "16")])
+@pytest.mark.parametrize("record", [True, False])
+def test_queue_resident_is_what_runs(kind, cap, n, blocks, record, monkeypatch):
+    """Every instance -- one, four and eight targets per thread, FIFO slots in LDS and not, with a tape and without -- is
+    reached: with one poll per wait its waits run out, and a launch pair per step has none."""
+    monkeypatch.setenv("ADSEQ_QUEUE_BLOCKS", blocks)
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    wl = synth.ragged_network(n, 30, 20, seed=45, rate_hz=700.0, t=40, b=1, w_mean=0.02, w_std=0.01)
+    for resident in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_QUEUE_RESIDENT", resident)
+        sim = _run(wl, kind, cap, 40, 1, [40], record)
+        assert (sim.counters()["error_bits"] & 32 != 0) == (resident == "1")
+        sim.close()
+
+
 def test_queue_resident_wait_that_runs_out_is_reported(monkeypatch):
     """Failure path of the bounded waits, forced from the host (one poll per wait): the kernel runs to its end, the error
     word carries bit 32, a reset clears it."""
