@@ -40,7 +40,7 @@
  *
  * Queue kinds (Section 4.3)
  *   ADSEQ_RING    dense delay line: one summed cell per (arrival step, target) for
- *                 the arrival steps of the current window of 16 steps, plus the
+ *                 the arrival steps of the current window of 16, 32 or 64 steps, plus the
  *                 spikes of the last d_max_steps + 1 steps as bit masks, from
  *                 which the cells of the next window are filled when it opens;
  *                 lossless ("Ring").
@@ -151,9 +151,12 @@ typedef struct {
                                   (tape_spike_capacity * ceil(S / N))                         */
   int64_t step_event_capacity; /* FIFO/SORTED: events per step that may wait in the overflow
                                   list of their target (more than 8 contenders for one target
-                                  in one step); 0 = default: twice B * S up to 2^29 for runs in
-                                  one kernel, without a tape 64 times that up to 2^27 for
-                                  open-loop stretches; else min(B * S, 2^24).  RING: events
+                                  in one step), 28 bytes of workspace each.  0 = default: 2 B S
+                                  where that is at most 2^29 (15 GB): what the runs in one kernel
+                                  need (adseq_run); without a tape up to 64 B S, halved until it is at
+                                  most 2^27, for the stretches of adseq_run_open; where 2 B S is
+                                  more than 2^29, 2^24.  A value below 2 B S saves the memory: runs
+                                  and open-loop runs then take two launches per step.  RING: events
                                   the staging buffer of a window holds (the rest takes a slower
                                   route, same result); 0 = default                            */
   void *workspace;             /* device memory, 256-byte aligned                             */
@@ -256,12 +259,15 @@ int adseq_run(adseq_t *h, int64_t step0, int64_t n_steps, void *stream);
  * the spike-time mode's E), summed over
  * trials.  dL_dcount: fp32 [B*N] or NULL; dL_dU: fp32 [T][B*N] or NULL; grad_w, grad_d: fp32 [S],
  * overwritten.  Synchronises the stream once at the start to read the device error word.
- * ADSEQ_RING runs the reverse steps of a window in one kernel whose blocks wait for one another's
- * results (for the adjoint cells they gather; every wait bounded); should such a wait run out --
- * the blocks of a launch were not running together, or a cotangent held the NaN that marks a cell
- * as not written yet (bits 0x7fa5c3e1) -- the kernels still run to their end, the gradients are void, and
- * the error word carries bit 32 afterwards: read it with adseq_counters once the stream is done
- * (adseq_drop_count and the next adseq_backward refuse the run with ADSEQ_E_HIP). */
+ * The reverse steps of a window run in one kernel whose blocks wait for one another's results
+ * (for the adjoint cells they gather; every wait bounded, see adseq_run) -- with every queue kind, unless
+ * the synapse is double-exponential, the state array has more than 2^20 cells (or more than 2^17 and a number
+ * of them that no 4 divides), the handle is a static one of a bounded kind, or a very small ring
+ * is swept window by window.  Should such a wait run out --
+ * the blocks of a launch were not running together -- the kernels still run to their end, the gradients are
+ * void, and the error word carries bit 32 afterwards: read it with adseq_counters once the stream is done
+ * (adseq_drop_count and the next adseq_backward refuse the run with ADSEQ_E_HIP).  (A cell that is not
+ * written yet holds a signalling NaN, which no sum or product is: NaN cotangents of any bits propagate.) */
 int adseq_backward(adseq_t *h, const float *dL_dcount, const float *dL_dU, float *grad_w,
                    float *grad_d, void *stream);
 
@@ -317,7 +323,8 @@ int adseq_spike_counts(adseq_t *h, int32_t *counts, void *stream);
  * are created by the library on first use and destroyed with the handle).  adseq_profile_read
  * synchronises `stream` and returns, per kernel class, the summed time in ms and the number of
  * launches since the last read, then forgets them.  Classes for FIFO / SORTED (an event after
- * every launch; while timing is on every step goes by its own launches): [0] fan-out + contender registration, [1] admission + pop + drive + LIF,
+ * every launch; while timing is on every step goes by its own two launches, not by the kernel that
+ * takes the steps of a run otherwise): [0] fan-out + contender registration, [1] admission + pop + drive + LIF,
  * [2] backward queue term + gradients, [3] backward neuron update (where the reverse sweep goes window
  * by window, the far gather of a window and its reverse steps, as for RING; [3] counts the steps).  Classes for RING: [0] the
  * expansion of one window (staging pass + accumulation pass, timed as a pair and counted as one
