@@ -574,10 +574,13 @@ int env_pow2(const char* name, int dflt, int lo, int hi) {
 // little to expand, so longer windows are cheaper -- until the entries that a spike's row holds inside the window, which
 // the step kernels handle one step at a time, outweigh that.  While they are no more than the 64 that the resident kernels
 // request with one load (row length x W / d_max) the longest window is the fastest; beyond that what counts is how many they
-// are in a step, which goes with B S W / d_max: up to 4 million 32 steps are still faster than 16.
+// are in a step, which goes with B S W / d_max: up to 4 million 32 steps are taken.  (The line is cautious: 32 steps win up to
+// 7.7 million at least, and lose at 12.8 million.)
 // Measured at 16 / 32 / 64 steps, ms per run: 16 x 1,000 neurons x 100 synapses, d_max 50: 8.57 / 7.20 / -; 60,000 x 100, 200:
 // 3.34 / 2.84 / 2.57; 250,000 x 60, 100: 3.27 / 2.87 / 2.70; 9,973 x 2 trials x 150 with a current state, 150: 5.07 / 4.31 / 3.98;
-// 10,000 x 1,000, 200: 31.1 / 27.9 / 30.9; 100,000 x 1,000, 250: 9.7 / 11.2 / 13.0.
+// 10,000 x 1,000, 200: 31.1 / 27.9 / 30.9; 100,000 x 1,000, 250: 9.7 / 11.2 / 13.0; at 16 / 32 steps, 1,000 steps forward and back:
+// 15,000 x 1,000, 200 (load 2.4 million): 5.40 / 4.91; 25,000 x 1,000, 200 (4.0): 5.58 / 5.11; 40,000 x 1,000, 250 (5.1): 6.05 / 5.49;
+// 60,000 x 1,000, 250 (7.7): 6.95 / 6.45.
 // No window of more than 16 steps is longer than four fifths of the largest delay, beyond which hardly an event is left for
 // the expansion (a cautious bound: at d_max = 40 a window of 32 steps would still win, 7.4 against 8.6 ms).
 // small: 16 steps at most (two buffers of W rows each).
@@ -792,7 +795,9 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->qsteps = 1;
   if (ptq) {
     const double bs = (double)c->batch * (double)S;
-    // (two of them, what k_queue_run takes, are worth four times the room)
+    // (Overflow entries are 28 bytes.  For the two buffers of k_queue_run, whose half of the list each has to hold every synapse of
+    // every trial, up to 2^29 of them, 15 GB or a twentieth of the card's memory; at that, 256 x 4,096 neurons x 256, a
+    // forward step takes 11.0 us instead of 25.9 by two launches.  For longer open-loop stretches, which save less, a quarter.)
     auto too_much = [&](int q) {
       const double room = q > 2 ? 1.0 : 4.0;
       return (double)q * BN * (kCont * 16 + 8) > room * 1073741824.0 ||

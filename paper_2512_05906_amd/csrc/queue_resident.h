@@ -3,8 +3,8 @@
 // synchronising wavefront it shares.
 //
 // Two launches per step (k_neurons, k_fanout_step) are bound by the launches and by the state they read again every time:
-// 16 x 1,000 neurons with FIFO[32] 11.9 us per step by those, 4.9 here; 100,000 neurons 19.3 and 14.9; 256 x 4,096 neurons with
-// sorted[128] 27 and 11.9.  Here a block owns the targets [rank * chunk, + chunk) for the whole launch; membrane and synaptic state and row
+// 16 x 1,000 neurons with FIFO[32] 11.6 us per step by those, 4.4 here; 100,000 neurons 18.9 and 14.1; 256 x 4,096 neurons with
+// sorted[128] 25.9 and 11.0.  Here a block owns the targets [rank * chunk, + chunk) for the whole launch; membrane and synaptic state and row
 // bounds stay in registers, the queues' occupancy, front, first mask word and earliest stored arrival in LDS (the slots
 // themselves in global memory, private to the block: they are touched only when something is due or admitted).  A step is
 //   before the barrier   what is due at step n leaves the queues (its own state alone decides that), drive bits
@@ -16,7 +16,10 @@
 // known to the others in step n.  What is known a step ahead is that a full queue with nothing due at step n stays full: the
 // owners leave that as one bit per target, every block takes all the bits into LDS behind the barrier (one target per
 // thread: 16 KB at most), and events for such targets are dropped at once (100,000 neurons, FIFO[32], seven events in ten:
-// 18.4 -> 16 us per step).  All others are contenders, and the admission -- same rule, same canonical order -- drops what is left to drop;
+// 18.4 -> 16 us per step).  With several targets per thread there are too many bits for that, and looking them up in memory cost
+// more (11.0 -> 12.2 us per step where no queue is full) than the tickets it saves below some 400,000 events per step at full queues; beyond
+// that two launches per step are the faster ones (256,000 targets, 2 million events per step, 993 in 1,000 dropped: 332 against 122 us).
+// All others are contenders, and the admission -- same rule, same canonical order -- drops what is left to drop;
 // the overflow list has room for every synapse (that is what decides whether this kernel runs).  Admission flags are
 // written once, by whoever decides.  The tape's places are claimed block by block, spikes
 // and events in one 64-bit counter per step, so that their orders agree and the spikes of a 64-neuron word stay
