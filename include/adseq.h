@@ -213,8 +213,9 @@ int adseq_enqueue(adseq_t *h, int64_t step, const int32_t *spike_ids, const int3
  * adseq_enqueue(step0 + k) of the spikes spike_ids[spike_offsets[k] .. + n_spikes[k]).  spike_ids
  * and n_spikes [n_steps] are DEVICE pointers, spike_offsets [n_steps] is a HOST array.  The shape
  * of the paper's Poisson benchmark (Section 5.1: externally generated spike trains through the
- * queues).  Same results as those calls; the ring does the two of a step in one launch.  Stops at
- * the first error. */
+ * queues).  Same results as those calls, in fewer launches: the ring takes the steps of a window in two,
+ * FIFO and SORTED up to 64 steps unless many events per step are to be expected (from the distances
+ * of spike_offsets).  Stops at the first error. */
 int adseq_run_open(adseq_t *h, int64_t step0, int64_t n_steps, const int32_t *spike_ids,
                    const int64_t *spike_offsets /*host*/, const int32_t *n_spikes, float *I_out,
                    int64_t I_stride, void *stream);
@@ -226,8 +227,8 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
 
 /* n_steps closed-loop steps starting at `step0` (same results as calling adseq_step in a loop with
  * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries, and
- * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (where half the overflow list has room for every
- * synapse of every trial, and kernels are not being timed: adseq_profile), in ONE kernel
+ * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (of at most 2^20 targets, where half the overflow list has
+ * room for every synapse of every trial, and kernels are not being timed: adseq_profile), in ONE kernel
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
  * launch needs the device free enough for all its blocks to run at the same time.  Calls that
  * make such launches (adseq_backward too) wait, on their stream, for the last such call of the
