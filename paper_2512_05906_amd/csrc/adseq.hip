@@ -198,6 +198,12 @@ struct Dev {
   int* near_spk;        // [W][kNearSpikeCap] neuron of every numbered spike
   int* near_counts;     // [2][max_steps] spikes and near events of every recorded step
   int near_ev_cap;
+  // SYN_* with tape, resident kernel (synapse_resident.h); spike_bits: [R][words] spikes whose events are held
+  int* syn_cells;                   // [8][BN] Q8.24 sums by arrival step mod 8
+  unsigned long long* syn_mask;     // SYN_FIFO: [syn_R2][BN][syn_mw] delays whose queues admitted the spike, one bit each
+  unsigned long long* syn_flagged;  // SYN_FIFO: [syn_R2][words] spikes that have such a mask (the others were admitted everywhere)
+  int syn_mw, syn_R2;               // syn_R2: 0 where the kernel is not used
+  int syn_gshift;                   // log2 of the lanes that take a row piece
 };
 
 // Trial b = g / N of the state index g = b * N + i (0 <= g < 2^31) without an integer division:
@@ -401,6 +407,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 #include "ring_resident_forward.h"
 #include "ring_chain.h"
 #include "queue_resident.h"
+#include "synapse_resident.h"
 
 // ---------------------------------------------------------------- backward (FIFO / SORTED)
 
@@ -530,6 +537,9 @@ struct adseq {
   bool rev_flow = false;                      // RING: the resident reverse kernel without a grid barrier (ring_flow_reverse.h)
   int fwd_P = 0, fwd_chunk = 0;                // RING: the same for the forward kernel over the whole chip (ring_resident_forward.h; 0: not used)
   int q_P = 0, q_chunk = 0;                    // FIFO / SORTED: the same for k_queue_run (0: two launches per step)
+  int syn_P = 0, syn_chunk = 0, syn_near = 0;  // SYN_*: the same for k_syn_run (0: three launches per step), row-front entries in LDS
+  bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
+  bool syn_live = false;                       // ... and the events in flight are in the spike words, not in the queue arrays
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
   hipStream_t aux = nullptr;
@@ -549,7 +559,7 @@ struct adseq {
 namespace {
 
 struct Layout {
-  size_t claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
+  size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
       tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
       total;
@@ -558,6 +568,7 @@ struct Layout {
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
   int qsteps;           // FIFO / SORTED: contender buffers
+  int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
 
@@ -675,6 +686,33 @@ ResidentPlan queue_plan(long long BN) {
   }
   return r;
 }
+// k_syn_run: up to 256 x 2,048 neurons whose spike words of the last R steps fit LDS.  Blocks as for the ring's forward kernel: where
+// the rows are long multiples of 64 neurons, so that more blocks share the events.  near: entries of a row's front kept in LDS.
+// gshift: log2 of the lanes that take a row piece, whose mean length is row / d_max: few pieces are longer, whose rest is a trip more.
+struct SynPlan { int P = 0, chunk = 0, near = 0, gshift = 0; };
+SynPlan syn_plan(const adseq_config* c) {
+  SynPlan r;
+  const long long BN = (long long)c->n_neurons * c->batch, row = c->n_synapses / c->n_neurons, R = c->d_max_steps + 1;
+  const int blocks = env_pow2("ADSEQ_SYN_BLOCKS", 256, 8, 256);
+  const long long unit = row >= 128 ? 64 : 256;
+  const long long chunk = ((BN + blocks - 1) / blocks + unit - 1) / unit * unit;
+  const long long words = R * (chunk / 64) * (c->kind == ADSEQ_SYN_FIFO ? 2 : 1);
+  if (!env_pow2("ADSEQ_SYN_RESIDENT", 1, 0, 1) || chunk > 4 * kResThreads || words > kSynLdsWords) return r;
+  const long long near = (kSynLdsWords - words) / chunk;
+  r.near = (int)(near < kSynNear ? near : kSynNear);
+  const double piece = (double)row / c->d_max_steps;
+  r.gshift = piece <= 3.0 ? 3 : (piece <= 9.0 ? 4 : (piece <= 22.0 ? 5 : 6));
+  r.chunk = (int)chunk;
+  r.P = (int)((BN + chunk - 1) / chunk);
+  return r;
+}
+typedef void (*SynKernel)(long long, int, unsigned, int, int, int, int, Dev);
+SynKernel syn_kernel(int kind, int capacity, int chunk) {
+  const bool deep = kind != ADSEQ_SYN_FIFO || capacity >= 3;   // (a front of three steps: no queue of delay 3 refuses an event)
+  if (kind != ADSEQ_SYN_FIFO) return chunk <= kResThreads ? k_syn_run<1, false, true> : k_syn_run<4, false, true>;
+  if (chunk <= kResThreads) return deep ? k_syn_run<1, true, true> : k_syn_run<1, true, false>;
+  return deep ? k_syn_run<4, true, true> : k_syn_run<4, true, false>;
+}
 typedef void (*QueueKernel)(long long, int, unsigned, int, int, int, unsigned long long*, Dev);
 template <int KIND, bool RECORD>
 QueueKernel queue_kernel_of(int chunk) {
@@ -768,9 +806,10 @@ bool host_validate(const adseq_config* c) {
 
 // sorted_rev: bounded kinds with tape get what the ring's reverse kernels need (rows sorted by arrival offset, window
 // buffers, admission bits) instead of an adjoint delay line.
+// runs: SYN_* with sorted_rev get what k_syn_run needs, where the FIFO masks (a bit per delay, neuron and step) stay below 2 GB.
 // qsteps: steps of an open-loop stretch that FIFO and SORTED register at once; fewer where their buffers, or the overflow
 // entries that their worst case needs (every synapse of every trial in every step), would be out of proportion.
-bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bool small) {
+bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bool small, bool runs) {
   if (!host_validate(c)) return false;
   if (c->kind == ADSEQ_RING || !c->record_tape) sorted_rev = false;
   const size_t BN = (size_t)c->n_neurons * c->batch;
@@ -864,6 +903,12 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
     L->cap = (int)(per > 65536.0 ? 65536.0 : per);
     if (L->cap >= 16) L->cap &= ~15;   // regions begin on 128-byte lines: a run's first 16 events are one line
   }
+  L->syn_mw = L->syn_R2 = 0;
+  if (synq && sorted_rev && runs && syn_plan(c).P > 0) {
+    const int mw = synfifo ? (c->d_max_steps + 63) / 64 : 0, R2 = L->R + kSynChunk;
+    if ((double)R2 * (double)BN * mw * 8.0 <= 2147483648.0) { L->syn_mw = mw; L->syn_R2 = R2; }
+  }
+  const bool synrun = L->syn_R2 > 0;
   L->ctr = take(sizeof(Counters));
   L->blk = take(bounded ? ((size_t)L->nblk + fan_slots(L->nblk) + (synq ? kSynqBlocks : 0)) * sizeof(BlkCtr)
                         : kMaxBinBlocks * sizeof(BlkCtr));
@@ -871,7 +916,10 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   const size_t nstates = c->tau_rise_ms > 0.0f ? 2 : 1;   // double-exponential synapse: every adjoint twice
   L->J = take(c->tau_syn_ms > 0.0f ? nstates * BN * 4 : 0);
   L->win = take(bounded ? 0 : 2 * (size_t)L->W * BN * 4);
-  L->spike_bits = take(bounded ? 0 : (size_t)L->R * L->words * 8);
+  L->spike_bits = take(bounded && !synrun ? 0 : (size_t)L->R * L->words * 8);
+  L->syn_cells = take(synrun ? 8 * BN * 4 : 0);
+  L->syn_mask = take(synrun ? (size_t)L->syn_R2 * BN * L->syn_mw * 8 : 0);
+  L->syn_flagged = take(synrun && synfifo ? (size_t)L->syn_R2 * L->words * 8 : 0);
   L->drive_words = take(bounded ? 0 : (size_t)kDriveSteps * resident_plan((long long)BN).P * kResThreads * 2);   // [kDriveSteps][taking-part blocks][kResThreads] u16
   const bool fifo = c->kind == ADSEQ_FIFO;
   L->slot = take(c->kind == ADSEQ_SORTED ? (size_t)c->capacity * BN * 8 : 0);
@@ -904,7 +952,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->stepcnt = take(bounded ? 2 * (size_t)L->nblk * 16 : 0);
   L->packed = take(bounded ? S * 4 : 0);
   L->a_q = take(bounded ? S * 4 : 0);
-  L->synf = take(bounded ? 0 : S * 8);
+  L->synf = take(bounded && !synrun ? 0 : S * 8);
   const bool windows = !bounded || sorted_rev;
   L->synb = take(windows ? S * 8 : 0);
   L->dstart = take(windows ? (size_t)c->n_neurons * (c->d_max_steps + 2) * 4 : 0);
@@ -922,7 +970,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->tape_bits = take(windows ? T * L->words * 8 : 0);
   L->spk_count = take(c->record_tape ? BN * 4 : 0);
   L->step_off = take(c->record_tape ? (T + 1) * 8 : 0);
-  L->claims = take(c->record_tape && ptq && L->qsteps >= 2 ? (T + 1) * 8 : 0);
+  L->claims = take((c->record_tape && ptq && L->qsteps >= 2) || synrun ? (T + 1) * 8 : 0);
   L->step_evoff = take(c->record_tape && bounded ? (T + 1) * 8 : 0);
   L->tape_spk = take(bounded ? (size_t)L->spike_cap * 4 : 0);
   L->tape_evb = take(bounded ? (size_t)L->spike_cap * 8 : 0);
@@ -963,11 +1011,12 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
 // (k_queue_steps).  small: neither -- an
 // adjoint delay line and two launches per reverse step, a stretch of one step, and windows of 16 steps -- for what only so
 // fits the static workspace.
-bool make_layout(const adseq_config* c, Layout* L, bool small = false) {
+// runs: the workspace may hold what k_syn_run needs (the static handle's, which has no turn for such launches, does not).
+bool make_layout(const adseq_config* c, Layout* L, bool small = false, bool runs = true) {
   if (!c) return false;
   if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
-      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps), false)) return true;
-  return layout_as(c, L, false, 1, small);
+      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps), false, runs)) return true;
+  return layout_as(c, L, false, 1, small, false);
 }
 
 int fail(adseq* h, int code, const char* fmt, ...) {
@@ -1026,6 +1075,12 @@ void launch_reset(adseq* h, hipStream_t st) {
     if (d.kind == ADSEQ_SYN_FIFO) fill_u32(st, d.sq_hs, 0u, ((size_t)d.B * d.S + 1) / 2);   // (the keys need no clearing)
     fill_u32(st, d.I_acc, 0u, BN);
     fill_u32(st, d.blk, 0u, ((size_t)d.blk_pop + kSynqBlocks) * sizeof(BlkCtr) / 4);
+    if (d.syn_R2 > 0) {
+      fill_u32(st, d.spike_bits, 0u, (size_t)d.R * d.words * 2);
+      fill_u32(st, d.syn_cells, 0u, 8 * BN);
+    }
+    h->syn_ok = h->syn_P > 0;
+    h->syn_live = false;
     h->pending_admit = false;
   } else {
     fill_u32(st, d.occ, 0u, BN);
@@ -1040,13 +1095,27 @@ void launch_reset(adseq* h, hipStream_t st) {
   if (d.record) {
     fill_u32(st, d.step_off, 0u, 2);  // step_off[0] = 0 (int64)
     if (d.kind != ADSEQ_RING) fill_u32(st, d.step_evoff, 0u, 2);
-    if (d.qsteps >= 2) fill_u32(st, d.claims, 0u, ((size_t)d.max_steps + 1) * 2);
+    if (d.qsteps >= 2 || d.syn_R2 > 0) fill_u32(st, d.claims, 0u, ((size_t)d.max_steps + 1) * 2);
     fill_u32(st, d.spk_count, 0u, BN);
   }
   h->next_step = 0;
   h->enq_calls = 0;
   h->tape_ok = d.record != 0;
   h->bits_clear_for = -1;
+}
+
+// SYN_*: called before anything that needs the queue arrays: they get the events that k_syn_run has left in the spike words.  From
+// here to the next reset the handle's steps go by three launches each.
+void syn_leave(adseq* h, hipStream_t st) {
+  h->syn_ok = false;
+  if (!h->syn_live) return;
+  h->syn_live = false;
+  const Dev& d = h->dev;
+  const unsigned g = (unsigned)((d.BN + kBlock / 64 - 1) / (kBlock / 64));
+  fill_u32(st, d.ctr->in_flight, 0u, 4);
+  hipLaunchKernelGGL(k_syn_in_flight, dim3(1024), dim3(kBlock), 0, st, d, h->next_step, d.ctr->in_flight);
+  hipLaunchKernelGGL(k_syn_delivered, dim3(1), dim3(64), 0, st, d, d.blk_pop + kSynqBlocks, d.ctr->in_flight);
+  hipLaunchKernelGGL(k_syn_queues, dim3(g < 16384 ? g : 16384), dim3(kBlock), 0, st, d, h->next_step);
 }
 
 // FIFO / SORTED: admission of what is pending, then (MODE 1) pop or (MODE 2) the closed-loop step.
@@ -1058,6 +1127,7 @@ void launch_neurons(adseq* h, hipStream_t st, long long n, int parity, const flo
   if (per_synapse_kind(d.kind)) {
     // per-synapse queues: every queue is looked at first (nothing is pending for MODE 0)
     if (MODE == 0) return;
+    syn_leave(h, st);
     if (d.kind == ADSEQ_SYN_FIFO) {
       hipLaunchKernelGGL(k_synq_pop<false>, dim3(kSynqBlocks), block, 0, st, d, n, 0LL);
       hipLaunchKernelGGL((k_neurons<ADSEQ_SYN_FIFO, MODE>), grid, block, 0, st, d, n, parity, i_ext, spikes_out, I_out);
@@ -1082,6 +1152,7 @@ void launch_neurons(adseq* h, hipStream_t st, long long n, int parity, const flo
 void launch_fanout(adseq* h, hipStream_t st, long long n, const int* spk, const int* n_spk, int parity, int record) {
   const Dev& d = h->dev;
   const dim3 block(kBlock);
+  if (per_synapse_kind(d.kind)) syn_leave(h, st);
   if (!spk) {
     const dim3 grid((unsigned)d.nblk * d.fsplit);
     if (d.kind == ADSEQ_FIFO) hipLaunchKernelGGL((k_fanout_step<ADSEQ_FIFO>), grid, block, 0, st, d, n, parity, record);
@@ -1402,6 +1473,31 @@ void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_s
   h->last_stream = st;
 }
 
+// SYN_* with tape: steps step0 .. step0 + n_steps - 1, all recorded, by k_syn_run, up to kSynChunk of them in one launch, and their
+// spike list and admission flags.
+void syn_run_resident(adseq* h, hipStream_t st, long long step0, long long n_steps) {
+  const Dev& d = h->dev;
+  long long n = step0;
+  const long long end = step0 + n_steps;
+  int stride = env_pow2("ADSEQ_RING_RESIDENT_STRIDE", kResStride, 1, 8);
+  while (stride > 1 && (long long)h->syn_P * stride > 32 * 8) stride >>= 1;
+  while (n < end) {
+    const int cnt = (int)(end - n < kSynChunk ? end - n : kSynChunk);
+    hipLaunchKernelGGL(syn_kernel(d.kind, d.C, h->syn_chunk), dim3((unsigned)(h->syn_P * stride)), dim3(kResLaunch), 0, st, n, cnt, h->rev_base,
+                       h->syn_P, h->syn_chunk, stride, h->syn_near, d);
+    h->rev_base += (unsigned)(cnt - 1) * (unsigned)h->syn_P;
+    hipLaunchKernelGGL(k_syn_list, dim3((unsigned)cnt), dim3(kBlock), 0, st, d, n);
+    const long long back = d.kind == ADSEQ_SYN_FIFO ? 0 : (n < d.d_max - 1 ? n : d.d_max - 1);   // (earlier steps whose events may have been replaced)
+    const unsigned steps = (unsigned)(cnt + back), shares = (2048 + steps - 1) / steps;
+    hipLaunchKernelGGL(k_syn_flags, dim3(steps, shares), dim3(kBlock), 0, st, d, n - back, n, n + cnt);
+    h->enq_calls += cnt;
+    n += cnt;
+    h->next_step = n;
+  }
+  h->syn_live = true;
+  h->last_stream = st;
+}
+
 // RING, chained step launches (ring_chain.h): the step launches go to the caller's stream and to a
 // stream of the library's own in turn and wait for one another themselves.  The stream and the two
 // events are made at the first use.
@@ -1630,8 +1726,8 @@ int adseq_create(const adseq_config* cfg, adseq_t** out) {
 int adseq_create_static(const adseq_config* cfg, adseq_t** out) {
   if (!cfg || !out) return ADSEQ_E_INVALID_ARG;
   Layout L;
-  if (!make_layout(cfg, &L)) return ADSEQ_E_INVALID_ARG;
-  if (L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES && (!make_layout(cfg, &L, true) || L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES))
+  if (!make_layout(cfg, &L, false, false)) return ADSEQ_E_INVALID_ARG;
+  if (L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES && (!make_layout(cfg, &L, true, false) || L.total > (size_t)ADSEQ_STATIC_WORKSPACE_BYTES))
     return ADSEQ_E_WORKSPACE;   // does not fit the static workspace
   int dev = -1;
   void* ws = static_workspace(&dev);
@@ -1709,6 +1805,9 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.nblk = L.nblk; d.words = L.words; d.blk = (BlkCtr*)(ws + L.blk);
   d.V = (float*)(ws + L.V); d.spike_bits = (unsigned long long*)(ws + L.spike_bits);
   d.drive_words = (unsigned long long*)(ws + L.drive_words);
+  d.syn_cells = (int*)(ws + L.syn_cells); d.syn_mask = (unsigned long long*)(ws + L.syn_mask);
+  d.syn_flagged = (unsigned long long*)(ws + L.syn_flagged);
+  d.syn_mw = L.syn_mw; d.syn_R2 = L.syn_R2;
 #if defined(ADSEQ_PHASE_CLOCK) || defined(ADSEQ_ABLATE)
   d.dbg = getenv("ADSEQ_DBG") ? atoi(getenv("ADSEQ_DBG")) : 0;
 #endif
@@ -1799,6 +1898,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     if (qp.P > 0 && resident_fits((const void*)queue_kernel(d.kind, true, qp.chunk, d.C)) && resident_fits((const void*)queue_kernel(d.kind, false, qp.chunk, d.C))) {
       h->q_P = qp.P; h->q_chunk = qp.chunk;
     }
+  }
+  if (d.syn_R2 > 0) {
+    const SynPlan sp = syn_plan(cfg);
+    if (sp.P > 0 && resident_fits((const void*)syn_kernel(d.kind, d.C, sp.chunk))) { h->syn_P = sp.P; h->syn_chunk = sp.chunk; h->syn_near = sp.near; d.syn_gshift = sp.gshift; }
   }
   if (d.kind == ADSEQ_RING) {
     ResidentPlan rp = resident_plan((long long)d.BN);
@@ -2065,10 +2168,16 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
     // add; so does everything while kernels are timed, class by class, and where the call has no turn)
     int64_t ahead = 0;
     {
-      WholeChipCall turn(h, (hipStream_t)stream, h->q_P > 0 && n_steps >= 4 && !h->prof);
-      if (turn.on) {
+      // (per-synapse queues: as far as the tape goes.  One or two steps are sooner done by three launches each -- 10,000 x 1,000 synapses, us
+      // per step in calls of 1 / 2 / 3 / 16 steps: 23.5 / 14.7 / 10.3 / 4.1, by launches 14 --, but then so are all steps to the next reset)
+      const int64_t recorded = h->syn_ok && n_steps >= 3 && h->tape_ok && step0 < h->dev.max_steps ? (n_steps < h->dev.max_steps - step0 ? n_steps : h->dev.max_steps - step0) : 0;
+      WholeChipCall turn(h, (hipStream_t)stream, ((h->q_P > 0 && n_steps >= 4) || recorded > 0) && !h->prof);
+      if (turn.on && h->q_P > 0) {
         ahead = n_steps - 1;
         queue_run_resident(h, (hipStream_t)stream, step0, ahead);
+      } else if (turn.on) {
+        ahead = recorded;
+        syn_run_resident(h, (hipStream_t)stream, step0, ahead);
       }
     }
     for (int64_t n = ahead; n < n_steps; ++n) {
@@ -2174,6 +2283,10 @@ int adseq_counters(adseq_t* h, int64_t* out8, void* stream) {
                          h->fold_upto, h->next_step, d.ctr->fold);
     }
   }
+  if (h->syn_live) {   // k_syn_run counts nothing: delivered = admitted - in flight, the latter counted here
+    fill_u32(st, d.ctr->in_flight, 0u, 4);
+    hipLaunchKernelGGL(k_syn_in_flight, dim3(1024), dim3(kBlock), 0, st, d, h->next_step, d.ctr->in_flight);
+  }
   HIP_TRY(h, hipMemcpyAsync(&c, d.ctr, sizeof(c), hipMemcpyDeviceToHost, st));
   HIP_TRY(h, hipStreamSynchronize(st));
   out8[0] = (int64_t)c.offered; out8[1] = (int64_t)c.dropped; out8[2] = (int64_t)c.delivered;
@@ -2193,6 +2306,7 @@ int adseq_counters(adseq_t* h, int64_t* out8, void* stream) {
     // every offered event has been admitted or refused by now (what was pending was admitted above)
     out8[1] = out8[0] - admitted;
     out8[4] = out8[3] - sum_admitted;
+    if (h->syn_live) { out8[2] = admitted - (int64_t)c.in_flight[0]; out8[5] = sum_admitted - (int64_t)c.in_flight[1]; }
   }
   if (d.kind == ADSEQ_RING) {
     // spikes and offered events up to the last window boundary: private counters of the staging

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_rows(Dev d, ExpCoef ec) {
       if (c < 0 || c >= d.N) c = 0;
       const long long q = r0 + atomicAdd(&s_hist[s.D], 1u);
       const unsigned pk = ((unsigned)c << d.dbits) | (unsigned)s.D;
-      if (d.kind == ADSEQ_RING) d.synf[q] = make_uint2(pk, (unsigned)s.a_q);
+      if (d.kind == ADSEQ_RING || d.syn_R2 > 0) d.synf[q] = make_uint2(pk, (unsigned)s.a_q);
       d.synb[q] = make_uint2(pk, __float_as_uint(s.amp));
       if (d.continuous) d.fdec[q] = s.f;
       d.perm[q] = (unsigned)(p - r0);

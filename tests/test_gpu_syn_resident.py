@@ -1,0 +1,130 @@
+"""One queue per synapse, closed loop, many steps in one launch (k_syn_run) against the oracle: trace bit for bit, counters, which
+events were admitted, replaced and dropped, gradients; one and four neurons per thread, rows whose front does not fit LDS, masks of
+one delay word and of several, runs cut into pieces, mixed with single steps and with the queue entry points, and agreement with
+three launches per step."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+KINDS = [(adseq.SYN_FIFO, 1), (adseq.SYN_FIFO, 3), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 1), (adseq.SYN_BINS, 3), (adseq.SYN_BINS, 8)]
+
+
+def _run(wl, kind, cap, T, b, pieces, **kw):
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T, **kw)
+    n = 0
+    for p in pieces:
+        if p == "s":
+            sim.step(n); n += 1
+        else:
+            sim.run(n, p); n += p
+    assert n == T
+    torch.cuda.synchronize()
+    return sim
+
+
+@pytest.mark.parametrize("kind,cap", KINDS)
+@pytest.mark.parametrize("n,b,T,d_max,fan,rate,gain,tau_syn,tau_rise,continuous,blocks", [
+    (701, 3, 80, 40, 200, 900.0, 0.6, 0.0, 0.0, False, ""), (100, 1, 60, 1, 60, 900.0, 0.6, 0.0, 0.0, False, ""),
+    (63, 1, 300, 130, 40, 900.0, 1.5, 0.0, 0.0, False, ""), (200, 2, 270, 64, 30, 2500.0, 0.5, 0.0, 0.0, False, ""),
+    (1501, 4, 50, 30, 150, 900.0, 0.6, 5.0, 0.0, True, "8"), (4100, 4, 40, 20, 40, 900.0, 0.6, 5.0, 1.0, False, "16"),
+    (1100, 8, 24, 8, 2500, 1500.0, 0.6, 0.0, 0.0, False, "8")])
+def test_syn_resident(kind, cap, n, b, T, d_max, fan, rate, gain, tau_syn, tau_rise, continuous, blocks, monkeypatch):
+    if blocks:   # (few blocks: four neurons per thread)
+        monkeypatch.setenv("ADSEQ_SYN_BLOCKS", blocks)
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=gain / fan, w_std=gain / fan, continuous=continuous)
+    wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, n_threads=8)
+    assert ref.spikes.sum() > 50
+    kw = dict(tape_spike_capacity=T * b * n // 2, tape_event_capacity=T * b * wl.n_synapses // 2)
+    rc = ref.counters()
+    if d_max > 50:
+        assert rc["dropped"] > 0 or cap == 8
+    dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    for resident, pieces in (("1", [T]), ("1", [3, 9, T - 12]), ("1", [T // 2, "s", T - 1 - T // 2]), ("0", [T])):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = _run(wl, kind, cap, T, b, pieces, **kw)
+        c = sim.counters()
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], (key, resident, pieces)
+        assert c["error_bits"] & ~64 == 0 and c["tape_spikes"] == ref.spikes.sum()
+        np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+        cnt = torch.empty(b * n, dtype=torch.int32, device=sim.dev)
+        sim.spike_counts(cnt)
+        np.testing.assert_array_equal(cnt.cpu().numpy().reshape(b, -1), ref.spikes.sum(axis=0))
+        g_w, g_d = (torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2))
+        sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+        torch.cuda.synchronize()
+        H.grad_close(g_w.cpu().numpy(), gw)
+        H.grad_close(g_d.cpu().numpy(), gd)
+        sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 2)])
+@pytest.mark.parametrize("pieces", [[200], [140, 60], [70, "s", 129]])
+def test_syn_resident_admission_flags_and_reset(kind, cap, pieces):
+    """Every recorded spike once, every event with its own flag, also those of steps before the call that replaced them; the same
+    after a reset."""
+    T, b = 200, 2
+    wl = synth.ragged_network(90, 30, 70, seed=5, rate_hz=900.0, t=T, b=b, w_mean=0.03, w_std=0.03)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, log_events=True)
+    sim = _run(wl, kind, cap, T, b, pieces, tape_spike_capacity=T * b * 90, tape_event_capacity=T * b * wl.n_synapses)
+    for _ in range(2):
+        tp = sim.tape()
+        out = {k: tp[k].cpu().numpy() for k in ("step_offset", "spike_id", "event_base")}
+        np.testing.assert_array_equal(H.spikes_from_tape(out, wl, b), ref.spikes)
+        admitted, dropped = H.gpu_dropped_set(sim, out, wl)
+        delivered, want_dropped = H.oracle_sets(ref)
+        assert dropped == want_dropped and len(dropped) > 0 and delivered <= admitted
+        sim.reset()
+        sim.run(0, T)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 3)])
+def test_syn_resident_then_queue_entry_points(kind, cap, monkeypatch):
+    """What is in flight after a run comes out of the queues step by step as after launches per step, and so do the events pushed on
+    top of it."""
+    T, b, n = 150, 2, 120
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    got = []
+    for resident in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = _run(wl, kind, cap, T, b, [T])
+        cur = torch.zeros((70, b * n), device=sim.dev)
+        ids = torch.arange(0, b * n, 3, dtype=torch.int32, device=sim.dev)
+        count = torch.tensor([ids.numel()], dtype=torch.int32, device=sim.dev)
+        for k in range(70):
+            sim.deliver(T + k, cur[k])
+            if k in (0, 5, 9):
+                sim.enqueue(T + k, ids, count)
+        got.append((cur.cpu().numpy(), sim.counters()))
+        sim.close()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    assert np.abs(got[0][0]).sum() > 0
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert got[0][1][key] == got[1][1][key], key
+
+
+def test_syn_resident_past_the_tape_and_wait_that_runs_out(monkeypatch):
+    """The steps beyond the tape go by launches per step; a wait that runs out (one poll) ends the launch and is reported."""
+    wl = synth.ragged_network(3000, 40, 20, seed=4, rate_hz=400.0, t=60, b=1, w_mean=0.01, w_std=0.01)
+    ref = oracle.Run(wl, adseq.SYN_FIFO, 2, n_steps=60, batch=1)
+    sim = adseq.Adseq(wl, adseq.SYN_FIFO, 2, record_tape=True, max_steps=40)
+    sim.run(0, 60)
+    c, rc = sim.counters(), ref.counters()
+    assert (c["enqueued"], c["dropped"], c["delivered"]) == (rc["enqueued"], rc["dropped"], rc["delivered"])
+    sim.close()
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    sim = adseq.Adseq(wl, adseq.SYN_FIFO, 2, record_tape=True, max_steps=60)
+    sim.run(0, 60)
+    torch.cuda.synchronize()
+    if sim.counters()["error_bits"] & 32:
+        with pytest.raises(adseq.AdseqError):
+            sim.drop_count()
+    sim.close()
