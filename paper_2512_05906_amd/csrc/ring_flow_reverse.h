@@ -28,6 +28,10 @@
 // thread where the blocks are small enough, the two block barriers per step instead of three.
 
 constexpr unsigned kFlowSentinel = 0x7fa5c3e1u;   // "not written yet" (a NaN with this payload)
+// Past the end of every row (at most 256 x 4,096 cells): a buffer load there gives zero and a store does nothing, without a branch.
+// So the far queue terms, which only spikes have, are moved for the threads that own a spike, not for every cell and step: 12 of
+// some 28 bytes per cell and step (256 x 4,096 neurons: 5.75 -> 4.1 us per reverse step, 500 steps of SORTED[128] forward and back 9.45 -> 8.61 ms).
+constexpr int kFlowNowhere = 0x7f000000;
 
 // Repeats the lanes' gathers (p: the lane's cell; want: the lane gathers at all; v: what its first
 // load returned) until none of them holds the sentinel.  The whole wavefront takes the same way.
@@ -178,7 +182,7 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
   {
     const __amdgpu_buffer_rsrc_t t2 = res_rows(S.tape2, hi * 4), f1 = res_rows(d.Gacc + (size_t)slot1 * d.BN, hi * 4);
     S.Uc = flow_load<NPT, kBufNonTemporal>(t2, g0 * 4);
-    S.Gb = flow_load<NPT, kBufNonTemporal>(f1, g0 * 4);
+    S.Gb = flow_load<NPT, kBufNonTemporal>(f1, s1 ? g0 * 4 : kFlowNowhere);
     if (ADM) Ac = *S.abase2;
     if (HAS_DU) S.dUb = flow_load<NPT, kBufNonTemporal>(res_rows(S.du1, hi * 4), g0 * 4);
   }
@@ -195,8 +199,8 @@ __device__ __forceinline__ void flow_step(const Dev& d, FlowState<NPT>& S, const
     }
     const __amdgpu_buffer_rsrc_t row = res_rows(gwin, hi * 4), far = res_rows(d.Gacc + (size_t)S.slot * d.BN, hi * 4);
     flow_store<NPT, kBufAgent>(gu4, row, g0 * 4);
-    // the far queue terms are used up: the slot is another step's R steps on (stored by every lane, set or not)
-    flow_store<NPT, 0>(flow_splat<NPT>(0.0f), far, g0 * 4);
+    // the far queue terms are used up: the slot is another step's R steps on (only a spike's cell was ever added to)
+    flow_store<NPT, 0>(flow_splat<NPT>(0.0f), far, smask ? g0 * 4 : kFlowNowhere);
     // the same row of the OTHER window buffer, which the next launch sweeps: "not written yet"
     if (fill_row) flow_store<NPT, 0>(flow_splat<NPT>(__uint_as_float(kFlowSentinel)), res_rows(fill_row, hi * 4), g0 * 4);
   }
