@@ -204,6 +204,7 @@ struct Dev {
   unsigned long long* syn_flagged;  // SYN_FIFO: [syn_R2][words] spikes that have such a mask (the others were admitted everywhere)
   int syn_mw, syn_R2;               // syn_R2: 0 where the kernel is not used
   int syn_gshift;                   // log2 of the lanes that take a row piece
+  unsigned long long* trial_words;  // RING, small networks (ring_trial.h): [B][R][ceil(N / 64)] spikes of the last R steps
 };
 
 // Trial b = g / N of the state index g = b * N + i (0 <= g < 2^31) without an integer division:
@@ -408,6 +409,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 #include "ring_chain.h"
 #include "queue_resident.h"
 #include "synapse_resident.h"
+#include "ring_trial.h"
 
 // ---------------------------------------------------------------- backward (FIFO / SORTED)
 
@@ -540,6 +542,9 @@ struct adseq {
   int syn_P = 0, syn_chunk = 0, syn_near = 0;  // SYN_*: the same for k_syn_run (0: three launches per step), row-front entries in LDS
   bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
   bool syn_live = false;                       // ... and the events in flight are in the spike words, not in the queue arrays
+  int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
+  bool trial_ok = false;                       // every step since the reset went by k_trial_run, or none has been run
+  bool trial_live = false;                     // ... and the queue state is in trial_words only
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
   hipStream_t aux = nullptr;
@@ -559,7 +564,7 @@ struct adseq {
 namespace {
 
 struct Layout {
-  size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
+  size_t trial_words, syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
       tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
       total;
@@ -568,6 +573,7 @@ struct Layout {
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
   int qsteps;           // FIFO / SORTED: contender buffers
+  int trial_near;       // RING: the workspace holds what k_trial_run needs (-1: it does not)
   int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
@@ -686,9 +692,31 @@ ResidentPlan queue_plan(long long BN) {
   }
   return r;
 }
+// log2 of the lanes that take a row piece, whose mean length is row / d_max: few pieces are longer, whose rest is a trip more.
+int piece_lanes(const adseq_config* c) {
+  const double piece = (double)c->n_synapses / c->n_neurons / c->d_max_steps;
+  return piece <= 3.0 ? 3 : (piece <= 9.0 ? 4 : (piece <= 22.0 ? 5 : 6));
+}
+// k_trial_run: networks of up to 1,024 neurons and kTrialSynapses synapses whose delay line, with at least one entry of every row, fits
+// LDS (see ring_trial.h).  ADSEQ_RING_TRIALS: 0 never,
+// 1 wherever it fits; unset: not where a knob asks for one of the other forward kernels or their waits.  near < 0: not used.
+struct TrialPlan { int near = -1; };
+TrialPlan trial_plan(const adseq_config* c) {
+  TrialPlan r;
+  int on = env_pow2("ADSEQ_RING_TRIALS", 2, 0, 2);
+  if (on == 2)
+    for (const char* k : {"ADSEQ_RING_RESIDENT", "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_FORWARD_CHIP", "ADSEQ_RING_CHAIN", "ADSEQ_RING_OVERLAP",
+                          "ADSEQ_RING_COUNT_POPPED", "ADSEQ_RING_LAZY_ROWS", "ADSEQ_RING_ASSUME_CUS", "ADSEQ_RING_DENSE"})
+      if (getenv(k)) on = 0;
+  // 8-byte words of LDS: spikes and cells of R steps (and a spare one: the cells begin on a whole word, N may be odd)
+  const long long R = c->d_max_steps + 1, words = R * ((c->n_neurons + 63) / 64) + (R * c->n_neurons + 1) / 2;
+  if (!on || c->n_neurons > kTrialNeurons || c->batch > kTrialMost || c->n_synapses > kTrialSynapses || words + c->n_neurons > kTrialLdsWords) return r;
+  const long long near = (kTrialLdsWords - words) / c->n_neurons;
+  r.near = (int)(near < kSynNear ? near : kSynNear);
+  return r;
+}
 // k_syn_run: up to 256 x 2,048 neurons whose spike words of the last R steps fit LDS.  Blocks as for the ring's forward kernel: where
 // the rows are long multiples of 64 neurons, so that more blocks share the events.  near: entries of a row's front kept in LDS.
-// gshift: log2 of the lanes that take a row piece, whose mean length is row / d_max: few pieces are longer, whose rest is a trip more.
 struct SynPlan { int P = 0, chunk = 0, near = 0, gshift = 0; };
 SynPlan syn_plan(const adseq_config* c) {
   SynPlan r;
@@ -700,8 +728,7 @@ SynPlan syn_plan(const adseq_config* c) {
   if (!env_pow2("ADSEQ_SYN_RESIDENT", 1, 0, 1) || chunk > 4 * kResThreads || words > kSynLdsWords) return r;
   const long long near = (kSynLdsWords - words) / chunk;
   r.near = (int)(near < kSynNear ? near : kSynNear);
-  const double piece = (double)row / c->d_max_steps;
-  r.gshift = piece <= 3.0 ? 3 : (piece <= 9.0 ? 4 : (piece <= 22.0 ? 5 : 6));
+  r.gshift = piece_lanes(c);
   r.chunk = (int)chunk;
   r.P = (int)((BN + chunk - 1) / chunk);
   return r;
@@ -917,6 +944,8 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->J = take(c->tau_syn_ms > 0.0f ? nstates * BN * 4 : 0);
   L->win = take(bounded ? 0 : 2 * (size_t)L->W * BN * 4);
   L->spike_bits = take(bounded && !synrun ? 0 : (size_t)L->R * L->words * 8);
+  L->trial_near = bounded || small ? -1 : trial_plan(c).near;
+  L->trial_words = take(L->trial_near < 0 ? 0 : (size_t)c->batch * L->R * ((c->n_neurons + 63) / 64) * 8);
   L->syn_cells = take(synrun ? 8 * BN * 4 : 0);
   L->syn_mask = take(synrun ? (size_t)L->syn_R2 * BN * L->syn_mw * 8 : 0);
   L->syn_flagged = take(synrun && synfifo ? (size_t)L->syn_R2 * L->words * 8 : 0);
@@ -1066,6 +1095,9 @@ void launch_reset(adseq* h, hipStream_t st) {
   if (d.kind == ADSEQ_RING) {
     fill_u32(st, d.win, 0u, 2 * (size_t)d.W * BN);
     fill_u32(st, d.spike_bits, 0u, (size_t)d.R * d.words * 2);
+    if (h->trial_near >= 0) fill_u32(st, d.trial_words, 0u, (size_t)d.B * d.R * ((d.N + 63) / 64) * 2);
+    h->trial_ok = h->trial_near >= 0;
+    h->trial_live = false;
     fill_u32(st, d.blk, 0u, kMaxBinBlocks * sizeof(BlkCtr) / 4);
     // staging counters: zero except between the two passes of a window's expansion
     if (d.cap > 0) fill_u32(st, d.ecnt, 0u, (size_t)(d.P < kMaxParts ? d.P : kMaxParts) * d.NB);
@@ -1217,9 +1249,26 @@ void join_ahead(adseq* h, hipStream_t st) {
   if (h->ahead_for >= 0 && h->ev_ahead) (void)hipStreamWaitEvent(st, h->ev_ahead, 0);
 }
 
+// RING: called before anything that needs the window or the circular spike words: they get what k_trial_run has left in the
+// trials' own words.  From here to the next reset the handle's steps go by the other kernels.
+void trial_words_out(adseq* h, hipStream_t st) {
+  const Dev& d = h->dev;
+  hipLaunchKernelGGL(k_trial_words, dim3((unsigned)grid_for((size_t)d.R * d.words)), dim3(kBlock), 0, st, d);
+}
+void trial_leave(adseq* h, hipStream_t st) {
+  h->trial_ok = false;
+  if (!h->trial_live) return;
+  h->trial_live = false;
+  const Dev& d = h->dev;
+  trial_words_out(h, st);
+  // (at a window's first step the window is yet to be opened)
+  if (h->next_step & (long long)(d.W - 1)) hipLaunchKernelGGL(k_trial_window, dim3(512), dim3(kBlock), 0, st, d, h->next_step);
+}
+
 // clear: see launch_expansion.  Returns whether there was a window to open.
 bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0) {
   const Dev& d = h->dev;
+  trial_leave(h, st);
   if ((k0 & (long long)(d.W - 1)) != 0 || k0 <= 0) return false;
   close_group(h, st, 1);
   mark(h, st, -1);
@@ -1374,6 +1423,30 @@ void ring_run_resident(adseq* h, hipStream_t st, long long step0, long long n_st
     n += cnt;
     h->next_step = n;
   }
+}
+
+// RING: steps step0 .. step0 + n_steps - 1 in one launch, a workgroup per trial (ring_trial.h).
+void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_steps) {
+  const Dev& d = h->dev;
+  long long n = step0;
+  const long long end = step0 + n_steps;
+  while (n < end) {
+    int cnt = (int)(end - n < (1 << 20) ? end - n : (1 << 20));
+    // a launch either records all its steps or none: it ends where the tape ends
+    const bool record = d.record && h->tape_ok && n < d.max_steps;
+    if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
+    if (d.record && n >= d.max_steps) h->tape_ok = false;
+    if (record) fill_u32(st, d.tape_bits + (size_t)n * d.words, 0u, (size_t)cnt * d.words * 2);
+    const int threads = trial_threads(d.N);
+    const dim3 grid((unsigned)d.B), block((unsigned)threads);
+    if (threads <= 256) hipLaunchKernelGGL((k_trial_run<256>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, d);
+    else hipLaunchKernelGGL((k_trial_run<1024>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, d);
+    h->enq_calls += cnt;
+    n += cnt;
+    h->next_step = n;
+  }
+  h->fold_upto = n;   // (counted by the launches)
+  h->trial_live = true;
 }
 
 // RING: steps step0 .. step0 + n_steps - 1 with one launch per window over the whole chip (ring_resident_forward.h).
@@ -1808,6 +1881,8 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.syn_cells = (int*)(ws + L.syn_cells); d.syn_mask = (unsigned long long*)(ws + L.syn_mask);
   d.syn_flagged = (unsigned long long*)(ws + L.syn_flagged);
   d.syn_mw = L.syn_mw; d.syn_R2 = L.syn_R2;
+  d.trial_words = (unsigned long long*)(ws + L.trial_words);
+  if (d.kind == ADSEQ_RING) { h->trial_near = L.trial_near; }
 #if defined(ADSEQ_PHASE_CLOCK) || defined(ADSEQ_ABLATE)
   d.dbg = getenv("ADSEQ_DBG") ? atoi(getenv("ADSEQ_DBG")) : 0;
 #endif
@@ -2047,6 +2122,7 @@ int adseq_enqueue(adseq_t* h, int64_t step, const int32_t* spike_ids, const int3
     return fail(h, ADSEQ_E_ORDER, "adseq_enqueue: got step %lld, expected %lld (the step last delivered)",
                 (long long)step, h->next_step - 1);
   const int parity = (int)(h->enq_calls & 1);
+  if (h->dev.kind == ADSEQ_RING) trial_leave(h, (hipStream_t)stream);
   if (h->dev.kind == ADSEQ_RING)
     hipLaunchKernelGGL(k_enqueue_win, dim3(kFanoutBlocks), dim3(kBlock), 0, (hipStream_t)stream, h->dev,
                        (long long)step, spike_ids, n_spikes);
@@ -2154,7 +2230,13 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   if (n_steps < 0) return fail(h, ADSEQ_E_INVALID_ARG, "adseq_run: negative step count");
   if (step0 != h->next_step)
     return fail(h, ADSEQ_E_ORDER, "adseq_run: got step %lld, expected %lld", (long long)step0, h->next_step);
-  if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
+  // (not under capture, where a reset between replays would not be seen, nor while kernels are timed class by class)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool trials = h->dev.kind == ADSEQ_RING && h->trial_ok && n_steps >= kTrialSteps && !h->prof &&
+                      hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  if (trials) {
+    ring_run_trials(h, (hipStream_t)stream, step0, n_steps);
+  } else if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
     WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);
     ring_run_chip(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->res_P > 0) {
@@ -2273,6 +2355,7 @@ int adseq_counters(adseq_t* h, int64_t* out8, void* stream) {
     // the spike words: up to the last window boundary by the boundary pass (device counters),
     // since then here; and delivered = offered - still in flight, the latter counted here from
     // the spike words of the last d_max + 1 steps.
+    if (h->trial_live) trial_words_out(h, st);
     fill_u32(st, d.ctr->in_flight, 0u, 4 + 6);
     const long long items = (long long)d.R * d.words;
     hipLaunchKernelGGL(k_ring_in_flight, dim3((unsigned)items), dim3(kBlock), 0, st, d, h->next_step,

@@ -60,7 +60,9 @@ struct SynLds {
 template <int NPT, class Take>
 __device__ __forceinline__ int syn_walk(const Dev& d, SynLds<NPT>& L, int wpb, int dlo, int slot0, int most, Take take) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = lane * (kResThreads / 64) + wave;   // (few words are shared out among all wavefronts)
+  // (lane by lane over the wavefronts: pieces are shared out evenly, which is worth more than the LDS banks that meet -- sixteen words
+  // at a time 7.6 instead of 7.3 ms for 1,000 steps of 10,000 x 1,000 synapses)
+  const int t = lane * (kResThreads / 64) + wave;
   unsigned* list = L.list[wave];
   const int items = (d.d_max - dlo + 1) * wpb;
   const int dj = kResThreads / wpb, dw = kResThreads - dj * wpb;

@@ -1,0 +1,83 @@
+"""Small ring networks, closed loop, a run in one launch with a workgroup per trial (k_trial_run) against the oracle: trace bit for
+bit, counters, gradients; one wavefront and many, trials that share a spike word, rows whose front does not fit LDS, runs cut
+into pieces and mixed with single steps and with the queue entry points in the middle of a window."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,b,T,d_max,fan,rate,gain,tau_syn,tau_rise,continuous", [
+    (63, 1, 300, 130, 40, 900.0, 1.0, 0.0, 0.0, False), (100, 3, 130, 1, 60, 900.0, 0.6, 0.0, 0.0, False),
+    (1000, 3, 160, 30, 100, 400.0, 0.6, 0.0, 0.0, False), (903, 2, 130, 35, 90, 400.0, 0.6, 5.0, 0.0, True),
+    (1024, 2, 100, 31, 50, 400.0, 0.6, 5.0, 1.0, False), (150, 2, 90, 5, 1500, 900.0, 0.6, 0.0, 0.0, False),
+    (200, 7, 140, 3, 30, 2500.0, 1.5, 0.0, 0.0, False)])
+def test_ring_trial(n, b, T, d_max, fan, rate, gain, tau_syn, tau_rise, continuous, monkeypatch):
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=gain / fan, w_std=gain / fan, continuous=continuous)
+    wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
+    words = (d_max + 1) * ((n + 63) // 64) + ((d_max + 1) * n + 1) // 2 + n
+    assert wl.n_synapses <= 262144 and words <= 18432   # (the kernel takes it)
+    ref = oracle.Run(wl, adseq.RING, 0, n_steps=T, batch=b, n_threads=8)
+    assert ref.spikes.sum() > 50
+    rc = ref.counters()
+    dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    for trials, pieces, record in (("1", [T], True), ("1", [65, T - 65], True), ("1", [T - 9, "s", 8], True), ("1", [T - 19, 16, 3], False),
+                                   ("0", [T], True)):
+        monkeypatch.setenv("ADSEQ_RING_TRIALS", trials)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=record, max_steps=T)
+        for _ in range(2):   # (the second time after a reset)
+            sim.reset()
+            k = 0
+            for p in pieces:
+                if p == "s":
+                    sim.step(k); k += 1
+                else:
+                    sim.run(k, p); k += p
+            for _ in range(2):   # (asking for the counters changes nothing)
+                c = sim.counters()
+                for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+                    assert c[key] == rc[key], (key, trials, pieces)
+                assert c["error_bits"] & ~64 == 0 and c["tape_spikes"] == ref.spikes.sum()
+        if record:
+            np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+            cnt = torch.empty(b * n, dtype=torch.int32, device=sim.dev)
+            sim.spike_counts(cnt)
+            np.testing.assert_array_equal(cnt.cpu().numpy().reshape(b, -1), ref.spikes.sum(axis=0))
+            g_w, g_d = (torch.empty(wl.n_synapses, device=sim.dev) for _ in range(2))
+            sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+            torch.cuda.synchronize()
+            H.grad_close(g_w.cpu().numpy(), gw)
+            H.grad_close(g_d.cpu().numpy(), gd)
+        sim.close()
+
+
+@pytest.mark.parametrize("T", [96, 107, 150])
+def test_ring_trial_then_queue_entry_points(T, monkeypatch):
+    """What is in flight after a run is delivered step by step as after the other kernels, at a window's first step and inside one, and
+    so are the events of spikes listed on top of it; the steps beyond the tape are run too."""
+    b, n = 2, 120
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    got = []
+    for trials in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_RING_TRIALS", trials)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T - 20)
+        sim.run(0, T)
+        cur = torch.zeros((70, b * n), device=sim.dev)
+        ids = torch.arange(0, b * n, 3, dtype=torch.int32, device=sim.dev)
+        count = torch.tensor([ids.numel()], dtype=torch.int32, device=sim.dev)
+        for k in range(70):
+            sim.deliver(T + k, cur[k])
+            if k in (0, 5, 9):
+                sim.enqueue(T + k, ids, count)
+        got.append((cur.cpu().numpy(), sim.counters()))
+        sim.close()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    assert np.abs(got[0][0]).sum() > 0
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert got[0][1][key] == got[1][1][key], key
