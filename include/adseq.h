@@ -228,14 +228,16 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
 /* n_steps closed-loop steps starting at `step0` (same results as calling adseq_step in a loop with
  * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries, and
  * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (of at most 2^20 targets, where half the overflow list has
- * room for every synapse of every trial, and kernels are not being timed: adseq_profile), in ONE kernel
+ * room for every synapse of every trial, and kernels are not being timed: adseq_profile), and the per-synapse
+ * kinds up to 128 steps (calls of three steps or more while every step since the reset has been recorded by such calls), in ONE kernel
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
  * launch needs the device free enough for all its blocks to run at the same time.  Calls that
  * make such launches (adseq_backward too) wait, on their stream, for the last such call of the
  * process on the device.  Under stream capture they cannot: there, and with the handle of adseq_create_static,
- * the bounded kinds keep to launches whose blocks wait for nobody, one or two per step; a captured ring's launches stay what they are, and
+ * the bounded kinds keep to launches whose blocks wait for nobody, one to three per step; a captured ring's launches stay what they are, and
  * the program keeps the graph's replays apart from other such launches (same stream, or events of
- * its own).  adseq_create
+ * its own).  A small ring network whose delay line fits a compute unit's LDS runs by one workgroup per
+ * trial that waits for nobody (calls of 64 steps or more, every step since the reset run so).  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
  * launch per step (same results).  Every wait is
  * bounded (tens of ms, with the bounded kinds a second and more): if one runs out, the kernels still run to their end, the run is void, and the error

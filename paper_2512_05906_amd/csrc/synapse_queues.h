@@ -11,7 +11,7 @@
 // (arrival steps lie within d_max <= 1023 steps of now, so the residue is unambiguous).
 // All events of a synapse have the same delay, so the head is always the earliest, and since a
 // source spikes at most once per step at most one event per queue is due per step.
-// A step is three launches:
+// A step is three launches (long recorded runs go by k_syn_run instead, synapse_resident.h):
 //   k_synq_pop      looks at every queue: the heads' arrival steps, eight per thread in one
 //                   16-byte load; only a queue whose head is due touches the rest of its state;
 //                   a due event adds the synapse's amplitude to the target's cell of I_acc
