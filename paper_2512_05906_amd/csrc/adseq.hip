@@ -1439,13 +1439,14 @@ void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_step
     if (record) fill_u32(st, d.tape_bits + (size_t)n * d.words, 0u, (size_t)cnt * d.words * 2);
     const int threads = trial_threads(d.N);
     const dim3 grid((unsigned)d.B), block((unsigned)threads);
-    if (threads <= 256) hipLaunchKernelGGL((k_trial_run<256>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, d);
-    else hipLaunchKernelGGL((k_trial_run<1024>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, d);
+    const long long boundary = (n + cnt - 1) & ~(long long)(d.W - 1), fold = boundary >= n && boundary > 0 ? boundary : h->fold_upto;
+    if (threads <= 256) hipLaunchKernelGGL((k_trial_run<256>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, h->fold_upto, fold, d);
+    else hipLaunchKernelGGL((k_trial_run<1024>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, h->fold_upto, fold, d);
+    h->fold_upto = fold;
     h->enq_calls += cnt;
     n += cnt;
     h->next_step = n;
   }
-  h->fold_upto = n;   // (counted by the launches)
   h->trial_live = true;
 }
 

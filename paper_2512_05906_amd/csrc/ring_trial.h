@@ -31,8 +31,11 @@ struct TrialLds {
 
 // Steps n0 .. n0 + nsteps - 1 of trial blockIdx.x; N <= blockDim.x <= kMost, thread t owns neuron t.  near: entries of a row's
 // front in LDS.  record: the tape is written; its spike words of these steps are zero when the launch begins.
+// Spikes of steps [fold_lo, fold_hi) and the events they emit are counted: fold_lo <= n0, fold_hi the last window boundary of these
+// steps (fold_lo if there is none), as where the other kernels stop counting, so that what is listed on top of the last step is still
+// counted later.  Both n0 - fold_lo and n0 + nsteps - fold_hi are at most W < R.
 template <int kMost>
-__global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, Dev d) {
+__global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, long long fold_lo, long long fold_hi, Dev d) {
   __shared__ TrialLds<kMost> L;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int threads = (int)blockDim.x, waves = threads >> 6;
@@ -60,6 +63,17 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
   }
   int slot = (int)(n0 % R);   // row of spike words and cells that belongs to the step
   __syncthreads();
+  // the thread's spikes of the last `steps` steps before the one of `slot`
+  auto recent = [&](int steps) {
+    int c = 0;
+    for (int a = 1; a <= steps; ++a) {
+      int s = slot - a;
+      if (s < 0) s += R;
+      c += (int)((L.words[s * wpb + (tid >> 6)] >> (tid & 63)) & 1ull);
+    }
+    return c;
+  };
+  const int before = act ? recent((int)(n0 - fold_lo)) : 0;
   // ---- the cells as the steps before n0 left them: the tails of the held spikes' rows, a wavefront per spike word
   if (n0 > 0)
     for (int x = wave; x < d.d_max * wpb; x += waves) {
@@ -151,7 +165,7 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
     if (syn) d.J[g] = J;
     if (dexp) d.J[(size_t)d.BN + g] = Jf;
     if (record) d.spk_count[g] += count;
-    c0 = count; c1 = count * (d.row_ptr[tid + 1] - d.row_ptr[tid]); c2 = count * d.rowsum[tid];
+    c0 = before + count - recent((int)(n0 + nsteps - fold_hi)); c1 = c0 * (d.row_ptr[tid + 1] - d.row_ptr[tid]); c2 = c0 * d.rowsum[tid];
   }
   c0 = wave_total64(c0); c1 = wave_total64(c1); c2 = wave_total64(c2);
   if (lane == 0 && c0) {

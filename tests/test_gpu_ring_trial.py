@@ -81,3 +81,38 @@ def test_ring_trial_then_queue_entry_points(T, monkeypatch):
     assert np.abs(got[0][0]).sum() > 0
     for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
         assert got[0][1][key] == got[1][1][key], key
+
+
+@pytest.mark.parametrize("pieces", [[96], [107], [64, 64], [70, 80], [100, 64, 3]])
+def test_ring_trial_enqueue_after_run(pieces, monkeypatch):
+    """Spikes listed for the run's last step, straight after the run, are counted and delivered as after the other kernels; at a window's
+    first step and inside one, over calls of any length and past the tape's end."""
+    b, n, T = 2, 120, sum(pieces)
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    got = []
+    for trials in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_RING_TRIALS", trials)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T - 20)
+        cur = torch.zeros((62, b * n), device=sim.dev)
+        ids = torch.arange(0, b * n, 3, dtype=torch.int32, device=sim.dev)
+        count = torch.tensor([ids.numel()], dtype=torch.int32, device=sim.dev)
+        k, seen = 0, []
+        for p in pieces:
+            sim.run(k, p); k += p
+            seen.append(sim.counters())
+        # (neurons that did not spike themselves in that step)
+        spiked = torch.from_numpy(oracle.Run(wl, adseq.RING, 0, n_steps=T, batch=b).spikes[T - 1].reshape(-1)).to(sim.dev)
+        ids = ids[spiked[ids.long()] == 0].contiguous()
+        count.fill_(ids.numel())
+        sim.enqueue(T - 1, ids, count)
+        seen.append(sim.counters())
+        for j in range(62):
+            sim.deliver(T + j, cur[j])
+        seen.append(sim.counters())
+        got.append((cur.cpu().numpy(), seen))
+        sim.close()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    assert got[1][1][-2]["enqueued"] > got[1][1][-3]["enqueued"] and got[1][1][-1]["delivered"] == got[1][1][-1]["enqueued"]
+    for one, many in zip(got[0][1], got[1][1]):
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered", "tape_spikes"):
+            assert one[key] == many[key], key
