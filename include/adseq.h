@@ -237,7 +237,7 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * the bounded kinds keep to launches whose blocks wait for nobody, one to three per step; a captured ring's launches stay what they are, and
  * the program keeps the graph's replays apart from other such launches (same stream, or events of
  * its own).  A small ring network whose delay line fits a compute unit's LDS runs by one workgroup per
- * trial that waits for nobody (calls of 64 steps or more, every step since the reset run so).  adseq_create
+ * trial that waits for nobody (calls of 64 steps or more).  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
  * launch per step (same results).  Every wait is
  * bounded (tens of ms, with the bounded kinds a second and more): if one runs out, the kernels still run to their end, the run is void, and the error

@@ -204,7 +204,6 @@ struct Dev {
   unsigned long long* syn_flagged;  // SYN_FIFO: [syn_R2][words] spikes that have such a mask (the others were admitted everywhere)
   int syn_mw, syn_R2;               // syn_R2: 0 where the kernel is not used
   int syn_gshift;                   // log2 of the lanes that take a row piece
-  unsigned long long* trial_words;  // RING, small networks (ring_trial.h): [B][R][ceil(N / 64)] spikes of the last R steps
 };
 
 // Trial b = g / N of the state index g = b * N + i (0 <= g < 2^31) without an integer division:
@@ -543,8 +542,6 @@ struct adseq {
   bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
   bool syn_live = false;                       // ... and the events in flight are in the spike words, not in the queue arrays
   int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
-  bool trial_ok = false;                       // every step since the reset went by k_trial_run, or none has been run
-  bool trial_live = false;                     // ... and the queue state is in trial_words only
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
   hipStream_t aux = nullptr;
@@ -564,7 +561,7 @@ struct adseq {
 namespace {
 
 struct Layout {
-  size_t trial_words, syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
+  size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
       tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
       total;
@@ -573,7 +570,6 @@ struct Layout {
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
   int qsteps;           // FIFO / SORTED: contender buffers
-  int trial_near;       // RING: the workspace holds what k_trial_run needs (-1: it does not)
   int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
@@ -698,22 +694,20 @@ int piece_lanes(const adseq_config* c) {
   return piece <= 3.0 ? 3 : (piece <= 9.0 ? 4 : (piece <= 22.0 ? 5 : 6));
 }
 // k_trial_run: networks of up to 1,024 neurons and kTrialSynapses synapses whose delay line, with at least one entry of every row, fits
-// LDS (see ring_trial.h).  ADSEQ_RING_TRIALS: 0 never,
-// 1 wherever it fits; unset: not where a knob asks for one of the other forward kernels or their waits.  near < 0: not used.
-struct TrialPlan { int near = -1; };
-TrialPlan trial_plan(const adseq_config* c) {
-  TrialPlan r;
+// LDS (see ring_trial.h).  ADSEQ_RING_TRIALS: 0 never, 1 wherever it fits; unset: not where a knob asks for one of the other forward
+// kernels or their waits.  Returns the entries of a row's front kept in LDS, -1: not used.
+int trial_near(const adseq_config* c) {
   int on = env_pow2("ADSEQ_RING_TRIALS", 2, 0, 2);
   if (on == 2)
     for (const char* k : {"ADSEQ_RING_RESIDENT", "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_FORWARD_CHIP", "ADSEQ_RING_CHAIN", "ADSEQ_RING_OVERLAP",
                           "ADSEQ_RING_COUNT_POPPED", "ADSEQ_RING_LAZY_ROWS", "ADSEQ_RING_ASSUME_CUS", "ADSEQ_RING_DENSE"})
       if (getenv(k)) on = 0;
+  if (env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1)) on = 0;   // (a window that is being expanded ahead is not rebuilt)
   // 8-byte words of LDS: spikes and cells of R steps (and a spare one: the cells begin on a whole word, N may be odd)
   const long long R = c->d_max_steps + 1, words = R * ((c->n_neurons + 63) / 64) + (R * c->n_neurons + 1) / 2;
-  if (!on || c->n_neurons > kTrialNeurons || c->batch > kTrialMost || c->n_synapses > kTrialSynapses || words + c->n_neurons > kTrialLdsWords) return r;
+  if (!on || c->n_neurons > kTrialNeurons || c->batch > kTrialMost || c->n_synapses > kTrialSynapses || words + c->n_neurons > kTrialLdsWords) return -1;
   const long long near = (kTrialLdsWords - words) / c->n_neurons;
-  r.near = (int)(near < kSynNear ? near : kSynNear);
-  return r;
+  return (int)(near < kSynNear ? near : kSynNear);
 }
 // k_syn_run: up to 256 x 2,048 neurons whose spike words of the last R steps fit LDS.  Blocks as for the ring's forward kernel: where
 // the rows are long multiples of 64 neurons, so that more blocks share the events.  near: entries of a row's front kept in LDS.
@@ -944,8 +938,6 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->J = take(c->tau_syn_ms > 0.0f ? nstates * BN * 4 : 0);
   L->win = take(bounded ? 0 : 2 * (size_t)L->W * BN * 4);
   L->spike_bits = take(bounded && !synrun ? 0 : (size_t)L->R * L->words * 8);
-  L->trial_near = bounded || small ? -1 : trial_plan(c).near;
-  L->trial_words = take(L->trial_near < 0 ? 0 : (size_t)c->batch * L->R * ((c->n_neurons + 63) / 64) * 8);
   L->syn_cells = take(synrun ? 8 * BN * 4 : 0);
   L->syn_mask = take(synrun ? (size_t)L->syn_R2 * BN * L->syn_mw * 8 : 0);
   L->syn_flagged = take(synrun && synfifo ? (size_t)L->syn_R2 * L->words * 8 : 0);
@@ -1095,9 +1087,6 @@ void launch_reset(adseq* h, hipStream_t st) {
   if (d.kind == ADSEQ_RING) {
     fill_u32(st, d.win, 0u, 2 * (size_t)d.W * BN);
     fill_u32(st, d.spike_bits, 0u, (size_t)d.R * d.words * 2);
-    if (h->trial_near >= 0) fill_u32(st, d.trial_words, 0u, (size_t)d.B * d.R * ((d.N + 63) / 64) * 2);
-    h->trial_ok = h->trial_near >= 0;
-    h->trial_live = false;
     fill_u32(st, d.blk, 0u, kMaxBinBlocks * sizeof(BlkCtr) / 4);
     // staging counters: zero except between the two passes of a window's expansion
     if (d.cap > 0) fill_u32(st, d.ecnt, 0u, (size_t)(d.P < kMaxParts ? d.P : kMaxParts) * d.NB);
@@ -1249,26 +1238,9 @@ void join_ahead(adseq* h, hipStream_t st) {
   if (h->ahead_for >= 0 && h->ev_ahead) (void)hipStreamWaitEvent(st, h->ev_ahead, 0);
 }
 
-// RING: called before anything that needs the window or the circular spike words: they get what k_trial_run has left in the
-// trials' own words.  From here to the next reset the handle's steps go by the other kernels.
-void trial_words_out(adseq* h, hipStream_t st) {
-  const Dev& d = h->dev;
-  hipLaunchKernelGGL(k_trial_words, dim3((unsigned)grid_for((size_t)d.R * d.words)), dim3(kBlock), 0, st, d);
-}
-void trial_leave(adseq* h, hipStream_t st) {
-  h->trial_ok = false;
-  if (!h->trial_live) return;
-  h->trial_live = false;
-  const Dev& d = h->dev;
-  trial_words_out(h, st);
-  // (at a window's first step the window is yet to be opened)
-  if (h->next_step & (long long)(d.W - 1)) hipLaunchKernelGGL(k_trial_window, dim3(512), dim3(kBlock), 0, st, d, h->next_step);
-}
-
 // clear: see launch_expansion.  Returns whether there was a window to open.
 bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0) {
   const Dev& d = h->dev;
-  trial_leave(h, st);
   if ((k0 & (long long)(d.W - 1)) != 0 || k0 <= 0) return false;
   close_group(h, st, 1);
   mark(h, st, -1);
@@ -1425,13 +1397,17 @@ void ring_run_resident(adseq* h, hipStream_t st, long long step0, long long n_st
   }
 }
 
-// RING: steps step0 .. step0 + n_steps - 1 in one launch, a workgroup per trial (ring_trial.h).
+// RING: steps step0 .. step0 + n_steps - 1 in one launch, a workgroup per trial (ring_trial.h).  Host and device are left as the
+// launches per window leave them, down to the barriers' arrivals.
 void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_steps) {
   const Dev& d = h->dev;
+  const int waiting = h->fwd_P > 0 ? h->fwd_P : h->res_P;   // blocks that would wait for one another
+  const int arrive_bar = h->fwd_P == 0 && !d.res_wide;
   long long n = step0;
   const long long end = step0 + n_steps;
   while (n < end) {
-    int cnt = (int)(end - n < (1 << 20) ? end - n : (1 << 20));
+    const int most = (1 << 20) - (int)(n & (long long)(d.W - 1));
+    int cnt = (int)(end - n < most ? end - n : most);
     // a launch either records all its steps or none: it ends where the tape ends
     const bool record = d.record && h->tape_ok && n < d.max_steps;
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
@@ -1440,14 +1416,16 @@ void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_step
     const int threads = trial_threads(d.N);
     const dim3 grid((unsigned)d.B), block((unsigned)threads);
     const long long boundary = (n + cnt - 1) & ~(long long)(d.W - 1), fold = boundary >= n && boundary > 0 ? boundary : h->fold_upto;
-    if (threads <= 256) hipLaunchKernelGGL((k_trial_run<256>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, h->fold_upto, fold, d);
-    else hipLaunchKernelGGL((k_trial_run<1024>), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, h->fold_upto, fold, d);
+    const int windows = (int)(((n + cnt - 1) >> d.wshift) - (n >> d.wshift)) + 1;
+    const unsigned arrivals = (unsigned)(cnt - windows) * (unsigned)waiting;
+    hipLaunchKernelGGL(threads <= 256 ? k_trial_run<256> : k_trial_run<1024>, grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0,
+                       h->fold_upto, fold, arrivals, arrive_bar, d);
+    (arrive_bar ? h->bar_base : h->rev_base) += arrivals;
     h->fold_upto = fold;
     h->enq_calls += cnt;
     n += cnt;
     h->next_step = n;
   }
-  h->trial_live = true;
 }
 
 // RING: steps step0 .. step0 + n_steps - 1 with one launch per window over the whole chip (ring_resident_forward.h).
@@ -1882,8 +1860,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.syn_cells = (int*)(ws + L.syn_cells); d.syn_mask = (unsigned long long*)(ws + L.syn_mask);
   d.syn_flagged = (unsigned long long*)(ws + L.syn_flagged);
   d.syn_mw = L.syn_mw; d.syn_R2 = L.syn_R2;
-  d.trial_words = (unsigned long long*)(ws + L.trial_words);
-  if (d.kind == ADSEQ_RING) { h->trial_near = L.trial_near; }
+  if (d.kind == ADSEQ_RING) h->trial_near = trial_near(cfg);
 #if defined(ADSEQ_PHASE_CLOCK) || defined(ADSEQ_ABLATE)
   d.dbg = getenv("ADSEQ_DBG") ? atoi(getenv("ADSEQ_DBG")) : 0;
 #endif
@@ -2123,7 +2100,6 @@ int adseq_enqueue(adseq_t* h, int64_t step, const int32_t* spike_ids, const int3
     return fail(h, ADSEQ_E_ORDER, "adseq_enqueue: got step %lld, expected %lld (the step last delivered)",
                 (long long)step, h->next_step - 1);
   const int parity = (int)(h->enq_calls & 1);
-  if (h->dev.kind == ADSEQ_RING) trial_leave(h, (hipStream_t)stream);
   if (h->dev.kind == ADSEQ_RING)
     hipLaunchKernelGGL(k_enqueue_win, dim3(kFanoutBlocks), dim3(kBlock), 0, (hipStream_t)stream, h->dev,
                        (long long)step, spike_ids, n_spikes);
@@ -2231,11 +2207,8 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   if (n_steps < 0) return fail(h, ADSEQ_E_INVALID_ARG, "adseq_run: negative step count");
   if (step0 != h->next_step)
     return fail(h, ADSEQ_E_ORDER, "adseq_run: got step %lld, expected %lld", (long long)step0, h->next_step);
-  // (not under capture, where a reset between replays would not be seen, nor while kernels are timed class by class)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool trials = h->dev.kind == ADSEQ_RING && h->trial_ok && n_steps >= kTrialSteps && !h->prof &&
-                      hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-  if (trials) {
+  // (not while kernels are timed class by class)
+  if (h->dev.kind == ADSEQ_RING && h->trial_near >= 0 && n_steps >= kTrialSteps && !h->prof) {
     ring_run_trials(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
     WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);
@@ -2356,7 +2329,6 @@ int adseq_counters(adseq_t* h, int64_t* out8, void* stream) {
     // the spike words: up to the last window boundary by the boundary pass (device counters),
     // since then here; and delivered = offered - still in flight, the latter counted here from
     // the spike words of the last d_max + 1 steps.
-    if (h->trial_live) trial_words_out(h, st);
     fill_u32(st, d.ctr->in_flight, 0u, 4 + 6);
     const long long items = (long long)d.R * d.words;
     hipLaunchKernelGGL(k_ring_in_flight, dim3((unsigned)items), dim3(kBlock), 0, st, d, h->next_step,

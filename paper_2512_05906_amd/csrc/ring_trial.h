@@ -10,8 +10,9 @@
 // (An earlier form kept a window of eight rows in LDS and added the entries of all held spikes two steps ahead, as k_syn_run does; it
 // took 16 x 1,000 neurons, d_max 50, from 2.0 to 1.7 us per step, but with 500 spikes per step and trial from 21 to 71.)
 //
-// The window and the circular spike words of the other kernels are not touched: between calls the spikes stay in trial_words.
-// Another entry point that needs them gets them from there (k_trial_words, k_trial_window).
+// Between launches there is nothing but what the other forward kernels leave, too: circular spike words, the window of the next step,
+// counters, barrier arrivals.  A launch rebuilds its cells from the spike words and hands everything back at its end, so any other
+// entry point, captured or not, may come before or after it.
 
 constexpr int kTrialNeurons = 1024;
 constexpr int kTrialMost = 512;                  // trials: a workgroup fills a compute unit's LDS, so that 256 run at a time, two rounds of 0.5 us per step
@@ -34,8 +35,11 @@ struct TrialLds {
 // Spikes of steps [fold_lo, fold_hi) and the events they emit are counted: fold_lo <= n0, fold_hi the last window boundary of these
 // steps (fold_lo if there is none), as where the other kernels stop counting, so that what is listed on top of the last step is still
 // counted later.  Both n0 - fold_lo and n0 + nsteps - fold_hi are at most W < R.
+// arrivals: what the barriers of these steps would have added to the arrival counter that the host counts along with (arrive_bar: that
+// of the kernels over one XCD).
 template <int kMost>
-__global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, long long fold_lo, long long fold_hi, Dev d) {
+__global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, long long fold_lo, long long fold_hi,
+                                                     unsigned arrivals, int arrive_bar, Dev d) {
   __shared__ TrialLds<kMost> L;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int threads = (int)blockDim.x, waves = threads >> 6;
@@ -46,8 +50,20 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
   const unsigned long long G64 = 0x9E3779B97F4A7C15ull;
   uint2* const fronts = reinterpret_cast<uint2*>(L.words + (size_t)R * wpb);
   int* const cells = reinterpret_cast<int*>(L.words + (size_t)R * wpb + (size_t)near * N);
-  unsigned long long* const held = d.trial_words + (size_t)blockIdx.x * R * wpb;
-  for (int x = tid; x < R * wpb; x += threads) L.words[x] = held[x];
+  // The trial's spike word x = step slot * wpb + word: bits [sh, ..) of the circular words' at[0], the rest in at[1] (hi: there is a
+  // rest).  Trials share words: of such a word only the trial's own bits are looked at or changed.
+  struct Place { unsigned long long* at; int sh; unsigned long long own; bool hi; };
+  auto place = [&](int x) {
+    const int s = x / wpb, w = x - s * wpb, n = N - w * 64 < 64 ? N - w * 64 : 64, g0 = base + w * 64;
+    Place p;
+    p.at = d.spike_bits + (size_t)s * d.words + (g0 >> 6);
+    p.sh = g0 & 63;
+    p.own = n < 64 ? (1ull << n) - 1ull : ~0ull;
+    p.hi = p.sh + n > 64;
+    return p;
+  };
+  auto held = [&](const Place& p) { return ((p.at[0] >> p.sh) | (p.hi ? p.at[1] << (64 - p.sh) : 0ull)) & p.own; };
+  for (int x = tid; x < R * wpb; x += threads) L.words[x] = held(place(x));
   for (int x = tid; x < R * N; x += threads) cells[x] = 0;
   if (tid < 2) L.n_spk[tid] = 0;
   float V = 0.0f, J = 0.0f, Jf = 0.0f;
@@ -157,8 +173,27 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
     if (++slot == R) slot = 0;
   }
   __syncthreads();
-  // ---- what outlives the launch; spikes and the events they emit into the counters that the window's expansion keeps
-  for (int x = tid; x < R * wpb; x += threads) held[x] = L.words[x];
+  // ---- what outlives the launch.  Spike words: the bits that have changed
+  for (int x = tid; x < R * wpb; x += threads) {
+    const Place p = place(x);
+    const unsigned long long flip = held(p) ^ L.words[x];
+    if (flip << p.sh) atomicXor(&p.at[0], flip << p.sh);
+    if (p.hi && (flip >> (64 - p.sh))) atomicXor(&p.at[1], flip >> (64 - p.sh));
+  }
+  // the window of the next step from there on (if that step opens a window, it is empty as yet), and nothing in the one this launch began in
+  const long long end = n0 + nsteps;
+  const int phi = (int)(end & (long long)(d.W - 1));
+  int* const win = win_of(d, end);
+  int* const first = n0 > 0 ? win_of(d, n0 - 1) : win;
+  for (int x = tid; x < d.W * N; x += threads) {
+    const int r = x / N, i = x - r * N;
+    int s = slot + r - phi;
+    if (s >= R) s -= R;
+    if (phi) win[(size_t)r * d.BN + base + i] = r >= phi ? cells[s * N + i] : 0;
+    if (first != win || !phi) first[(size_t)r * d.BN + base + i] = 0;
+  }
+  if (blockIdx.x == 0 && tid == 0 && arrivals) atomicAdd(arrive_bar ? &d.ctr->bar[0] : &d.ctr->rev_arrivals[0][0], arrivals);
+  // spikes and the events they emit, into the counters that the window's expansion keeps
   long long c0 = 0, c1 = 0, c2 = 0;
   if (act) {
     d.V[g] = V;
@@ -173,50 +208,5 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
     atomicAdd((unsigned long long*)&bc.pad[0], (unsigned long long)c0);
     atomicAdd(&bc.offered, (unsigned long long)c1);
     atomicAdd((unsigned long long*)&bc.sum_offered, (unsigned long long)c2);
-  }
-}
-
-// The circular spike words of all trials from the trials' own.
-__global__ __launch_bounds__(kBlock) void k_trial_words(Dev d) {
-  const int wpb = (d.N + 63) >> 6;
-  const long long items = (long long)d.R * d.words;
-  for (long long x = (long long)blockIdx.x * kBlock + threadIdx.x; x < items; x += (long long)gridDim.x * kBlock) {
-    const int s = (int)(x / d.words);
-    const long long g0 = (x - (long long)s * d.words) * 64;
-    unsigned long long out = 0ull;
-    for (int at = 0; at < 64 && g0 + at < d.BN;) {
-      const int g = (int)g0 + at, b = trial_of(d, g), i = g - b * d.N;
-      int take = 64 - (i & 63);                         // bits left in the trial's word
-      if (take > d.N - i) take = d.N - i;
-      if (take > 64 - at) take = 64 - at;
-      const unsigned long long v = d.trial_words[((size_t)b * d.R + s) * wpb + (i >> 6)] >> (i & 63);
-      out |= (take < 64 ? v & ((1ull << take) - 1ull) : v) << at;
-      at += take;
-    }
-    d.spike_bits[x] = out;
-  }
-}
-// The window that step n_end falls into, from the circular spike words: what arrives at its steps from n_end on.  (Its rows are zero
-// when the launch begins.)  One wavefront per spike word.
-__global__ __launch_bounds__(kBlock) void k_trial_window(Dev d, long long n_end) {
-  const int lane = threadIdx.x & 63, nb = d.d_max + 2;
-  const long long items = (long long)d.d_max * d.words, waves = (long long)gridDim.x * (kBlock / 64);
-  const int left = d.W - (int)(n_end & (long long)(d.W - 1));
-  int* __restrict__ win = win_of(d, n_end);
-  for (long long x = (long long)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); x < items; x += waves) {
-    const int age = 1 + (int)(x / d.words), word = (int)(x - (long long)(age - 1) * d.words);
-    if (age > n_end) break;
-    unsigned long long bits = d.spike_bits[(size_t)((n_end - age) % d.R) * d.words + word];
-    for (; bits; bits &= bits - 1) {
-      const int g = word * 64 + __ffsll((long long)bits) - 1, b = trial_of(d, g), i = g - b * d.N;
-      const unsigned* ds = d.dstart + (size_t)i * nb;
-      const long long r0 = d.row_ptr[i];
-      const unsigned q1 = ds[age + left < nb - 1 ? age + left : nb - 1];
-      for (unsigned q = ds[age] + lane; q < q1; q += 64) {
-        const uint2 e = d.synf[r0 + q];
-        const int row = (int)((n_end - age + (long long)(e.x & d.dmask)) & (long long)(d.W - 1));
-        atomicAdd(&win[(size_t)row * d.BN + (size_t)b * d.N + (e.x >> d.dbits)], (int)e.y);
-      }
-    }
   }
 }

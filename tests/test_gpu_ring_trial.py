@@ -116,3 +116,86 @@ def test_ring_trial_enqueue_after_run(pieces, monkeypatch):
     for one, many in zip(got[0][1], got[1][1]):
         for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered", "tape_spikes"):
             assert one[key] == many[key], key
+
+
+def _capture(*calls):
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        for fn, args in calls:
+            fn(*args)
+    return graph
+
+
+def _same(sim, ref, T):
+    torch.cuda.synchronize()
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    assert c["error_bits"] & ~64 == 0 and c["tape_spikes"] == ref.spikes.sum()
+    np.testing.assert_array_equal(sim.membrane_tape(T).cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+
+
+@pytest.mark.parametrize("n,b", [(120, 2), (1000, 3)])
+@pytest.mark.parametrize("pieces", [[107], [50, 57], [40, 67], [32, 40, 35]])
+def test_ring_trial_and_graph_replay(pieces, n, b):
+    """Replays of a captured {reset, run} in between eager runs of the same handle, whatever kernels either of them takes: every replay
+    and every eager run leaves the oracle's counters and trace, and single steps go on from there."""
+    T, more = 107, 30
+    wl = synth.ragged_network(n, 40, 30, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref, longer = (oracle.Run(wl, adseq.RING, 0, n_steps=t, batch=b) for t in (T, T + more))
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T + more)
+    sim.run(0, T)
+    _same(sim, ref, T)
+    k, calls = 0, [(sim.reset, ())]
+    for p in pieces:
+        calls.append((sim.run, (k, p))); k += p
+    graph = _capture(*calls)
+    for cut in (T, 40, T):
+        sim.reset()
+        sim.run(0, cut)
+        if cut < T:
+            sim.run(cut, T - cut)
+        _same(sim, ref, T)
+        sim.membrane_tape(T).zero_()
+        graph.replay()
+        _same(sim, ref, T)
+        for j in range(more):
+            sim.step(T + j)
+        _same(sim, longer, T + more)
+    sim.close()
+
+
+@pytest.mark.parametrize("n,b", [(120, 2), (1000, 3), (63, 1)])
+@pytest.mark.parametrize("first,second", [([80], 30), ([32, 16, 32], 30), ([80], 90), ([40, 40], 90)])
+def test_ring_trial_runs_go_on_after_a_replay(first, second, n, b):
+    """A captured run that begins where an eager one ended, and eager runs that begin where a replay ended, by either forward kernel."""
+    T = 200
+    wl = synth.ragged_network(n, 40, 30, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref = oracle.Run(wl, adseq.RING, 0, n_steps=T, batch=b)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T)
+    sim.run(0, 80)
+    graph = _capture((sim.run, (80, second)))
+    for _ in range(2):   # (the handle itself does not know of the steps of a replay)
+        sim.reset()
+        k = 0
+        for p in first:
+            sim.run(k, p); k += p
+        graph.replay()
+        torch.cuda.synchronize()
+        assert sim.counters()["error_bits"] & ~64 == 0
+        np.testing.assert_array_equal(sim.membrane_tape(80 + second).cpu().numpy().view(np.uint32), ref.U[:80 + second].view(np.uint32))
+    sim.reset()
+    calls, k = [(sim.reset, ())], 0
+    for p in first + [second]:
+        calls.append((sim.run, (k, p))); k += p
+    graph = _capture(*calls)
+    for tail in ([T - k], [10] * ((T - k) // 10)):
+        for fn, args in calls:
+            fn(*args)
+        graph.replay()
+        at = k
+        for p in tail:
+            sim.run(at, p); at += p
+        _same(sim, ref, T)
+    sim.close()
