@@ -234,7 +234,8 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * launch needs the device free enough for all its blocks to run at the same time.  Calls that
  * make such launches (adseq_backward too) wait, on their stream, for the last such call of the
  * process on the device.  Under stream capture they cannot: there, and with the handle of adseq_create_static,
- * the bounded kinds keep to launches whose blocks wait for nobody, one to three per step; a captured ring's launches stay what they are, and
+ * the bounded kinds keep to launches whose blocks wait for nobody, one to three per step (the per-synapse kinds in
+ * every later call of a handle of which a call has been captured, too); a captured ring's launches stay what they are, and
  * the program keeps the graph's replays apart from other such launches (same stream, or events of
  * its own).  A small ring network whose delay line fits a compute unit's LDS runs by one workgroup per
  * trial that waits for nobody (calls of 64 steps or more).  adseq_create

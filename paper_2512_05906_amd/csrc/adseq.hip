@@ -58,6 +58,7 @@ struct Counters {
   long long pieces;                 // RING: row pieces of the last expansion, estimated from its first block
   unsigned long long in_flight[2];  // scratch of k_ring_in_flight: events, Q8.24 sum
   unsigned long long fold[3];       // scratch of k_count_spikes: spikes, events, Q8.24 sum
+  unsigned syn_live;                // SYN_*: the events in flight are in the spike words (k_syn_run), not in the queue arrays
   alignas(128) unsigned bar[32];    // bar[0]: arrivals at the barriers of the resident step kernels (a line of its own)
   alignas(128) unsigned arrive[8][32];  // arrive[x][0]: blocks with index x mod 8 of the chained step launches that have arrived (ring_chain.h)
   alignas(128) unsigned rev_arrivals[kArriveLines][32];  // rev_arrivals[x][0]: arrivals of the blocks with rank x mod kArriveLines at the grid barriers of the resident reverse kernel and of the forward kernel over the whole chip
@@ -540,7 +541,9 @@ struct adseq {
   int q_P = 0, q_chunk = 0;                    // FIFO / SORTED: the same for k_queue_run (0: two launches per step)
   int syn_P = 0, syn_chunk = 0, syn_near = 0;  // SYN_*: the same for k_syn_run (0: three launches per step), row-front entries in LDS
   bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
-  bool syn_live = false;                       // ... and the events in flight are in the spike words, not in the queue arrays
+  bool syn_live = false;                       // the events in flight may be in the spike words (Counters::syn_live knows: a graph's replay changes it)
+  bool syn_captured = false;                   // a call has been captured: replays may put steps of the queue arrays under the host's feet, so k_syn_run is not used any more
+  unsigned long long syn_left_in = 0;          // the capture in which the queue arrays are in use from some point on
   int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
@@ -1070,6 +1073,13 @@ void fill_u32(hipStream_t st, void* p, unsigned v, size_t count) {
 
 void join_ahead(adseq* h, hipStream_t st);
 
+// Whether the stream is being captured; *id tells one capture from another.
+bool capturing(hipStream_t st, unsigned long long* id) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamGetCaptureInfo(st, &cap, id) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 // Clears the dynamic state (not the prepared synapses).
 void launch_reset(adseq* h, hipStream_t st) {
   const Dev& d = h->dev;
@@ -1100,8 +1110,12 @@ void launch_reset(adseq* h, hipStream_t st) {
       fill_u32(st, d.spike_bits, 0u, (size_t)d.R * d.words * 2);
       fill_u32(st, d.syn_cells, 0u, 8 * BN);
     }
-    h->syn_ok = h->syn_P > 0;
-    h->syn_live = false;
+    if (h->syn_P > 0) {
+      unsigned long long id = 0;
+      if (capturing(st, &id)) { h->syn_captured = true; h->syn_left_in = id; }
+      else h->syn_live = false;
+      h->syn_ok = !h->syn_captured;
+    }
     h->pending_admit = false;
   } else {
     fill_u32(st, d.occ, 0u, BN);
@@ -1125,18 +1139,24 @@ void launch_reset(adseq* h, hipStream_t st) {
   h->bits_clear_for = -1;
 }
 
-// SYN_*: called before anything that needs the queue arrays: they get the events that k_syn_run has left in the spike words.  From
-// here to the next reset the handle's steps go by three launches each.
+// SYN_*: called before anything that needs the queue arrays: they get the events that k_syn_run has left in the spike words (the kernels
+// look whether it has).  From here to the next reset the handle's steps go by three launches each.
 void syn_leave(adseq* h, hipStream_t st) {
+  if (h->syn_P == 0) return;
+  unsigned long long id = 0;
+  const bool cap = (!h->syn_captured || h->syn_live) && capturing(st, &id);
+  h->syn_captured |= cap;
   h->syn_ok = false;
-  if (!h->syn_live) return;
-  h->syn_live = false;
+  if (!h->syn_live || (cap && id == h->syn_left_in)) return;
+  // (what is captured has not happened yet: an eager call that comes before the replay still finds the spike words)
+  if (cap) h->syn_left_in = id;
+  else h->syn_live = false;
   const Dev& d = h->dev;
   const unsigned g = (unsigned)((d.BN + kBlock / 64 - 1) / (kBlock / 64));
   fill_u32(st, d.ctr->in_flight, 0u, 4);
   hipLaunchKernelGGL(k_syn_in_flight, dim3(1024), dim3(kBlock), 0, st, d, h->next_step, d.ctr->in_flight);
-  hipLaunchKernelGGL(k_syn_delivered, dim3(1), dim3(64), 0, st, d, d.blk_pop + kSynqBlocks, d.ctr->in_flight);
   hipLaunchKernelGGL(k_syn_queues, dim3(g < 16384 ? g : 16384), dim3(kBlock), 0, st, d, h->next_step);
+  hipLaunchKernelGGL(k_syn_delivered, dim3(1), dim3(64), 0, st, d, d.blk_pop + kSynqBlocks, d.ctr->in_flight);
 }
 
 // FIFO / SORTED: admission of what is pending, then (MODE 1) pop or (MODE 2) the closed-loop step.
@@ -2362,7 +2382,7 @@ int adseq_counters(adseq_t* h, int64_t* out8, void* stream) {
     // every offered event has been admitted or refused by now (what was pending was admitted above)
     out8[1] = out8[0] - admitted;
     out8[4] = out8[3] - sum_admitted;
-    if (h->syn_live) { out8[2] = admitted - (int64_t)c.in_flight[0]; out8[5] = sum_admitted - (int64_t)c.in_flight[1]; }
+    if (c.syn_live) { out8[2] = admitted - (int64_t)c.in_flight[0]; out8[5] = sum_admitted - (int64_t)c.in_flight[1]; }
   }
   if (d.kind == ADSEQ_RING) {
     // spikes and offered events up to the last window boundary: private counters of the staging

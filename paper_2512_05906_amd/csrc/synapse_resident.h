@@ -497,7 +497,7 @@ __global__ __launch_bounds__(kBlock) void k_syn_list(Dev d, long long n0) {
   if (t == 0) {
     d.step_off[n + 1] = sp + (long long)(own >> 40);
     d.step_evoff[n + 1] = ev + (long long)(own & kEvents);
-    if (blockIdx.x + 1 == gridDim.x) { d.ctr->tape_spikes = sp + (long long)(own >> 40); d.ctr->tape_events = ev + (long long)(own & kEvents); }
+    if (blockIdx.x + 1 == gridDim.x) { d.ctr->tape_spikes = sp + (long long)(own >> 40); d.ctr->tape_events = ev + (long long)(own & kEvents); d.ctr->syn_live = 1u; }
   }
   if (own == 0ull) return;   // (uniform)
   const int nw = (d.BN + 63) >> 6;
@@ -603,8 +603,9 @@ __global__ __launch_bounds__(kBlock) void k_syn_flags(Dev d, long long n_lo, lon
 }
 
 // Events in flight before step n_end (arrival n_end or later) and their amplitudes, added to out[0], out[1]: the tails of the held
-// spikes' rows.  One wavefront per spike word.
+// spikes' rows.  One wavefront per spike word.  This and the next two do nothing unless the events are in the spike words.
 __global__ __launch_bounds__(kBlock) void k_syn_in_flight(Dev d, long long n_end, unsigned long long* out) {
+  if (!d.ctr->syn_live) return;
   const int lane = threadIdx.x & 63;
   const long long items = (long long)d.d_max * d.words, waves = (long long)gridDim.x * (kBlock / 64);
   int c = 0;
@@ -632,18 +633,11 @@ __global__ __launch_bounds__(kBlock) void k_syn_in_flight(Dev d, long long n_end
   const long long tc = wave_total(c), ts = wave_total64(s);
   if (lane == 0 && tc) { atomicAdd(&out[0], (unsigned long long)tc); atomicAdd(&out[1], (unsigned long long)ts); }
 }
-// Delivered so far: admitted and no longer in flight.  (Before the queues are popped by other kernels, which count for themselves.)
-__global__ void k_syn_delivered(Dev d, int lines, const unsigned long long* in_flight) {
-  long long c = 0, s = 0;
-  for (int x = threadIdx.x; x < lines; x += 64) { c += (long long)d.blk[x].admitted; s += d.blk[x].sum_admitted; }
-  c = wave_total64(c); s = wave_total64(s);
-  if (threadIdx.x == 0) { d.blk[0].delivered += (unsigned long long)c - in_flight[0]; d.blk[0].sum_delivered += s - (long long)in_flight[1]; }
-}
-
 // The queue arrays as three launches per step would have left them before step n_end, from the spike words (the arrays are as a
 // reset leaves them).  One wavefront per neuron and trial.
 __global__ __launch_bounds__(kBlock) void k_syn_queues(Dev d, long long n_end) {
   __shared__ unsigned short s_age[kBlock / 64][1024];
+  if (!d.ctr->syn_live) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   unsigned short* const ages = s_age[wave];
   const long long qpad = (((long long)d.B * d.S + 7) >> 3) << 3;
@@ -700,5 +694,19 @@ __global__ __launch_bounds__(kBlock) void k_syn_queues(Dev d, long long n_end) {
         }
       }
     }
+  }
+}
+
+// Delivered so far: admitted and no longer in flight.  (The last of the three: from here on the queue arrays hold the events, and are popped
+// by kernels that count for themselves.)
+__global__ void k_syn_delivered(Dev d, int lines, const unsigned long long* in_flight) {
+  if (!d.ctr->syn_live) return;
+  long long c = 0, s = 0;
+  for (int x = threadIdx.x; x < lines; x += 64) { c += (long long)d.blk[x].admitted; s += d.blk[x].sum_admitted; }
+  c = wave_total64(c); s = wave_total64(s);
+  if (threadIdx.x == 0) {
+    d.blk[0].delivered += (unsigned long long)c - in_flight[0];
+    d.blk[0].sum_delivered += s - (long long)in_flight[1];
+    d.ctr->syn_live = 0u;
   }
 }

@@ -128,3 +128,90 @@ def test_syn_resident_past_the_tape_and_wait_that_runs_out(monkeypatch):
         with pytest.raises(adseq.AdseqError):
             sim.drop_count()
     sim.close()
+
+
+def _capture(*calls):
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        for fn, args in calls:
+            fn(*args)
+    return graph
+
+
+def _same(sim, ref, T):
+    torch.cuda.synchronize()
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    assert c["error_bits"] & ~64 == 0 and c["tape_spikes"] == ref.spikes.sum()
+    np.testing.assert_array_equal(sim.membrane_tape(T).cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 3)])
+@pytest.mark.parametrize("pieces", [[90], [50, 40]])
+def test_syn_resident_and_graph_replay(kind, cap, pieces):
+    """Replays of a captured {reset, run} in between eager runs of the same handle: every replay and every eager run leaves the oracle's
+    counters and trace, and single steps and runs go on from there; a capture alone changes nothing."""
+    T, b, more = 90, 2, 30
+    wl = synth.ragged_network(120, 40, 40, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref, longer = (oracle.Run(wl, kind, cap, n_steps=t, batch=b) for t in (T, T + more))
+    room = (T + more) * b * wl.n_neurons // 2
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T + more, tape_spike_capacity=room,
+                      tape_event_capacity=(T + more) * b * wl.n_synapses // 2)
+    sim.run(0, T)
+    _same(sim, ref, T)
+    k, calls = 0, [(sim.reset, ())]
+    for p in pieces:
+        calls.append((sim.run, (k, p))); k += p
+    for captures in range(2):
+        graph = _capture(*calls)
+        _same(sim, ref, T)
+        for single in (True, False):
+            graph.replay()
+            _same(sim, ref, T)
+            for j in range(more if single else 0):
+                sim.step(T + j)
+            if not single:
+                sim.run(T, more)
+            _same(sim, longer, T + more)
+            sim.reset()
+            sim.run(0, T)
+            _same(sim, ref, T)
+            graph.replay()
+            _same(sim, ref, T)
+            sim.reset()
+            sim.run(0, T)
+    sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 3)])
+def test_syn_resident_then_captured_run(kind, cap):
+    """A captured run that begins where an eager one ended, replayed after a run and after single steps."""
+    T, b = 60, 2
+    wl = synth.ragged_network(120, 40, 40, seed=9, rate_hz=900.0, t=2 * T, b=b, w_mean=0.02, w_std=0.02)
+    ref = oracle.Run(wl, kind, cap, n_steps=2 * T, batch=b)
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=2 * T, tape_spike_capacity=T * b * wl.n_neurons,
+                      tape_event_capacity=T * b * wl.n_synapses)
+    sim.run(0, T)
+    graph = _capture((sim.run, (T, T)))
+    graph.replay()
+    _same(sim, ref, 2 * T)
+    for single in (False, True):
+        sim.reset()
+        if single:
+            for k in range(T):
+                sim.step(k)
+        else:
+            sim.run(0, T)
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(sim.membrane_tape(2 * T).cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+        # the counters of a handle that knows of the replayed steps
+        sim.reset()
+        sim.run(0, 2 * T)
+        sim.reset()
+        sim.run(0, T)
+        sim.run(T, T)
+        _same(sim, ref, 2 * T)
+    sim.close()
