@@ -539,6 +539,19 @@ __global__ __launch_bounds__(kBlock) void k_syn_list(Dev d, long long n0) {
   }
 }
 
+// Index of the first admission flag of the spike of neuron g at step n, from the tape's spike words: for spikes that the tape's list
+// had no room for.  -1: its flags do not fit.  Whole wavefront.
+__device__ __forceinline__ long long syn_flag_base(const Dev& d, long long n, int g) {
+  long long e = 0;
+  for (int w = threadIdx.x & 63; w <= (g >> 6); w += 64) {
+    unsigned long long bits = d.tape_bits[(size_t)n * d.words + w];
+    if (w == (g >> 6)) bits &= (1ull << (g & 63)) - 1ull;
+    for (; bits; bits &= bits - 1) { const int q = w * 64 + __ffsll((long long)bits) - 1; e += d.rowlen[q - trial_of(d, q) * d.N]; }
+  }
+  e = d.step_evoff[n] + wave_total64(e);
+  return e + d.rowlen[g - trial_of(d, g) * d.N] <= d.event_cap ? e : -1;
+}
+
 // The age at which the spike of neuron g at step n is replaced (SYN_LATEST, SYN_BINS), by the tape's spike words of steps below
 // n_end; 0: it is not, or none of its events is left then.  Whole wavefront.
 __device__ __forceinline__ int syn_replaced(const Dev& d, long long n, int g, long long n_end) {
@@ -560,12 +573,11 @@ __global__ __launch_bounds__(kBlock) void k_syn_flags(Dev d, long long n_lo, lon
   const long long n = n_lo + blockIdx.x;
   int lost = 0;          // events of these spikes that were refused or replaced, and their amplitudes
   long long s_lost = 0;
-  const long long lo = d.step_off[n], hi = d.step_off[n + 1] < d.spike_cap ? d.step_off[n + 1] : d.spike_cap;
-  for (long long e = lo + wave; e < hi; e += nwaves) {
-    const int g = d.tape_spk[e], i = g - trial_of(d, g) * d.N;
-    const long long evb = d.tape_evb[e], r0 = d.row_ptr[i];
+  auto one = [&](int g, long long evb) {
+    const int i = g - trial_of(d, g) * d.N;
+    const long long r0 = d.row_ptr[i];
     const int len = d.rowlen[i];
-    if (len == 0) continue;
+    if (len == 0) return;
     unsigned char* const flag = d.tape_adm + evb;
     bool some = false;
     int age = 0, slot2 = 0;
@@ -575,7 +587,7 @@ __global__ __launch_bounds__(kBlock) void k_syn_flags(Dev d, long long n_lo, lon
     } else {
       age = syn_replaced(d, n, g, n1);
       some = age > 0;
-      if (n < n0 && (!some || n + age < n0)) continue;   // (as it was)
+      if (n < n0 && (!some || n + age < n0)) return;   // (as it was)
     }
     if (!some && evb >= 0) {
       // all ones: whole words in the middle
@@ -587,13 +599,23 @@ __global__ __launch_bounds__(kBlock) void k_syn_flags(Dev d, long long n_lo, lon
       for (int x = lane; x < mid; x += 64) f4[x] = 0x01010101u;
       if (tail + lane < len) flag[tail + lane] = 1;
     }
-    if (!some) continue;
+    if (!some) return;
     for (int q = lane; q < len; q += 64) {
       const int D = (int)(d.packed[r0 + q] & d.dmask);
       const bool in = d.kind == ADSEQ_SYN_FIFO ? (syn_mask_load(d, slot2, g, (D - 1) >> 6) >> ((D - 1) & 63)) & 1ull : D <= age;
       if (evb >= 0) flag[q] = in ? 1 : 0;
       if (!in) { lost += 1; s_lost += d.a_q[r0 + q]; }
     }
+  };
+  const long long lo = d.step_off[n], hi = d.step_off[n + 1];
+  if (hi <= d.spike_cap) {
+    for (long long e = lo + wave; e < hi; e += nwaves) one(d.tape_spk[e], d.tape_evb[e]);
+  } else {   // (the list is full: the step's spikes from the tape's words)
+    for (int w = wave; w < (d.BN + 63) >> 6; w += nwaves)
+      for (unsigned long long bits = d.tape_bits[(size_t)n * d.words + w]; bits; bits &= bits - 1) {
+        const int g = w * 64 + __ffsll((long long)bits) - 1;
+        one(g, syn_flag_base(d, n, g));
+      }
   }
   if (__ballot(lost != 0)) {
     const long long t = wave_total(lost), ts = wave_total64(s_lost);

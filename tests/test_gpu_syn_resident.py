@@ -215,3 +215,32 @@ def test_syn_resident_then_captured_run(kind, cap):
         sim.run(T, T)
         _same(sim, ref, 2 * T)
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 1), (adseq.SYN_BINS, 3)])
+@pytest.mark.parametrize("spikes,events", [(300, 1 << 18), (301, 1 << 18), (1 << 14, 9000), (300, 9000), (1 << 14, 9001)])
+def test_syn_resident_full_tape(kind, cap, spikes, events, monkeypatch):
+    """A tape whose spike list or admission flags are full in the middle of a run: the counters are exact all the same, and the flags
+    those of launches per step."""
+    T, b, n = 150, 2, 120
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b)
+    rc = ref.counters()
+    assert ref.spikes.sum() > 600 and rc["enqueued"] > 18000 and rc["dropped"] > 1000
+    got = []
+    for resident in ("0", "1"):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T, tape_spike_capacity=spikes, tape_event_capacity=events)
+        flags = sim.admitted_flags(0, events)
+        flags.zero_()
+        sim.run(0, T)
+        torch.cuda.synchronize()
+        c = sim.counters()
+        assert c["error_bits"] & ~64 == (4 if spikes < 1000 else 0) + (8 if events < 18000 else 0)
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], (key, resident)
+        got.append(flags.cpu().numpy())
+        sim.close()
+    if kind != adseq.SYN_BINS or events > 18000:   # (by launches, a spike without flags of its own leaves those of what it replaces in a bin)
+        used = min(events, rc["enqueued"])
+        np.testing.assert_array_equal(got[1][:used], got[0][:used])
