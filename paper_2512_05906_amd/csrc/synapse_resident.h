@@ -680,12 +680,15 @@ __global__ __launch_bounds__(kBlock) void k_syn_queues(Dev d, long long n_end) {
       long long a = d.step_off[n_end - age], b = d.step_off[n_end - age + 1];
       if (b > d.spike_cap) b = d.spike_cap;
       while (a < b) { const long long mid = (a + b) >> 1; if (d.tape_spk[mid] < g) a = mid + 1; else b = mid; }
-      return a < d.spike_cap && d.tape_spk[a] == g ? d.tape_evb[a] : -1;
+      return a < d.spike_cap && d.tape_spk[a] == g ? d.tape_evb[a] : syn_flag_base(d, n_end - age, g);
     };
     const int b = trial_of(d, g), i = g - b * d.N;
     const long long r0 = d.row_ptr[i];
     const int len = d.rowlen[i];
-    if (d.kind == ADSEQ_SYN_LATEST && lane == 0) d.last_evb[(size_t)(d.spk_count[g] & 1) * d.BN + g] = evb_of(ages[cnt - 1]);
+    if (d.kind == ADSEQ_SYN_LATEST) {
+      const long long evb = evb_of(ages[cnt - 1]);
+      if (lane == 0) d.last_evb[(size_t)(d.spk_count[g] & 1) * d.BN + g] = evb;
+    }
     for (int x = 0; x < (d.kind == ADSEQ_SYN_FIFO ? 1 : cnt); ++x) {
       const int age0 = ages[x];
       const long long evb = d.kind == ADSEQ_SYN_BINS ? evb_of(age0) : -1;
@@ -712,7 +715,7 @@ __global__ __launch_bounds__(kBlock) void k_syn_queues(Dev d, long long n_end) {
           const long long k = n_end - age0 + D;
           const long long at = d.kind == ADSEQ_SYN_BINS ? (k % d.C) * qpad + q : q;
           d.sq_next[at] = (unsigned short)synq_key(k);
-          if (d.kind == ADSEQ_SYN_BINS && d.sq_flag) d.sq_flag[at] = evb + p;
+          if (d.kind == ADSEQ_SYN_BINS && d.sq_flag && evb >= 0) d.sq_flag[at] = evb + p;   // (once the flags are full, none is looked at)
         }
       }
     }

@@ -244,3 +244,34 @@ def test_syn_resident_full_tape(kind, cap, spikes, events, monkeypatch):
     if kind != adseq.SYN_BINS or events > 18000:   # (by launches, a spike without flags of its own leaves those of what it replaces in a bin)
         used = min(events, rc["enqueued"])
         np.testing.assert_array_equal(got[1][:used], got[0][:used])
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 1), (adseq.SYN_BINS, 3)])
+@pytest.mark.parametrize("spikes,events", [(300, 1 << 18), (301, 1 << 18), (1 << 14, 9000), (300, 9000), (1 << 14, 9001)])
+def test_syn_resident_full_tape_then_steps(kind, cap, spikes, events, monkeypatch):
+    """A tape whose spike list or admission flags are full in the middle of a run: single steps on top of it change the flags that they
+    would after launches per step, and no byte in front of them."""
+    T, b, n, more = 150, 2, 120, 20
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref = oracle.Run(wl, kind, cap, n_steps=T + more, batch=b)
+    assert ref.spikes[:T].sum() > 600 and ref.counters()["enqueued"] > 18000
+    got = []
+    for resident in ("0", "1"):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T + more, tape_spike_capacity=spikes, tape_event_capacity=events)
+        flags = sim.admitted_flags(-64, events + 64)
+        flags.zero_()   # (and 64 bytes that nothing lies in)
+        sim.run(0, T)
+        for k in range(T, T + more):
+            sim.step(k)
+        torch.cuda.synchronize()
+        c, rc = sim.counters(), ref.counters()
+        assert c["error_bits"] & 12
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], (key, resident)
+        got.append(flags.cpu().numpy())
+        sim.close()
+    np.testing.assert_array_equal(got[1][:64], got[0][:64])
+    used = 64 + min(events, int(ref.counters()["enqueued"]))
+    if kind != adseq.SYN_BINS or events > 18000:   # (see the test before)
+        np.testing.assert_array_equal(got[1][64:used], got[0][64:used])
