@@ -713,16 +713,20 @@ int trial_near(const adseq_config* c) {
   return (int)(near < kSynNear ? near : kSynNear);
 }
 // k_syn_run: up to 256 x 2,048 neurons whose spike words of the last R steps fit LDS.  Blocks as for the ring's forward kernel: where
-// the rows are long multiples of 64 neurons, so that more blocks share the events.  near: entries of a row's front kept in LDS.
+// the rows are long multiples of 64 neurons, so that more blocks share the events; so too for a FIFO whose rows hold less than one entry
+// per delay, where a step's work is looking at what the sources hold (4,000 x 100, d_max 250, 63 blocks instead of 16: 3.8 instead of 4.4 us per
+// step at 0.2 % firing, 26 instead of 66 at 30 %; 16 x 1,000 x 100, d_max 50, 250 instead of 63 blocks would take 3.8 instead of 3.3 at
+// 0.2 % and 20 instead of 39 to 50 at 30 %).  near: entries of a row's front kept in LDS.
 struct SynPlan { int P = 0, chunk = 0, near = 0, gshift = 0; };
 SynPlan syn_plan(const adseq_config* c) {
   SynPlan r;
   const long long BN = (long long)c->n_neurons * c->batch, row = c->n_synapses / c->n_neurons, R = c->d_max_steps + 1;
   const int blocks = env_pow2("ADSEQ_SYN_BLOCKS", 256, 8, 256);
-  const long long unit = row >= 128 ? 64 : 256;
+  const bool fifo = c->kind == ADSEQ_SYN_FIFO;
+  const long long unit = row >= 128 || (fifo && row < c->d_max_steps) ? 64 : 256;
   const long long chunk = ((BN + blocks - 1) / blocks + unit - 1) / unit * unit;
-  const long long words = R * (chunk / 64) * (c->kind == ADSEQ_SYN_FIFO ? 2 : 1);
-  if (!env_pow2("ADSEQ_SYN_RESIDENT", 1, 0, 1) || chunk > 4 * kResThreads || words > kSynLdsWords) return r;
+  const long long words = R * (chunk / 64) * (fifo ? 2 : 1);
+  if (!env_pow2("ADSEQ_SYN_RESIDENT", 1, 0, 1) || (fifo && c->d_max_steps > kSynFifoDelay) || chunk > 4 * kResThreads || words > kSynLdsWords) return r;
   const long long near = (kSynLdsWords - words) / chunk;
   r.near = (int)(near < kSynNear ? near : kSynNear);
   r.gshift = piece_lanes(c);

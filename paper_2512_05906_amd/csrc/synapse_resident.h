@@ -29,14 +29,21 @@
 // A step is bound by its barrier and by two trips to memory (cells, adds): 1.9 us while nothing spikes; then by the adds of the step's
 // events (27 per ns at best).  Measured, SYN_FIFO[4], 10,000 x 1,000 synapses at 20 spikes and 20,000 events per step: 19.4 us per step
 // by launches, 4.3 so (1,000 steps forward and back 21.0 -> 7.3 ms); 54 trials x 1,396 x 16, 31 spikes per step 14.5 -> 3.6 us.
+// Under load a FIFO is bound by what its sources hold, most of it refused: pieces are looked up one per lane and sifted before their rows
+// are (eight lanes per piece and three trips after one another took 2 to 3 times the step below), and a mask is made of set bits, 64 held
+// spikes at a time (each bit of each delay by a ballot: five times the step below at d_max 1,000).  SYN_FIFO[1], 4,000 x 100, us per step by
+// launches / so at 0.2, 2, 10 and 30 % of the neurons firing: d_max 250 13.7 18.7 34 68 / 3.8 7.0 12.1 26; 512 13.5 18.6 34 70 / 4.9 9.8 19 49;
+// 1,000 13.5 18.5 34 71 / 6.3 12.4 27 94, hence kSynFifoDelay.  SYN_LATEST and SYN_BINS, which hold one spike per source or bin, are faster than
+// launches at all of these (1.6 to 10 times).
 //
 // What crosses blocks are the cells (atomic adds, agent-scope loads and clears) and the claim counters.  Waits are bounded as in
 // the ring's resident kernels; a run whose waits ran out is void, and reads nothing of other blocks that is used as an index.
 
 constexpr int kSynChunk = 128;         // steps of one launch: FIFO masks are kept for R + kSynChunk steps
 constexpr int kSynLdsWords = 16384;    // 8-byte words of LDS for spike words (FIFO: twice) and the rows' fronts
+constexpr int kSynFifoDelay = 512;     // SYN_FIFO: largest delay (see above)
 constexpr int kSynNear = 64;           // entries of a row's front kept in LDS, at most
-constexpr int kSynList = 128;          // pieces a wavefront collects before it takes them
+constexpr int kSynList = 256;          // pieces a wavefront collects before it takes them
 constexpr int kSynAhead = 4;           // accesses per lane that are under way between two steps
 
 __device__ __forceinline__ int* syn_cells_of(const Dev& d, long long n) { return d.syn_cells + (size_t)(n & 7) * d.BN; }
@@ -55,7 +62,8 @@ struct SynLds {
 };
 
 // Collects the pieces (D, place) of all spikes with dlo <= D <= d_max into the wavefront's list and hands them to
-// take(number of pieces) whenever the list may be full and at the end.  slot0: row of the spike words that D = 0 would have.
+// take(number of pieces, whether these are the last) whenever the list may be full and at the end; it returns how many it leaves at the
+// list's front, kSynList - 64 at most, none of the last.  slot0: row of the spike words that D = 0 would have.
 // Returns the number of pieces; most >= 0: gives up, with -1, when there are more than that (take is not called then).
 template <int NPT, class Take>
 __device__ __forceinline__ int syn_walk(const Dev& d, SynLds<NPT>& L, int wpb, int dlo, int slot0, int most, Take take) {
@@ -79,7 +87,7 @@ __device__ __forceinline__ int syn_walk(const Dev& d, SynLds<NPT>& L, int wpb, i
       const unsigned long long m = __ballot(bits != 0ull);
       if (!m) break;
       if (most >= 0 && np + __popcll(m) > most) return -1;
-      if (np > kSynList - 64) { take(np); np = 0; }
+      if (np > kSynList - 64) np = take(np, false);
       if (bits) {
         list[np + __popcll(m & ((1ull << lane) - 1ull))] = ((unsigned)D << 12) | (unsigned)(w * 64 + __ffsll((long long)bits) - 1);
         bits &= bits - 1;
@@ -89,7 +97,7 @@ __device__ __forceinline__ int syn_walk(const Dev& d, SynLds<NPT>& L, int wpb, i
     j += dj; w += dw;
     if (w >= wpb) { w -= wpb; j += 1; }
   }
-  if (most < 0 && np) take(np);
+  if (most < 0 && np) take(np, true);
   return np;
 }
 
@@ -248,7 +256,42 @@ __global__ __launch_bounds__(kResLaunch) void k_syn_run(long long n0, int nsteps
       }
     }
   };
-  auto none = [](int) {};
+  auto none = [](int, bool) { return 0; };
+  // more pieces than are requested ahead: list[0 .. np) added to the cells of step n + 2 in one go
+  auto take_all = [&](int np, int* cells, int slot0, int slot20) {
+    for (int t0 = 0; t0 < np; t0 += kSynAhead * per) {
+      request_rows(t0, np, slot0, slot20);
+      request_entries(np - t0, slot0, slot20);
+      add_entries(np - t0, cells, slot0);
+    }
+  };
+  // FIFO, where a source may hold many spikes that were refused: a lane looks one piece up, and only those that are admitted and not empty stay
+  // in list[kept ..].  Returns their number.
+  auto sift = [&](int kept, int np, int slot0, int slot20) {
+    unsigned* const list = L.list[wave];
+    unsigned pc[kSynList / 64];
+    bool in[kSynList / 64];
+#pragma unroll
+    for (int u = 0; u < kSynList / 64; ++u) {
+      const int x = kept + 64 * u + lane;
+      pc[u] = 0u; in[u] = x < np;
+      if (in[u]) {
+        pc[u] = list[x];
+        const int D = (int)(pc[u] >> 12), place = (int)(pc[u] & 0xfffu), g = lo + place;
+        const unsigned* ds = d.dstart + (size_t)(g - trial_of(d, g) * d.N) * nb + D;
+        const unsigned q0 = ds[0], q1 = ds[1];
+        in[u] = !refused(D, place, slot0, slot20) && q1 > q0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kSynList / 64; ++u) {
+      const unsigned long long m = __ballot(in[u]);
+      if (in[u]) list[kept + __popcll(m & ((1ull << lane) - 1ull))] = pc[u];
+      kept += __popcll(m);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return kept;
+  };
   for (int k = 0; k < nsteps; ++k) {
     const long long n = n0 + k;
     const int par = k & 1;
@@ -392,12 +435,30 @@ __global__ __launch_bounds__(kResLaunch) void k_syn_run(long long n0, int nsteps
           };
           int count = 0;
           for (int a0 = 0; a0 < d.d_max - 1; a0 += 64) count += __popcll(__ballot(held(a0 + lane + 1)));
-          if (count < d.C) continue;   // (uniform)
+          if (__builtin_expect(count < d.C, 1)) continue;   // (uniform)
+          // The held spikes, 64 at a time: by the list of their ages where that has room for them, else as they come.  A lane has one spike
+          // and 64 delays of its mask; each spike's word is then handed to the whole wavefront, whose lanes are the delays.
+          const bool listed = count <= kSynList;
+          if (listed) {
+            int at = 0;
+#pragma unroll 1
+            for (int a0 = 0; a0 < d.d_max - 1; a0 += 64) {
+              const bool has = held(a0 + lane + 1);
+              const unsigned long long m = __ballot(has);
+              if (has) L.list[wave][at + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned)(a0 + lane + 1);
+              at += __popcll(m);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          }
+          const int chunks = ((listed ? count : d.d_max - 1) + 63) >> 6;
+#pragma unroll 1
           for (int r = 0; r < d.syn_mw; ++r) {
             int mine = 0;   // events in the queues of delay 64 r + lane + 1
-            for (int a0 = 0; a0 <= 64 * r; a0 += 64) {
-              const int a = a0 + lane + 1;
-              const bool has = held(a);
+#pragma unroll 1
+            for (int x = 0; x < chunks; ++x) {
+              const int a = !listed ? 64 * x + lane + 1 : (64 * x + lane < count ? (int)L.list[wave][64 * x + lane] : d.d_max);
+              const int gone = a - 64 * r;   // (in the queue of delay D while a < D)
+              const bool has = gone < 64 && (listed ? a < d.d_max : held(a));
               if (!__ballot(has)) continue;
               unsigned long long w = 0ull;
               if (has) {
@@ -405,13 +466,13 @@ __global__ __launch_bounds__(kResLaunch) void k_syn_run(long long n0, int nsteps
                 if (s < 0) s += d.R;
                 if (t < 0) t += d.syn_R2;
                 w = ((flagged[s * wpb + pw] >> pb) & 1ull) ? syn_mask_load(d, t, g, r) : ~0ull;
-                // (in the queue of delay D while a < D)
-                if (a0 == 64 * r) w &= lane < 63 ? ~0ull << (lane + 1) : 0ull;
+                if (gone > 0) w &= ~0ull << gone;
               }
-#pragma unroll 4
-              for (int j = 0; j < 64; ++j) {
-                const int c = __popcll(__ballot((w >> j) & 1ull));
-                if (lane == j) mine += c;
+#pragma unroll 1
+              for (unsigned long long m = __ballot(w != 0ull); m; m &= m - 1) {
+                const int j = __ffsll((long long)m) - 1;
+                const unsigned lo32 = lane_get((unsigned)w, j), hi32 = lane_get((unsigned)(w >> 32), j);
+                mine += (int)(((lane < 32 ? lo32 : hi32) >> (lane & 31)) & 1u);
               }
             }
             const unsigned long long in = __ballot(mine < d.C && 64 * r + lane < d.d_max);
@@ -435,14 +496,16 @@ __global__ __launch_bounds__(kResLaunch) void k_syn_run(long long n0, int nsteps
     if (d.d_max > kFront) {
       const bool due = DEEP && npB >= 0;
       if (due) add_entries(npB, after, slot + 2);
-      else
-        syn_walk<NPT>(d, L, wpb, kFront + 1, slot + 2, -1, [&](int np) {
-          for (int t0 = 0; t0 < np; t0 += kSynAhead * per) {
-            request_rows(t0, np, slot + 2, slot2 + 2);
-            request_entries(np - t0, slot + 2, slot2 + 2);
-            add_entries(np - t0, after, slot + 2);
-          }
+      else {
+        int kept = 0;
+        syn_walk<NPT>(d, L, wpb, kFront + 1, slot + 2, -1, [&](int np, bool last) {
+          if (FIFO) np = kept = sift(kept, np, slot + 2, slot2 + 2);
+          if (FIFO && !last && np <= kSynList - 64) return np;
+          take_all(np, after, slot + 2, slot2 + 2);
+          kept = 0;
+          return 0;
         });
+      }
       if (DEEP) {
         // (what was under way for the next step is requested anew where the registers were needed)
 #pragma unroll 1

@@ -275,3 +275,25 @@ def test_syn_resident_full_tape_then_steps(kind, cap, spikes, events, monkeypatc
     used = 64 + min(events, int(ref.counters()["enqueued"]))
     if kind != adseq.SYN_BINS or events > 18000:   # (see the test before)
         np.testing.assert_array_equal(got[1][64:used], got[0][64:used])
+
+
+@pytest.mark.parametrize("cap", [1, 2, 4, 8])
+@pytest.mark.parametrize("n,b,T,d_max,fan,rate,blocks", [
+    (130, 1, 420, 300, 30, 9900.0, ""),      # 300 held spikes per source: more than a list has room for
+    (200, 2, 300, 250, 40, 6000.0, ""), (70, 1, 560, 512, 300, 2500.0, ""), (2500, 1, 150, 140, 20, 6000.0, "8")])
+def test_syn_resident_many_spikes(n, b, T, d_max, fan, rate, blocks, cap, monkeypatch):
+    """FIFO queues that refuse most of what comes: masks made of many held spikes, more pieces than one look at the rows takes."""
+    if blocks:
+        monkeypatch.setenv("ADSEQ_SYN_BLOCKS", blocks)
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=0.1 / fan, w_std=0.1 / fan, continuous=d_max > 255)
+    wl.ext_weight = 1.1
+    ref = oracle.Run(wl, adseq.SYN_FIFO, cap, n_steps=T, batch=b, n_threads=8)
+    rc = ref.counters()
+    assert rc["dropped"] > rc["enqueued"] // 2
+    sim = _run(wl, adseq.SYN_FIFO, cap, T, b, [T // 3, T - T // 3], tape_spike_capacity=T * b * n, tape_event_capacity=T * b * wl.n_synapses)
+    c = sim.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    assert c["error_bits"] & ~64 == 0
+    np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    sim.close()
