@@ -57,6 +57,21 @@ def test_ring_trial(n, b, T, d_max, fan, rate, gain, tau_syn, tau_rise, continuo
         sim.close()
 
 
+@pytest.mark.parametrize("n,b", [(100, 16), (250, 8), (1000, 1)])
+@pytest.mark.parametrize("record", [True, False])
+def test_ring_trial_is_what_runs(n, b, record, monkeypatch):
+    """Every block size is reached: with one poll per wait the other forward kernels' waits run out, and a workgroup per trial has none;
+    calls shorter than 64 steps go by the others."""
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    wl = synth.ragged_network(n, 40, 20, seed=4, rate_hz=400.0, t=64, b=b, w_mean=0.01, w_std=0.01)
+    for trials, steps in (("1", 64), ("0", 64), ("1", 63)):
+        monkeypatch.setenv("ADSEQ_RING_TRIALS", trials)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=record, max_steps=64)
+        sim.run(0, steps)
+        assert (sim.counters()["error_bits"] & 32 == 0) == (trials == "1" and steps == 64)
+        sim.close()
+
+
 @pytest.mark.parametrize("T", [96, 107, 150])
 def test_ring_trial_then_queue_entry_points(T, monkeypatch):
     """What is in flight after a run is delivered step by step as after the other kernels, at a window's first step and inside one, and

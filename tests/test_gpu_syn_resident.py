@@ -32,7 +32,8 @@ def _run(wl, kind, cap, T, b, pieces, **kw):
     (701, 3, 80, 40, 200, 900.0, 0.6, 0.0, 0.0, False, ""), (100, 1, 60, 1, 60, 900.0, 0.6, 0.0, 0.0, False, ""),
     (63, 1, 300, 130, 40, 900.0, 1.5, 0.0, 0.0, False, ""), (200, 2, 270, 64, 30, 2500.0, 0.5, 0.0, 0.0, False, ""),
     (1501, 4, 50, 30, 150, 900.0, 0.6, 5.0, 0.0, True, "8"), (4100, 4, 40, 20, 40, 900.0, 0.6, 5.0, 1.0, False, "16"),
-    (1100, 8, 24, 8, 2500, 1500.0, 0.6, 0.0, 0.0, False, "8")])
+    (1100, 8, 24, 8, 2500, 1500.0, 0.6, 0.0, 0.0, False, "8"), (300, 2, 60, 2, 40, 2500.0, 0.6, 0.0, 0.0, False, ""),
+    (300, 2, 60, 3, 40, 2500.0, 0.03, 5.0, 1.0, False, ""), (300, 2, 60, 4, 40, 2500.0, 0.6, 0.0, 0.0, False, "")])
 def test_syn_resident(kind, cap, n, b, T, d_max, fan, rate, gain, tau_syn, tau_rise, continuous, blocks, monkeypatch):
     if blocks:   # (few blocks: four neurons per thread)
         monkeypatch.setenv("ADSEQ_SYN_BLOCKS", blocks)
@@ -124,10 +125,56 @@ def test_syn_resident_past_the_tape_and_wait_that_runs_out(monkeypatch):
     sim = adseq.Adseq(wl, adseq.SYN_FIFO, 2, record_tape=True, max_steps=60)
     sim.run(0, 60)
     torch.cuda.synchronize()
-    if sim.counters()["error_bits"] & 32:
-        with pytest.raises(adseq.AdseqError):
-            sim.drop_count()
+    assert sim.counters()["error_bits"] & 32
+    with pytest.raises(adseq.AdseqError):
+        sim.drop_count()
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 2), (adseq.SYN_FIFO, 3), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 3)])
+@pytest.mark.parametrize("n,blocks", [(3000, ""), (6000, "8")])
+def test_syn_resident_is_what_runs(kind, cap, n, blocks, monkeypatch):
+    """Every instance -- one and four neurons per thread, a front of one step and of three -- is reached: with one poll per wait its
+    waits run out, and three launches per step have none."""
+    if blocks:
+        monkeypatch.setenv("ADSEQ_SYN_BLOCKS", blocks)
+    monkeypatch.setenv("ADSEQ_RING_RESIDENT_SPINS", "1")
+    wl = synth.ragged_network(n, 40, 20, seed=4, rate_hz=400.0, t=60, b=1, w_mean=0.01, w_std=0.01)
+    for resident in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = _run(wl, kind, cap, 60, 1, [60])
+        assert (sim.counters()["error_bits"] & 32 != 0) == (resident == "1")
+        sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.SYN_FIFO, 1), (adseq.SYN_FIFO, 4), (adseq.SYN_LATEST, 1), (adseq.SYN_BINS, 3)])
+@pytest.mark.parametrize("pieces", [[90], [60, 30]])
+def test_syn_resident_enqueue_after_run(kind, cap, pieces, monkeypatch):
+    """Spikes listed for the run's last step, straight after the run, are admitted, counted and delivered as after launches per step."""
+    T, b, n = sum(pieces), 2, 120
+    wl = synth.ragged_network(n, 40, 60, seed=9, rate_hz=900.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    # (neurons that did not spike themselves in that step)
+    spiked = oracle.Run(wl, kind, cap, n_steps=T, batch=b).spikes[T - 1].reshape(-1)
+    listed = np.array([g for g in range(0, b * n, 3) if not spiked[g]], np.int32)
+    got = []
+    for resident in ("1", "0"):
+        monkeypatch.setenv("ADSEQ_SYN_RESIDENT", resident)
+        sim = _run(wl, kind, cap, T, b, pieces)
+        before = sim.counters()
+        sim.enqueue(T - 1, torch.from_numpy(listed).to(sim.dev), torch.tensor([len(listed)], dtype=torch.int32, device=sim.dev))
+        seen = [before, sim.counters()]
+        cur = torch.zeros((62, b * n), device=sim.dev)
+        for j in range(62):
+            sim.deliver(T + j, cur[j])
+        seen.append(sim.counters())
+        got.append((cur.cpu().numpy(), seen))
+        sim.close()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    assert got[1][1][1]["enqueued"] > got[1][1][0]["enqueued"]
+    assert got[1][1][2]["delivered"] == got[1][1][2]["enqueued"] - got[1][1][2]["dropped"]
+    for one, many in zip(got[0][1], got[1][1]):
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert one[key] == many[key], key
 
 
 def _capture(*calls):
