@@ -1437,12 +1437,13 @@ void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_step
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
     if (d.record && n >= d.max_steps) h->tape_ok = false;
     if (record) fill_u32(st, d.tape_bits + (size_t)n * d.words, 0u, (size_t)cnt * d.words * 2);
-    const int threads = trial_threads(d.N);
+    const bool long_rows = trial_long(d.N, d.S);
+    const int threads = trial_threads(d.N, long_rows);
     const dim3 grid((unsigned)d.B), block((unsigned)threads);
     const long long boundary = (n + cnt - 1) & ~(long long)(d.W - 1), fold = boundary >= n && boundary > 0 ? boundary : h->fold_upto;
     const int windows = (int)(((n + cnt - 1) >> d.wshift) - (n >> d.wshift)) + 1;
     const unsigned arrivals = (unsigned)(cnt - windows) * (unsigned)waiting;
-    hipLaunchKernelGGL(threads <= 256 ? k_trial_run<256> : k_trial_run<1024>, grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0,
+    hipLaunchKernelGGL((long_rows ? k_trial_run<1024, true> : (threads <= 256 ? k_trial_run<256, false> : k_trial_run<1024, false>)), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0,
                        h->fold_upto, fold, arrivals, arrive_bar, d);
     (arrive_bar ? h->bar_base : h->rev_base) += arrivals;
     h->fold_upto = fold;

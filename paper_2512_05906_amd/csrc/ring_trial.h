@@ -6,7 +6,8 @@
 // the L2, the adds' acknowledgement, and the window's expansion besides.  The front of every row is in LDS too, as far as there
 // is room; what is behind it is one trip to the L2.  A step is bound by the instructions of the one compute unit (drive hash, update)
 // and by its LDS.  Measured, us per forward step, by launches per window / so: 100 neurons x 10 synapses 2.3 / 0.43; 3 trials x 212 x 253
-// 3.4 / 0.48; 756 x 95 2.2 / 0.63; 4 x 200 x 1,000 with 3 spikes per step 3.5 / 1.3, with 142 18.7 / 13.3; 100 x 10 with 62 8.5 / 6.6.
+// 3.4 / 0.48; 756 x 95 2.2 / 0.63; 100 x 10 with 50 spikes per step 9.1 / 5.4.  Faster at all of 0.2 to 50 % of the neurons firing, 10 to 1,000 synapses
+// per neuron, 100 to 1,000 neurons, 1 to 512 trials (see trial_long).
 // (An earlier form kept a window of eight rows in LDS and added the entries of all held spikes two steps ahead, as k_syn_run does; it
 // took 16 x 1,000 neurons, d_max 50, from 2.0 to 1.7 us per step, but with 500 spikes per step and trial from 21 to 71.)
 //
@@ -16,8 +17,15 @@
 
 constexpr int kTrialNeurons = 1024;
 constexpr int kTrialMost = 512;                  // trials: a workgroup fills a compute unit's LDS, so that 256 run at a time, two rounds of 0.5 us per step
+// Long rows: a step with many spikes is a chain of trips to the L2 for every wavefront, so there sixteen share them, and each requests a row's
+// next piece before it adds the last one.  One trial, us per step at 0.2, 2, 10, 30 and 50 % of the neurons firing, by launches per window / short
+// rows' way / long rows': 250 x 1,000, d_max 50: 3.1 10.6 24 41 54 / 1.1 4.7 17 54 86 / 1.1 2.2 4.3 11 17; 1,000 x 262, d_max 30: 3.7 8.6 21 46 70 /
+// 1.5 3.1 12 35 58 / 1.3 2.5 7.9 22 36; 250 x 130: 1.9 3.0 6.7 10 13.6 / 0.68 1.4 3.9 10 16 / 0.74 1.2 2.0 3.9 5.8; 100 x 262: 2.2 4.4 11 15 20 /
+// 0.53 1.2 3.4 9.1 15 / 0.62 1.05 1.5 2.3 3.1.  The line: where the short rows' way could be slower than launches (100 x 1,000 and 250 x 130 at half the
+// neurons firing, 4 trials of 1,000 x 260 at 30 %), and no lower, since it is up to a sixth faster while little spikes.
+constexpr bool trial_long(int N, long long synapses) { return synapses > (N <= 128 ? 512 : (N <= 256 ? 128 : 256)) * (long long)N; }
 // (what every wavefront does costs the compute unit as often as there are wavefronts)
-constexpr int trial_threads(int N) { return N <= 128 ? 128 : (N <= 256 ? 256 : 1024); }
+constexpr int trial_threads(int N, bool long_rows) { return long_rows ? 1024 : (N <= 128 ? 128 : (N <= 256 ? 256 : 1024)); }
 constexpr int kTrialLdsWords = 18432;            // 8-byte words of LDS for cells, spike words and fronts
 constexpr long long kTrialSynapses = 262144;     // synapses of a trial at most: 2 MB of rows, which the L2 holds
 constexpr long long kTrialSteps = 64;            // steps of a call at least: a launch takes in the fronts and rebuilds the cells (100 neurons, in
@@ -27,21 +35,22 @@ template <int kMost>
 struct TrialLds {
   alignas(16) unsigned long long words[kTrialLdsWords];   // spikes [R][wpb]; fronts [near][N]; cells [R][N] by step mod R
   unsigned short spk[kMost];                            // the step's spikes
+  int row[kMost + 1];                                   // LONG: where the rows begin
   int n_spk[2];                                         // spikes of the step, by step parity
 };
 
-// Steps n0 .. n0 + nsteps - 1 of trial blockIdx.x; N <= blockDim.x <= kMost, thread t owns neuron t.  near: entries of a row's
+// Steps n0 .. n0 + nsteps - 1 of trial blockIdx.x; N <= blockDim.x <= kMost, thread t owns neuron t.  LONG: see trial_long.  near: entries of a row's
 // front in LDS.  record: the tape is written; its spike words of these steps are zero when the launch begins.
 // Spikes of steps [fold_lo, fold_hi) and the events they emit are counted: fold_lo <= n0, fold_hi the last window boundary of these
 // steps (fold_lo if there is none), as where the other kernels stop counting, so that what is listed on top of the last step is still
 // counted later.  Both n0 - fold_lo and n0 + nsteps - fold_hi are at most W < R.
 // arrivals: what the barriers of these steps would have added to the arrival counter that the host counts along with (arrive_bar: that
 // of the kernels over one XCD).
-template <int kMost>
+template <int kMost, bool LONG>
 __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, long long fold_lo, long long fold_hi,
                                                      unsigned arrivals, int arrive_bar, Dev d) {
   __shared__ TrialLds<kMost> L;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int threads = (int)blockDim.x, waves = threads >> 6;
   const int N = d.N, wpb = (N + 63) >> 6, R = d.R;
   const int base = (int)blockIdx.x * N, g = base + tid;
@@ -66,6 +75,7 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
   for (int x = tid; x < R * wpb; x += threads) L.words[x] = held(place(x));
   for (int x = tid; x < R * N; x += threads) cells[x] = 0;
   if (tid < 2) L.n_spk[tid] = 0;
+  if (LONG) for (int x = tid; x <= N; x += threads) L.row[x] = (int)d.row_ptr[x];
   float V = 0.0f, J = 0.0f, Jf = 0.0f;
   unsigned long long zg = 0ull;
   int count = 0;
@@ -150,25 +160,74 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
       }
     }
     __syncthreads();   // spikes known, cells of the step taken
-    const int nspk = L.n_spk[par];
+    const int nspk = __builtin_amdgcn_readfirstlane(L.n_spk[par]);
     if (tid == 0) L.n_spk[par ^ 1] = 0;   // (the last step's has been read)
     auto add = [&](const uint2& e) {
       int row = slot + (int)(e.x & d.dmask);
       if (row >= R) row -= R;
       atomicAdd(&cells[row * N + (int)(e.x >> d.dbits)], (int)e.y);
     };
-    for (int x = wave; x < nspk; x += waves) {
-      const int i = L.spk[x];   // (the same in every lane)
-      const int r0 = (int)d.row_ptr[i], len = (int)d.row_ptr[i + 1] - r0;
-      if (lane < near && lane < len) add(fronts[lane * N + i]);
-      for (int q0 = near + lane; q0 < len; q0 += 256) {   // what is behind the front: four loads under way
-        uint2 e[4];
+    if (LONG && wave < nspk) {   // uniform
+      // the rows of every waves-th spike, 64 at most: lane j has the j-th one's neuron and row
+      int own = 0, first = 0, length = 0;
+      if (wave + lane * waves < nspk) { own = L.spk[wave + lane * waves]; first = L.row[own]; length = L.row[own + 1] - first; }
+      // What is behind the front, 256 entries at a time: a piece is requested before the one ahead of it is added.  (A request is four
+      // loads whatever is left of the row, so that it can be counted what is waited for.)
+      int x = wave, j = 0, r0 = lane_get(first, 0), len = lane_get(length, 0), q0 = near;
+      auto request = [&](uint2 (&e)[4], int& left) {
+        while (x < nspk && q0 >= len) {
+          x += waves; ++j;
+          if (x < nspk) { r0 = lane_get(first, j); len = lane_get(length, j); q0 = near; }
+        }
+        const int here = x < nspk ? len - q0 : 0;
+        const __amdgpu_buffer_rsrc_t piece = res_rows(d.synf + r0 + q0, here * 8);
+        left = here - lane;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { e[u] = make_uint2(0u, 0u); if (q0 + 64 * u < len) e[u] = load_stream(&d.synf[r0 + q0 + 64 * u]); }
+        for (int u = 0; u < 4; ++u) {
+          const unsigned long long v = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(piece, lane * 8 + 512 * u, 0, 0));
+          e[u] = make_uint2((unsigned)v, (unsigned)(v >> 32));
+        }
+        q0 += 256;
+        return here > 0;
+      };
+      auto put = [&](const uint2 (&e)[4], int left) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) if (q0 + 64 * u < len) add(e[u]);
+        for (int u = 0; u < 4; ++u) if (64 * u < left) add(e[u]);
+      };
+      auto add_fronts = [&]() {
+        for (int y = wave, f = 0; y < nspk; y += waves, ++f)
+          if (lane < near && lane < lane_get(length, f)) add(fronts[lane * N + lane_get(own, f)]);
+      };
+      if (__ballot(length > near) == 0ull) {
+        add_fronts();
+      } else {
+        uint2 ea[4], eb[4];
+        int la = 0, lb = 0;
+        bool more = request(ea, la);
+        add_fronts();
+        while (more) {
+          more = request(eb, lb);
+          put(ea, la);
+          if (!more) break;
+          more = request(ea, la);
+          put(eb, lb);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // (vmcnt(0): else it is waited for, and the tape's store with it, before every use of the registers)
       }
     }
+    if (!LONG)
+      for (int x = wave; x < nspk; x += waves) {
+        const int i = L.spk[x];   // (the same in every lane)
+        const int r0 = (int)d.row_ptr[i], len = (int)d.row_ptr[i + 1] - r0;
+        if (lane < near && lane < len) add(fronts[lane * N + i]);
+        for (int q0 = near + lane; q0 < len; q0 += 256) {   // what is behind the front: four loads under way
+          uint2 e[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { e[u] = make_uint2(0u, 0u); if (q0 + 64 * u < len) e[u] = load_stream(&d.synf[r0 + q0 + 64 * u]); }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) if (q0 + 64 * u < len) add(e[u]);
+        }
+      }
     if (record && act) __builtin_nontemporal_store(U, &d.tapeU[(size_t)n * d.BN + g]);
     if (++slot == R) slot = 0;
   }

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
     (63, 1, 300, 130, 40, 900.0, 1.0, 0.0, 0.0, False), (100, 3, 130, 1, 60, 900.0, 0.6, 0.0, 0.0, False),
     (1000, 3, 160, 30, 100, 400.0, 0.6, 0.0, 0.0, False), (903, 2, 130, 35, 90, 400.0, 0.6, 5.0, 0.0, True),
     (1024, 2, 100, 31, 50, 400.0, 0.6, 5.0, 1.0, False), (150, 2, 90, 5, 1500, 900.0, 0.6, 0.0, 0.0, False),
-    (200, 7, 140, 3, 30, 2500.0, 1.5, 0.0, 0.0, False)])
+    (200, 7, 140, 3, 30, 2500.0, 1.5, 0.0, 0.0, False), (1000, 2, 80, 20, 524, 2500.0, 0.3, 0.0, 0.0, False),
+    (256, 3, 90, 40, 1300, 3000.0, 0.3, 5.0, 0.0, True), (100, 2, 90, 60, 1300, 3000.0, 0.3, 0.0, 0.0, False)])
 def test_ring_trial(n, b, T, d_max, fan, rate, gain, tau_syn, tau_rise, continuous, monkeypatch):
     wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=gain / fan, w_std=gain / fan, continuous=continuous)
     wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
