@@ -57,9 +57,15 @@
  *                 event is dropped (and counted) when its own synapse already holds
  *                 `capacity` undelivered events.  All events of a synapse share one
  *                 delay, so arrival order is emission order and an ordered queue
- *                 ("SortedArray") behaves the same.  Every queue is looked at in every
- *                 step (the cost the per-target kinds avoid); state: 2 capacity + 4
- *                 bytes per synapse and trial.
+ *                 ("SortedArray") behaves the same.  State: 2 capacity + 4 bytes per
+ *                 synapse and trial.  Single steps, capture, runs without a tape and
+ *                 handles out of the range below look at every queue in every step (the
+ *                 cost the per-target kinds avoid).  With a tape, for up to 2^19 B*N and
+ *                 (this kind) d_max 512, adseq_run looks at none; the workspace then holds 8 bytes per
+ *                 synapse more, and with this kind (d_max + 129) * B*N * ceil(d_max / 64) * 8
+ *                 bytes of admission masks (where that is beyond 2 GB, neither).  The
+ *                 environment variable ADSEQ_SYN_RESIDENT=0, read at adseq_workspace_bytes
+ *                 and adseq_create, declines both.
  *   ADSEQ_SYN_LATEST one slot per synapse and trial in which a new spike always takes the place
  *                 of the one held ("SingleSpike(Drop)"): the event that was held is lost --
  *                 counted as dropped, never delivered, its admission flag on the tape
@@ -229,7 +235,8 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries, and
  * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (of at most 2^20 targets, where half the overflow list has
  * room for every synapse of every trial, and kernels are not being timed: adseq_profile), and the per-synapse
- * kinds up to 128 steps (calls of three steps or more while every step since the reset has been recorded by such calls), in ONE kernel
+ * kinds up to 128 steps (calls of three steps or more while every step since the reset has been recorded by such calls: one
+ * shorter call or single step, and the steps to the next reset go by three launches each), in ONE kernel
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
  * launch needs the device free enough for all its blocks to run at the same time.  Calls that
  * make such launches (adseq_backward too) wait, on their stream, for the last such call of the

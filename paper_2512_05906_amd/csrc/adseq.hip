@@ -2250,7 +2250,8 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
     int64_t ahead = 0;
     {
       // (per-synapse queues: as far as the tape goes.  One or two steps are sooner done by three launches each -- 10,000 x 1,000 synapses, us
-      // per step in calls of 1 / 2 / 3 / 16 steps: 23.5 / 14.7 / 10.3 / 4.1, by launches 14 --, but then so are all steps to the next reset)
+      // per step in calls of 1 / 2 / 3 / 16 steps: 23.5 / 14.7 / 10.3 / 4.1, by launches 14; 100 x 10 in calls of 3 / 16: 7.6 / 3.6, by launches 14 --, but
+      // then so are all steps to the next reset)
       const int64_t recorded = h->syn_ok && n_steps >= 3 && h->tape_ok && step0 < h->dev.max_steps ? (n_steps < h->dev.max_steps - step0 ? n_steps : h->dev.max_steps - step0) : 0;
       WholeChipCall turn(h, (hipStream_t)stream, ((h->q_P > 0 && n_steps >= 4) || recorded > 0) && !h->prof);
       if (turn.on && h->q_P > 0) {
