@@ -110,9 +110,16 @@ def _copy_out(ptr: int, nbytes: int, dev) -> torch.Tensor:
     return torch.as_tensor(_RawDeviceBytes(ptr, nbytes), device=dev)
 
 
+# (functions that torch does not promise to keep: None where it has not got them)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
     # (the raw handle, without the Stream object around it: 1 us of the 8 that a one-step call takes)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def _dptr(t: Optional[torch.Tensor]):

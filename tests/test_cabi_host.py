@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2512_05906_amd import adseq
 
@@ -98,3 +99,11 @@ def test_null_handle_is_an_error_not_a_crash():
     assert lib.adseq_profile(None, 1) == -1
     assert lib.adseq_profile_read(None, None, None, None) == -1
     assert lib.adseq_last_error(None) == b"null handle"
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_stream_handle_without_the_private_functions(missing, monkeypatch):
+    """The current stream's handle comes the public way where torch has not got the short one."""
+    monkeypatch.setattr(adseq, missing, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 4711}))
+    assert adseq._stream() == 4711
