@@ -1197,7 +1197,7 @@ void launch_neurons(adseq* h, hipStream_t st, long long n, int parity, const flo
 void launch_fanout(adseq* h, hipStream_t st, long long n, const int* spk, const int* n_spk, int parity, int record) {
   const Dev& d = h->dev;
   const dim3 block(kBlock);
-  if (per_synapse_kind(d.kind)) syn_leave(h, st);
+  if (spk && per_synapse_kind(d.kind)) syn_leave(h, st);   // (without a list the step's launch_neurons has done so)
   if (!spk) {
     const dim3 grid((unsigned)d.nblk * d.fsplit);
     if (d.kind == ADSEQ_FIFO) hipLaunchKernelGGL((k_fanout_step<ADSEQ_FIFO>), grid, block, 0, st, d, n, parity, record);
