@@ -81,6 +81,16 @@ struct BlkCtr {
 struct ExpCoef { double c[21]; };
 struct RowSpan { long long r0, r1; };
 
+// RING, crowded windows (ring_pull.h): an argument of its own for the few kernels that take it (56 bytes more in Dev cost every launch 0.1 us).
+struct Pull {
+  int parts, pt, lb;        // parts (0: not used), targets of a part, bits of a target's place in its part
+  int K, Q, hmask;          // shares of the offsets; windows that a delay reaches back; hist holds hmask + 1 windows
+  int near;                 // entries of a part that k_fwd_chip has room for in LDS, whose parts these are then (0: far events only)
+  uint2* list;              // [S] by part, then by arrival offset
+  unsigned* pos;            // [parts][d_max + 2]: first entry with that offset, and the end
+  unsigned* hist;           // [hmask + 1][BN] a neuron's spikes of a window, a bit per step
+};
+
 struct Dev {
   int N, B, BN, R, C, kind, dbits, d_max;
   unsigned dmask;
@@ -174,7 +184,7 @@ struct Dev {
   float* bwd_G;         // FIFO/SORTED: [fsplit][BN] partial queue terms of the spikes of the step being swept
   Counters* ctr;
   BlkCtr* blk;   // FIFO / SORTED: [nblk + kFanoutBlocks]
-  int dense_rows, dense_G, dense_K; // RING, dense windows: rows of a tile, row groups, shares of the spikes (0: never)
+  int dense_rows, dense_G, dense_K; // RING, dense windows: rows of a tile, row groups, shares of the spikes (0: never; -1: by ring_pull.h only)
   // (what was added later stays behind what the per-step kernels read, whose place in the argument block is tuned)
   int sorted_rev;       // bounded kinds with tape: the reverse sweep runs on rows sorted by arrival offset (the ring's kernels)
   unsigned* adm_base;   // bounded kinds: [T][words] first word in adm_bits of the spikes of a (step, spike word)
@@ -558,6 +568,9 @@ struct adseq {
   unsigned chain_turn = 0;       // chained launches so far: the parity picks the stream
   int chain_tpb = 256;           // threads per block of the chained launches (256 or 1024)
   bool range_warn = false;    // some target's incoming |amplitudes| add up to 128 or more (ERR_RANGE, reported with the counters)
+  Pull pull = {};             // RING: ring_pull.h
+  long long pull_at = 0;      // RING: from how many spikes in a window's history on the next is pulled (ring_pull.h)
+  long long hist_from = 0, hist_upto = 0;   // RING: steps whose window words (Pull::hist) are in place
   bool in_static = false;     // the handle is the device's static one (adseq_create_static): never deleted
 };
 
@@ -566,12 +579,13 @@ namespace {
 struct Layout {
   size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
-      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk,
+      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk, pull, pull_pos, pull_hist,
       total;
   long long spike_cap, event_cap, pool_cap;
   int R, dbits, nblk, words;
   int W, wshift, tp_shift, P, NB, cap, wgroups;  // RING
   int near_ev_cap;
+  int pull_parts, pull_pt, pull_lb, pull_hist_windows;   // RING: ring_pull.h (0: not used)
   int qsteps;           // FIFO / SORTED: contender buffers
   int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
@@ -579,6 +593,7 @@ struct Layout {
 
 // A power of two in [lo, hi] from the environment, else the default (tuning knobs of the ring:
 // results do not depend on them).
+int bit_width(unsigned v) { int b = 0; while (v) { ++b; v >>= 1; } return b; }
 int env_pow2(const char* name, int dflt, int lo, int hi) {
   if (const char* e = getenv(name)) {
     const int v = atoi(e);
@@ -712,6 +727,24 @@ int trial_near(const adseq_config* c) {
   const long long near = (kTrialLdsWords - words) / c->n_neurons;
   return (int)(near < kSynNear ? near : kSynNear);
 }
+// Crowded windows pulled by the targets (ring_pull.h): every list entry is looked at once per window and trial, whatever spikes, hence
+// B S up to 2^25 (10,000 x 1,000: 2^23); a pair of window words per source and a part's tile have to fit LDS; below 2^21 synapses no
+// window is crowded enough for the lists' 8 bytes a synapse.  One trial: the parts are the blocks of k_fwd_chip.
+struct PullPlan { int parts = 0, pt = 0, lb = 0; };
+PullPlan pull_plan(const adseq_config* c, int W, int dbits) {
+  PullPlan r;
+  const long long N = c->n_neurons, S = c->n_synapses, B = c->batch;
+  if (env_pow2("ADSEQ_RING_DENSE", 1, 0, 2) == 0 || env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1) || trial_near(c) >= 0) return r;
+  if (B * S > (1LL << 25) || (S < (1LL << 21) && env_pow2("ADSEQ_RING_DENSE", 1, 0, 2) < 2) || W > 32) return r;
+  const ResidentPlan fp = reverse_plan(N * B, true, S / N);
+  if (fp.P == 0 || fp.chunk > kResThreads) return r;   // (the window words are made by k_fwd_chip with one neuron per thread)
+  const long long blocks = B < 256 ? 256 / B : 1;
+  const int pt = B == 1 ? fp.chunk : (int)((N + blocks - 1) / blocks < 32 ? 32 : (N + blocks - 1) / blocks);
+  const int lb = bit_width((unsigned)(pt - 1));
+  if (bit_width((unsigned)(N - 1)) + dbits + lb > 32 || N * 8 + (long long)W * pt * 4 > kDenseCells * 4) return r;
+  r.pt = pt; r.lb = lb; r.parts = (int)((N + pt - 1) / pt);
+  return r;
+}
 // k_syn_run: up to 256 x 2,048 neurons whose spike words of the last R steps fit LDS.  Blocks as for the ring's forward kernel: where
 // the rows are long multiples of 64 neurons, so that more blocks share the events; so too for a FIFO whose rows hold less than one entry
 // per delay, where a step's work is looking at what the sources hold (4,000 x 100, d_max 250, 63 blocks instead of 16: 3.8 instead of 4.4 us per
@@ -782,17 +815,17 @@ FlowKernel flow_kernel_adm(bool du, int syn, int surrogate, int chunk) {
 FlowKernel flow_kernel(bool adm, bool du, int syn, int surrogate, int chunk) {
   return adm ? flow_kernel_adm<true>(du, syn, surrogate, chunk) : flow_kernel_adm<false>(du, syn, surrogate, chunk);
 }
-typedef void (*ChipKernel)(long long, int, unsigned, int, int, int, float, Dev);
+typedef void (*ChipKernel)(long long, int, unsigned, int, int, int, float, Dev, Pull);
 template <bool RECORD, int SYN>
-ChipKernel chip_kernel_of(int chunk) {
-  if (chunk <= kResThreads) return k_fwd_chip<RECORD, 1, SYN>;
-  if (chunk <= 4 * kResThreads) return k_fwd_chip<RECORD, 4, SYN>;
-  return k_fwd_chip<RECORD, 8, SYN>;
+ChipKernel chip_kernel_of(int chunk, bool pull) {
+  if (chunk <= kResThreads) return pull ? k_fwd_chip<RECORD, 1, SYN, true> : k_fwd_chip<RECORD, 1, SYN, false>;
+  if (chunk <= 4 * kResThreads) return k_fwd_chip<RECORD, 4, SYN, false>;
+  return k_fwd_chip<RECORD, 8, SYN, false>;
 }
-ChipKernel chip_kernel(bool record, int syn, int chunk) {
-  if (syn == 2) return record ? chip_kernel_of<true, 2>(chunk) : chip_kernel_of<false, 2>(chunk);
-  if (syn == 1) return record ? chip_kernel_of<true, 1>(chunk) : chip_kernel_of<false, 1>(chunk);
-  return record ? chip_kernel_of<true, 0>(chunk) : chip_kernel_of<false, 0>(chunk);
+ChipKernel chip_kernel(bool record, int syn, int chunk, bool pull) {
+  if (syn == 2) return record ? chip_kernel_of<true, 2>(chunk, pull) : chip_kernel_of<false, 2>(chunk, pull);
+  if (syn == 1) return record ? chip_kernel_of<true, 1>(chunk, pull) : chip_kernel_of<false, 1>(chunk, pull);
+  return record ? chip_kernel_of<true, 0>(chunk, pull) : chip_kernel_of<false, 0>(chunk, pull);
 }
 const void* run_xcd_kernel(bool record, int syn, int npt) {
   return record ? run_xcd_kernel_of<true>(syn, npt) : run_xcd_kernel_of<false>(syn, npt);
@@ -805,8 +838,6 @@ size_t fan_slots(int nblk) {
   const size_t a = (size_t)nblk * kFanSplitMax;
   return a > (size_t)kFanoutBlocks ? a : (size_t)kFanoutBlocks;
 }
-
-int bit_width(unsigned v) { int b = 0; while (v) { ++b; v >>= 1; } return b; }
 
 bool host_validate(const adseq_config* c) {
   if (!c) return false;
@@ -1030,6 +1061,15 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
     L->near_spk = take(byw ? (size_t)L->W * kNearSpikeCap * 4 : 0);
     L->near_counts = take(byw ? 2 * T * 4 : 0);
   }
+  {
+    const PullPlan pp = bounded || small ? PullPlan() : pull_plan(c, L->W, L->dbits);
+    L->pull_parts = pp.parts; L->pull_pt = pp.pt; L->pull_lb = pp.lb;
+    L->pull_hist_windows = 1;
+    while (pp.parts > 0 && L->pull_hist_windows < (c->d_max_steps + L->W - 1) / L->W + 2) L->pull_hist_windows <<= 1;
+    L->pull = take(pp.parts > 0 ? S * 8 : 0);
+    L->pull_pos = take(pp.parts > 0 ? (2 * (size_t)pp.parts * (c->d_max_steps + 2) + 1) * 4 : 0);   // (behind the positions the cursors of their making)
+    L->pull_hist = take(pp.parts > 0 ? (size_t)L->pull_hist_windows * BN * 4 : 0);
+  }
   L->total = o;
   return true;
 }
@@ -1094,6 +1134,7 @@ void launch_reset(adseq* h, hipStream_t st) {
   h->rev_base = 0;   // (likewise)
   h->chain_arrivals = 0;   // (likewise)
   h->drive_from = h->drive_upto = 0;
+  h->hist_from = h->hist_upto = 0;
   const size_t BN = (size_t)d.BN;
   fill_u32(st, d.ctr, 0u, sizeof(Counters) / 4);
   fill_u32(st, d.V, 0u, BN);
@@ -1247,11 +1288,14 @@ void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, lo
   // staging mode: 0 none (atomics), 1 one store per event, 2 ordered by part in LDS first
   static const int sort_stage = env_pow2("ADSEQ_RING_SORTSTAGE", 1, 0, 1);
   const int stage = d.cap > 0 ? ((sort_stage && d.P <= kSortParts) ? 2 : 1) : 0;
-  hipLaunchKernelGGL(k_win_bin, dim3((unsigned)d.NB), dim3(kRingThreads), 0, st, d, k0, n_lo, n_hi, 0, d.NB,
-                     stage, count_from, h->res_P > 0 ? 1 : 0);
+  // (the window words of all the steps that the window's events may come from are there)
+  const long long oldest = k0 - (long long)h->pull.Q * d.W > 0 ? k0 - (long long)h->pull.Q * d.W : 0;
+  const int pull = h->pull.parts > 0 && n_hi == k0 && h->hist_upto == k0 && h->hist_from <= oldest && count_from >= k0 - d.W ? 1 : 0;
+  hipLaunchKernelGGL((pull ? k_win_bin<true> : k_win_bin<false>), dim3((unsigned)d.NB), dim3(kRingThreads), 0, st, d, k0, n_lo, n_hi, 0, d.NB,
+                     stage, count_from, h->res_P > 0 ? 1 : 0, h->pull);
   if (d.cap > 0) {
     const int parts = d.P < kMaxParts ? d.P : kMaxParts;
-    hipLaunchKernelGGL(k_win_acc, dim3((unsigned)parts), dim3(kRingThreads), 0, st, d, k0, 0, clear);
+    hipLaunchKernelGGL(k_win_acc, dim3((unsigned)parts), dim3(kRingThreads), 0, st, d, k0, 0, clear, pull, h->pull_at);
   } else if (clear > 0) {
     clear_spike_rows(h, st, k0, clear);
   }
@@ -1471,8 +1515,12 @@ void ring_run_chip(adseq* h, hipStream_t st, long long step0, long long n_steps)
     const bool record = d.record && h->tape_ok && n < d.max_steps;
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
     if (d.record && n >= d.max_steps) h->tape_ok = false;
-    hipLaunchKernelGGL(chip_kernel(record, syn, h->fwd_chunk), grid, block, 0, st, n, cnt, h->rev_base, h->fwd_P, h->fwd_chunk, stride, h->fwd_margin, d);
+    hipLaunchKernelGGL(chip_kernel(record, syn, h->fwd_chunk, h->pull.parts > 0), grid, block, 0, st, n, cnt, h->rev_base, h->fwd_P, h->fwd_chunk, stride, h->fwd_margin, d, h->pull);
     h->rev_base += (unsigned)(cnt - 1) * (unsigned)h->fwd_P;
+    if (cnt == d.W) {   // (a whole window: it has left its words)
+      if (h->hist_upto != n) h->hist_from = n;
+      h->hist_upto = n + cnt;
+    }
     h->grp_count += 1;   // (launches of the group)
     h->enq_calls += cnt;
     n += cnt;
@@ -1899,7 +1947,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.W = L.W; d.wshift = L.wshift; d.tp_shift = L.tp_shift; d.P = L.P; d.NB = L.NB; d.cap = L.cap;
   d.wgroups = L.wgroups;
   static_assert(sizeof(uint2) == 2 * sizeof(int), "tiles of a dense window are laid over the staging buffer");
-  if (d.kind == ADSEQ_RING && L.cap > 0 && d.N <= kDenseCells && env_pow2("ADSEQ_RING_DENSE", 1, 0, 1) && !env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1)) {
+  if (d.kind == ADSEQ_RING && L.cap > 0 && d.N <= kDenseCells && env_pow2("ADSEQ_RING_DENSE", 1, 0, 2) && !env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1)) {
     // rows of the window that a tile of all targets holds; as many shares of the spikes as blocks and staging buffer allow, a
     // block for every trial and row group at least eight times over
     const int most = kDenseCells / d.N < L.W ? kDenseCells / d.N : L.W;
@@ -1908,6 +1956,27 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     const long long K1 = L.NB / ((long long)d.B * G), K2 = (long long)(ebuf / (tile * d.B * G));
     const long long K = K1 < K2 ? K1 : K2;
     if (K >= 8) { d.dense_rows = rows; d.dense_G = G; d.dense_K = (int)K; }
+  }
+  h->pull_at = 0x7fffffffffffffffLL;
+  if (L.pull_parts > 0 && L.cap > 0) {
+    h->pull.parts = L.pull_parts; h->pull.pt = L.pull_pt; h->pull.lb = L.pull_lb;
+    h->pull.list = (uint2*)(ws + L.pull); h->pull.pos = (unsigned*)(ws + L.pull_pos); h->pull.hist = (unsigned*)(ws + L.pull_hist);
+    h->pull.hmask = L.pull_hist_windows - 1;
+    h->pull.Q = (d.d_max + d.W - 1) / d.W;
+    // shares: as even a load of the pass's blocks as few of them give (a share takes in the words of its windows and adds its tile to memory)
+    int best = 1;
+    double least = 1e30;
+    for (int K = 1; K <= h->pull.Q && K <= 4; ++K) {
+      const int items = d.B * h->pull.parts * K, rounds = (items + L.NB - 1) / L.NB;
+      const double t = (double)rounds / K * (1.0 + 0.05 * K);
+      if (t < least) { least = t; best = K; }
+    }
+    h->pull.K = best;
+    if (d.dense_K == 0) d.dense_K = -1;
+    // from half as many events in a window as the lists have entries on (10,000 x 1,000, 2,000 steps, ms with few / 166 / 341 / 491 / 741 Hz:
+    // by the spikes 5.6 / 9.03 / 14.6 / 24.3 / 40.8; pulled 8.3 / 8.5 / 8.9 / 9.0 / 9.4)
+    h->pull_at = (long long)d.BN * d.d_max / (2 * d.W);
+    if (env_pow2("ADSEQ_RING_DENSE", 1, 0, 2) == 2) h->pull_at = -1;
   }
   d.win = (int*)(ws + L.win);
   d.dstart = (unsigned*)(ws + L.dstart); d.nearcnt = (unsigned*)(ws + L.nearcnt);
@@ -1989,10 +2058,11 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     // reverse kernel's layout (ADSEQ_RING_FORWARD_BLOCKS taking-part blocks, default 256).  ADSEQ_RING_FORWARD_CHIP:
     // see reverse_plan; ADSEQ_RING_FORWARD_MARGIN: candidate margin in thousandths of the membrane unit (default 5).
     ResidentPlan fp = reverse_plan((long long)d.BN, true, d.S / d.N);
-    if (fp.P > 0 && !(resident_fits((const void*)chip_kernel(true, syn, fp.chunk)) && resident_fits((const void*)chip_kernel(false, syn, fp.chunk))))
+    if (fp.P > 0 && !(resident_fits((const void*)chip_kernel(true, syn, fp.chunk, h->pull.parts > 0)) && resident_fits((const void*)chip_kernel(false, syn, fp.chunk, h->pull.parts > 0))))
       fp = ResidentPlan();
     if (fp.P > 0 && !d.count_pop) {
       h->fwd_P = fp.P; h->fwd_chunk = fp.chunk; h->res_P = 0;
+      if (h->pull.parts > 0 && d.B == 1 && (long long)d.W * d.words * 8 <= kPullLds / 2) h->pull.near = (kPullLds - d.W * d.words * 8) / 8;
       if (const char* e = getenv("ADSEQ_RING_FORWARD_MARGIN")) { const int v = atoi(e); if (v >= 0 && v <= 100000) h->fwd_margin = (float)v * 1e-3f; }
     }
     // chained step launches (ring_chain.h; experimental, off by default: measured slower than a launch per step on
@@ -2032,6 +2102,15 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
       const unsigned g = (unsigned)(d.N < 262144 ? d.N : 262144);
       hipLaunchKernelGGL(k_sort_rows, dim3(g), dim3(kBlock), 0, st, d, ec);
       e = read_err();
+    }
+    if (h->fwd_P == 0) { h->pull.parts = 0; h->pull_at = 0x7fffffffffffffffLL; if (d.dense_K < 0) d.dense_K = 0; }   // (nobody makes window words)
+    if (e == hipSuccess && !(err & (ERR_GRAPH | ERR_DELAY)) && h->pull.parts > 0) {
+      const size_t n = (size_t)h->pull.parts * (d.d_max + 2);
+      unsigned* const cursors = h->pull.pos + n + 1;
+      fill_u32(st, cursors, 0u, n);
+      hipLaunchKernelGGL(k_pull_count, dim3((unsigned)(d.S < 4096 * kBlock ? grid_for((size_t)d.S) : 4096)), dim3(kBlock), 0, st, d, h->pull, cursors);
+      hipLaunchKernelGGL(k_pull_scan, dim3(1), dim3(1024), 0, st, d, h->pull, cursors);
+      hipLaunchKernelGGL(k_pull_fill, dim3((unsigned)(d.N < 65536 ? (d.N + 3) / 4 : 16384)), dim3(kBlock), 0, st, d, h->pull, cursors);
     }
   } else {
     size_t work = (size_t)(d.S > d.N ? d.S : d.N);

@@ -50,28 +50,125 @@ __device__ __forceinline__ void fwd_row_tail(const Dev& d, int* __restrict__ win
   }
 }
 
+// A crowded window (ring_pull.h), from the launch's first step to the window's end: a block takes the events that its neurons receive inside
+// the window from the spikes of the launch so far.  Their sources' spike words of every step, and the synapses with offsets inside a
+// window (pull.near of them, the rest is read again every step), are in LDS; behind the barrier of a step there are the words of the
+// step before, one load for a thread at most, and the synapses of offset 1.  Nobody adds to anybody else's cells.
+constexpr int kPullLds = 122880;   // bytes: spike words [W][words], then synapses
+struct PullLds { unsigned long long* words; uint2* near; int* acc; int* pos; };   // acc: [512] sums of the step; pos: [W + 1] where the synapses of an offset begin
+template <bool RECORD, int SYN>
+__device__ __forceinline__ unsigned fwd_pull_steps(const Dev& d, const Pull& pull, FwdState<1>& S, const PullLds& L, long long n0, int nsteps, unsigned bar_base, int P,
+                                                   int rank, int chunk, int my_word, int* s_dead) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const unsigned long long G64 = 0x9E3779B97F4A7C15ull;
+  const int shift = d.dbits + pull.lb;
+  const unsigned lmask = (1u << pull.lb) - 1u;
+  const unsigned first = pull.pos[(size_t)rank * (d.d_max + 2)];
+  const uint2* const list = pull.list + first;
+  for (int x = tid; x <= d.W; x += kResThreads) L.pos[x] = (int)(pull.pos[(size_t)rank * (d.d_max + 2) + (x < d.d_max + 1 ? x : d.d_max + 1)] - first);
+  L.acc[tid] = 0;
+  __syncthreads();
+  const int room = pull.near;
+  for (int e = tid; e < L.pos[d.W] && e < room; e += kResThreads) L.near[e] = list[e];
+  int slot = (int)(n0 % d.R), phi = (int)(n0 & (long long)(d.W - 1));
+  int* win = win_of(d, n0) + (size_t)phi * d.BN;
+  const int lo = rank * chunk;
+  unsigned bits = 0u;   // the thread's neuron's spikes of the launch, by step of the window
+  auto take = [&](const uint2& e, int k) {   // spikes of launch step k - D
+    const int D = (int)((e.x >> pull.lb) & d.dmask), i = (int)(e.x >> shift);
+    if ((L.words[(k - D) * d.words + (i >> 6)] >> (i & 63)) & 1ull) atomicAdd(&L.acc[e.x & lmask], (int)e.y);
+  };
+  auto take_all = [&](int e0, int e1, int k) {
+    const int held = e1 < room ? e1 : room;
+    for (int e = e0 + tid; e < held; e += kResThreads) take(L.near[e], k);
+    for (int e = (e0 > room ? e0 : room) + tid; e < e1; e += kResThreads) take(list[e], k);
+  };
+  __syncthreads();
+  for (int k = 0; k < nsteps; ++k) {
+    const long long n = n0 + k;
+    const bool xi = d.p_thresh && (mix64(S.zg[0] + G64 * ((unsigned long long)n + 1ull)) >> 32) < d.p_thresh;
+    const __amdgpu_buffer_rsrc_t cells = res_rows(win, S.hi * 4);
+    const int far = __builtin_amdgcn_raw_buffer_load_b32(cells, S.g0 * 4, 0, kBufAgent);   // (complete: the expansion was a launch before)
+    if (k >= 2) take_all(L.pos[2], L.pos[k + 1], k);
+    if (k > 0) {
+      rev_wait(d, bar_base + (unsigned)k * (unsigned)P, s_dead);
+      const int before = slot == 0 ? d.R - 1 : slot - 1;
+      for (int w = tid; w < d.words; w += kResThreads) L.words[(k - 1) * d.words + w] = q_load<true>(&d.spike_bits[(size_t)before * d.words + w]);
+    }
+    __syncthreads();
+    if (k > 0) take_all(L.pos[1], L.pos[2], k);
+    __syncthreads();
+    float I = (float)wrap_add(far, L.acc[tid]) * 0x1p-24f;
+    L.acc[tid] = 0;
+    if (SYN) {   // the jumps go into the synaptic current state(s)
+      const float jump = I;
+      I = __fmaf_rn(d.alpha_s, S.J[0], jump);
+      S.J[0] = I;
+      if (SYN == 2) {
+        const float fast = __fmaf_rn(d.alpha_r, S.Jf[0], jump);
+        S.Jf[0] = fast;
+        I = I - fast;
+      }
+    }
+    if (d.p_thresh) I = I + (xi ? d.ext_w : 0.0f);
+    const float U = __fmaf_rn(d.alpha, S.V[0], I);
+    const bool spike = (S.actmask & 1u) && U >= d.theta;
+    S.V[0] = spike ? d.v_reset : U;
+    bits |= spike ? 1u << phi : 0u;
+    const unsigned long long m = __ballot(spike);
+    if (my_word >= 0) q_store<true>(&d.spike_bits[(size_t)slot * d.words + my_word], lane == 0 ? m : 0ull);
+    rev_arrive(d, k + 1 < nsteps, rank);   // (words acknowledged)
+    flow_store<1, 0>(flow_splat<1>(0.0f), cells, S.g0 * 4);
+    if (RECORD) {
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(U), res_rows(d.tapeU + (size_t)n * d.BN, S.hi * 4), S.g0 * 4, 0, kBufNonTemporal);
+      if (spike) atomicAdd(&d.spk_count[S.g0], 1);
+      if (my_word >= 0) d.tape_bits[(size_t)n * d.words + my_word] = lane == 0 ? m : 0ull;
+    }
+    if (++slot == d.R) slot = 0;
+    phi += 1;
+    win += d.BN;
+  }
+  return bits;
+}
+
 // Steps n0 .. n0 + nsteps - 1, all inside one window.  P taking-part blocks (every stride-th block of
 // the grid), each owning `chunk` <= NPT * 512 neurons, NPT consecutive ones per thread (four; eight for state arrays
 // beyond 256 x 2,048 cells; one where a block owns no more neurons than it has threads: a step's instructions then
 // spread over all its wavefronts); B N a multiple of 4 unless NPT = 1 (whose accesses are of 4 bytes).  SYN: synaptic
 // current states, as in k_step_win; they stay in registers too.  (9,973 neurons x 2 trials with a current state, 1,000
 // steps with the reverse sweep: 8.4 ms by a launch per step, 5.1 ms so.)  bar_base: sum of the arrival counters when the launch begins.  margin: how far below the
-// threshold the early value of a candidate may lie.
-template <bool RECORD, int NPT, int SYN>
+// threshold the early value of a candidate may lie.  PULL: the network's crowded windows are pulled (ring_pull.h; fwd_pull_steps where the
+// launch ends with its window), and a launch of a whole window leaves its neurons' window words.
+template <bool RECORD, int NPT, int SYN, bool PULL>
 __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nsteps, unsigned bar_base, int P, int chunk,
-                                                          int stride, float margin, Dev d) {
+                                                          int stride, float margin, Dev d, Pull pull) {
   __shared__ int s_dead, s_ncand, s_nslow;
   __shared__ RevSpike s_cand[kFwdCand];            // candidates of the step: row bounds, place | trial << kRevLocBits
   __shared__ RevSpike s_slow[(NPT < 4 ? 4 : NPT) * kResThreads];     // spikes that were no candidates (one entry per neuron at most)
   __shared__ unsigned char s_fired[(NPT < 4 ? 4 : NPT) * kResThreads];   // by the neuron's place in the block: it spiked in this step
+  __shared__ alignas(16) unsigned char s_pull[PULL ? kPullLds : 16];
+  static_assert(!PULL || NPT == 1, "window words and pulled windows: one neuron per thread");
+  __shared__ int s_pulled;   // (the same in all blocks)
   if (blockIdx.x % stride) return;
   const int rank = blockIdx.x / stride;
   if (rank >= P) return;
   if (threadIdx.x == 0) { s_dead = (ld_agent(&d.ctr->err) & ERR_BARRIER) ? 1 : 0; s_ncand = 0; s_nslow = 0; }
+  // (one thread looks, beside the loads of the others: a test in front of them is a trip to memory more)
+  if (PULL && threadIdx.x == kResThreads) s_pulled = pull.near > 0 && (int)(n0 & (long long)(d.W - 1)) + nsteps == d.W && dense_window(d, n0) != 0u;
   const bool worker = threadIdx.x < kResThreads;   // uniform per wavefront
   if (!worker) {
     // the block barriers of a step, in the workers' order: candidates listed, grid barrier, spikes known, arrival
     __syncthreads();
+    if (PULL && s_pulled) {
+      __syncthreads(); __syncthreads();
+      for (int k = 0; k < nsteps; ++k) {
+        if (k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &s_dead);
+        __syncthreads();
+        __syncthreads();
+        rev_arrive(d, k + 1 < nsteps, rank);
+      }
+      return;
+    }
     for (int k = 0; k < nsteps; ++k) {
       __syncthreads();
       if (k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &s_dead);
@@ -113,8 +210,19 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
   int phi = (int)(n0 & (long long)(d.W - 1));
   int* __restrict__ win = win_of(d, n0) + (size_t)phi * d.BN;   // row of the step being run
   const float cand_theta = d.theta - margin;
+  unsigned wbits_all = 0u;   // PULL: the neuron's spikes of the launch, by step of the window
   __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();
+  if constexpr (PULL) {
+    if (s_pulled) {
+      PullLds L;
+      L.words = reinterpret_cast<unsigned long long*>(s_pull);
+      L.near = reinterpret_cast<uint2*>(s_pull + (size_t)d.W * d.words * 8);
+      L.acc = reinterpret_cast<int*>(s_slow); L.pos = L.acc + kResThreads;   // (the list of slow spikes is not used)
+      wbits_all = fwd_pull_steps<RECORD, SYN>(d, pull, S, L, n0, nsteps, bar_base, P, rank, chunk, my_word, &s_dead);
+      nsteps = 0;
+    }
+  }
   for (int k = 0; k < nsteps; ++k) {
     const long long n = n0 + k;
     int near_h = d.W - 1 - phi;
@@ -344,10 +452,12 @@ __global__ __launch_bounds__(kResLaunch) void k_fwd_chip(long long n0, int nstep
       d.spike_bits[(size_t)slot * d.words + my_word] = wbits;
       if (RECORD) d.tape_bits[(size_t)n * d.words + my_word] = wbits;
     }
+    if (PULL) wbits_all |= (smask & 1u) << phi;
     if (++slot == d.R) slot = 0;
     phi += 1;
     win += d.BN;
   }
+  if (PULL && (S.actmask & 1u)) pull_words(d, pull, n0 >> d.wshift)[g0] = wbits_all;   // (used if the launch was a whole window)
 #pragma unroll
   for (int c = 0; c < NPT; ++c)
     if ((S.actmask >> c) & 1u) {

@@ -432,7 +432,8 @@ __global__ __launch_bounds__(kBlock) void k_open_pop(Dev d, long long n0, float*
 // is known when its first pass is over, and neighbouring windows are alike: the pass of one window decides for the next
 // (block 0's pieces stand for all: lines are dealt out round-robin).  The sums are integers, so that results do not depend on it.
 constexpr int kDenseCells = 40000;   // cells of a tile: 160,000 bytes of LDS
-__device__ __forceinline__ bool dense_window(const Dev& d, long long k0) { return d.dense_K > 0 && d.ctr->dense[(k0 >> d.wshift) & 1] != 0; }
+// 0: events staged, 1: pulled by the targets where their lists and the spikes' window words are there (ring_pull.h), 2: otherwise so.
+__device__ __forceinline__ unsigned dense_window(const Dev& d, long long k0) { return d.dense_K != 0 ? d.ctr->dense[(k0 >> d.wshift) & 1] : 0u; }
 
 // Pass 1 for block x: trial, row group and share from x; spikes of steps [n_lo, n_hi).
 __device__ __forceinline__ void role_dense(const Dev& d, int* tile, int* s_pieces, long long k0, long long n_lo, long long n_hi, int x, long long count_from);
@@ -1009,21 +1010,28 @@ __device__ __forceinline__ void role_dense(const Dev& d, int* tile, int* s_piece
   for (int c = threadIdx.x; c < cells; c += kRingThreads) out[c] = tile[c];
 }
 
+#include "ring_pull.h"
+
 // The two passes of the expansion as kernels.
 // The same roles as launches of their own (window boundaries, catching up, open loop).
+// (PULL: the window may be pulled.  In one kernel for both, the other passes
+// took 0.3 us longer: 29 scalar registers spilled instead of 6.)
+template <bool PULL>
 __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, long long n_lo, long long n_hi,
-                                                          int vb0, int nvb, int stage, long long count_from, int clear_other) {
+                                                          int vb0, int nvb, int stage, long long count_from, int clear_other, Pull pull) {
   // (the roles share the LDS: queues and ordering buffers of the staging, or a tile of a dense window)
   constexpr size_t kStageBytes = sizeof(ExpandLds) + sizeof(SortLds), kTileBytes = (size_t)kDenseCells * 4;
   __shared__ __align__(16) unsigned char lds[kStageBytes > kTileBytes ? kStageBytes : kTileBytes];
   __shared__ int s_pieces;
   static_assert(sizeof(ExpandLds) % 16 == 0, "the second buffer begins on 16 bytes");
   XPH_SPAN(0, 0)
-  if (stage && dense_window(d, k0)) role_dense(d, reinterpret_cast<int*>(lds), &s_pieces, k0, n_lo, n_hi, vb0 + (int)blockIdx.x, count_from);
+  const unsigned dense = stage ? dense_window(d, k0) : 0u;
+  if (PULL && dense) role_pull(d, pull, reinterpret_cast<unsigned long long*>(lds), &s_pieces, k0, vb0 + (int)blockIdx.x, nvb, count_from);
+  else if (dense == 2u) role_dense(d, reinterpret_cast<int*>(lds), &s_pieces, k0, n_lo, n_hi, vb0 + (int)blockIdx.x, count_from);
   else {
     ExpandLds& L = *reinterpret_cast<ExpandLds*>(lds);
     role_bin(d, L, *reinterpret_cast<SortLds*>(lds + sizeof(ExpandLds)), k0, n_lo, n_hi, vb0 + (int)blockIdx.x, nvb, stage, count_from);
-    if (d.dense_K > 0 && vb0 + (int)blockIdx.x == 0 && threadIdx.x == 0) d.ctr->pieces = (long long)L.qn * nvb;
+    if (d.dense_K != 0 && vb0 + (int)blockIdx.x == 0 && threadIdx.x == 0) d.ctr->pieces = (long long)L.qn * nvb;
   }
   XPH_SPAN(0, 1)
   // The other window buffer -- the one the steps before k0 have just used up -- is zeroed here, a
@@ -1046,7 +1054,7 @@ __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, l
 }
 // clear > 0: the launch also zeroes the spike words of steps k0 .. k0 + clear - 1 (at most R), which the staging pass
 // before it was the last to read as those of the steps R before (open loop: the next launch sets their bits).
-__global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, int p0, int clear) {
+__global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, int p0, int clear, int pull, long long pull_at) {
   __shared__ int tile[kMaxTileCells];
   XPH_SPAN(1, 0)
   if (clear > 0) {
@@ -1054,11 +1062,14 @@ __global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, i
     for (long long x = (long long)blockIdx.x * kRingThreads + threadIdx.x; x < cnt; x += (long long)gridDim.x * kRingThreads)
       d.spike_bits[first + x < all ? first + x : first + x - all] = 0ull;
   }
-  if (dense_window(d, k0)) role_dense_sum(d, k0);
-  else role_acc(d, tile, k0, p0 + (int)blockIdx.x);
+  const unsigned dense = dense_window(d, k0);
+  if (!(dense && pull)) {   // (else all is done)
+    if (dense == 2u) role_dense_sum(d, k0);
+    else role_acc(d, tile, k0, p0 + (int)blockIdx.x);
+  }
   // which way the next window goes
-  if (d.dense_K > 0 && blockIdx.x == 0 && threadIdx.x == 0)
-    d.ctr->dense[((k0 >> d.wshift) + 1) & 1] = d.ctr->pieces > (long long)kSegQueue * d.NB ? 1u : 0u;
+  if (d.dense_K != 0 && blockIdx.x == 0 && threadIdx.x == 0)
+    d.ctr->dense[((k0 >> d.wshift) + 1) & 1] = d.dense_K > 0 && d.ctr->pieces > (long long)kSegQueue * d.NB ? 2u : (d.ctr->pieces > pull_at ? 1u : 0u);
   XPH_SPAN(1, 1)
 }
 

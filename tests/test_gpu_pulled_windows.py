@@ -1,0 +1,83 @@
+"""Crowded windows of the ring pulled by the targets (ring_pull.h) against the oracle: trace bit for bit, spike counts, counters and both
+gradients.  Parts with a remainder, delays that are no multiple of the window, trials that share spike words, synaptic current
+states, more synapses of a part than LDS has room for, runs cut inside windows, and what changes between pulled and staged windows."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(sim, ref):
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+
+
+@pytest.mark.parametrize("n,b,fan,d_max,T,window,syn", [(2000, 1, 200, 40, 90, 16, 0), (2049, 1, 150, 65, 130, 32, 1), (2500, 1, 300, 33, 80, 16, 2),
+                                                        (1501, 2, 90, 33, 90, 16, 0), (901, 3, 120, 70, 150, 32, 1), (6001, 1, 60, 50, 100, 32, 0),
+                                                        (2000, 1, 100, 9, 60, 8, 0), (2100, 1, 1600, 40, 70, 32, 0)])
+def test_pulled_windows(n, b, fan, d_max, T, window, syn, monkeypatch):
+    monkeypatch.setenv("ADSEQ_RING_DENSE", "2")            # every window from the second on
+    monkeypatch.setenv("ADSEQ_RING_FORWARD_CHIP", "1")
+    monkeypatch.setenv("ADSEQ_RING_WINDOW", str(window))
+    monkeypatch.setenv("ADSEQ_RING_BINBLOCKS", "32")
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=700.0, t=T, b=b, w_mean=1.2 / fan, w_std=1.0 / fan)
+    wl.tau_syn_ms, wl.tau_rise_ms = (0.0, 5.0, 5.0)[syn], (0.0, 0.0, 1.0)[syn]
+    ref = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=b, n_threads=8)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T, step_event_capacity=4000000)
+    cut = 2 * window + 3
+    for pieces in ([T], [cut, T - cut], [window, 1, 1, T - window - 2]):   # whole, cut inside a window, single steps in between
+        sim.reset()
+        n0 = 0
+        for p in pieces:
+            sim.step(n0) if p == 1 else sim.run(n0, p)
+            n0 += p
+        _check(sim, ref)
+        base = -sim.workspace.data_ptr() % 256             # Counters::dense, at byte 76 of the workspace
+        assert any(sim.workspace[base + 76:base + 84].cpu().numpy().view(np.uint32).tolist())
+    dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+    sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+    np.testing.assert_allclose(g_w.cpu().numpy(), gw, rtol=1e-5, atol=1e-6)
+    np.testing.assert_allclose(g_d.cpu().numpy(), gd, rtol=1e-5, atol=1e-6)
+    sim.close()
+
+
+def test_from_quiet_to_crowded(monkeypatch):
+    """More than 2^21 synapses at the default line: a network that starts quiet and runs away, by staged and then by pulled windows,
+    against the same run by staged windows alone (which the other tests hold against the oracle, too slow at this size)."""
+    n, fan, d_max, T = 2200, 1000, 60, 400
+    wl = synth.ragged_network(n, 4, d_max, seed=5, rate_hz=60.0, t=T, b=1, w_mean=0.0, w_std=0.0)
+    rng = np.random.default_rng(5)
+    wl.row_ptr = np.arange(n + 1, dtype=np.int64) * fan
+    wl.col = rng.integers(0, n, n * fan, dtype=np.int32)
+    wl.weight = rng.normal(4.0 / fan, 1.0 / fan, n * fan).astype(np.float32)
+    wl.delay_steps = rng.integers(1, d_max + 1, n * fan).astype(np.uint8)
+    monkeypatch.setenv("ADSEQ_RING_DENSE", "0")
+    ref = adseq.Adseq(wl, adseq.RING, 0, batch=1, record_tape=True, max_steps=T)
+    monkeypatch.delenv("ADSEQ_RING_DENSE")
+    ref.run(0, T)
+    U = ref.tape()["U"]
+    per_step = (U.view(T, n) >= wl.v_thresh).sum(dim=1)
+    assert per_step[:64].float().mean() < 20 and per_step[-40:].float().mean() > 200
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=1, record_tape=True, max_steps=T)
+    base = -sim.workspace.data_ptr() % 256
+    crowded = lambda: sim.workspace[base + 76:base + 84].cpu().numpy().view(np.uint32).tolist()
+    for cut in (64, 203):   # (the second one inside a window)
+        sim.reset()
+        sim.run(0, 64)
+        assert not any(crowded())
+        if cut > 64:
+            sim.run(64, cut - 64)
+        sim.run(cut, T - cut)
+        assert any(crowded())
+        assert torch.equal(sim.tape()["U"].view(torch.int32), U.view(torch.int32))
+        assert sim.counters() == ref.counters()
+    sim.close(); ref.close()
