@@ -568,6 +568,7 @@ struct adseq {
   unsigned chain_turn = 0;       // chained launches so far: the parity picks the stream
   int chain_tpb = 256;           // threads per block of the chained launches (256 or 1024)
   bool range_warn = false;    // some target's incoming |amplitudes| add up to 128 or more (ERR_RANGE, reported with the counters)
+  unsigned long long* open_steps = nullptr;   // FIFO / SORTED, qsteps > 64: [qsteps / 64][BN] steps of a long open-loop stretch in which a target has contenders
   Pull pull = {};             // RING: ring_pull.h
   long long pull_at = 0;      // RING: from how many spikes in a window's history on the next is pulled (ring_pull.h)
   long long hist_from = 0, hist_upto = 0;   // RING: steps whose window words (Pull::hist) are in place
@@ -579,7 +580,7 @@ namespace {
 struct Layout {
   size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
-      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk, pull, pull_pos, pull_hist,
+      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk, pull, pull_pos, pull_hist, open_steps,
       total;
   long long spike_cap, event_cap, pool_cap;
   int R, dbits, nblk, words;
@@ -902,6 +903,8 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
              (double)q * bs > (c->step_event_capacity ? (double)c->step_event_capacity : room * 134217728.0);
     };
     while (qsteps > 1 && too_much(qsteps)) qsteps >>= 1;
+    // (more buffers than a stretch of 64 steps needs: up to 1 GB of them, and half a GB of overflow entries)
+    while (qsteps > kQueueSteps && ((double)qsteps * BN * (kCont * 16 + 8) > 1073741824.0 || (double)qsteps * bs > 16777216.0)) qsteps >>= 1;
     L->qsteps = qsteps;
     long long cap = c->step_event_capacity;
     if (!cap) {
@@ -992,6 +995,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->full_bits = take(ptq && L->qsteps >= 2 ? 2 * (size_t)L->words * 8 : 0);
   L->cont = take(ptq ? (size_t)L->qsteps * kCont * BN * 16 : 0);
   L->c_head = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
+  L->open_steps = take(ptq && L->qsteps > 2 ? (size_t)((L->qsteps + 63) / 64) * BN * 8 : 0);
   L->pool_p = take((size_t)L->pool_cap * 8);
   L->pool_t = take((size_t)L->pool_cap * 8);
   L->pool_next = take((size_t)L->pool_cap * 4);
@@ -1083,7 +1087,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
 bool make_layout(const adseq_config* c, Layout* L, bool small = false, bool runs = true) {
   if (!c) return false;
   if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
-      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kQueueSteps, 1, kQueueSteps), false, runs)) return true;
+      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kEventSteps, 1, kEventSteps), false, runs)) return true;
   return layout_as(c, L, false, 1, small, false);
 }
 
@@ -1125,7 +1129,7 @@ bool capturing(hipStream_t st, unsigned long long* id) {
 }
 
 // Clears the dynamic state (not the prepared synapses).
-void launch_reset(adseq* h, hipStream_t st) {
+void launch_reset(adseq* h, hipStream_t st, bool first = false) {
   const Dev& d = h->dev;
   join_ahead(h, st);
   h->ahead_for = -1;
@@ -1165,10 +1169,13 @@ void launch_reset(adseq* h, hipStream_t st) {
   } else {
     fill_u32(st, d.occ, 0u, BN);
     fill_u32(st, d.head, 0u, BN);
-    fill_u32(st, d.c_head, 0xffffffffu, (size_t)d.qsteps * BN);
+    // (the contender buffers of a stretch are empty whenever its two launches are over: only the first two can hold anything)
+    const size_t bufs = first || d.qsteps < 2 ? d.qsteps : 2;
+    fill_u32(st, d.c_head, 0xffffffffu, bufs * BN);
+    if (first && d.qsteps > 2) fill_u32(st, h->open_steps, 0u, (size_t)((d.qsteps + 63) / 64) * BN * 2);
     fill_u32(st, d.min_k, 0xffffffffu, BN);
     if (d.kind == ADSEQ_FIFO) fill_u32(st, d.vmask, 0u, (size_t)d.nw * BN);
-    fill_u32(st, d.cnt, 0u, (size_t)d.qsteps * BN);
+    fill_u32(st, d.cnt, 0u, bufs * BN);
     fill_u32(st, d.blk, 0u, ((size_t)d.nblk + fan_slots(d.nblk)) * sizeof(BlkCtr) / 4);
     h->pending_admit = false;
   }
@@ -1987,6 +1994,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.spk_count = (int*)(ws + L.spk_count);
   d.sorted_rev = L.sorted_rev ? 1 : 0;
   d.qsteps = L.qsteps;
+  h->open_steps = (unsigned long long*)(ws + L.open_steps);
   d.adm_base = (unsigned*)(ws + L.adm_base); d.adm_bits = (unsigned long long*)(ws + L.adm_bits);
   d.gwin = (float*)(ws + L.gwin); d.Gacc = (float*)(ws + L.Gacc); d.gsum = (float*)(ws + L.gsum);
   d.wspk = (unsigned long long*)(ws + L.wspk); d.near_nspk = (int*)(ws + L.near_cnt); d.near_nev = d.near_nspk + 64;
@@ -2082,7 +2090,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     chip_event_make(hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && g_static_busy[dev]);
   }
   hipStream_t st = (hipStream_t)cfg->stream;
-  launch_reset(h, st);
+  launch_reset(h, st, true);
   ExpCoef ec;
   ec.c[0] = 1.0;
   for (int k = 1; k <= 20; ++k) ec.c[k] = ec.c[k - 1] / (double)k;
@@ -2257,7 +2265,7 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }
-  // FIFO / SORTED: stretches of steps (k_fanout_steps, k_queue_steps) for all steps but the last, whose events stay
+  // FIFO / SORTED: stretches of steps (k_fanout_lanes, k_queue_events; k_fanout_steps, k_queue_steps) for all steps but the last, whose events stay
   // pending: an adseq_enqueue for the same step may add to them.  Output rows that overlap, where the later step's
   // values stay, go step by step; so do two steps (three launches, two of them wide, against four), and crowded ones.  Within a
   // stretch nothing is dropped where it is emitted, as a step's own fan-out does when the target is full, so every event
@@ -2269,7 +2277,42 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
   hipStream_t st = (hipStream_t)stream;
   const bool stretches = d.qsteps > 1 && (I_stride == 0 || I_stride >= d.BN) && step0 == h->next_step;
   for (int64_t k = 0; k < n_steps;) {
-    const int cnt = (int)(n_steps - 1 - k < d.qsteps ? n_steps - 1 - k : d.qsteps);
+    const int64_t left = n_steps - 1 - k;
+    if (stretches && d.qsteps > 2 && left >= 3) {
+      // Rows of up to 128 entries, no more events in a step than targets: as many steps as there are buffers.  (Longer rows want a block
+      // of threads each: 10,000 x 1,000, 10 spikes per step 5.8 us per step by those, 7.7 so; 500 x 300 in calls of 6 steps 8.4 / 8.9.  Two
+      // events per target and step: 5,000 x 30, SORTED[32] 13.9 / 17.4; 2,000 x 100, SORTED[32], five events 46 / 50.)
+      int long_cnt = (int)(left < d.qsteps ? left : d.qsteps);
+      EventOffsets so;
+      for (int j = 0; j < long_cnt; ++j) {
+        const int64_t at = spike_offsets[k + j] - spike_offsets[k];
+        if (at < 0 || at > 0xffffffffLL) { long_cnt = j; break; }
+        so.off[j] = (unsigned)at;
+      }
+      const double spikes = long_cnt > 1 ? (double)so.off[long_cnt - 1] / (long_cnt - 1) : 0.0, row = (double)d.S / (double)d.N;
+      if (long_cnt >= 3 && row <= 128.0 && spikes * row <= (double)d.BN) {
+        flush_admit(h, st);
+        int lanes = 0;
+        while (lanes < 6 && (1 << lanes) < row) ++lanes;
+        // four wavefronts a block: one trip through the step's spikes, and rows of zeros shared by four blocks at least where they are long
+        double gx = spikes * (1 << lanes) / kBlock + 1.0;
+        if (gx < (double)d.BN / 16384.0) gx = (double)d.BN / 16384.0;
+        const dim3 fan((unsigned)(gx > 64.0 ? 64.0 : gx), (unsigned)long_cnt), fb(kBlock), own((unsigned)((d.BN + 63) / 64)), ob(64);
+        float* const out = I_out + k * I_stride;
+        const int* const ids = spike_ids + spike_offsets[k];
+        hipLaunchKernelGGL(k_fanout_lanes, fan, fb, 0, st, d, h->open_steps, (long long)(step0 + k), ids, n_spikes + k, lanes, out, (long long)I_stride, so);
+        hipLaunchKernelGGL((d.kind == ADSEQ_FIFO ? k_queue_events<ADSEQ_FIFO> : k_queue_events<ADSEQ_SORTED>), own, ob, 0, st, d, h->open_steps, (long long)(step0 + k),
+                           long_cnt, out, (long long)I_stride);
+        k += long_cnt;
+        h->next_step = step0 + k;
+        h->enq_calls += long_cnt;
+        h->tape_ok = false;
+        HIP_TRY(h, hipGetLastError());
+        continue;
+      }
+    }
+    const int most = d.qsteps < kQueueSteps ? d.qsteps : kQueueSteps;
+    const int cnt = (int)(left < most ? left : most);
     if (stretches && cnt >= 3) {
       const double spikes = std::fabs((double)(spike_offsets[k + cnt - 1] - spike_offsets[k])) / (cnt - 1);
       const double events = spikes * (double)d.S / (double)d.N;

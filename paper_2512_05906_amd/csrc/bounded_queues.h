@@ -926,6 +926,141 @@ __global__ __launch_bounds__(64) void k_queue_steps(Dev d, long long n0, int cnt
   }
 }
 
+// The same where rows are short (adseq_run_open has the line), for up to 512 steps: a target has an event every few steps or hundreds of
+// them, and looking at its contender count of every step, and handing every step's zero through LDS, is most of what a stretch of 64
+// steps costs, the other part a block of threads for every spike.  So the registering launch takes as many lanes per spike as a row
+// needs, marks the steps in which a target has contenders (open_steps: [steps / 64][BN], zero but between the two launches; one bit,
+// by the first of them) and fills the output rows with zeros on the side, over the whole chip; the owners go from event to event and
+// store what is delivered.  What bounds them: the chain of the target with the most events (27 us per 512 steps of 10,000 independent
+// FIFO[4] queues, 2.5 spikes per step; the launch before it 8 us).  us per step, stretches of 64 with a block per spike / so: those
+// queues 0.34 / 0.07; 10,000 x 1, FIFO[8], 1,000 spikes per step 2.42 / 0.56; 100,000 x 10, 60,000 events per step 15.6 / 8.1; 5,000 x 30,
+// 1,000 events 1.36 / 1.21, in calls of 20 steps 2.53 / 2.40.
+constexpr int kEventSteps = 512;
+struct EventOffsets { unsigned off[kEventSteps]; };   // first spike of every step, counted from the stretch's first
+typedef float open_v4f __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(kBlock) void k_fanout_lanes(Dev d, unsigned long long* __restrict__ open_steps, long long n0, const int* __restrict__ spk, const int* __restrict__ n_spk, int lanes_log2,
+                                                          float* __restrict__ I_out, long long I_stride, EventOffsets o) {
+  const int j = blockIdx.y, lane = threadIdx.x & 63, sub = lane & ((1 << lanes_log2) - 1);
+  const long long n = n0 + j;
+  if (I_stride != 0 || j + 1 == (int)gridDim.y) {
+    float* const row = I_out + j * I_stride;
+    const int bad = (int)((16u - ((unsigned)reinterpret_cast<size_t>(row) & 15u)) & 15u) / 4, head = bad < d.BN ? bad : d.BN;   // up to the first 16-byte boundary
+    const int whole = (d.BN - head) >> 2;
+    const open_v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int x = (int)(blockIdx.x * kBlock + threadIdx.x); x < whole; x += (int)gridDim.x * kBlock)
+      __builtin_nontemporal_store(zero, reinterpret_cast<open_v4f*>(row + head) + x);
+    if (blockIdx.x == 0 && (int)threadIdx.x < head) row[threadIdx.x] = 0.0f;
+    if (blockIdx.x == 0 && head + 4 * whole + (int)threadIdx.x < d.BN) row[head + 4 * whole + threadIdx.x] = 0.0f;
+  }
+  const QBuf qb = queue_buf(d, j);
+  int count = n_spk[j];
+  count = count < 0 ? 0 : (count > d.BN ? d.BN : count);
+  const int* const list = spk + o.off[j];
+  int c_off = 0;
+  long long s_off = 0;
+  const int per = 64 >> lanes_log2, waves = (int)gridDim.x * (kBlock / 64);
+  for (int e0 = ((int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6)) * per; e0 < count; e0 += waves * per) {   // uniform over the wavefront
+    const int e = e0 + (lane >> lanes_log2);
+    const int g = e < count ? list[e] : -1;
+    int len = 0, base = 0;
+    long long r0 = 0;
+    if ((unsigned)g < (unsigned)d.BN) {
+      const int b = trial_of(d, g), i = g - b * d.N;
+      r0 = d.row_ptr[i]; len = (int)(d.row_ptr[i + 1] - r0); base = b * d.N;
+      if (sub == 0) { c_off += len; s_off += d.rowsum[i]; }
+    }
+    for (int q = sub; __ballot(q < len); q += 1 << lanes_log2) {
+      const bool have = q < len;
+      unsigned pk = 0u;
+      int a = 0, tk = -1;
+      if (have) { pk = d.packed[r0 + q]; a = d.a_q[r0 + q]; }
+      const int gt = base + (int)(pk >> d.dbits), D = (int)(pk & d.dmask);
+      if (have) tk = atomicAdd(&qb.cnt[gt], 1);
+      if (tk == 0) atomicOr(&open_steps[(size_t)(j >> 6) * d.BN + gt], 1ull << (j & 63));
+      if (have && tk < kCont) qb.cont[(size_t)tk * d.BN + gt] = cont_pack(r0 + q, -1, (unsigned)(n + D) & 0xffffu, a);
+      const bool over = tk >= kCont;
+      if (__ballot(over)) overflow_push<false>(d, qb, over, gt, r0 + q, -1, (unsigned)(n + D), a);
+    }
+  }
+  const long long t_off = wave_total(c_off), t_soff = wave_total64(s_off);
+  if (lane == 0 && t_off) {
+    BlkCtr& bc = d.blk[d.nblk + (blockIdx.x + blockIdx.y * gridDim.x) % kFanoutBlocks];
+    atomicAdd(&bc.offered, (unsigned long long)t_off);
+    atomicAdd((unsigned long long*)&bc.sum_offered, (unsigned long long)t_soff);
+  }
+}
+template <int KIND>
+__global__ __launch_bounds__(64) void k_queue_events(Dev d, unsigned long long* __restrict__ open_steps, long long n0, int cnt, float* __restrict__ I_out, long long I_stride) {
+  __shared__ unsigned long long s_steps[kEventSteps / 64][64];   // steps in which the lane's target has contenders
+  const int lane = threadIdx.x, g = blockIdx.x * 64 + lane, nw = (cnt + 63) >> 6;
+  StepAcc r; r.acc = 0; r.popped = 0; r.c_adm = 0; r.s_adm = 0;
+  long long s_del = 0;
+  if (blockIdx.x == 0 && lane == 0) d.ctr->pool_n[0] = 0;   // the overflow pool is consumed by this launch
+  if (g < d.BN) {
+    QState q;
+    q.hd = KIND == ADSEQ_SORTED ? d.head[g] : 0;
+    q.m0 = KIND == ADSEQ_FIFO ? d.vmask[(size_t)g * d.nw] : 0u;
+    q.occ = d.occ[g];
+    q.mn = KIND == ADSEQ_SORTED ? d.min_k[g] : 0xffffffffu;
+#pragma unroll
+    for (int w = 0; w < kEventSteps / 64; ++w) {
+      const unsigned long long m = w < nw ? open_steps[(size_t)w * d.BN + g] : 0ull;
+      s_steps[w][lane] = m;
+      if (m) open_steps[(size_t)w * d.BN + g] = 0ull;
+    }
+    const QState q0 = q;
+    if (KIND == ADSEQ_FIFO && q.occ > 0) fifo_scan<false>(d, g, (unsigned)n0, q, r);
+    int w = 0;
+    unsigned long long offered = s_steps[0][lane];
+    for (;;) {
+      while (!offered && w + 1 < nw) offered = s_steps[++w][lane];
+      // the next step in which something is due, or after which something was offered
+      const int jk = offered ? 64 * w + __ffsll((long long)offered) : cnt + 1;
+      const unsigned away = q.mn - (unsigned)n0;
+      const int jd = q.mn != 0xffffffffu && away < (unsigned)cnt ? (int)away : cnt + 1;
+      const int j = jk < jd ? jk : jd;
+      if (j > cnt) break;
+      const unsigned kn = (unsigned)n0 + (unsigned)j;
+      int K = 0;
+      uint4 cc[kCont];
+#pragma unroll
+      for (int x = 0; x < kCont; ++x) cc[x] = make_uint4(0u, 0u, 0u, 0u);
+      const QBuf qb = queue_buf(d, j > 0 ? j - 1 : 0);
+      if (jk == j) {   // (requesting the next such step's records here already was slower: 27 -> 30 us per 512 steps)
+        offered &= offered - 1ull;
+        K = qb.cnt[g];
+        cc[0] = qb.cont[g]; cc[1] = qb.cont[(size_t)d.BN + g];   // (beside the count: few have more)
+#pragma unroll
+        for (int x = 2; x < kCont; ++x) if (x < K) cc[x] = qb.cont[(size_t)x * d.BN + g];
+      }
+      const int room = d.C - q.occ;     // what the contenders found when they were emitted
+      r.acc = 0;
+      if (j < cnt) {
+        if (jd == j) {
+          if (KIND == ADSEQ_FIFO) fifo_scan<true>(d, g, kn, q, r); else sorted_pop(d, g, kn, q, r);
+        }
+        if (K > 0) admit_contenders<KIND, 1>(d, qb, g, K, room, kn, q, r, cc);
+        if (r.acc != 0 && (I_stride != 0 || j + 1 == cnt)) I_out[j * I_stride + g] = (float)r.acc * 0x1p-24f;
+        s_del += r.acc;
+      } else if (K > 0) {
+        admit_contenders<KIND, 0>(d, qb, g, K, room, kn, q, r, cc);
+      }
+    }
+    if (KIND == ADSEQ_SORTED) { if (q.mn != q0.mn) d.min_k[g] = q.mn; if (q.hd != q0.hd) d.head[g] = q.hd; }
+    if (KIND == ADSEQ_FIFO && q.m0 != q0.m0) d.vmask[(size_t)g * d.nw] = q.m0;
+    if (q.occ != q0.occ) d.occ[g] = q.occ;
+  }
+  if (__ballot(r.popped != 0 || r.c_adm != 0)) {
+    const long long t_pop = wave_total(r.popped), t_adm = wave_total(r.c_adm), t_sadm = wave_total64(r.s_adm), t_del = wave_total64(s_del);
+    if (lane == 0) {
+      BlkCtr& bc = d.blk[blockIdx.x % d.nblk];   // (atomics without return value)
+      atomicAdd(&bc.delivered, (unsigned long long)t_pop); atomicAdd(&bc.admitted, (unsigned long long)t_adm);
+      atomicAdd((unsigned long long*)&bc.sum_admitted, (unsigned long long)t_sadm);
+      atomicAdd((unsigned long long*)&bc.sum_delivered, (unsigned long long)t_del);
+    }
+  }
+}
+
 // Q8.24 amplitude sum (for the offered-event counters) and length of every row: one wavefront
 // per row.
 __global__ __launch_bounds__(kBlock) void k_row_sums(Dev d) {

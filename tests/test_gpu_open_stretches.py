@@ -136,3 +136,49 @@ def test_crowded_stretches_go_step_by_step(kind, cap, n, rate, crowded):
     # (29 steps in stretches, the last one in two launches; or all 30 in two each)
     assert _launches(lambda: sim.run_open(0, 30, ids, offs[:30], counts, out, n)) == (60 if crowded else 4)
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 1), (adseq.FIFO, 40), (adseq.SORTED, 3)])
+@pytest.mark.parametrize("n,fan,b,d_max,events,steps", [(3001, 1, 1, 80, 0.001, "512"), (700, 30, 3, 37, 0.05, "512"), (1, 5, 1, 3, 0.05, "128"),
+                                                        (97, 250, 1, 250, 0.06, "256")])
+@pytest.mark.parametrize("stride", ["apart", "odd", "one"])
+def test_stretches_of_short_rows(kind, cap, n, fan, b, d_max, events, steps, stride, monkeypatch):
+    """k_fanout_lanes and k_queue_events (events: per target and step): stretches of up to 512 steps, events in the first and the last
+    step of a 64-step group, several contenders in a step, rows shorter and longer than a wavefront, output rows on any alignment,
+    and what an enqueue adds to the last step; two runs of the handle."""
+    monkeypatch.setenv("ADSEQ_QUEUE_STEPS", steps)
+    T = 1100
+    wl = synth.ragged_network(n, fan, d_max, seed=n + b, rate_hz=0.0, t=T, b=b, w_mean=0.01, w_std=0.02)
+    bn = b * n
+    rng = np.random.default_rng(9)
+    forced = (rng.random((T, bn)) < 1.5 * events / max(1.0, wl.n_synapses / n)).astype(np.uint8)
+    forced[[0, 63, 64, 127, 128, 511, 512]] |= (rng.random((7, bn)) < min(1.0, 2.0 / bn)).astype(np.uint8)
+    forced[200:230] = 0
+    lists = [np.flatnonzero(x).astype(np.int32) for x in forced]
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, forced_spikes=forced.reshape(T, b, n), keep_currents=True)
+    want = ref.Iq.reshape(T, bn).astype(np.float32) * np.float32(2.0 ** -24)
+    sim = adseq.Adseq(wl, kind, cap, batch=b)
+    step = {"apart": bn, "odd": bn + 3, "one": 0}[stride]
+    ids = torch.from_numpy(np.concatenate(lists + [np.zeros(1, np.int32)])).to(sim.dev)
+    offs = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    for _ in range(2):
+        sim.reset()
+        s = 0
+        for piece in (65, 66, 600, 20, T - 751):
+            lens = [len(x) for x in lists[s:s + piece]]
+            half = lens[-1] // 2
+            counts = torch.tensor(lens[:-1] + [half, lens[-1] - half], dtype=torch.int32, device=sim.dev)
+            buf = torch.full(((piece - 1) * step + bn + 1,), 7.0, dtype=torch.float32, device=sim.dev)
+            out = buf[1:] if stride == "odd" else buf[:-1]     # (rows that begin anywhere on four bytes)
+            sim.run_open(s, piece, ids, offs[s:s + piece], counts, out, step)
+            sim.enqueue(s + piece - 1, ids[int(offs[s + piece - 1]) + half:], counts[piece:])
+            exp = np.full((piece - 1) * step + bn, 7.0, np.float32)
+            for k in range(piece):
+                exp[k * step:k * step + bn] = want[s + k]
+            np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), exp.view(np.uint32))
+            s += piece
+        assert s == T
+        c, rc = sim.counters(), ref.counters()
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], key
+    sim.close()
