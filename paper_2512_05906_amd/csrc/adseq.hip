@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstddef>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -420,6 +421,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 #include "queue_resident.h"
 #include "synapse_resident.h"
 #include "ring_trial.h"
+#include "ring_trial_reverse.h"
 
 // ---------------------------------------------------------------- backward (FIFO / SORTED)
 
@@ -555,6 +557,8 @@ struct adseq {
   bool syn_captured = false;                   // a call has been captured: replays may put steps of the queue arrays under the host's feet, so k_syn_run is not used any more
   unsigned long long syn_left_in = 0;          // the capture in which the queue arrays are in use from some point on
   int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
+  int rtrial_H = 0, rtrial_P = 0;              // k_bwd_trial: adjoint rows in LDS, pieces of a row (0: not used)
+  bool rtrial_always = false;                  // whatever spikes (ADSEQ_REVERSE_TRIALS = 1)
   float fwd_margin = 0.005f;                   // how far below the threshold the early value of a candidate may lie
   // RING, experimental (ADSEQ_RING_OVERLAP = 1): the far part of the next window expanded ahead on a stream of the library's own
   hipStream_t aux = nullptr;
@@ -815,6 +819,21 @@ FlowKernel flow_kernel_adm(bool du, int syn, int surrogate, int chunk) {
 }
 FlowKernel flow_kernel(bool adm, bool du, int syn, int surrogate, int chunk) {
   return adm ? flow_kernel_adm<true>(du, syn, surrogate, chunk) : flow_kernel_adm<false>(du, syn, surrogate, chunk);
+}
+typedef void (*RevTrialKernel)(long long, int, int, const float*, const float*, Dev);
+template <bool DU, int SURR>
+RevTrialKernel rev_trial_kernel_of(bool adm, int syn) {
+  if (adm) return syn ? k_bwd_trial<DU, SURR, 1, true> : k_bwd_trial<DU, SURR, 0, true>;
+  return syn ? k_bwd_trial<DU, SURR, 1, false> : k_bwd_trial<DU, SURR, 0, false>;
+}
+template <bool DU>
+RevTrialKernel rev_trial_kernel_du(bool adm, int syn, int surrogate) {
+  if (surrogate == ADSEQ_SURR_SUPERSPIKE) return rev_trial_kernel_of<DU, ADSEQ_SURR_SUPERSPIKE>(adm, syn);
+  if (surrogate == ADSEQ_GRAD_SPIKE_TIME) return rev_trial_kernel_of<DU, ADSEQ_GRAD_SPIKE_TIME>(adm, syn);
+  return rev_trial_kernel_of<DU, ADSEQ_SURR_OFF>(adm, syn);
+}
+RevTrialKernel rev_trial_kernel(bool adm, bool du, int syn, int surrogate) {
+  return du ? rev_trial_kernel_du<true>(adm, syn, surrogate) : rev_trial_kernel_du<false>(adm, syn, surrogate);
 }
 typedef void (*ChipKernel)(long long, int, unsigned, int, int, int, float, Dev, Pull);
 template <bool RECORD, int SYN>
@@ -1699,7 +1718,7 @@ int gather_blocks(const Dev& d, long long n_lo, long long n_hi) {
 // a window is complete the far queue terms of all earlier spikes that arrive in it are gathered in
 // one pass.
 void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, const float* dL_dcount,
-                          const float* dL_dU, float* grad_w, float* grad_d, const int* counts, bool resident) {
+                          const float* dL_dU, float* grad_w, float* grad_d, const int* counts, bool resident, bool trials) {
   const Dev& d = h->dev;
   const dim3 block(kBlock), gn((unsigned)d.nblk);
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
@@ -1712,9 +1731,18 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
     hipLaunchKernelGGL(k_tape_words, dim3(steps), block, 0, st, d, T);
     hipLaunchKernelGGL(k_adm_bits, dim3(steps, shares), block, 0, st, d, T);
   }
+  fill_u32(st, d.gsum, 0u, nst * (size_t)d.S);
+  const unsigned gf = (unsigned)(d.N < 65536 ? d.N : 65536);
+  if (trials) {
+    if (h->rtrial_P > 1) fill_u32(st, d.Gacc, 0u, (size_t)d.R * d.BN);
+    const int threads = 640;   // (two neurons per thread, and the two wavefronts that read the tape)
+    hipLaunchKernelGGL(rev_trial_kernel(adm, dL_dU != nullptr, d.alpha_s > 0.0f ? 1 : 0, d.surrogate), dim3((unsigned)d.B), dim3((unsigned)threads), 0, st, T, h->rtrial_H, h->rtrial_P,
+                       dL_dcount, dL_dU, d);
+    hipLaunchKernelGGL(k_grad_finish, dim3(gf), block, 0, st, d, dscale, grad_w, grad_d);
+    return;
+  }
   fill_u32(st, d.bwd_carry, 0u, (size_t)d.BN);
   if (d.alpha_s > 0.0f) fill_u32(st, d.bwd_carryJ, 0u, nst * (size_t)d.BN);
-  fill_u32(st, d.gsum, 0u, nst * (size_t)d.S);
   fill_u32(st, d.gwin, 0u, nst * 2 * (size_t)d.W * d.BN);
   fill_u32(st, d.Gacc, 0u, (size_t)d.R * d.BN);
   if (counts) fill_u32(st, d.near_nspk, 0u, 128);
@@ -1804,7 +1832,6 @@ void ring_backward_launch(adseq* h, hipStream_t st, long long T, float dscale, c
     }
   }
   close_group(h, st, 3);
-  const unsigned gf = (unsigned)(d.N < 65536 ? d.N : 65536);
   hipLaunchKernelGGL(k_grad_finish, dim3(gf), block, 0, st, d, dscale, grad_w, grad_d);
 }
 
@@ -2046,6 +2073,21 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
         (adm || syn || d.BN % 4 != 0 || vp.chunk > 4 * kResThreads || !(resident_fits((const void*)k_bwd_xcd<true>) && resident_fits((const void*)k_bwd_xcd<false>))))
       vp = ResidentPlan();
     h->rev_chunk = vp.chunk; h->rev_P = vp.P; h->rev_npt = vp.npt;
+  }
+  if ((d.kind == ADSEQ_RING || d.sorted_rev) && d.record && syn < 2) {
+    // k_bwd_trial: ADSEQ_REVERSE_TRIALS 0 never, 1 wherever it fits; unset: not where a knob asks for one of the other reverse kernels
+    int on = env_pow2("ADSEQ_REVERSE_TRIALS", 2, 0, 2);
+    if (on == 2)
+      for (const char* k : {"ADSEQ_RING_RESIDENT_REVERSE", "ADSEQ_RING_REVERSE_FLOW", "ADSEQ_RING_REVERSE_BLOCKS", "ADSEQ_RING_REVERSE_WINDOWS", "ADSEQ_RING_FLOW_WITHHOLD",
+                            "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_CHAIN", "ADSEQ_RING_LAZY_ROWS", "ADSEQ_RING_ASSUME_CUS"})
+        if (getenv(k)) on = 0;
+    h->rtrial_always = on == 1;
+    if (on && d.N <= kTrialNeurons && d.B <= kTrialMost)
+      for (int P = 1; P <= kRevTrialPieces && !h->rtrial_P; ++P) {
+        long long H = (kRevTrialLds - rev_trial_fixed(d.N, P)) / (4LL * d.N);
+        if (H > d.d_max) H = d.d_max;
+        if (H * P >= d.d_max && (P == 1 || H >= 16) && P * ((d.N + 63) / 64 + 1) <= kRevTrialWords) { h->rtrial_H = (int)H; h->rtrial_P = P; }
+      }
   }
   if ((d.kind == ADSEQ_FIFO || d.kind == ADSEQ_SORTED) && d.qsteps >= 2 && (double)d.B * (double)d.S * 2.0 <= (double)d.pool_cap) {
     // (half of the overflow pool has room for every synapse of every trial)
@@ -2416,14 +2458,26 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   // per step unless the whole window sits in the caches -- so by default only up to 1,024 state
   // cells; ADSEQ_RING_REVERSE_WINDOWS = 1: always, 0: never)
   const int rw = env_pow2("ADSEQ_RING_REVERSE_WINDOWS", 2, 0, 2);
+  // the error word and what follows it, up to the spikes on the tape (k_tape_total)
+  constexpr size_t kErrBytes = offsetof(Counters, in_flight) + sizeof(unsigned long long) - offsetof(Counters, err);
+  unsigned char head[kErrBytes] = {};
+  if (h->rtrial_P > 0 && !h->prof) hipLaunchKernelGGL(k_tape_total, dim3(1), dim3(1024), 0, st, d);
   const bool by_windows = d.kind == ADSEQ_RING && d.near_ev_cap > 0 && T > 0 && (rw == 1 || (rw == 2 && d.BN <= 1024));
   if (by_windows) {
     near_counts.resize(2 * (size_t)T);
     hipLaunchKernelGGL(k_bwd_near_counts, dim3((unsigned)(T < 4096 ? T : 4096)), dim3(kBlock), 0, st, d, T, d.near_counts);
     HIP_TRY(h, hipMemcpyAsync(near_counts.data(), d.near_counts, sizeof(int) * 2 * (size_t)T, hipMemcpyDeviceToHost, st));
   }
-  HIP_TRY(h, hipMemcpyAsync(&err, &d.ctr->err, sizeof(err), hipMemcpyDeviceToHost, st));
+  HIP_TRY(h, hipMemcpyAsync(head, &d.ctr->err, sizeof(head), hipMemcpyDeviceToHost, st));
   HIP_TRY(h, hipStreamSynchronize(st));
+  memcpy(&err, head, sizeof(err));
+  const bool bounded = d.kind != ADSEQ_RING;
+  bool trials = h->rtrial_P > 0 && !h->prof && T > 0;
+  if (trials && !h->rtrial_always) {
+    unsigned long long spikes = 0;
+    memcpy(&spikes, head + kErrBytes - sizeof(spikes), sizeof(spikes));
+    trials = (double)spikes * rev_trial_weight(d.S, d.N, h->rtrial_P, bounded) <= rev_trial_load(d.N, d.B, h->rtrial_P, bounded) * (double)T * (double)d.B;
+  }
   if (err & ERR_BARRIER)
     return fail(h, ADSEQ_E_HIP, "adseq_backward: a wait inside a resident kernel ran out (the blocks of a launch were not running together); the run is void, reset and run again");
   if (err & (ERR_TAPE_SPIKES | ERR_TAPE_EVENTS | ERR_POOL))
@@ -2433,12 +2487,11 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   const float dscale = d.alpha_r > 0.0f ? d.dt
                        : d.continuous ? (float)(1.0 / (double)d.tau) : (float)((double)d.dt / (double)d.tau);
   const dim3 block(kBlock), gn(grid_for((size_t)d.BN));
-  const bool bounded = d.kind != ADSEQ_RING;
   const size_t nst = d.alpha_r > 0.0f ? 2 : 1;
   if (!bounded || d.sorted_rev) {
-    WholeChipCall turn(h, st, (h->rev_P > 0 || h->chain) && T > 0);
+    WholeChipCall turn(h, st, !trials && (h->rev_P > 0 || h->chain) && T > 0);
     ring_backward_launch(h, st, T, dscale, dL_dcount, dL_dU, grad_w, grad_d, by_windows ? near_counts.data() : nullptr,
-                         h->rev_P > 0 && (!bounded || turn.on));
+                         h->rev_P > 0 && (!bounded || turn.on), trials);
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }

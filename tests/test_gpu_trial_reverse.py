@@ -1,0 +1,64 @@
+"""Reverse sweep of small networks in one launch, a workgroup per trial (k_bwd_trial), against the oracle: both gradients, gradient modes,
+cotangents, queue kinds; rows of a run in LDS as a whole and in pieces, sizes around a wavefront and the largest, trials that share
+spike words (with rows of another trial's spikes in front), empty rows, rows of more than 64 and 256 entries, steps with more pieces than
+are requested ahead and than the list holds, runs shorter than what is loaded ahead."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests.helpers import grad_close
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # n, b, fan, d_max, T, rate, tau_syn
+    (1, 1, 3, 4, 12, 3000.0, 0.0), (63, 3, 20, 30, 60, 300.0, 0.0), (64, 2, 150, 7, 50, 200.0, 5.0), (65, 4, 10, 250, 300, 150.0, 0.0),
+    (100, 1, 300, 60, 90, 900.0, 0.0), (513, 2, 40, 200, 230, 60.0, 5.0), (1000, 3, 60, 50, 70, 100.0, 0.0), (1024, 1, 30, 120, 140, 3000.0, 0.0),
+    (1023, 2, 700, 45, 40, 40.0, 0.0), (200, 2, 12, 9, 3, 2000.0, 0.0)]
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.RING, 0), (adseq.FIFO, 3), (adseq.SORTED, 20), (adseq.SYN_LATEST, 1)])
+@pytest.mark.parametrize("n,b,fan,d_max,T,rate,tau_syn", CASES)
+def test_trial_reverse(kind, cap, n, b, fan, d_max, T, rate, tau_syn, monkeypatch):
+    monkeypatch.setenv("ADSEQ_REVERSE_TRIALS", "1")     # whatever spikes
+    wl = synth.ragged_network(n, fan, d_max, seed=n + b, rate_hz=rate, t=T, b=b, w_mean=0.4 / fan, w_std=0.5 / fan)
+    wl.tau_syn_ms = tau_syn
+    rng = np.random.default_rng(n)
+    for mode, du in ((adseq.SURR_SUPERSPIKE, False), (adseq.GRAD_SPIKE_TIME, True)):
+        ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, surrogate=mode)
+        sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T, surrogate=mode, tape_spike_capacity=T * b * n + 64,
+                          tape_event_capacity=(T * b + 1) * wl.n_synapses + 64)
+        sim.run(0, T)
+        dc = None if du else rng.normal(0, 1e-2, (b, n)).astype(np.float32)
+        dU = rng.normal(0, 1e-2, (T, b, n)).astype(np.float32) if du else None
+        gw, gd = ref.backward(dc, dU)
+        g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+        for _ in range(2):
+            sim.backward(None if dc is None else torch.from_numpy(dc).to(sim.dev), None if dU is None else torch.from_numpy(dU).to(sim.dev), g_w, g_d)
+            # (an element may be what is left of terms as large as the largest gradient: fp32 sums of them in another order differ by some
+            # eight roundings, 8 x 6e-8 of it, which the absolute part has to allow beyond 1e-6)
+            for got, want in ((g_w, gw), (g_d, gd)):
+                grad_close(got.cpu().numpy(), want, atol=1e-6 + 5e-7 * float(np.abs(want).max(initial=0.0)))
+        sim.close()
+
+
+def _kernels(call):
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.name for e in p.events())
+
+
+@pytest.mark.parametrize("rate,trials", [(20.0, True), (3000.0, False)])
+def test_the_line_is_on_the_spikes(rate, trials):
+    """Few spikes: a workgroup per trial; many: the kernels over the whole chip."""
+    n, T = 900, 80
+    wl = synth.ragged_network(n, 60, 50, seed=3, rate_hz=rate, t=T, b=8, w_mean=0.001, w_std=0.001)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=8, record_tape=True, max_steps=T)
+    sim.run(0, T)
+    g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+    names = _kernels(lambda: sim.backward(torch.ones(8 * n, device=sim.dev), None, g_w, g_d))
+    assert ("k_bwd_trial" in names) == trials and ("k_bwd_flow" in names) != trials
+    sim.close()
