@@ -551,6 +551,7 @@ struct adseq {
   bool rev_flow = false;                      // RING: the resident reverse kernel without a grid barrier (ring_flow_reverse.h)
   int fwd_P = 0, fwd_chunk = 0;                // RING: the same for the forward kernel over the whole chip (ring_resident_forward.h; 0: not used)
   int q_P = 0, q_chunk = 0;                    // FIFO / SORTED: the same for k_queue_run (0: two launches per step)
+  QTrial q_trial = {nullptr, nullptr, 0};      // ... with a block per trial (words 0: not used)
   int syn_P = 0, syn_chunk = 0, syn_near = 0;  // SYN_*: the same for k_syn_run (0: three launches per step), row-front entries in LDS
   bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
   bool syn_live = false;                       // the events in flight may be in the spike words (Counters::syn_live knows: a graph's replay changes it)
@@ -584,7 +585,7 @@ namespace {
 struct Layout {
   size_t syn_cells, syn_mask, syn_flagged, claims, full_bits, V, J, bwd_carryJ, win, spike_bits, drive_words, sq_next, sq_hs, sq_key, sq_flag, I_acc, last_evb, slot, fkey, famp, vmask, occ, head, min_k, cnt, cont, c_head, pool_p, pool_t, pool_next,
       pool_k, pool_a, spk_words, stepcnt, packed, a_q, synf, synb, dstart, nearcnt, perm, rowsum, rowlen, ebuf, ecnt, amp, fdec, tapeU,
-      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk, pull, pull_pos, pull_hist, open_steps,
+      tape_bits, spk_count, step_off, step_evoff, tape_spk, tape_evb, tape_row, tape_adm, bwd_ring, bwd_carry, bwd_G, gwin, Gacc, gsum, adm_base, adm_bits, insum, wspk, near_cnt, near_ev, near_spk, near_counts, ctr, blk, pull, pull_pos, pull_hist, open_steps, trial_bits, trial_evb,
       total;
   long long spike_cap, event_cap, pool_cap;
   int R, dbits, nblk, words;
@@ -592,6 +593,7 @@ struct Layout {
   int near_ev_cap;
   int pull_parts, pull_pt, pull_lb, pull_hist_windows;   // RING: ring_pull.h (0: not used)
   int qsteps;           // FIFO / SORTED: contender buffers
+  int trial_words;      // FIFO / SORTED: spike words of a trial where k_queue_run gives every block a trial (0: it does not)
   int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
 };
@@ -711,6 +713,21 @@ ResidentPlan queue_plan(long long BN) {
   }
   return r;
 }
+// k_queue_run with a block per trial: up to 4,096 neurons, where there are so many trials, or neurons so few, that a trial's events are not
+// the sooner done by several compute units.  us per step by blocks over the whole chip / so, at 0.1 / 1 / 5 / 20 spikes per step and trial:
+//   FIFO[4]: 100 x 10, one trial 2.3 4.4 6.7 10.4 / 1.7 3.8 6.2 10.1; 300 x 100, 4 trials 3.3 5.9 8.4 23.6 / 2.5 4.9 8.3 21.2, one 2.7 4.7 7.1 19.4 / 2.6 4.7 7.5 20.6;
+//   500 x 50, 64 trials 4.9 6.7 8.2 12.8 / 2.4 4.6 6.7 9.9, 16 4.0 6.0 7.2 10.9 / 2.6 4.8 7.3 10.2; 1,000 x 100, 256 trials 7.1 10.6 16.1 - / 3.6 6.3 10.1 -, 64 5.1 7.3
+//   9.7 13.8 / 3.5 6.1 9.6 19.4; 4,096 x 256, 256 trials 12.1 20.5 39.6 - / 7.9 14.3 24.4 -; SORTED[64] 12.6 29.8 144 - / 7.6 19.0 89 -.
+// ADSEQ_QUEUE_TRIALS: 0 never, 1 wherever it fits; unset: not where a knob asks for the other kernels or their waits.
+bool queue_trials(const adseq_config* c) {
+  const int on = env_pow2("ADSEQ_QUEUE_TRIALS", 2, 0, 2);
+  if (on == 0 || c->n_neurons > 8 * kResThreads || c->n_synapses > 0x7fffffffLL) return false;
+  if (on == 1) return true;
+  const int least = c->n_neurons <= 128 ? 1 : (c->n_neurons <= 320 ? 4 : (c->n_neurons <= kResThreads ? 32 : 192));   // trials
+  if (c->batch < least) return false;
+  for (const char* k : {"ADSEQ_QUEUE_RESIDENT", "ADSEQ_QUEUE_BLOCKS", "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_ASSUME_CUS"}) if (getenv(k)) return false;
+  return true;
+}
 // log2 of the lanes that take a row piece, whose mean length is row / d_max: few pieces are longer, whose rest is a trip more.
 int piece_lanes(const adseq_config* c) {
   const double piece = (double)c->n_synapses / c->n_neurons / c->d_max_steps;
@@ -779,18 +796,29 @@ SynKernel syn_kernel(int kind, int capacity, int chunk) {
   if (chunk <= kResThreads) return deep ? k_syn_run<1, true, true> : k_syn_run<1, true, false>;
   return deep ? k_syn_run<4, true, true> : k_syn_run<4, true, false>;
 }
-typedef void (*QueueKernel)(long long, int, unsigned, int, int, int, unsigned long long*, Dev);
+typedef void (*QueueKernel)(long long, int, unsigned, int, int, int, unsigned long long*, QTrial, Dev);
 template <int KIND, bool RECORD>
 QueueKernel queue_kernel_of(int chunk) {
-  if (chunk <= kResThreads) return k_queue_run<KIND, RECORD, 1, false>;
-  if (chunk <= 4 * kResThreads) return k_queue_run<KIND, RECORD, 4, false>;
-  return k_queue_run<KIND, RECORD, 8, false>;
+  if (chunk <= kResThreads) return k_queue_run<KIND, RECORD, 1, false, false, 0>;
+  if (chunk <= 4 * kResThreads) return k_queue_run<KIND, RECORD, 4, false, false, 0>;
+  return k_queue_run<KIND, RECORD, 8, false, false, 0>;
 }
 QueueKernel queue_kernel(int kind, bool record, int chunk, int capacity) {
   if (kind == ADSEQ_FIFO && chunk <= kResThreads && capacity <= 32)   // (the slots in LDS)
-    return record ? k_queue_run<ADSEQ_FIFO, true, 1, true> : k_queue_run<ADSEQ_FIFO, false, 1, true>;
+    return record ? k_queue_run<ADSEQ_FIFO, true, 1, true, false, 0> : k_queue_run<ADSEQ_FIFO, false, 1, true, false, 0>;
   if (kind == ADSEQ_FIFO) return record ? queue_kernel_of<ADSEQ_FIFO, true>(chunk) : queue_kernel_of<ADSEQ_FIFO, false>(chunk);
   return record ? queue_kernel_of<ADSEQ_SORTED, true>(chunk) : queue_kernel_of<ADSEQ_SORTED, false>(chunk);
+}
+template <int KIND>
+QueueKernel queue_trial_kernel_of(int N, bool syn) {
+  if (N <= kResThreads) return k_queue_run<KIND, true, 1, false, true, 1>;
+  if (N <= 2 * kResThreads) return k_queue_run<KIND, true, 2, false, true, 1>;
+  if (N <= 4 * kResThreads) return k_queue_run<KIND, true, 4, false, true, 1>;
+  return syn ? k_queue_run<KIND, true, 8, false, true, 0> : k_queue_run<KIND, true, 8, false, true, 2>;
+}
+QueueKernel queue_trial_kernel(int kind, int N, int capacity, bool syn) {
+  if (kind == ADSEQ_FIFO && N <= kResThreads && capacity <= 32) return k_queue_run<ADSEQ_FIFO, true, 1, true, true, 1>;   // (the slots in LDS)
+  return kind == ADSEQ_FIFO ? queue_trial_kernel_of<ADSEQ_FIFO>(N, syn) : queue_trial_kernel_of<ADSEQ_SORTED>(N, syn);
 }
 template <bool RECORD>
 const void* run_xcd_kernel_of(int syn, int npt) {
@@ -1058,6 +1086,12 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->tape_evb = take(bounded ? (size_t)L->spike_cap * 8 : 0);
   L->tape_row = take(!windows ? (size_t)L->spike_cap * sizeof(RowSpan) : 0);
   L->tape_adm = take((size_t)L->event_cap);
+  L->trial_words = ptq && sorted_rev && L->qsteps >= 2 && !small && queue_trials(c) ? (c->n_neurons + 63) / 64 : 0;
+  {
+    const size_t steps = T < (size_t)kTrialQueueSteps ? T : (size_t)kTrialQueueSteps;
+    L->trial_bits = take(steps * c->batch * L->trial_words * 8);
+    L->trial_evb = take(steps * c->batch * L->trial_words * 8);
+  }
   const bool tape = c->record_tape != 0;
   L->bwd_ring = take(tape && !windows ? nstates * (size_t)L->R * BN * 4 : 0);
   L->bwd_carry = take(tape ? BN * 4 : 0);
@@ -1613,9 +1647,15 @@ void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_s
     const bool record = d.record && h->tape_ok && n < d.max_steps;
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
     if (d.record && n >= d.max_steps) h->tape_ok = false;
-    hipLaunchKernelGGL(queue_kernel(d.kind, record, h->q_chunk, d.C), dim3((unsigned)(h->q_P * stride)), dim3(kResLaunch), 0, st, n, cnt, h->rev_base,
-                       h->q_P, h->q_chunk, stride, d.claims, d);
-    h->rev_base += (unsigned)cnt * (unsigned)h->q_P;
+    if (record && h->q_trial.words > 0) {
+      if (cnt > kTrialQueueSteps) cnt = kTrialQueueSteps;
+      hipLaunchKernelGGL(queue_trial_kernel(d.kind, d.N, d.C, d.alpha_s > 0.0f), dim3((unsigned)d.B), dim3(kResLaunch), 0, st, n, cnt, 0u, d.B, d.N, 1, d.claims, h->q_trial, d);
+      hipLaunchKernelGGL(k_trial_list, dim3((unsigned)cnt), dim3(kBlock), 0, st, d, n, h->q_trial);
+    } else {
+      hipLaunchKernelGGL(queue_kernel(d.kind, record, h->q_chunk, d.C), dim3((unsigned)(h->q_P * stride)), dim3(kResLaunch), 0, st, n, cnt, h->rev_base,
+                         h->q_P, h->q_chunk, stride, d.claims, h->q_trial, d);
+      h->rev_base += (unsigned)cnt * (unsigned)h->q_P;
+    }
     h->enq_calls += cnt;
     n += cnt;
     h->next_step = n;
@@ -2094,6 +2134,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     ResidentPlan qp = queue_plan((long long)d.BN);
     if (qp.P > 0 && resident_fits((const void*)queue_kernel(d.kind, true, qp.chunk, d.C)) && resident_fits((const void*)queue_kernel(d.kind, false, qp.chunk, d.C))) {
       h->q_P = qp.P; h->q_chunk = qp.chunk;
+      if (L.trial_words > 0) h->q_trial = {(unsigned long long*)(ws + L.trial_bits), (long long*)(ws + L.trial_evb), L.trial_words};
     }
   }
   if (d.syn_R2 > 0) {

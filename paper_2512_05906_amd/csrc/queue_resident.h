@@ -38,6 +38,10 @@ constexpr int kQueueItems = 1024;   // row pieces of a step that are shared out 
 // the row's flags, counted from the block's first event of the step.
 struct QItem { long long p; int cnt, base, ev, evend; };
 
+// TRIAL: per step of the launch, trial and 64 of its neurons, the spikes and where the first one's admission flags begin.
+struct QTrial { unsigned long long* bits; long long* evb; int words; };
+constexpr int kTrialQueueSteps = 256;   // steps of a launch
+
 // Phase clocks (builds with ADSEQ_PHASE_CLOCK only): ticks of 10 ns that thread 0 of the first block spent in each phase of
 // a step, in Counters::phase: [0] pops, [1] waiting, [2] admission, [3] update, [4] pieces written, [5] tickets and records,
 // [6] until the arrival, [7] tape.
@@ -52,15 +56,19 @@ struct QItem { long long p; int cnt, base, ev, evend; };
 #endif
 
 // LS: the slots of FIFO targets are in LDS too, for up to 32 of them and one target per thread.
-template <int NPT, bool LS>
+// LC (TRIAL): contender counts are in LDS too, so that a ticket is no trip to memory; 2: in the place of the synaptic current states (delta
+// synapse, eight targets per thread).
+template <int NPT, bool LS, int LC>
 struct QueueLds {
   static constexpr int kTargets = NPT * kResThreads;
   int acc[kTargets];            // Q8.24 sum delivered in the step; from its spike to the step's end, a spiking neuron's membrane value
   unsigned mw[kTargets];        // FIFO: first mask word; SORTED: index of the front
   unsigned mn[kTargets];        // earliest stored arrival step (0xffffffff: none)
   int occ[kTargets];            // stored events | events popped in the step << 16; from its spike to the step's end, a spike's number in the block << 16
-  float J[kTargets], Jf[kTargets];   // synaptic current states
-  unsigned long long full[NPT == 1 ? 2048 : 1];   // the whole network's targets that stay full in this step (at most 256 x 512)
+  float J[LC == 2 ? 1 : kTargets], Jf[LC == 2 ? 1 : kTargets];   // synaptic current states
+  int cnt[LC ? 2 : 1][LC ? kTargets : 1];   // contenders, by buffer
+  unsigned long long full[NPT == 1 ? 2048 : 1];   // the whole network's targets that stay full in this step (at most 256 x 512); TRIAL: the trial's, by step parity [2][8]
+  int pool_n[2];                // TRIAL: entries taken of the block's shares of the overflow list, by buffer
   int2 list[kTargets];          // targets to work off: place, contenders; then by a spiking neuron's place: its first piece, its first event
   QItem item[kQueueItems];
   alignas(16) unsigned short key[LS ? kTargets : 1][32];
@@ -80,15 +88,15 @@ __device__ __forceinline__ void cont_store(const Dev& d, const QBuf& qb, int x, 
   __builtin_amdgcn_raw_buffer_store_b128(v, res_rows(qb.cont, kCont * d.BN * 16), (x * d.BN + g) * 16, 0, kBufAgent);
 }
 
-template <int KIND, int NPT, bool LS>
-__device__ __forceinline__ QState qstate_of(const QueueLds<NPT, LS>& L, int t) {
+template <int KIND, int NPT, bool LS, int LC>
+__device__ __forceinline__ QState qstate_of(const QueueLds<NPT, LS, LC>& L, int t) {
   QState q;
   q.occ = L.occ[t] & 0xffff; q.mn = L.mn[t]; q.m0 = L.mw[t]; q.hd = (int)L.mw[t];
   return q;
 }
 // The events of target g (place t) that are due at step kn leave its queue.
-template <int KIND, int NPT, bool LS>
-__device__ __forceinline__ void pop_target(const Dev& d, QueueLds<NPT, LS>& L, int t, int g, unsigned kn, StepAcc& r, long long& s_del) {
+template <int KIND, int NPT, bool LS, int LC>
+__device__ __forceinline__ void pop_target(const Dev& d, QueueLds<NPT, LS, LC>& L, int t, int g, unsigned kn, StepAcc& r, long long& s_del) {
   QState q = qstate_of<KIND>(L, t);
   const int before = q.occ;
   r.acc = 0;
@@ -108,14 +116,15 @@ __device__ __forceinline__ void pop_target(const Dev& d, QueueLds<NPT, LS>& L, i
 // selected as often as there is room.  (Selecting in either case, an entry and then the link to the next, took longer than
 // two launches per step: 16,000 targets, 25 contenders for each in every step, us per step: SORTED[128] with room for all 1,002 -> 176,
 // two launches 262; FIFO[32], one event in six dropped, 693 -> 496, two launches 530; 10 contenders 194 -> 60, two launches 103.)
-template <int KIND, bool RECORD, int NPT, bool LS>
-__device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L, const QBuf& qb, int t, int g, int K, unsigned kn, bool deliver,
+// buf: the contender buffer's index.
+template <int KIND, bool RECORD, int NPT, bool LS, int LC>
+__device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS, LC>& L, const QBuf& qb, int buf, int t, int g, int K, unsigned kn, bool deliver,
                                              const uint4& c0, const uint4& c1, StepAcc& r, long long& s_del) {
   QState q = qstate_of<KIND>(L, t);
   const int room = d.C - q.occ - (L.occ[t] >> 16);   // what the contenders found when they were emitted
   const int take = K < room ? K : room;
   int acc = 0;
-  q_store<true>(&qb.cnt[g], 0);
+  if (LC) L.cnt[buf][t] = 0; else q_store<true>(&qb.cnt[g], 0);
   auto flag_it = [&](long long f, int won) { if (f >= 0 && f < d.event_cap) d.tape_adm[f] = (unsigned char)won; };
   auto linked = [&](int y) { return y >= 0 && y < d.pool_cap; };
   auto take_in = [&](unsigned k, int a) {
@@ -219,16 +228,24 @@ __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS>& L,
 // targets; thread t of a block owns the places t, t + 512, ... .  bar_base: sum of the arrival counters when the launch
 // begins; every block arrives nsteps times.  RECORD: the tape is written (claims: one counter per step, zero).  No
 // contender is pending when the launch begins, and none when it ends.
-template <int KIND, bool RECORD, int NPT, bool LS>
+// TRIAL: every block owns one whole trial (rank: the trial, chunk = N), so that no block has anything to do with another one's events: the grid
+// barrier goes -- a step then takes as long as a block's own, not as the longest of all blocks', whose spikes cost 5 us each time.  The tape's
+// spike list is ordered by step over all trials, which nobody knows any more while the blocks run apart: a block claims places for its
+// events' flags as it comes to them (claims[max_steps] counts the launch's; tape_evb says where they are, in whatever order) and leaves its
+// spike words and where their events begin for k_trial_list.  The block has shares of its own of the overflow list.  RECORD only.
+// 256 x 4,096 neurons, sorted[128]: 11.2 -> 6.7 us per step; queue_trials (adseq.hip) has the sizes.
+template <int KIND, bool RECORD, int NPT, bool LS, bool TRIAL, int LC>
 __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nsteps, unsigned bar_base, int P, int chunk, int stride,
-                                                          unsigned long long* __restrict__ claims, Dev d) {
-  __shared__ QueueLds<NPT, LS> L;
+                                                          unsigned long long* __restrict__ claims, QTrial tr, Dev d) {
+  static_assert(TRIAL || LC == 0, "counts in LDS: a block's own targets");
+  __shared__ QueueLds<NPT, LS, LC> L;
   if (blockIdx.x % stride) return;
   const int rank = blockIdx.x / stride;
   if (rank >= P) return;
   if (threadIdx.x == 0) {
     L.dead = (ld_agent(&d.ctr->err) & ERR_BARRIER) ? 1 : 0;
     L.n_list[0] = 0; L.n_list[1] = 0; L.items = 0; L.claim = 0ull; L.got = 0ull;
+    L.pool_n[0] = 0; L.pool_n[1] = 0;
     if (RECORD) { L.sp_base = d.step_off[n0]; L.ev_base = d.step_evoff[n0]; }
   }
   const bool worker = threadIdx.x < kResThreads;   // uniform per wavefront
@@ -238,7 +255,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
     for (int k = 0; k <= nsteps; ++k) {
       const bool last = k == nsteps;
       if (!last && NPT > 1) { __syncthreads(); __syncthreads(); }          // step before written up; due targets listed
-      if (k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &L.dead); else __syncthreads();
+      if (!TRIAL && k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &L.dead); else __syncthreads();
       if (NPT > 1) __syncthreads();                                        // targets with contenders listed
       __syncthreads();                                                     // admitted
       if (last) break;
@@ -248,12 +265,15 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       for (int b0 = 0; b0 < total || (RECORD && b0 == 0 && claim); b0 += kQueueItems) {
         __syncthreads();                                                   // pieces written
         if (RECORD && b0 == 0) {
-          if (threadIdx.x == kResThreads && claim) L.got = atomicAdd(&claims[n0 + k], claim);
+          if (threadIdx.x == kResThreads && claim) {
+            if (TRIAL) atomicAdd(&claims[n0 + k], claim);   // (what the step comes to, for k_trial_list)
+            L.got = atomicAdd(&claims[TRIAL ? d.max_steps : n0 + k], claim);
+          }
           __syncthreads();                                                 // places claimed
         }
         if (b0 + kQueueItems < total) __syncthreads();                     // pieces taken
       }
-      rev_arrive(d, true, rank);
+      if (TRIAL) __syncthreads(); else rev_arrive(d, true, rank);
     }
     return;
   }
@@ -261,7 +281,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
   constexpr int kWaves = kResThreads / 64;
   const int lo = rank * chunk;
   const int hi = lo + chunk < d.BN ? lo + chunk : d.BN;
-  const bool syn = d.alpha_s > 0.0f, dexp = d.alpha_r > 0.0f;
+  const bool syn = LC != 2 && d.alpha_s > 0.0f, dexp = LC != 2 && d.alpha_r > 0.0f;
   const unsigned long long G64 = 0x9E3779B97F4A7C15ull;
   float V[NPT];
   int r0[NPT], rlen[NPT];   // (2 B S entries fit the overflow pool: B S < 2^30)
@@ -275,7 +295,10 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
   for (int c = 0; c < NPT; ++c) {
     const int t = c * kResThreads + tid, g = lo + t;
     V[c] = 0.0f; r0[c] = 0; rlen[c] = 0; zg[c] = 0ull;
-    L.acc[t] = 0; L.J[t] = 0.0f; L.Jf[t] = 0.0f; L.mw[t] = 0u; L.mn[t] = 0xffffffffu; L.occ[t] = 0;
+    if (LC) { L.cnt[0][t] = 0; L.cnt[1][t] = 0; }
+    L.acc[t] = 0;
+    if (LC != 2) { L.J[t] = 0.0f; L.Jf[t] = 0.0f; }
+    L.mw[t] = 0u; L.mn[t] = 0xffffffffu; L.occ[t] = 0;
     if (g < hi) {
       actmask |= 1u << c;
       const int i = g - trial_of(d, g) * d.N;
@@ -293,7 +316,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       L.occ[t] = q.occ; L.mn[t] = q.mn; L.mw[t] = KIND == ADSEQ_FIFO ? q.m0 : (unsigned)q.hd;
     }
   }
-  if (NPT == 1) for (int w = tid; w < d.words; w += kResThreads) L.full[w & 2047] = 0ull;
+  if (NPT == 1) for (int w = tid; w < (TRIAL ? 16 : d.words); w += kResThreads) L.full[w & 2047] = 0ull;
   // appends the lane's target (place t) to the block's list
   auto enlist = [&](int* n, bool want, int t, int K) {
     const unsigned long long m = __ballot(want);
@@ -334,34 +357,40 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
     }
     QPH(0)
     // ---- every block has registered the contenders of step n - 1
-    if (k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &L.dead); else __syncthreads();
+    if (!TRIAL && k > 0) rev_wait(d, bar_base + (unsigned)k * (unsigned)P, &L.dead); else __syncthreads();
     QPH(1)
-    const QBuf in = queue_buf_half(d, (k & 1) ^ 1), out = queue_buf_half(d, k & 1);
+    QBuf in = queue_buf_half(d, (k & 1) ^ 1), out = queue_buf_half(d, k & 1);
+    if (TRIAL) {   // (a trial's synapses fit a share)
+      const int share = (int)d.S;
+      in.pool0 += rank * share; in.pool_cap = share; in.pool_n = &L.pool_n[(k & 1) ^ 1];
+      if (LC) { in.cnt = &L.cnt[(k & 1) ^ 1][0] - lo; out.cnt = &L.cnt[k & 1][0] - lo; }   // (generic pointers, for the way that is hardly ever taken)
+      out.pool0 += rank * share; out.pool_cap = share; out.pool_n = &L.pool_n[k & 1];
+    }
     unsigned long long before = 0ull;   // what the blocks claimed in step n - 1 (one thread)
-    if (RECORD && k > 0 && tid == kResThreads - 1) before = __hip_atomic_load(&claims[n - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (RECORD && !TRIAL && k > 0 && tid == kResThreads - 1) before = __hip_atomic_load(&claims[n - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned long long stay[4];   // targets that stay full in this step, as their owners saw it coming in the last one
     if (NPT == 1) {
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const int w = tid + x * kResThreads;
         stay[x] = 0ull;
-        if (k > 0 && w < d.words) stay[x] = q_load<true>(&d.full_bits[(size_t)((k & 1) ^ 1) * d.words + w]);
+        if (!TRIAL && k > 0 && w < d.words) stay[x] = q_load<true>(&d.full_bits[(size_t)((k & 1) ^ 1) * d.words + w]);
       }
       if (k > 0 && (actmask & 1u)) {
         const int g = lo + tid;
-        const int K = ld_agent(&in.cnt[g]);
+        const int K = LC ? L.cnt[(k & 1) ^ 1][tid] : ld_agent(&in.cnt[g]);
         // (the first two records are requested beside the count: most targets that have contenders have no more)
         const uint4 c0 = cont_load(d, in, 0, g), c1 = cont_load(d, in, 1, g);
-        if (K > 0) admit_target<KIND, RECORD>(d, L, in, tid, g, K, kn, !last, c0, c1, r, s_del);
+        if (K > 0) admit_target<KIND, RECORD>(d, L, in, (k & 1) ^ 1, tid, g, K, kn, !last, c0, c1, r, s_del);
       }
 #pragma unroll
-      for (int x = 0; x < 4; ++x) { const int w = tid + x * kResThreads; if (w < d.words && w < 2048) L.full[w] = stay[x]; }
+      for (int x = 0; x < 4; ++x) { const int w = tid + x * kResThreads; if (!TRIAL && w < d.words && w < 2048) L.full[w] = stay[x]; }
     } else {
       if (tid == 0) L.n_list[0] = 0;
       int K[NPT];
 #pragma unroll
       for (int c = 0; c < NPT; ++c)   // (past the block's last target: zero)
-        K[c] = __builtin_amdgcn_raw_buffer_load_b32(res_rows(in.cnt, k > 0 ? hi * 4 : 0), voff, c * kRow, kBufAgent);
+        K[c] = LC ? (k > 0 ? L.cnt[(k & 1) ^ 1][c * kResThreads + tid] : 0) : __builtin_amdgcn_raw_buffer_load_b32(res_rows(in.cnt, k > 0 ? hi * 4 : 0), voff, c * kRow, kBufAgent);
 #pragma unroll
       for (int c = 0; c < NPT; ++c) enlist(&L.n_list[1], K[c] > 0, c * kResThreads + tid, K[c]);
       __syncthreads();
@@ -369,11 +398,12 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       for (int x = tid; x < offered; x += kResThreads) {
         const int t = L.list[x].x, Kt = L.list[x].y, g = lo + t;
         const uint4 c0 = cont_load(d, in, 0, g), c1 = cont_load(d, in, 1, g);
-        admit_target<KIND, RECORD>(d, L, in, t, g, Kt, kn, !last, c0, c1, r, s_del);
+        admit_target<KIND, RECORD>(d, L, in, (k & 1) ^ 1, t, g, Kt, kn, !last, c0, c1, r, s_del);
       }
     }
-    if (rank == 0 && tid == 0) q_store<true>(in.pool_n, 0);   // (its entries are being consumed; the next ones come a barrier later)
-    if (RECORD && k > 0 && tid == kResThreads - 1) {
+    if (TRIAL) { if (tid == 0) L.pool_n[(k & 1) ^ 1] = 0; }
+    else if (rank == 0 && tid == 0) q_store<true>(in.pool_n, 0);   // (its entries are being consumed; the next ones come a barrier later)
+    if (RECORD && !TRIAL && k > 0 && tid == kResThreads - 1) {
       L.sp_base += (long long)(before >> 40); L.ev_base += (long long)(before & ((1ull << 40) - 1ull));
       if (rank == 0) { d.step_off[n] = L.sp_base; d.step_evoff[n] = L.ev_base; }
     }
@@ -407,9 +437,11 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       smask |= s ? 1u << c : 0u;
       if (NPT == 1) {
         const unsigned long long f = __ballot((actmask & 1u) && (o & 0xffff) == d.C && L.mn[t] != kn + 1u);
-        if (lane == 0 && lo + tid < hi) q_store<true>(&d.full_bits[(size_t)(k & 1) * d.words + ((lo + tid) >> 6)], f);
+        if (TRIAL) { if (lane == 0) L.full[(k & 1) * 8 + wave] = f; }
+        else if (lane == 0 && lo + tid < hi) q_store<true>(&d.full_bits[(size_t)(k & 1) * d.words + ((lo + tid) >> 6)], f);
       }
       const unsigned long long m = __ballot(s);
+      if (TRIAL && lane == 0 && c * 8 + wave < tr.words) tr.bits[((size_t)k * P + rank) * tr.words + c * 8 + wave] = m;
       if (m) {   // uniform
         const int seg = s ? (rlen[c] + 63) >> 6 : 0, len = s ? rlen[c] : 0;
         const int segs = dpp_scan_add(seg), lens = dpp_scan_add(len);
@@ -475,8 +507,11 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
           tk[u] = -1;
           gt[u] = it[u].base + (int)(pk[u] >> d.dbits);
           bool open = lane < it[u].cnt;
-          if (NPT == 1 && open) open = !((L.full[(gt[u] >> 6) & 2047] >> (gt[u] & 63)) & 1ull);
-          if (open) tk[u] = atomicAdd(&out.cnt[gt[u]], 1);
+          if (NPT == 1 && open) {
+            const int at = TRIAL ? gt[u] - lo : gt[u], w = TRIAL ? ((k & 1) ^ 1) * 8 + (at >> 6) : (at >> 6) & 2047;
+            open = !((L.full[w] >> (at & 63)) & 1ull);
+          }
+          if (open) tk[u] = LC ? atomicAdd(&L.cnt[k & 1][gt[u] - lo], 1) : atomicAdd(&out.cnt[gt[u]], 1);
         }
         if (first) { __syncthreads(); first = false; }
         const long long ev0 = RECORD ? L.ev_base + (long long)(L.got & ((1ull << 40) - 1ull)) : 0;
@@ -494,7 +529,7 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       if (b0 + kQueueItems < total) __syncthreads();
     }
     QPH(5)
-    rev_arrive(d, true, rank);
+    if (TRIAL) { __builtin_amdgcn_s_waitcnt(0x0F70); __syncthreads(); } else rev_arrive(d, true, rank);
     QPH(6)
     // ---- after the arrival, off the chain: tape, counts
     if (RECORD) {
@@ -514,6 +549,12 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
         if (RECORD) {
           atomicAdd(&d.spk_count[g], 1);
           const long long at = L.sp_base + (long long)(L.got >> 40) + (o >> 16);
+          if (TRIAL) {   // where the events of the word's first spike begin; that all find room is looked at with the list
+            const unsigned long long m = __ballot((smask >> c) & 1u);
+            if (lane == __ffsll((long long)m) - 1)
+              tr.evb[((size_t)k * P + rank) * tr.words + c * 8 + wave] = L.ev_base + (long long)(L.got & ((1ull << 40) - 1ull)) + L.list[t].y;
+            continue;
+          }
           long long evb = L.ev_base + (long long)(L.got & ((1ull << 40) - 1ull)) + L.list[t].y;
           if (evb + rlen[c] > d.event_cap) { evb = -1; atomicOr(&d.ctr->err, ERR_TAPE_EVENTS); }
           if (at < d.spike_cap) {
@@ -541,15 +582,68 @@ __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nste
       if (KIND == ADSEQ_FIFO) d.vmask[(size_t)g * d.nw] = L.mw[t];
       else { d.head[g] = (int)L.mw[t]; d.min_k[g] = L.mn[t]; }
     }
-  if (RECORD && rank == 0 && tid == kResThreads - 1) { d.ctr->tape_spikes = L.sp_base; d.ctr->tape_events = L.ev_base; }
+  if (RECORD && !TRIAL && rank == 0 && tid == kResThreads - 1) { d.ctr->tape_spikes = L.sp_base; d.ctr->tape_events = L.ev_base; }
   const long long t_pop = wave_total64(r.popped), t_adm = wave_total64(r.c_adm), t_sadm = wave_total64(r.s_adm), t_del = wave_total64(s_del);
   const long long t_off = wave_total64(c_off), t_soff = wave_total64(s_off);
   if (lane == 0) {
-    BlkCtr& bc = d.blk[rank];
+    BlkCtr& bc = d.blk[TRIAL ? rank % d.nblk : rank];
     if (t_pop) atomicAdd(&bc.delivered, (unsigned long long)t_pop);
     if (t_adm) { atomicAdd(&bc.admitted, (unsigned long long)t_adm); atomicAdd((unsigned long long*)&bc.sum_admitted, (unsigned long long)t_sadm); }
     if (t_del) atomicAdd((unsigned long long*)&bc.sum_delivered, (unsigned long long)t_del);
     if (t_off) { atomicAdd(&bc.offered, (unsigned long long)t_off); atomicAdd((unsigned long long*)&bc.sum_offered, (unsigned long long)t_soff); }
+  }
+}
+
+// The spike list of steps n0 .. n0 + gridDim.x - 1, run by k_queue_run<TRIAL> in one launch: a block per step.  Spikes ascend within a step.
+__global__ __launch_bounds__(kBlock) void k_trial_list(Dev d, long long n0, QTrial tr) {
+  __shared__ long long s_red[2][kBlock / 64];
+  __shared__ int s_wave[kBlock / 64];
+  const int k = (int)blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long n = n0 + k;
+  constexpr unsigned long long kEvents = (1ull << 40) - 1ull;
+  // spikes and events of the steps before
+  long long sp = 0, ev = 0;
+  for (int j = threadIdx.x; j < k; j += kBlock) { const unsigned long long c = d.claims[n0 + j]; sp += (long long)(c >> 40); ev += (long long)(c & kEvents); }
+  sp = wave_total64(sp); ev = wave_total64(ev);
+  if (lane == 0) { s_red[0][wave] = sp; s_red[1][wave] = ev; }
+  __syncthreads();
+  sp = d.step_off[n0]; ev = d.step_evoff[n0];
+  for (int w = 0; w < kBlock / 64; ++w) { sp += s_red[0][w]; ev += s_red[1][w]; }
+  const unsigned long long mine = d.claims[n];
+  if (threadIdx.x == 0) {
+    d.step_off[n + 1] = sp + (long long)(mine >> 40); d.step_evoff[n + 1] = ev + (long long)(mine & kEvents);
+    if (k + 1 == (int)gridDim.x) {
+      d.ctr->tape_spikes = sp + (long long)(mine >> 40); d.ctr->tape_events = ev + (long long)(mine & kEvents);
+      d.claims[d.max_steps] = 0ull;   // (of the next launch)
+    }
+  }
+  if (mine == 0ull) return;
+  const int all = d.B * tr.words;
+  const unsigned long long* const bits = tr.bits + (size_t)k * all;
+  long long at = sp;
+  for (int x0 = 0; x0 < all; x0 += kBlock) {
+    const int x = x0 + (int)threadIdx.x;
+    unsigned long long m = x < all ? bits[x] : 0ull;
+    const int c = __popcll(m), incl = dpp_scan_add(c);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int w = 0; w < kBlock / 64; ++w) { if (w < wave) before += s_wave[w]; total += s_wave[w]; }
+    __syncthreads();
+    if (m) {
+      long long p = at + before + incl - c, e = tr.evb[(size_t)k * all + x];
+      const int b = x / tr.words, i0 = (x - b * tr.words) * 64;
+      for (; m; m &= m - 1ull, ++p) {
+        const int i = i0 + __ffsll((long long)m) - 1;
+        const long long len = d.row_ptr[i + 1] - d.row_ptr[i];
+        const bool fits = e + len <= d.event_cap;
+        if (!fits) atomicOr(&d.ctr->err, ERR_TAPE_EVENTS);
+        if (p < d.spike_cap) { d.tape_spk[p] = b * d.N + i; d.tape_evb[p] = fits ? e : -1; }
+        else atomicOr(&d.ctr->err, ERR_TAPE_SPIKES);
+        e += len;
+      }
+    }
+    at += total;
   }
 }
 

@@ -1484,14 +1484,29 @@ __global__ __launch_bounds__(kRingThreads) void k_bwd_win(Dev d, long long k0, l
 // 64) each, from adm_base[step][word] = (index of the first one's first flag) / 64 + (its number on the tape), so
 // that the ranges never overlap (sum of ceil(len / 64) <= (sum of len) / 64 + number of rows).
 // A wavefront takes a row 256 entries at a time: positions in the caller's row, then the flags there.
+// (events of the spikes before: counted, not taken from where the flags are, which need not be in the list's order, see k_trial_list)
 __global__ __launch_bounds__(kBlock) void k_tape_words(Dev d, long long T) {
+  __shared__ int s_wave[kBlock / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (long long n = blockIdx.x; n < T; n += gridDim.x) {
     const long long lo = d.step_off[n], hi = d.step_off[n + 1];
-    for (long long e = lo + threadIdx.x; e < hi; e += kBlock) {
-      const int g = d.tape_spk[e], word = g >> 6;     // (ascending within a step: see k_fanout_step)
-      atomicOr(&d.tape_bits[(size_t)n * d.words + word], 1ull << (g & 63));
-      if (e == lo || (d.tape_spk[e - 1] >> 6) != word)
-        d.adm_base[(size_t)n * d.words + word] = (unsigned)((d.tape_evb[e] >> 6) + e);
+    long long events = d.step_evoff[n];
+    for (long long e0 = lo; e0 < hi; e0 += kBlock) {   // uniform over the block
+      const long long e = e0 + threadIdx.x;
+      const int g = e < hi ? d.tape_spk[e] : 0, word = g >> 6;     // (ascending within a step: see k_fanout_step)
+      const int i = g - trial_of(d, g) * d.N, len = e < hi ? (int)(d.row_ptr[i + 1] - d.row_ptr[i]) : 0;
+      const int incl = dpp_scan_add(len);
+      if (lane == 63) s_wave[wave] = incl;
+      __syncthreads();
+      int before = 0, total = 0;
+      for (int w = 0; w < kBlock / 64; ++w) { if (w < wave) before += s_wave[w]; total += s_wave[w]; }
+      __syncthreads();
+      if (e < hi) {
+        atomicOr(&d.tape_bits[(size_t)n * d.words + word], 1ull << (g & 63));
+        if (e == lo || (d.tape_spk[e - 1] >> 6) != word)
+          d.adm_base[(size_t)n * d.words + word] = (unsigned)(((events + before + incl - len) >> 6) + e);
+      }
+      events += total;
     }
   }
 }
