@@ -557,6 +557,7 @@ struct adseq {
   bool syn_live = false;                       // the events in flight may be in the spike words (Counters::syn_live knows: a graph's replay changes it)
   bool syn_captured = false;                   // a call has been captured: replays may put steps of the queue arrays under the host's feet, so k_syn_run is not used any more
   unsigned long long syn_left_in = 0;          // the capture in which the queue arrays are in use from some point on
+  int trial_H = 0, trial_P = 1;                // ... rows of cells, pieces of a row
   int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
   int rtrial_H = 0, rtrial_P = 0;              // k_bwd_trial: adjoint rows in LDS, pieces of a row (0: not used)
   bool rtrial_always = false;                  // whatever spikes (ADSEQ_REVERSE_TRIALS = 1)
@@ -736,7 +737,7 @@ int piece_lanes(const adseq_config* c) {
 // k_trial_run: networks of up to 1,024 neurons and kTrialSynapses synapses whose delay line, with at least one entry of every row, fits
 // LDS (see ring_trial.h).  ADSEQ_RING_TRIALS: 0 never, 1 wherever it fits; unset: not where a knob asks for one of the other forward
 // kernels or their waits.  Returns the entries of a row's front kept in LDS, -1: not used.
-int trial_near(const adseq_config* c) {
+int trial_near(const adseq_config* c, int* H_out = nullptr, int* P_out = nullptr) {
   int on = env_pow2("ADSEQ_RING_TRIALS", 2, 0, 2);
   if (on == 2)
     for (const char* k : {"ADSEQ_RING_RESIDENT", "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_FORWARD_CHIP", "ADSEQ_RING_CHAIN", "ADSEQ_RING_OVERLAP",
@@ -745,7 +746,20 @@ int trial_near(const adseq_config* c) {
   if (env_pow2("ADSEQ_RING_OVERLAP", 0, 0, 1)) on = 0;   // (a window that is being expanded ahead is not rebuilt)
   // 8-byte words of LDS: spikes and cells of R steps (and a spare one: the cells begin on a whole word, N may be odd)
   const long long R = c->d_max_steps + 1, words = R * ((c->n_neurons + 63) / 64) + (R * c->n_neurons + 1) / 2;
-  if (!on || c->n_neurons > kTrialNeurons || c->batch > kTrialMost || c->n_synapses > kTrialSynapses || words + c->n_neurons > kTrialLdsWords) return -1;
+  if (!on || c->n_neurons > kTrialNeurons || c->batch > kTrialMost || c->n_synapses > kTrialSynapses) return -1;
+  if (H_out) { *H_out = (int)R; *P_out = 1; }
+  if (words + c->n_neurons > kTrialLdsWords) {
+    // H rows, a spike's row in P pieces; where they begin, and P N places in the step's list
+    const long long N = c->n_neurons;
+    for (int P = 2; P <= kTrialPieces; ++P) {
+      const long long left = kTrialLdsWords * 8 - R * ((N + 63) / 64) * 8 - (P + 1) * N * 4 - (long long)P * N * 2 - 16, H = left / (4 * N);
+      if (H < 2 || H * P < c->d_max_steps || (P - 1) * ((N + 63) / 64) > N) continue;
+      if (env_pow2("ADSEQ_RING_TRIALS", 2, 0, 2) != 1 && !trial_pieces_pay(P, (double)c->n_synapses / N, c->batch)) return -1;
+      if (H_out) { *H_out = (int)H; *P_out = P; }
+      return 0;
+    }
+    return -1;
+  }
   const long long near = (kTrialLdsWords - words) / c->n_neurons;
   return (int)(near < kSynNear ? near : kSynNear);
 }
@@ -1542,13 +1556,13 @@ void ring_run_trials(adseq* h, hipStream_t st, long long step0, long long n_step
     if (d.record && n >= d.max_steps) h->tape_ok = false;
     if (record) fill_u32(st, d.tape_bits + (size_t)n * d.words, 0u, (size_t)cnt * d.words * 2);
     const bool long_rows = trial_long(d.N, d.S);
-    const int threads = trial_threads(d.N, long_rows);
+    const int threads = h->trial_P > 1 ? 1024 : trial_threads(d.N, long_rows);
     const dim3 grid((unsigned)d.B), block((unsigned)threads);
     const long long boundary = (n + cnt - 1) & ~(long long)(d.W - 1), fold = boundary >= n && boundary > 0 ? boundary : h->fold_upto;
     const int windows = (int)(((n + cnt - 1) >> d.wshift) - (n >> d.wshift)) + 1;
     const unsigned arrivals = (unsigned)(cnt - windows) * (unsigned)waiting;
-    hipLaunchKernelGGL((long_rows ? k_trial_run<1024, true> : (threads <= 256 ? k_trial_run<256, false> : k_trial_run<1024, false>)), grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0,
-                       h->fold_upto, fold, arrivals, arrive_bar, d);
+    const auto kernel = h->trial_P > 1 ? k_trial_run<1024, false, true> : long_rows ? k_trial_run<1024, true, false> : (threads <= 256 ? k_trial_run<256, false, false> : k_trial_run<1024, false, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, n, cnt, h->trial_near, record ? 1 : 0, h->fold_upto, fold, arrivals, arrive_bar, d, h->trial_H, h->trial_P);
     (arrive_bar ? h->bar_base : h->rev_base) += arrivals;
     h->fold_upto = fold;
     h->enq_calls += cnt;
@@ -2007,7 +2021,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.syn_cells = (int*)(ws + L.syn_cells); d.syn_mask = (unsigned long long*)(ws + L.syn_mask);
   d.syn_flagged = (unsigned long long*)(ws + L.syn_flagged);
   d.syn_mw = L.syn_mw; d.syn_R2 = L.syn_R2;
-  if (d.kind == ADSEQ_RING) h->trial_near = trial_near(cfg);
+  if (d.kind == ADSEQ_RING) h->trial_near = trial_near(cfg, &h->trial_H, &h->trial_P);
 #if defined(ADSEQ_PHASE_CLOCK) || defined(ADSEQ_ABLATE)
   d.dbg = getenv("ADSEQ_DBG") ? atoi(getenv("ADSEQ_DBG")) : 0;
 #endif

@@ -31,10 +31,24 @@ constexpr long long kTrialSynapses = 262144;     // synapses of a trial at most:
 constexpr long long kTrialSteps = 64;            // steps of a call at least: a launch takes in the fronts and rebuilds the cells (100 neurons, in
                                                  // calls of 64 steps 1.7 / 0.63 us per step)
 
+// Where the R rows do not fit, H rows are held and a spike's row is taken in up to kTrialPieces pieces of H offsets: the piece with the offsets
+// (q H, (q + 1) H] is added q H steps after the spike, when the rows it adds to are those of the next H steps.  The spikes of those steps
+// back are in the spike words, so that a step just lists them beside its own.  (With windows of eight rows, see above, the pieces were seven.)
+// us per forward step by launches per window / so, 0.2, 2, 10, 30 and 50 % of the neurons firing:
+//   1,000 x 100, d_max 50 (P = 2), 16 trials 2.40 3.15 8.3 21 34 / 1.24 2.38 6.3 15.5 24.5, one 2.74 3.76 7.0 15.6 23.7 / 1.23 2.34 6.3 15.5 24.4
+//   1,024 x 50, 45 (2), 16 trials 2.39 2.73 5.9 14.0 21.6 / 1.17 2.24 5.7 13.8 22.0, one 2.48 3.28 5.6 12.1 18.2 / 1.16 2.20 5.6 13.7 22.0
+//   1,000 x 262, 50 (2), 64 trials 3.8 9.6 52 167 282 / 1.39 2.95 9.1 24 39, 4 2.39 3.77 9.1 21.8 34.5 / 1.39 2.95 9.1 24.1 39.1
+//   700 x 300, 120 (3), 16 trials 2.39 4.1 8.6 16.3 24.6 / 1.38 2.95 8.9 22.9 37.0;  1,000 x 20, 100 (4), 16 trials 2.05 2.32 4.2 9.2 14.0 / 1.35 3.62 9.9 24.6 39.2
+// (16 x 1,000 x 100 at 0.2 spikes per step and trial: 2.06 / 0.83.)  A piece is a trip to the L2 whatever it holds, and one compute unit has
+// only so many under way: two pieces of 24 entries and more, and long rows or single trials only where that was no slower with a
+// third of the neurons firing in every step (trial_pieces_pay).
+inline bool trial_pieces_pay(int P, double row, int batch) { return P == 2 && row >= 48.0 && (batch >= 32 || (row <= 128.0 && (batch >= 16 || row >= 90.0))); }
+constexpr int kTrialPieces = 4;
+
 template <int kMost>
 struct TrialLds {
   alignas(16) unsigned long long words[kTrialLdsWords];   // spikes [R][wpb]; fronts [near][N]; cells [R][N] by step mod R
-  unsigned short spk[kMost];                            // the step's spikes
+  unsigned short spk[kMost];                            // the step's spikes; PIECES: see there
   int row[kMost + 1];                                   // LONG: where the rows begin
   int n_spk[2];                                         // spikes of the step, by step parity
 };
@@ -46,19 +60,26 @@ struct TrialLds {
 // counted later.  Both n0 - fold_lo and n0 + nsteps - fold_hi are at most W < R.
 // arrivals: what the barriers of these steps would have added to the arrival counter that the host counts along with (arrive_bar: that
 // of the kernels over one XCD).
-template <int kMost, bool LONG>
+// PIECES: H rows of cells, P pieces of a row (else H = R, P = 1, near > 0); in LDS behind the cells where the pieces of every row begin, and
+// the step's list: neuron | piece << 10, P N entries.
+template <int kMost, bool LONG, bool PIECES>
 __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, int near, int record, long long fold_lo, long long fold_hi,
-                                                     unsigned arrivals, int arrive_bar, Dev d) {
+                                                     unsigned arrivals, int arrive_bar, Dev d, int H_, int P) {
   __shared__ TrialLds<kMost> L;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int threads = (int)blockDim.x, waves = threads >> 6;
   const int N = d.N, wpb = (N + 63) >> 6, R = d.R;
   const int base = (int)blockIdx.x * N, g = base + tid;
   const bool act = tid < N;
+  const int H = PIECES ? H_ : R;
   const bool syn = d.alpha_s > 0.0f, dexp = d.alpha_r > 0.0f;
   const unsigned long long G64 = 0x9E3779B97F4A7C15ull;
   uint2* const fronts = reinterpret_cast<uint2*>(L.words + (size_t)R * wpb);
   int* const cells = reinterpret_cast<int*>(L.words + (size_t)R * wpb + (size_t)near * N);
+  int* const cut = cells + (size_t)H * N;                                                     // PIECES: [P + 1][N]
+  unsigned short* const spk = PIECES ? reinterpret_cast<unsigned short*>(cut + (size_t)(P + 1) * N) : &L.spk[0];
+  // offsets up to this have been added for a spike `age` steps ago
+  auto added = [&](int age) { return ((age - 1) / H + 1) * H; };
   // The trial's spike word x = step slot * wpb + word: bits [sh, ..) of the circular words' at[0], the rest in at[1] (hi: there is a
   // rest).  Trials share words: of such a word only the trial's own bits are looked at or changed.
   struct Place { unsigned long long* at; int sh; unsigned long long own; bool hi; };
@@ -73,7 +94,12 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
   };
   auto held = [&](const Place& p) { return ((p.at[0] >> p.sh) | (p.hi ? p.at[1] << (64 - p.sh) : 0ull)) & p.own; };
   for (int x = tid; x < R * wpb; x += threads) L.words[x] = held(place(x));
-  for (int x = tid; x < R * N; x += threads) cells[x] = 0;
+  for (int x = tid; x < H * N; x += threads) cells[x] = 0;
+  if (PIECES)
+    for (int x = tid; x < (P + 1) * N; x += threads) {
+      const int q = x / N, i = x - q * N, D = q * H + 1;
+      cut[x] = (int)d.row_ptr[i] + (int)d.dstart[(size_t)i * (d.d_max + 2) + (D < d.d_max + 1 ? D : d.d_max + 1)];
+    }
   if (tid < 2) L.n_spk[tid] = 0;
   if (LONG) for (int x = tid; x <= N; x += threads) L.row[x] = (int)d.row_ptr[x];
   float V = 0.0f, J = 0.0f, Jf = 0.0f;
@@ -87,7 +113,9 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
     zg = mix64(d.seed + G64 * ((unsigned long long)g + 1ull));
     for (int q = 0; q < near && q < len; ++q) fronts[q * N + tid] = d.synf[r0 + q];
   }
-  int slot = (int)(n0 % R);   // row of spike words and cells that belongs to the step
+  int slot = (int)(n0 % R);   // row of spike words that belongs to the step
+  int piece_row = PIECES ? (int)(n0 % H) : 0;
+  int& crow = PIECES ? piece_row : slot;   // and of cells
   __syncthreads();
   // the thread's spikes of the last `steps` steps before the one of `slot`
   auto recent = [&](int steps) {
@@ -109,11 +137,13 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
       unsigned long long bits = L.words[s * wpb + w];
       for (; bits; bits &= bits - 1) {
         const int i = w * 64 + __ffsll((long long)bits) - 1;
-        const int r0 = (int)d.row_ptr[i], r1 = (int)d.row_ptr[i + 1];
+        const int r0 = (int)d.row_ptr[i];
+        const int last = PIECES && added(age) < d.d_max ? added(age) + 1 : d.d_max + 1;   // (first offset that has not been added)
+        const int r1 = r0 + (int)d.dstart[(size_t)i * (d.d_max + 2) + last];
         for (int q = r0 + (int)d.dstart[(size_t)i * (d.d_max + 2) + age] + lane; q < r1; q += 64) {
           const uint2 e = load_stream(&d.synf[q]);
-          int row = slot + (int)(e.x & d.dmask) - age;
-          if (row >= R) row -= R;
+          int row = crow + (int)(e.x & d.dmask) - age;
+          if (row >= H) row -= H;
           atomicAdd(&cells[row * N + (int)(e.x >> d.dbits)], (int)e.y);
         }
       }
@@ -126,9 +156,9 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
     float U = 0.0f;
     bool spike = false;
     if (act) {
-      int* const cell = &cells[slot * N + tid];
+      int* const cell = &cells[crow * N + tid];
       float I = (float)*cell * 0x1p-24f;
-      *cell = 0;   // (for step n + R)
+      *cell = 0;   // (for step n + H)
       if (syn) {   // the jumps go into the synaptic current state(s)
         const float jump = I;
         I = __fmaf_rn(d.alpha_s, J, jump);
@@ -151,7 +181,7 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
       int at = 0;
       if (lane == 0) at = atomicAdd(&L.n_spk[par], __popcll(m));
       at = __builtin_amdgcn_readfirstlane(at);
-      if (spike) L.spk[at + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)tid;
+      if (spike) spk[at + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)tid;
       if (record && lane < 2) {
         // the tape's words count from the first trial's first neuron
         const int gw = base + wave * 64, sh = gw & 63;
@@ -159,18 +189,30 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
         if (part) atomicOr(&d.tape_bits[(size_t)n * d.words + (gw >> 6) + lane], part);
       }
     }
+    if (PIECES && tid < (P - 1) * wpb) {   // the spikes q H steps ago
+      const int q = 1 + tid / wpb, w = tid - (q - 1) * wpb;
+      if (q * H < d.d_max) {   // (never more than R - 1 steps back)
+        int s = slot - q * H;
+        if (s < 0) s += R;
+        unsigned long long b = L.words[s * wpb + w];
+        if (b) {
+          int at = atomicAdd(&L.n_spk[par], __popcll(b));
+          for (; b; b &= b - 1ull) spk[at++] = (unsigned short)((w * 64 + __ffsll((long long)b) - 1) | q << 10);
+        }
+      }
+    }
     __syncthreads();   // spikes known, cells of the step taken
     const int nspk = __builtin_amdgcn_readfirstlane(L.n_spk[par]);
     if (tid == 0) L.n_spk[par ^ 1] = 0;   // (the last step's has been read)
     auto add = [&](const uint2& e) {
-      int row = slot + (int)(e.x & d.dmask);
-      if (row >= R) row -= R;
+      int row = crow + (int)(e.x & d.dmask);
+      if (row >= H) row -= H;
       atomicAdd(&cells[row * N + (int)(e.x >> d.dbits)], (int)e.y);
     };
     if (LONG && wave < nspk) {   // uniform
       // the rows of every waves-th spike, 64 at most: lane j has the j-th one's neuron and row
       int own = 0, first = 0, length = 0;
-      if (wave + lane * waves < nspk) { own = L.spk[wave + lane * waves]; first = L.row[own]; length = L.row[own + 1] - first; }
+      if (wave + lane * waves < nspk) { own = spk[wave + lane * waves]; first = L.row[own]; length = L.row[own + 1] - first; }
       // What is behind the front, 256 entries at a time: a piece is requested before the one ahead of it is added.  (A request is four
       // loads whatever is left of the row, so that it can be counted what is waited for.)
       int x = wave, j = 0, r0 = lane_get(first, 0), len = lane_get(length, 0), q0 = near;
@@ -215,9 +257,42 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
         __builtin_amdgcn_s_waitcnt(0x0F70);   // (vmcnt(0): else it is waited for, and the tape's store with it, before every use of the registers)
       }
     }
-    if (!LONG)
+    if constexpr (PIECES) {
+      // four pieces of a wavefront under way together (eight: 0.83 -> 0.98 us per step of 16 x 1,000 at 0.2 spikes)
+      for (int x0 = wave; x0 < nspk; x0 += 4 * waves) {   // uniform
+        int p0[4], p1[4], back[4]; uint2 e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int x = x0 + u * waves;
+          p0[u] = 0; p1[u] = 0; back[u] = 0; e[u] = make_uint2(0u, 0u);
+          if (x < nspk) {
+            const int v = __builtin_amdgcn_readfirstlane((int)spk[x]), i = v & 1023, q = v >> 10;
+            p0[u] = __builtin_amdgcn_readfirstlane(cut[q * N + i]); p1[u] = __builtin_amdgcn_readfirstlane(cut[(q + 1) * N + i]); back[u] = q * H;
+            const __amdgpu_buffer_rsrc_t piece = res_rows(d.synf + p0[u], (p1[u] - p0[u] < 64 ? p1[u] - p0[u] : 64) * 8);
+            const unsigned long long r = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(piece, lane * 8, 0, 0));
+            e[u] = make_uint2((unsigned)r, (unsigned)(r >> 32));
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          auto put = [&](const uint2& x) {
+            int row = crow + (int)(x.x & d.dmask) - back[u];
+            if (row >= H) row -= H;
+            atomicAdd(&cells[row * N + (int)(x.x >> d.dbits)], (int)x.y);
+          };
+          if (p0[u] + lane < p1[u]) put(e[u]);
+          for (int p = p0[u] + 64 + lane; p < p1[u]; p += 256) {
+            uint2 t[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { t[c] = make_uint2(0u, 0u); if (p + 64 * c < p1[u]) t[c] = d.synf[p + 64 * c]; }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) if (p + 64 * c < p1[u]) put(t[c]);
+          }
+        }
+      }
+    } else if constexpr (!LONG)
       for (int x = wave; x < nspk; x += waves) {
-        const int i = L.spk[x];   // (the same in every lane)
+        const int i = spk[x];   // (the same in every lane)
         const int r0 = (int)d.row_ptr[i], len = (int)d.row_ptr[i + 1] - r0;
         if (lane < near && lane < len) add(fronts[lane * N + i]);
         for (int q0 = near + lane; q0 < len; q0 += 256) {   // what is behind the front: four loads under way
@@ -230,6 +305,7 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
       }
     if (record && act) __builtin_nontemporal_store(U, &d.tapeU[(size_t)n * d.BN + g]);
     if (++slot == R) slot = 0;
+    if (PIECES && ++piece_row == H) piece_row = 0;
   }
   __syncthreads();
   // ---- what outlives the launch.  Spike words: the bits that have changed
@@ -246,10 +322,31 @@ __global__ __launch_bounds__(kMost) void k_trial_run(long long n0, int nsteps, i
   int* const first = n0 > 0 ? win_of(d, n0 - 1) : win;
   for (int x = tid; x < d.W * N; x += threads) {
     const int r = x / N, i = x - r * N;
-    int s = slot + r - phi;
-    if (s >= R) s -= R;
-    if (phi) win[(size_t)r * d.BN + base + i] = r >= phi ? cells[s * N + i] : 0;
+    int s = crow + r - phi;
+    if (s >= H) s -= H;
+    if (phi) win[(size_t)r * d.BN + base + i] = r >= phi && r - phi < H ? cells[s * N + i] : 0;
     if (first != win || !phi) first[(size_t)r * d.BN + base + i] = 0;
+  }
+  if (PIECES && phi) {
+    // what of the held spikes' rows has not been added yet and arrives in this window
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();   // (the cells are in memory)
+    for (int x = wave; x < d.d_max * wpb; x += waves) {
+      const int age = 1 + x / wpb, w = x - (age - 1) * wpb, lo = added(age) + 1;   // offsets lo .. hi - 1
+      int hi = age + d.W - phi;
+      if (hi > d.d_max + 1) hi = d.d_max + 1;
+      int s = slot - age;
+      if (s < 0) s += R;
+      if (lo >= hi) continue;   // uniform
+      for (unsigned long long b = L.words[s * wpb + w]; b; b &= b - 1ull) {
+        const int i = w * 64 + __ffsll((long long)b) - 1, r0 = (int)d.row_ptr[i];
+        const unsigned* const ds = d.dstart + (size_t)i * (d.d_max + 2);
+        for (int p = r0 + (int)ds[lo] + lane; p < r0 + (int)ds[hi]; p += 64) {
+          const uint2 e = load_stream(&d.synf[p]);
+          atomicAdd(&win[(size_t)(phi + (int)(e.x & d.dmask) - age) * d.BN + base + (int)(e.x >> d.dbits)], (int)e.y);
+        }
+      }
+    }
   }
   if (blockIdx.x == 0 && tid == 0 && arrivals) atomicAdd(arrive_bar ? &d.ctr->bar[0] : &d.ctr->rev_arrivals[0][0], arrivals);
   // spikes and the events they emit, into the counters that the window's expansion keeps

@@ -1,0 +1,50 @@
+"""Small ring networks whose delay line does not fit LDS: a run in one launch with a spike's row in two to four pieces (k_trial_run with
+PIECES) against the oracle: trace, counters, gradients; runs cut anywhere -- in and between windows, within the delays of held spikes --,
+with single steps and a current from outside in between, so that the window and the spike words that a launch leaves are read by the other
+kernels and the other way round; delays of exactly one and two pieces, rows of more than 64 and 256 entries per piece, shared spike words."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2512_05906_amd import adseq, synth
+from tests.helpers import grad_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,b,fan,d_max,T,rate,tau_syn,tau_rise,continuous", [
+    (1000, 2, 60, 50, 400, 60.0, 0.0, 0.0, False), (1024, 1, 30, 45, 420, 2500.0, 0.0, 0.0, False), (1021, 3, 40, 62, 330, 200.0, 5.0, 0.0, True),
+    (600, 2, 50, 200, 500, 80.0, 5.0, 1.0, False), (700, 1, 1100, 60, 300, 30.0, 0.0, 0.0, False), (900, 2, 80, 100, 380, 100.0, 0.0, 0.0, False)])
+def test_trial_pieces(n, b, fan, d_max, T, rate, tau_syn, tau_rise, continuous, monkeypatch):
+    monkeypatch.setenv("ADSEQ_RING_TRIALS", "1")
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=0.6 / fan, w_std=0.6 / fan, continuous=continuous)
+    wl.tau_syn_ms, wl.tau_rise_ms = tau_syn, tau_rise
+    ext = np.zeros((T, b, n), np.float32)
+    ext[150:153] = (np.random.default_rng(1).random((3, b, n)) < 0.1) * 1.2
+    ref = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=b, i_ext=ext, n_threads=8)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T)
+    cur = torch.from_numpy(ext).to(sim.dev)
+    for first in ((150,), (64, 86), (67, 1, 82)):     # then three single steps with the current, then two launches
+        sim.reset()
+        s = 0
+        for p in first:
+            sim.step(s) if p == 1 else sim.run(s, p)
+            s += p
+        for s in range(150, 153):
+            sim.step(s, cur[s])
+        sim.run(153, 75)
+        sim.run(228, T - 228)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+        c, rc = sim.counters(), ref.counters()
+        for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+            assert c[key] == rc[key], key
+    if tau_rise == 0.0:
+        dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+        gw, gd = ref.backward(dc, None)
+        g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+        sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+        for got, want in ((g_w, gw), (g_d, gd)):   # (bound of the absolute part: see test_gpu_trial_reverse.py)
+            grad_close(got.cpu().numpy(), want, atol=1e-6 + 5e-7 * float(np.abs(want).max(initial=0.0)))
+    sim.close()
