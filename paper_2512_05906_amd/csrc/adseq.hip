@@ -1357,7 +1357,7 @@ void clear_spike_rows(adseq* h, hipStream_t st, long long n, int count) {
 // events, into the device counters.
 // Expansion of the events of the spikes of steps [n_lo, n_hi) that arrive in window [k0, k0 + W) on `st`.
 // clear: spike words of that many steps from k0 on to zero along the way (see k_win_acc).
-void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, long long n_hi, long long count_from, int clear = 0) {
+void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, long long n_hi, long long count_from, int clear = 0, const OpenPop* pop = nullptr) {
   const Dev& d = h->dev;
   // staging mode: 0 none (atomics), 1 one store per event, 2 ordered by part in LDS first
   static const int sort_stage = env_pow2("ADSEQ_RING_SORTSTAGE", 1, 0, 1);
@@ -1365,8 +1365,9 @@ void launch_expansion(adseq* h, hipStream_t st, long long k0, long long n_lo, lo
   // (the window words of all the steps that the window's events may come from are there)
   const long long oldest = k0 - (long long)h->pull.Q * d.W > 0 ? k0 - (long long)h->pull.Q * d.W : 0;
   const int pull = h->pull.parts > 0 && n_hi == k0 && h->hist_upto == k0 && h->hist_from <= oldest && count_from >= k0 - d.W ? 1 : 0;
-  hipLaunchKernelGGL((pull ? k_win_bin<true> : k_win_bin<false>), dim3((unsigned)d.NB), dim3(kRingThreads), 0, st, d, k0, n_lo, n_hi, 0, d.NB,
-                     stage, count_from, h->res_P > 0 ? 1 : 0, h->pull);
+  const OpenPop none = {nullptr, 0, 0, 0};
+  hipLaunchKernelGGL((pop ? k_win_bin<false, true> : pull ? k_win_bin<true, false> : k_win_bin<false, false>), dim3((unsigned)d.NB), dim3(kRingThreads), 0, st, d, k0, n_lo, n_hi, 0, d.NB,
+                     stage, count_from, h->res_P > 0 ? 1 : 0, h->pull, pop ? *pop : none);
   if (d.cap > 0) {
     const int parts = d.P < kMaxParts ? d.P : kMaxParts;
     hipLaunchKernelGGL(k_win_acc, dim3((unsigned)parts), dim3(kRingThreads), 0, st, d, k0, 0, clear, pull, h->pull_at);
@@ -1381,7 +1382,7 @@ void join_ahead(adseq* h, hipStream_t st) {
 }
 
 // clear: see launch_expansion.  Returns whether there was a window to open.
-bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0) {
+bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0, const OpenPop* pop = nullptr) {
   const Dev& d = h->dev;
   if ((k0 & (long long)(d.W - 1)) != 0 || k0 <= 0) return false;
   close_group(h, st, 1);
@@ -1404,7 +1405,7 @@ bool ring_open_window(adseq* h, hipStream_t st, long long k0, int clear = 0) {
     else join_ahead(h, st);
     h->ahead_for = -1;
   }
-  launch_expansion(h, st, k0, n_lo, k0, h->fold_upto, clear);
+  launch_expansion(h, st, k0, n_lo, k0, h->fold_upto, clear, pop);
   h->fold_upto = k0;
   if (ahead && h->aux) {
     // the next window's events from the spikes before this boundary: on the other stream, beside the steps of this window
@@ -2330,6 +2331,13 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
     hipStream_t st = (hipStream_t)stream;
     if (n_steps > 0 && step0 != h->next_step)
       return fail(h, ADSEQ_E_ORDER, "adseq_run_open: got step %lld, expected %lld", (long long)step0, h->next_step);
+    // (a window's steps are popped along with the next window's expansion, if there is one -- and it does not clear the rows behind itself)
+    OpenPop popped = {nullptr, 0, 0, 0};
+    auto pop_now = [&]() {
+      if (popped.cnt > 0)
+        hipLaunchKernelGGL(k_open_pop, dim3((unsigned)d.nblk, (unsigned)popped.cnt), dim3(kBlock), 0, st, d, popped.n0, popped.out, popped.stride);
+      popped.cnt = 0;
+    };
     for (int64_t k = 0; k < n_steps;) {
       const long long step = step0 + k;
       const long long in_win = (long long)d.W - (step & (long long)(d.W - 1));
@@ -2338,16 +2346,18 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
       // window's expansion where there is one); a shorter one, or output rows that overlap (the later step's values
       // stay), by a launch per step.
       if (cnt >= 3 && (I_stride == 0 || I_stride >= d.BN)) {
-        if (!ring_open_window(h, st, step, cnt)) clear_spike_rows(h, st, step, cnt);
+        const bool along = popped.cnt > 0 && h->res_P == 0 && h->dev.cap > 0 && step > 0 && (step & (long long)(d.W - 1)) == 0;
+        if (!along) pop_now();
+        if (!ring_open_window(h, st, step, cnt, along ? &popped : nullptr)) clear_spike_rows(h, st, step, cnt);
         OpenOffsets o;
         for (int j = 0; j < cnt; ++j) o.off[j] = spike_offsets[k + j];
         const int gx = d.nblk < 16 ? 4 : (d.nblk < 256 ? d.nblk / 4 : 64);
         hipLaunchKernelGGL(k_open_mark, dim3((unsigned)gx, (unsigned)cnt), dim3(kBlock), 0, st, d, step, spike_ids, n_spikes + k, o);
-        hipLaunchKernelGGL(k_open_pop, dim3((unsigned)d.nblk, (unsigned)cnt), dim3(kBlock), 0, st, d, step,
-                           I_out + k * I_stride, (long long)I_stride);
+        popped = {I_out + k * I_stride, (long long)I_stride, step, cnt};
         h->bits_clear_for = -1;
       } else {
         cnt = 1;
+        pop_now();
         ring_open_window(h, st, step);
         if (h->bits_clear_for != step) clear_spike_rows(h, st, step, 1);
         hipLaunchKernelGGL(k_open_step_win, dim3((unsigned)d.nblk), dim3(kBlock), 0, st, d, step,
@@ -2359,6 +2369,7 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
       h->enq_calls += cnt;
       h->tape_ok = false;
     }
+    pop_now();
     HIP_TRY(h, hipGetLastError());
     return ADSEQ_OK;
   }

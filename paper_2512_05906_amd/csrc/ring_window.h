@@ -1012,13 +1012,33 @@ __device__ __forceinline__ void role_dense(const Dev& d, int* tile, int* s_piece
 
 #include "ring_pull.h"
 
+// What an open-loop window delivers (k_open_pop), handed to the first pass of the next window's expansion: steps n0 .. n0 + cnt - 1.
+struct OpenPop { float* out; long long stride, n0; int cnt; };
+__device__ __forceinline__ void role_pop(const Dev& d, const OpenPop& p, int vb, int nvb) {
+  const int first = (int)(p.n0 & (long long)(d.W - 1));
+  int* const rows = win_of(d, p.n0) + (size_t)first * d.BN;
+  long long got = 0;
+  // (cells of all rows dealt out over the blocks, 1,024 at a time)
+  const int chunks = (d.BN + kRingThreads - 1) / kRingThreads;
+  for (int x = vb; x < p.cnt * chunks; x += nvb) {
+    const int k = x / chunks, g = (x - k * chunks) * kRingThreads + (int)threadIdx.x;
+    if (g >= d.BN) continue;
+    int* const cell = &rows[(size_t)k * d.BN + g];
+    const int popped = *cell;
+    if (popped != 0) { *cell = 0; got += popped; }
+    if (p.stride != 0 || k + 1 == p.cnt) __builtin_nontemporal_store((float)popped * 0x1p-24f, &p.out[k * p.stride + g]);
+  }
+  if (d.count_pop) count_popped(d, got);
+}
+
 // The two passes of the expansion as kernels.
 // The same roles as launches of their own (window boundaries, catching up, open loop).
 // (PULL: the window may be pulled.  In one kernel for both, the other passes
 // took 0.3 us longer: 29 scalar registers spilled instead of 6.)
-template <bool PULL>
+// POP: open loop; the pass also pops the window before, whose rows it does not touch (a launch less: 10,000 x 1,000, 20 spikes per step, 2,000 steps 1,873 -> 1,808 us).
+template <bool PULL, bool POP>
 __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, long long n_lo, long long n_hi,
-                                                          int vb0, int nvb, int stage, long long count_from, int clear_other, Pull pull) {
+                                                          int vb0, int nvb, int stage, long long count_from, int clear_other, Pull pull, OpenPop pop) {
   // (the roles share the LDS: queues and ordering buffers of the staging, or a tile of a dense window)
   constexpr size_t kStageBytes = sizeof(ExpandLds) + sizeof(SortLds), kTileBytes = (size_t)kDenseCells * 4;
   __shared__ __align__(16) unsigned char lds[kStageBytes > kTileBytes ? kStageBytes : kTileBytes];
@@ -1034,6 +1054,7 @@ __global__ __launch_bounds__(kRingThreads) void k_win_bin(Dev d, long long k0, l
     if (d.dense_K != 0 && vb0 + (int)blockIdx.x == 0 && threadIdx.x == 0) d.ctr->pieces = (long long)L.qn * nvb;
   }
   XPH_SPAN(0, 1)
+  if (POP) role_pop(d, pop, vb0 + (int)blockIdx.x, nvb);
   // The other window buffer -- the one the steps before k0 have just used up -- is zeroed here, a
   // slice per block, for the expansion that fills it next: the resident step kernels do not clear
   // the cells they pop (their one XCD would spend a fifth of a step on those stores), and the
