@@ -160,7 +160,9 @@ typedef struct {
                                   in one step), 28 bytes of workspace each.  0 = default: 2 B S
                                   where that is at most 2^29 (15 GB): what the runs in one kernel
                                   need (adseq_run); without a tape up to 64 B S, halved until it is at
-                                  most 2^27, for the stretches of adseq_run_open; where 2 B S is
+                                  most 2^27, for the stretches of adseq_run_open (up to 512 B S, with
+                                  as many steps' buffers, while that is at most 2^24 and the
+                                  buffers, 136 B N bytes a step, 1 GB); where 2 B S is
                                   more than 2^29, 2^24.  A value below 2 B S saves the memory: runs
                                   and open-loop runs then take two launches per step.  RING: events
                                   the staging buffer of a window holds (the rest takes a slower

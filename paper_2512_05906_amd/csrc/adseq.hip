@@ -594,6 +594,7 @@ struct Layout {
   int near_ev_cap;
   int pull_parts, pull_pt, pull_lb, pull_hist_windows;   // RING: ring_pull.h (0: not used)
   int qsteps;           // FIFO / SORTED: contender buffers
+  int open_words;       // FIFO / SORTED: 64-step words of an open-loop stretch of k_queue_events (0: not used)
   int trial_words;      // FIFO / SORTED: spike words of a trial where k_queue_run gives every block a trial (0: it does not)
   int syn_mw, syn_R2;   // SYN_*: the workspace holds what k_syn_run needs (syn_R2 = 0: it does not)
   bool sorted_rev;      // bounded kinds: the workspace holds what the ring's reverse kernels need
@@ -1056,7 +1057,8 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->full_bits = take(ptq && L->qsteps >= 2 ? 2 * (size_t)L->words * 8 : 0);
   L->cont = take(ptq ? (size_t)L->qsteps * kCont * BN * 16 : 0);
   L->c_head = take(ptq ? (size_t)L->qsteps * BN * 4 : 0);
-  L->open_steps = take(ptq && L->qsteps > 2 ? (size_t)((L->qsteps + 63) / 64) * BN * 8 : 0);
+  L->open_words = ptq && runs && L->qsteps > 2 ? (L->qsteps + 63) / 64 : 0;
+  L->open_steps = take((size_t)L->open_words * BN * 8);
   L->pool_p = take((size_t)L->pool_cap * 8);
   L->pool_t = take((size_t)L->pool_cap * 8);
   L->pool_next = take((size_t)L->pool_cap * 4);
@@ -1100,7 +1102,7 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
   L->tape_evb = take(bounded ? (size_t)L->spike_cap * 8 : 0);
   L->tape_row = take(!windows ? (size_t)L->spike_cap * sizeof(RowSpan) : 0);
   L->tape_adm = take((size_t)L->event_cap);
-  L->trial_words = ptq && sorted_rev && L->qsteps >= 2 && !small && queue_trials(c) ? (c->n_neurons + 63) / 64 : 0;
+  L->trial_words = ptq && sorted_rev && L->qsteps >= 2 && runs && queue_trials(c) ? (c->n_neurons + 63) / 64 : 0;
   {
     const size_t steps = T < (size_t)kTrialQueueSteps ? T : (size_t)kTrialQueueSteps;
     L->trial_bits = take(steps * c->batch * L->trial_words * 8);
@@ -1150,11 +1152,12 @@ bool layout_as(const adseq_config* c, Layout* L, bool sorted_rev, int qsteps, bo
 // (k_queue_steps).  small: neither -- an
 // adjoint delay line and two launches per reverse step, a stretch of one step, and windows of 16 steps -- for what only so
 // fits the static workspace.
-// runs: the workspace may hold what k_syn_run needs (the static handle's, which has no turn for such launches, does not).
+// runs: the workspace may hold what k_syn_run and k_queue_run with a block per trial need, and long open-loop stretches (the static handle's, which has no
+// turn for such launches and only so much room, does not).
 bool make_layout(const adseq_config* c, Layout* L, bool small = false, bool runs = true) {
   if (!c) return false;
   if (!small && env_pow2("ADSEQ_SORTED_REVERSE", 1, 0, 1) == 1 &&
-      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : kEventSteps, 1, kEventSteps), false, runs)) return true;
+      layout_as(c, L, true, env_pow2("ADSEQ_QUEUE_STEPS", c->record_tape ? 2 : (runs ? kEventSteps : kQueueSteps), 1, kEventSteps), false, runs)) return true;
   return layout_as(c, L, false, 1, small, false);
 }
 
@@ -1239,7 +1242,7 @@ void launch_reset(adseq* h, hipStream_t st, bool first = false) {
     // (the contender buffers of a stretch are empty whenever its two launches are over: only the first two can hold anything)
     const size_t bufs = first || d.qsteps < 2 ? d.qsteps : 2;
     fill_u32(st, d.c_head, 0xffffffffu, bufs * BN);
-    if (first && d.qsteps > 2) fill_u32(st, h->open_steps, 0u, (size_t)((d.qsteps + 63) / 64) * BN * 2);
+    if (first && h->open_steps) fill_u32(st, h->open_steps, 0u, (size_t)((d.qsteps + 63) / 64) * BN * 2);
     fill_u32(st, d.min_k, 0xffffffffu, BN);
     if (d.kind == ADSEQ_FIFO) fill_u32(st, d.vmask, 0u, (size_t)d.nw * BN);
     fill_u32(st, d.cnt, 0u, bufs * BN);
@@ -2076,7 +2079,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.spk_count = (int*)(ws + L.spk_count);
   d.sorted_rev = L.sorted_rev ? 1 : 0;
   d.qsteps = L.qsteps;
-  h->open_steps = (unsigned long long*)(ws + L.open_steps);
+  if (L.open_words > 0) h->open_steps = (unsigned long long*)(ws + L.open_steps);
   d.adm_base = (unsigned*)(ws + L.adm_base); d.adm_bits = (unsigned long long*)(ws + L.adm_bits);
   d.gwin = (float*)(ws + L.gwin); d.Gacc = (float*)(ws + L.Gacc); d.gsum = (float*)(ws + L.gsum);
   d.wspk = (unsigned long long*)(ws + L.wspk); d.near_nspk = (int*)(ws + L.near_cnt); d.near_nev = d.near_nspk + 64;
@@ -2386,7 +2389,7 @@ int adseq_run_open(adseq_t* h, int64_t step0, int64_t n_steps, const int32_t* sp
   const bool stretches = d.qsteps > 1 && (I_stride == 0 || I_stride >= d.BN) && step0 == h->next_step;
   for (int64_t k = 0; k < n_steps;) {
     const int64_t left = n_steps - 1 - k;
-    if (stretches && d.qsteps > 2 && left >= 3) {
+    if (stretches && h->open_steps && left >= 3) {
       // Rows of up to 128 entries, no more events in a step than targets: as many steps as there are buffers.  (Longer rows want a block
       // of threads each: 10,000 x 1,000, 10 spikes per step 5.8 us per step by those, 7.7 so; 500 x 300 in calls of 6 steps 8.4 / 8.9.  Two
       // events per target and step: 5,000 x 30, SORTED[32] 13.9 / 17.4; 2,000 x 100, SORTED[32], five events 46 / 50.)
