@@ -2315,7 +2315,7 @@ int adseq_enqueue(adseq_t* h, int64_t step, const int32_t* spike_ids, const int3
   const int parity = (int)(h->enq_calls & 1);
   if (h->dev.kind == ADSEQ_RING)
     hipLaunchKernelGGL(k_enqueue_win, dim3(kFanoutBlocks), dim3(kBlock), 0, (hipStream_t)stream, h->dev,
-                       (long long)step, spike_ids, n_spikes);
+                       (long long)step, spike_ids, n_spikes, h->pull.parts > 0 ? pull_words(h->dev, h->pull, step >> h->dev.wshift) : nullptr);
   else
     launch_fanout(h, (hipStream_t)stream, step, spike_ids, n_spikes, parity, 0);
   h->enq_calls += 1;

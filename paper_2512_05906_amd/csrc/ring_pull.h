@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kBlock) void k_pull_fill(Dev d, Pull L, unsigned* _
   }
 }
 
-__device__ __forceinline__ unsigned* pull_words(const Dev& d, const Pull& L, long long window) { return L.hist + (size_t)(window & L.hmask) * d.BN; }
+__host__ __device__ __forceinline__ unsigned* pull_words(const Dev& d, const Pull& L, long long window) { return L.hist + (size_t)(window & L.hmask) * d.BN; }
 
 // Virtual block x of nvb: (trial, part, share of the offsets) in turn.  lds: a pair of window words per source, a tile [W][pull_pt].
 // Spikes of steps from count_from on are counted: count_from >= k0 - W.

@@ -346,9 +346,19 @@ __device__ __forceinline__ void open_enqueue(const Dev& d, long long n, const in
       near_scatter(d, win, phi, d.row_ptr[i], d.nearcnt[(size_t)near_h * d.N + i], b * d.N);
   }
 }
+// hist: the window words of step n's window (ring_pull.h; null: there are none), which the spikes belong in too -- the run that ended
+// with step n may have left them complete.
 __global__ __launch_bounds__(kBlock) void k_enqueue_win(Dev d, long long n, const int* __restrict__ spk,
-                                                        const int* __restrict__ n_spk_ptr) {
-  open_enqueue(d, n, spk, *n_spk_ptr, (int)(blockIdx.x * kBlock + threadIdx.x) >> 6, (int)(gridDim.x * kBlock) >> 6);
+                                                        const int* __restrict__ n_spk_ptr, unsigned* __restrict__ hist) {
+  int nspk = *n_spk_ptr;
+  open_enqueue(d, n, spk, nspk, (int)(blockIdx.x * kBlock + threadIdx.x) >> 6, (int)(gridDim.x * kBlock) >> 6);
+  if (hist) {
+    nspk = nspk > d.BN ? d.BN : nspk;
+    for (int e = (int)(blockIdx.x * kBlock + threadIdx.x); e < nspk; e += (int)gridDim.x * kBlock) {
+      const int g = spk[e];
+      if ((unsigned)g < (unsigned)d.BN) atomicOr(&hist[g], 1u << (int)(n & (long long)(d.W - 1)));
+    }
+  }
 }
 
 // Open loop, pop and enqueue of one step in ONE launch (adseq_run_open knows both): block b pops

@@ -81,3 +81,45 @@ def test_from_quiet_to_crowded(monkeypatch):
         assert torch.equal(sim.tape()["U"].view(torch.int32), U.view(torch.int32))
         assert sim.counters() == ref.counters()
     sim.close(); ref.close()
+
+
+@pytest.mark.parametrize("n,b,fan,d_max,window", [(2000, 1, 200, 40, 16), (1501, 2, 90, 70, 32)])
+@pytest.mark.parametrize("stop", ["window", "inside"])
+@pytest.mark.parametrize("go_on", ["run", "deliver"])
+def test_spikes_listed_after_a_run(n, b, fan, d_max, window, stop, go_on, monkeypatch):
+    """Spikes listed on top of the run's last step, the last one of a window or one inside it, travel with the run's own: counted, and
+    delivered by the windows that follow, pulled or staged."""
+    T = 4 * window + (0 if stop == "window" else 5)
+    monkeypatch.setenv("ADSEQ_RING_FORWARD_CHIP", "1")
+    monkeypatch.setenv("ADSEQ_RING_WINDOW", str(window))
+    monkeypatch.setenv("ADSEQ_RING_BINBLOCKS", "32")
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=700.0, t=T, b=b, w_mean=1.2 / fan, w_std=1.0 / fan)
+    spiked = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=b, n_threads=8).spikes[T - 1].reshape(-1)
+    listed = np.flatnonzero(spiked == 0)[::3].astype(np.int32)     # (neurons that did not spike themselves)
+    got = []
+    for dense in ("0", "2"):
+        monkeypatch.setenv("ADSEQ_RING_DENSE", dense)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, step_event_capacity=4000000)
+        ids = torch.from_numpy(listed).to(sim.dev)
+        sim.run(0, T)
+        seen = [sim.counters()]
+        sim.enqueue(T - 1, ids, torch.tensor([len(listed)], dtype=torch.int32, device=sim.dev))
+        seen.append(sim.counters())
+        at, more = T, 0
+        spikes = torch.zeros((4, b * n), dtype=torch.uint8, device=sim.dev)
+        if go_on == "run":
+            for k in range(4):      # (two windows and a step, whose spikes are handed back)
+                sim.run(at, 2 * window)
+                sim.step(at + 2 * window, None, spikes[k])
+                at += 2 * window + 1
+            seen.append(sim.counters())
+        cur = torch.zeros((d_max + 1, b * n), device=sim.dev)
+        for j in range(d_max + 1):
+            sim.deliver(at + j, cur[j])
+        seen.append(sim.counters())
+        got.append((spikes.cpu().numpy(), cur.cpu().numpy().view(np.uint32), seen))
+        sim.close()
+    assert got[1][2][1]["enqueued"] > got[1][2][0]["enqueued"] and got[1][2][-1]["delivered"] == got[1][2][-1]["enqueued"]
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    assert got[0][2] == got[1][2]
