@@ -2140,12 +2140,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
                             "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_CHAIN", "ADSEQ_RING_LAZY_ROWS", "ADSEQ_RING_ASSUME_CUS"})
         if (getenv(k)) on = 0;
     h->rtrial_always = on == 1;
-    if (on && d.N <= kTrialNeurons && d.B <= kTrialMost)
-      for (int P = 1; P <= kRevTrialPieces && !h->rtrial_P; ++P) {
-        long long H = (kRevTrialLds - rev_trial_fixed(d.N, P)) / (4LL * d.N);
-        if (H > d.d_max) H = d.d_max;
-        if (H * P >= d.d_max && (P == 1 || H >= 16) && P * ((d.N + 63) / 64 + 1) <= kRevTrialWords) { h->rtrial_H = (int)H; h->rtrial_P = P; }
-      }
+    if (on) {
+      const RevTrialPlan tp = rev_trial_plan(d.N, d.B, d.S, d.d_max);
+      h->rtrial_H = tp.H; h->rtrial_P = tp.P;
+    }
   }
   if ((d.kind == ADSEQ_FIFO || d.kind == ADSEQ_SORTED) && d.qsteps >= 2 && (double)d.B * (double)d.S * 2.0 <= (double)d.pool_cap) {
     // (half of the overflow pool has room for every synapse of every trial)

@@ -19,21 +19,10 @@
 // Hence a line on the spikes of the run, which the host reads with the error word: a spike weighs a piece more or less, its entries and,
 // in the bounded kinds, their admission bits; up to 256 neurons in one piece, and single trials of the ring, where the other kernels
 // run on few blocks, it lies higher.
-inline double rev_trial_weight(long long S, int N, int P, bool adm) { return (1.5 * P - 0.5 + (double)S / N / 64.0) * (adm ? 2.0 : 1.0); }
-inline double rev_trial_load(int N, int B, int P, bool adm) { return 7.0 * (N <= 256 && P == 1 ? 8.0 : (B == 1 && !adm ? 4.0 : 1.0)); }
+#include "reverse_trial_plan.h"
 
-constexpr int kRevTrialLds = 160000;     // bytes
-constexpr int kRevTrialItems = 384;      // listed pieces of a step
-constexpr int kRevTrialWords = 128;      // spike words of a step at most: two per lane of the loading wavefront
-constexpr int kRevTrialPieces = 16;      // P at most
 // A listed piece: first entry, entries, neuron | piece << 16; ADM: first word of the row's admission bits.
 struct RevPiece { int p0, len, iq; unsigned adm; };
-
-// LDS of a workgroup: bytes besides the adjoint rows, and the rows H that fit.
-inline long long rev_trial_fixed(int N, int P) {
-  const long long words = (long long)P * ((N + 63) / 64 + 1);
-  return (2LL * kRevTrialItems * 16) + 2 * words * 8 + 2 * words * 4 + 4LL * (N + 1) + 4LL * N + 16LL * ((N + 63) & ~63) + 4LL * (P + 1) * N + 64;
-}
 
 // T steps of the tape; H adjoint rows in LDS, P = ceil(d_max / H) pieces of a row.  Workers: all wavefronts but the last two.
 template <bool HAS_DU, int SURR, int SYN, bool ADM>
