@@ -156,8 +156,9 @@ __global__ __launch_bounds__(640) void k_bwd_trial(long long T, int H, int P, co
             const int i = first[c] + __ffsll((long long)b) - 1 - base;
             b &= b - 1ull;
             const int c0 = cut[wq[c] * N + i], c1 = cut[(wq[c] + 1) * N + i];
-            // (the first piece is listed even if it is empty where there are others: it takes their sums in)
-            put = c1 > c0 || (P > 1 && wq[c] == 0);
+            // (the first piece is listed even if it is empty: it takes the other pieces' sums in, and a step with a spike has its second
+            // barrier, without which the tape row of the step before, which the spike-time rule reads, could still be on its way)
+            put = c1 > c0 || wq[c] == 0;
             p.p0 = row0[i] + c0; p.len = c1 - c0; p.iq = i | wq[c] << 16; p.adm = adm;
             if (ADM) adm += (unsigned)((row0[i + 1] - row0[i] + 63) >> 6);
           }
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(640) void k_bwd_trial(long long T, int H, int P, co
             p.len = __builtin_amdgcn_readfirstlane(cut[(q + 1) * N + i] - cut[q * N + i]);
             p.iq = i | q << 16; p.adm = adm;
             if (ADM) adm += (unsigned)((row0[i + 1] - row0[i] + 63) >> 6);
-            if (mine && (p.len > 0 || (P > 1 && q == 0))) {
+            if (mine && (p.len > 0 || q == 0)) {
               const float f = far_of(p, rslot);
               finish(p, rest(p, 0, 0.0f), f);
             }
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(640) void k_bwd_trial(long long T, int H, int P, co
         const float U = tape[par * NS + i], dU = HAS_DU ? tape_dU[par * NS + i] : 0.0f;
         float gu;
         if (U >= d.theta) {
-          const float G = P > 1 || cut[N + i] > 0 ? near[i] : 0.0f;
+          const float G = near[i];
           // (the membrane value the step started from: that of the step before; only the spike-time rule looks at it)
           const float before = SURR == ADSEQ_GRAD_SPIKE_TIME && m > 0 ? tape[(par ^ 1) * NS + i] : 0.0f;
           carry[c] = bwd_update_as<SURR>(d, m, U, before, true, 0.0f, dLc[c], G, dU, &gu);

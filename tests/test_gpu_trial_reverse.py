@@ -43,6 +43,32 @@ def test_trial_reverse(kind, cap, n, b, fan, d_max, T, rate, tau_syn, monkeypatc
         sim.close()
 
 
+@pytest.mark.parametrize("kind,cap", [(adseq.RING, 0), (adseq.FIFO, 3)])
+@pytest.mark.parametrize("n,d_max,rate", [(64, 20, 150.0), (300, 30, 200.0), (200, 15, 20000.0)])
+def test_steps_that_hand_out_nothing(kind, cap, n, d_max, rate, monkeypatch):
+    """Steps whose only spikes are of neurons without synapses, which the spike-time rule takes through the membrane value of the step before
+    nonetheless, between steps with rows."""
+    monkeypatch.setenv("ADSEQ_REVERSE_TRIALS", "1")
+    T, b = 150, 3
+    wl = synth.ragged_network(n, 12, d_max, seed=n, rate_hz=rate, t=T, b=b, w_mean=0.05, w_std=0.05)
+    keep = np.repeat(np.arange(n) % 4 == 0, np.diff(wl.row_ptr))
+    wl.row_ptr = np.concatenate([[0], np.cumsum(np.where(np.arange(n) % 4 == 0, np.diff(wl.row_ptr), 0))]).astype(np.int64)
+    wl.col, wl.weight, wl.delay_steps = wl.col[keep], wl.weight[keep], wl.delay_steps[keep]
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b, surrogate=adseq.GRAD_SPIKE_TIME)
+    per_step = ref.spikes.reshape(T, b, n).sum(axis=2)
+    with_rows = (ref.spikes.reshape(T, b, n) * (np.diff(wl.row_ptr) > 0)).sum(axis=2)
+    assert rate > 1000.0 or ((per_step > 0) & (with_rows == 0)).sum() > 5
+    dU = np.random.default_rng(n).normal(0, 1e-2, (T, b, n)).astype(np.float32)
+    gw, gd = ref.backward(None, dU)
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T, surrogate=adseq.GRAD_SPIKE_TIME, tape_spike_capacity=T * b * n + 64)
+    sim.run(0, T)
+    g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+    sim.backward(None, torch.from_numpy(dU).to(sim.dev), g_w, g_d)
+    for got, want in ((g_w, gw), (g_d, gd)):   # (bound of the absolute part: see above)
+        grad_close(got.cpu().numpy(), want, atol=1e-6 + 5e-7 * float(np.abs(want).max(initial=0.0)))
+    sim.close()
+
+
 def _kernels(call):
     from torch.profiler import ProfilerActivity, profile
     with profile(activities=[ProfilerActivity.CUDA]) as p:
