@@ -2525,24 +2525,28 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   // per step unless the whole window sits in the caches -- so by default only up to 1,024 state
   // cells; ADSEQ_RING_REVERSE_WINDOWS = 1: always, 0: never)
   const int rw = env_pow2("ADSEQ_RING_REVERSE_WINDOWS", 2, 0, 2);
-  // the error word and what follows it, up to the spikes on the tape (k_tape_total)
-  constexpr size_t kErrBytes = offsetof(Counters, in_flight) + sizeof(unsigned long long) - offsetof(Counters, err);
-  unsigned char head[kErrBytes] = {};
-  if (h->rtrial_P > 0 && !h->prof) hipLaunchKernelGGL(k_tape_total, dim3(1), dim3(1024), 0, st, d);
+  // the spikes on the tape (the ring's: k_tape_total, in in_flight[0]), the error word, and what lies between them
+  constexpr size_t kHead = offsetof(Counters, tape_spikes);
+  unsigned char head[offsetof(Counters, in_flight) + sizeof(unsigned long long) - kHead] = {};
+  if (d.kind == ADSEQ_RING && h->rtrial_P > 0 && !h->rtrial_always && !h->prof) {
+    const unsigned blocks = tape_total_blocks(d.BN);
+    if (blocks > 1) fill_u32(st, d.ctr->in_flight, 0u, 2);
+    hipLaunchKernelGGL(k_tape_total, dim3(blocks), dim3(1024), 0, st, d);
+  }
   const bool by_windows = d.kind == ADSEQ_RING && d.near_ev_cap > 0 && T > 0 && (rw == 1 || (rw == 2 && d.BN <= 1024));
   if (by_windows) {
     near_counts.resize(2 * (size_t)T);
     hipLaunchKernelGGL(k_bwd_near_counts, dim3((unsigned)(T < 4096 ? T : 4096)), dim3(kBlock), 0, st, d, T, d.near_counts);
     HIP_TRY(h, hipMemcpyAsync(near_counts.data(), d.near_counts, sizeof(int) * 2 * (size_t)T, hipMemcpyDeviceToHost, st));
   }
-  HIP_TRY(h, hipMemcpyAsync(head, &d.ctr->err, sizeof(head), hipMemcpyDeviceToHost, st));
+  HIP_TRY(h, hipMemcpyAsync(head, reinterpret_cast<const char*>(d.ctr) + kHead, sizeof(head), hipMemcpyDeviceToHost, st));
   HIP_TRY(h, hipStreamSynchronize(st));
-  memcpy(&err, head, sizeof(err));
+  memcpy(&err, head + offsetof(Counters, err) - kHead, sizeof(err));
   const bool bounded = d.kind != ADSEQ_RING;
   bool trials = h->rtrial_P > 0 && !h->prof && T > 0;
   if (trials && !h->rtrial_always) {
     unsigned long long spikes = 0;
-    memcpy(&spikes, head + kErrBytes - sizeof(spikes), sizeof(spikes));
+    memcpy(&spikes, head + (d.kind == ADSEQ_RING ? offsetof(Counters, in_flight) - kHead : 0), sizeof(spikes));
     trials = (double)spikes * rev_trial_weight(d.S, d.N, h->rtrial_P, bounded) <= rev_trial_load(d.N, d.B, h->rtrial_P, bounded) * (double)T * (double)d.B;
   }
   if (err & ERR_BARRIER)

@@ -368,16 +368,27 @@ __global__ __launch_bounds__(640) void k_bwd_trial(long long T, int H, int P, co
   }
 }
 
-// Spikes on the tape, where the host reads them together with the error word (one block).
+// RING: spikes on the tape, where the host reads them together with the error word.  One block stores the sum, several (tape_total_blocks) add
+// to zero: a block's loop over the cells is a chain of trips to memory (512 x 1,000 cells, us per adseq_backward of 10 steps: by one
+// block of 4-byte loads 296, without the sum at all 159, so 162).
 __global__ __launch_bounds__(1024) void k_tape_total(Dev d) {
   __shared__ unsigned long long s_sum;
   if (threadIdx.x == 0) s_sum = 0ull;
   __syncthreads();
+  const int whole = d.BN >> 2;   // (the counts begin on 256 bytes)
   long long c = 0;
-  if (d.kind == ADSEQ_RING)
-    for (int g = threadIdx.x; g < d.BN; g += 1024) c += d.spk_count[g];
+  for (int x = (int)(blockIdx.x * 1024 + threadIdx.x); x < whole; x += (int)gridDim.x * 1024) {
+    const int4 v = reinterpret_cast<const int4*>(d.spk_count)[x];
+    c += (long long)v.x + v.y + v.z + v.w;
+  }
+  if (blockIdx.x == 0 && threadIdx.x < (d.BN & 3)) c += d.spk_count[4 * whole + (int)threadIdx.x];
   c = wave_total64(c);
   if ((threadIdx.x & 63) == 0 && c) atomicAdd(&s_sum, (unsigned long long)c);
   __syncthreads();
-  if (threadIdx.x == 0) d.ctr->in_flight[0] = d.kind == ADSEQ_RING ? s_sum : (unsigned long long)d.ctr->tape_spikes;
+  if (threadIdx.x == 0) {
+    if (gridDim.x == 1) d.ctr->in_flight[0] = s_sum;
+    else if (s_sum) atomicAdd(&d.ctr->in_flight[0], s_sum);
+  }
 }
+// A block up to 16,384 cells, four loads of a thread; beyond, one for every 8,192.
+inline unsigned tape_total_blocks(int BN) { return BN <= 16384 ? 1u : (unsigned)((BN + 8191) / 8192); }

@@ -88,3 +88,24 @@ def test_the_line_is_on_the_spikes(rate, trials):
     names = _kernels(lambda: sim.backward(torch.ones(8 * n, device=sim.dev), None, g_w, g_d))
     assert ("k_bwd_trial" in names) == trials and ("k_bwd_flow" in names) != trials
     sim.close()
+
+
+@pytest.mark.parametrize("b", [54, 109])
+@pytest.mark.parametrize("of_the_line,trials", [(0.93, True), (1.07, False)])
+def test_all_spikes_are_counted_for_the_line(b, of_the_line, trials):
+    """Spikes a little below and a little above the line (7 pieces of work per step and trial), summed by one block and by several, cells
+    that no 4 divides: a share of the cells left out or taken twice would turn the choice."""
+    n, T = 301, 40
+    wl = synth.ragged_network(n, 60, 50, seed=3, rate_hz=1.0, t=T, b=b, w_mean=1e-4, w_std=1e-5)
+    wl.ext_weight = 1.5                                    # (every event of the drive is a spike)
+    line = 7.0 / (1.0 + wl.n_synapses / n / 64.0)          # spikes per step and trial
+    wl.ext_rate_hz = of_the_line * line / n * 1e4
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T)
+    sim.run(0, T)
+    counts = torch.empty(b * n, dtype=torch.int32, device=sim.dev)
+    sim.spike_counts(counts)
+    assert abs(int(counts.sum()) / (T * b) / line - of_the_line) < 0.05
+    g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+    names = _kernels(lambda: sim.backward(torch.ones(b * n, device=sim.dev), None, g_w, g_d))
+    assert ("k_bwd_trial" in names) == trials and ("k_bwd_flow" in names) != trials
+    sim.close()
