@@ -2142,7 +2142,7 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     h->rtrial_always = on == 1;
     if (on) {
       const RevTrialPlan tp = rev_trial_plan(d.N, d.B, d.S, d.d_max);
-      h->rtrial_H = tp.H; h->rtrial_P = tp.P;
+      if (h->rtrial_always || rev_trial_load(d.S, d.N, d.B, tp.P, d.kind != ADSEQ_RING) > 0.0) { h->rtrial_H = tp.H; h->rtrial_P = tp.P; }
     }
   }
   if ((d.kind == ADSEQ_FIFO || d.kind == ADSEQ_SORTED) && d.qsteps >= 2 && (double)d.B * (double)d.S * 2.0 <= (double)d.pool_cap) {
@@ -2547,7 +2547,7 @@ int adseq_backward(adseq_t* h, const float* dL_dcount, const float* dL_dU, float
   if (trials && !h->rtrial_always) {
     unsigned long long spikes = 0;
     memcpy(&spikes, head + (d.kind == ADSEQ_RING ? offsetof(Counters, in_flight) - kHead : 0), sizeof(spikes));
-    trials = (double)spikes * rev_trial_weight(d.S, d.N, h->rtrial_P, bounded) <= rev_trial_load(d.N, d.B, h->rtrial_P, bounded) * (double)T * (double)d.B;
+    trials = (double)spikes * rev_trial_weight(d.S, d.N, h->rtrial_P, bounded) <= rev_trial_load(d.S, d.N, d.B, h->rtrial_P, bounded) * (double)T * (double)d.B;
   }
   if (err & ERR_BARRIER)
     return fail(h, ADSEQ_E_HIP, "adseq_backward: a wait inside a resident kernel ran out (the blocks of a launch were not running together); the run is void, reset and run again");

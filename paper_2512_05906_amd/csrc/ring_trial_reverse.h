@@ -17,8 +17,7 @@
 //   8 x 600 x 300, 250 (P = 3)        1.64 1.85 2.16 2.51 3.15 / 1.22 1.74 2.46 4.20 8.26
 //   1 x 1,000 x 100, 50               1.94 3.69 5.31 6.06 7.46 / 1.02 1.37 1.63 2.20 3.88     64 x 100 x 100, 50   1.93 2.47 3.21 5.00 11.8 / 0.88 1.53 2.13 3.10 5.72
 // Hence a line on the spikes of the run, which the host reads with the error word: a spike weighs a piece more or less, its entries and,
-// in the bounded kinds, their admission bits; up to 256 neurons in one piece, and single trials of the ring, where the other kernels
-// run on few blocks, it lies higher.
+// in the bounded kinds, their admission bits; where it lies, and why, is in reverse_trial_plan.h.
 #include "reverse_trial_plan.h"
 
 // A listed piece: first entry, entries, neuron | piece << 16; ADM: first word of the row's admission bits.
