@@ -419,6 +419,7 @@ __global__ __launch_bounds__(kBlock) void k_in_check(Dev d) {
 #include "ring_resident_forward.h"
 #include "ring_chain.h"
 #include "queue_resident.h"
+#include "queue_trial_plan.h"
 #include "synapse_resident.h"
 #include "ring_trial.h"
 #include "ring_trial_reverse.h"
@@ -715,18 +716,13 @@ ResidentPlan queue_plan(long long BN) {
   }
   return r;
 }
-// k_queue_run with a block per trial: up to 4,096 neurons, where there are so many trials, or neurons so few, that a trial's events are not
-// the sooner done by several compute units.  us per step by blocks over the whole chip / so, at 0.1 / 1 / 5 / 20 spikes per step and trial:
-//   FIFO[4]: 100 x 10, one trial 2.3 4.4 6.7 10.4 / 1.7 3.8 6.2 10.1; 300 x 100, 4 trials 3.3 5.9 8.4 23.6 / 2.5 4.9 8.3 21.2, one 2.7 4.7 7.1 19.4 / 2.6 4.7 7.5 20.6;
-//   500 x 50, 64 trials 4.9 6.7 8.2 12.8 / 2.4 4.6 6.7 9.9, 16 4.0 6.0 7.2 10.9 / 2.6 4.8 7.3 10.2; 1,000 x 100, 256 trials 7.1 10.6 16.1 - / 3.6 6.3 10.1 -, 64 5.1 7.3
-//   9.7 13.8 / 3.5 6.1 9.6 19.4; 4,096 x 256, 256 trials 12.1 20.5 39.6 - / 7.9 14.3 24.4 -; SORTED[64] 12.6 29.8 144 - / 7.6 19.0 89 -.
+// k_queue_run with a block per trial: where queue_trial_plan.h says so, and its 32-bit positions in the rows suffice.
 // ADSEQ_QUEUE_TRIALS: 0 never, 1 wherever it fits; unset: not where a knob asks for the other kernels or their waits.
 bool queue_trials(const adseq_config* c) {
   const int on = env_pow2("ADSEQ_QUEUE_TRIALS", 2, 0, 2);
   if (on == 0 || c->n_neurons > 8 * kResThreads || c->n_synapses > 0x7fffffffLL) return false;
   if (on == 1) return true;
-  const int least = c->n_neurons <= 128 ? 1 : (c->n_neurons <= 320 ? 4 : (c->n_neurons <= kResThreads ? 32 : 192));   // trials
-  if (c->batch < least) return false;
+  if (!queue_trials_pay(c->n_neurons, c->batch)) return false;
   for (const char* k : {"ADSEQ_QUEUE_RESIDENT", "ADSEQ_QUEUE_BLOCKS", "ADSEQ_RING_RESIDENT_SPINS", "ADSEQ_RING_ASSUME_CUS"}) if (getenv(k)) return false;
   return true;
 }

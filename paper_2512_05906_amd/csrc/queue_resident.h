@@ -233,7 +233,7 @@ __device__ __forceinline__ void admit_target(const Dev& d, QueueLds<NPT, LS, LC>
 // spike list is ordered by step over all trials, which nobody knows any more while the blocks run apart: a block claims places for its
 // events' flags as it comes to them (claims[max_steps] counts the launch's; tape_evb says where they are, in whatever order) and leaves its
 // spike words and where their events begin for k_trial_list.  The block has shares of its own of the overflow list.  RECORD only.
-// 256 x 4,096 neurons, sorted[128]: 11.2 -> 6.7 us per step; queue_trials (adseq.hip) has the sizes.
+// 256 x 4,096 neurons, sorted[128]: 11.2 -> 6.7 us per step; queue_trial_plan.h has the sizes.
 template <int KIND, bool RECORD, int NPT, bool LS, bool TRIAL, int LC>
 __global__ __launch_bounds__(kResLaunch) void k_queue_run(long long n0, int nsteps, unsigned bar_base, int P, int chunk, int stride,
                                                           unsigned long long* __restrict__ claims, QTrial tr, Dev d) {
