@@ -69,11 +69,14 @@ __device__ __forceinline__ void role_pull(const Dev& d, const Pull& L, unsigned 
   const int cells = W * L.pt;
   const long long w0 = k0 >> d.wshift;
   int* __restrict__ win = win_of(d, k0);
-  int seen = 0, looked = 0;   // spikes in the words that block 0 takes in
+  int seen = 0;   // spikes in the words taken in with a trial's first share, by its first part's block
+  bool counting = false;
   for (int x = vb; x < d.B * L.parts * L.K; x += nvb) {
     const int part = x % L.parts, rest = x / L.parts, share = rest % L.K, base = rest / L.K * N;
     const int q_lo = 1 + share * L.Q / L.K, q_hi = 1 + (share + 1) * L.Q / L.K;   // windows back from k0
     const unsigned* __restrict__ pos = L.pos + (size_t)part * nb;
+    const bool counted = part == 0 && share == 0;
+    counting |= counted;
     for (int c = threadIdx.x; c < cells; c += kRingThreads) tile[c] = 0;
     for (int q = q_lo; q < q_hi && w0 - q >= -1; ++q) {
       const unsigned* lo = w0 - q >= 0 ? pull_words(d, L, w0 - q) + base : nullptr;
@@ -83,9 +86,8 @@ __device__ __forceinline__ void role_pull(const Dev& d, const Pull& L, unsigned 
         const unsigned a = lo ? lo[i] : 0u;
         const unsigned long long b = q == q_lo ? (hi ? hi[i] : 0u) : pair[i] & wmask;
         pair[i] = (unsigned long long)a | b << W;
-        if (vb == 0 && x == 0) seen += __popc(a);
+        if (counted) seen += __popc(a);
       }
-      looked += 1;
       __syncthreads();
       const int d1 = q * W < d.d_max ? q * W : d.d_max, top = q * W;
       const unsigned e0 = pos[(q - 1) * W + 1], e1 = pos[d1 + 1];
@@ -111,14 +113,15 @@ __device__ __forceinline__ void role_pull(const Dev& d, const Pull& L, unsigned 
     }
     __syncthreads();
   }
-  if (vb == 0) {   // (the words of its first share stand for all)
+  // which way the next window goes (k_win_acc, which has left `pieces` zero): the windows of the first shares stand for all
+  if (counting) {   // uniform
     if (threadIdx.x == 0) *s_count = 0;
     __syncthreads();
     const long long mine = wave_total(seen);
     if ((threadIdx.x & 63) == 0) atomicAdd(s_count, (int)mine);
     __syncthreads();
     const int windows = L.Q / L.K > 0 ? L.Q / L.K : 1;
-    if (threadIdx.x == 0) d.ctr->pieces = (long long)*s_count * d.B * L.Q / windows;
+    if (threadIdx.x == 0 && *s_count) atomicAdd((unsigned long long*)&d.ctr->pieces, (unsigned long long)((long long)*s_count * L.Q / windows));
   }
   // spikes of the window just finished, their events and amplitudes
   long long cnt[3] = {0, 0, 0};

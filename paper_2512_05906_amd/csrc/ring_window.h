@@ -1099,8 +1099,11 @@ __global__ __launch_bounds__(kRingThreads) void k_win_acc(Dev d, long long k0, i
     else role_acc(d, tile, k0, p0 + (int)blockIdx.x);
   }
   // which way the next window goes
-  if (d.dense_K != 0 && blockIdx.x == 0 && threadIdx.x == 0)
-    d.ctr->dense[((k0 >> d.wshift) + 1) & 1] = d.dense_K > 0 && d.ctr->pieces > (long long)kSegQueue * d.NB ? 2u : (d.ctr->pieces > pull_at ? 1u : 0u);
+  if (d.dense_K != 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    const long long pieces = d.ctr->pieces;
+    d.ctr->dense[((k0 >> d.wshift) + 1) & 1] = d.dense_K > 0 && pieces > (long long)kSegQueue * d.NB ? 2u : (pieces > pull_at ? 1u : 0u);
+    d.ctr->pieces = 0;   // (role_pull adds to it)
+  }
   XPH_SPAN(1, 1)
 }
 

@@ -123,3 +123,45 @@ def test_spikes_listed_after_a_run(n, b, fan, d_max, window, stop, go_on, monkey
     np.testing.assert_array_equal(got[0][0], got[1][0])
     np.testing.assert_array_equal(got[0][1], got[1][1])
     assert got[0][2] == got[1][2]
+
+
+def _kernels(call):
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events()]
+
+
+def _pulled(names):
+    return sum("k_win_bin<true, false>" in x for x in names)
+
+
+@pytest.mark.parametrize("crowded", [0, 1])
+def test_one_trial_of_two_is_crowded(crowded, monkeypatch):
+    """Two trials, no drive, one of them set off from outside and running away: whichever it is, the windows are pulled from then on, one after the
+    other.  Results as by staged windows."""
+    n, fan, d_max, T = 2200, 1000, 60, 320
+    wl = synth.ragged_network(n, 4, d_max, seed=6, rate_hz=0.0, t=T, b=2, w_mean=0.0, w_std=0.0)
+    rng = np.random.default_rng(6)
+    wl.row_ptr = np.arange(n + 1, dtype=np.int64) * fan
+    wl.col = rng.integers(0, n, n * fan, dtype=np.int32)
+    wl.weight = rng.normal(4.0 / fan, 1.0 / fan, n * fan).astype(np.float32)
+    wl.delay_steps = rng.integers(1, d_max + 1, n * fan).astype(np.uint8)
+    got = []
+    for dense in ("0", "1"):
+        monkeypatch.setenv("ADSEQ_RING_DENSE", dense)
+        sim = adseq.Adseq(wl, adseq.RING, 0, batch=2, record_tape=True, max_steps=T)
+        current = torch.zeros((2, n), device=sim.dev)
+        current[crowded] = 2.0
+        sim.step(0, current)
+        sim.run(1, T - 1 - 32)
+        base = -sim.workspace.data_ptr() % 256             # Counters::dense, at byte 76 of the workspace
+        flags = sim.workspace[base + 76:base + 84].cpu().numpy().view(np.uint32).tolist()
+        names = _kernels(lambda: sim.run(T - 32, 32))
+        got.append((sim.tape()["U"].clone(), sim.counters()))
+        assert dense == "0" or (all(flags) and _pulled(names) == 1), (flags, names)
+        sim.close()
+    spikes = (got[0][0] >= wl.v_thresh).sum(dim=(0, 2))
+    assert int(spikes[crowded]) > 50 * T and int(spikes[1 - crowded]) == 0
+    assert torch.equal(got[0][0].view(torch.int32), got[1][0].view(torch.int32)) and got[0][1] == got[1][1]
