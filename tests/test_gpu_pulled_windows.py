@@ -165,3 +165,24 @@ def test_one_trial_of_two_is_crowded(crowded, monkeypatch):
     spikes = (got[0][0] >= wl.v_thresh).sum(dim=(0, 2))
     assert int(spikes[crowded]) > 50 * T and int(spikes[1 - crowded]) == 0
     assert torch.equal(got[0][0].view(torch.int32), got[1][0].view(torch.int32)) and got[0][1] == got[1][1]
+
+
+@pytest.mark.parametrize("n,b,fan,d_max,window", [(2000, 1, 200, 40, 16), (1501, 2, 90, 64, 32)])
+def test_which_windows_are_pulled(n, b, fan, d_max, window, monkeypatch):
+    """The kernels of a run: every window's expansion may pull where the window words of all the steps its events come from are there, from the
+    first window of a run on; after a run that ended inside a window, from the one on that looks no further back than the next boundary."""
+    monkeypatch.setenv("ADSEQ_RING_DENSE", "2")
+    monkeypatch.setenv("ADSEQ_RING_FORWARD_CHIP", "1")
+    monkeypatch.setenv("ADSEQ_RING_WINDOW", str(window))
+    windows, back, cut = 12, -(-d_max // window), 2 * window + 3
+    T = windows * window
+    wl = synth.ragged_network(n, fan, d_max, seed=n, rate_hz=700.0, t=T, b=b, w_mean=1.2 / fan, w_std=1.0 / fan)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, step_event_capacity=4000000)
+    names = _kernels(lambda: sim.run(0, T))
+    assert _pulled(names) == windows - 1 and not any("k_win_bin<false, false>" in x for x in names)
+    sim.reset()
+    names = _kernels(lambda: (sim.run(0, cut), sim.run(cut, T - cut)))
+    staged = [x for x in names if "k_win_bin<" in x]
+    # boundaries 1 and 2 pulled, 3 staged; the words begin again with window 3
+    assert ["k_win_bin<true, false>" in x for x in staged] == [k < 3 or k >= 3 + back for k in range(1, windows)]
+    sim.close()
