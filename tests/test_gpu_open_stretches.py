@@ -182,3 +182,27 @@ def test_stretches_of_short_rows(kind, cap, n, fan, b, d_max, events, steps, str
         for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
             assert c[key] == rc[key], key
     sim.close()
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 3), (adseq.SORTED, 6)])
+@pytest.mark.parametrize("n,fan,b,same", [(301, 40, 2, 200), (90, 3, 1, 90), (4000, 2, 1, 17)])
+def test_steps_that_share_one_list(kind, cap, n, fan, b, same, monkeypatch):
+    """Every step of a call has the same spikes, listed once: the positions of the lists do not say how many there are."""
+    T = 140
+    wl = synth.ragged_network(n, fan, 30, seed=n, rate_hz=0.0, t=T, b=b, w_mean=0.01, w_std=0.02)
+    lists = [np.random.default_rng(k).choice(b * n, same, replace=False).astype(np.int32) for k in range(5)]
+    sims = [adseq.Adseq(wl, kind, cap, batch=b) for _ in range(2)]
+    out = [torch.zeros((T, b * n), dtype=torch.float32, device=s.dev) for s in sims]
+    counts = torch.full((T,), same, dtype=torch.int32, device=sims[0].dev)
+    at = 0
+    for piece, ids in zip((100, 4, 5, 30, 1), lists):
+        ids = torch.from_numpy(ids).to(sims[0].dev)
+        sims[0].run_open(at, piece, ids, np.zeros(piece, np.int64), counts, out[0][at], b * n)
+        for k in range(piece):
+            sims[1].deliver(at + k, out[1][at + k])
+            sims[1].enqueue(at + k, ids, counts)
+        at += piece
+    assert at == T and torch.equal(out[0].view(torch.int32), out[1].view(torch.int32)) and bool((out[0] != 0).any())
+    assert sims[0].counters() == sims[1].counters()
+    for s in sims:
+        s.close()
