@@ -553,6 +553,7 @@ struct adseq {
   int fwd_P = 0, fwd_chunk = 0;                // RING: the same for the forward kernel over the whole chip (ring_resident_forward.h; 0: not used)
   int q_P = 0, q_chunk = 0;                    // FIFO / SORTED: the same for k_queue_run (0: two launches per step)
   QTrial q_trial = {nullptr, nullptr, 0};      // ... with a block per trial (words 0: not used)
+  int q_trial_least = 1;                       // ... launches of so many steps
   int syn_P = 0, syn_chunk = 0, syn_near = 0;  // SYN_*: the same for k_syn_run (0: three launches per step), row-front entries in LDS
   bool syn_ok = false;                         // every step since the reset went by k_syn_run, or none has been run
   bool syn_live = false;                       // the events in flight may be in the spike words (Counters::syn_live knows: a graph's replay changes it)
@@ -1661,7 +1662,7 @@ void queue_run_resident(adseq* h, hipStream_t st, long long step0, long long n_s
     const bool record = d.record && h->tape_ok && n < d.max_steps;
     if (record && n + cnt > d.max_steps) cnt = (int)(d.max_steps - n);
     if (d.record && n >= d.max_steps) h->tape_ok = false;
-    if (record && h->q_trial.words > 0) {
+    if (record && h->q_trial.words > 0 && cnt >= h->q_trial_least) {
       if (cnt > kTrialQueueSteps) cnt = kTrialQueueSteps;
       hipLaunchKernelGGL(queue_trial_kernel(d.kind, d.N, d.C, d.alpha_s > 0.0f), dim3((unsigned)d.B), dim3(kResLaunch), 0, st, n, cnt, 0u, d.B, d.N, 1, d.claims, h->q_trial, d);
       hipLaunchKernelGGL(k_trial_list, dim3((unsigned)cnt), dim3(kBlock), 0, st, d, n, h->q_trial);
@@ -2146,7 +2147,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     ResidentPlan qp = queue_plan((long long)d.BN);
     if (qp.P > 0 && resident_fits((const void*)queue_kernel(d.kind, true, qp.chunk, d.C)) && resident_fits((const void*)queue_kernel(d.kind, false, qp.chunk, d.C))) {
       h->q_P = qp.P; h->q_chunk = qp.chunk;
-      if (L.trial_words > 0) h->q_trial = {(unsigned long long*)(ws + L.trial_bits), (long long*)(ws + L.trial_evb), L.trial_words};
+      if (L.trial_words > 0) {
+        h->q_trial = {(unsigned long long*)(ws + L.trial_bits), (long long*)(ws + L.trial_evb), L.trial_words};
+        if (env_pow2("ADSEQ_QUEUE_TRIALS", 2, 0, 2) != 1) h->q_trial_least = queue_trial_steps(d.N);
+      }
     }
   }
   if (d.syn_R2 > 0) {

@@ -21,5 +21,9 @@ inline bool queue_trials_pay(int N, int B) {
   const int per = N <= 512 ? 512 : 256, rounds = (B + per - 1) / per;
   return 8LL * B >= 7LL * rounds * per && (N <= 512 ? rounds == 1 : N <= 2048 && rounds <= 3);
 }
+// Steps of a launch at least: a block takes the states of its whole trial in and out, and the spike list is a launch more.  us per step in calls of 4 / 8 / 16
+// steps (whose last one goes by itself), FIFO[8]: 512 x 100, 32 trials, 0.3 spikes 11.6 8.6 7.0 / 11.9 7.8 5.8; 1,000 x 100, 256 trials 15.9 12.3 10.5 / 17.6 11.6 8.1; 2,000 x 100, 192
+// trials 17.5 13.2 11.0 / 21.9 14.4 10.2, 5 spikes 27.7 22.0 19.1 / 33.1 23.2 17.9; 4,096 x 100, 192 trials, 5 spikes 37.9 29.9 25.9 / 49.6 34.7 26.7.
+inline int queue_trial_steps(int N) { return N <= 1024 ? 7 : 20; }
 
 #endif

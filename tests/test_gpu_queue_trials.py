@@ -68,3 +68,33 @@ def test_tape_ends_and_overflows(monkeypatch):
         assert got[0] == got[1]
         for key in ("enqueued", "dropped", "delivered"):
             assert got[1][key] == ref.counters()[key]
+
+
+@pytest.mark.parametrize("kind,cap", [(adseq.FIFO, 3), (adseq.SORTED, 5)])
+def test_short_calls_between_long_ones(kind, cap):
+    """Calls of a few steps go by blocks over the whole chip, longer ones by a block per trial: queues, tape and counters pass from one to the other."""
+    n, b, pieces = 90, 3, (40, 5, 12, 4, 4, 30, 1, 6, 8)
+    T = sum(pieces)
+    wl = synth.ragged_network(n, 25, 20, seed=9, rate_hz=300.0, t=T, b=b, w_mean=0.02, w_std=0.02)
+    ref = oracle.Run(wl, kind, cap, n_steps=T, batch=b)
+    sim = adseq.Adseq(wl, kind, cap, batch=b, record_tape=True, max_steps=T, tape_spike_capacity=T * b * n, tape_event_capacity=T * b * wl.n_synapses + 1)
+    from torch.profiler import ProfilerActivity, profile
+    ran, at = [], 0
+    for p in pieces:
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            sim.run(at, p)
+            torch.cuda.synchronize()
+        ran.append("k_trial_list" in " ".join(e.name for e in prof.events()))
+        at += p
+    assert ran == [p >= 8 for p in pieces]                 # (the last step of a call goes by itself)
+    assert np.array_equal(sim.tape()["U"].cpu().numpy().reshape(-1).view(np.uint32), ref.U.reshape(-1).view(np.uint32))
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    dc = np.random.default_rng(n).normal(0, 1e-3, (b, n)).astype(np.float32)
+    gw, gd = ref.backward(dc, None)
+    g_w, g_d = torch.empty(wl.n_synapses, device=sim.dev), torch.empty(wl.n_synapses, device=sim.dev)
+    sim.backward(torch.from_numpy(dc).to(sim.dev), None, g_w, g_d)
+    np.testing.assert_allclose(g_w.cpu().numpy(), gw, rtol=1e-5, atol=1e-6)
+    np.testing.assert_allclose(g_d.cpu().numpy(), gd, rtol=1e-5, atol=1e-6)
+    sim.close()
