@@ -560,6 +560,7 @@ struct adseq {
   bool syn_captured = false;                   // a call has been captured: replays may put steps of the queue arrays under the host's feet, so k_syn_run is not used any more
   unsigned long long syn_left_in = 0;          // the capture in which the queue arrays are in use from some point on
   int trial_H = 0, trial_P = 1;                // ... rows of cells, pieces of a row
+  long long trial_least = kTrialSteps;         // ... calls of so many steps
   int trial_near = -1;                         // RING: k_trial_run, row-front entries in LDS (-1: not used)
   int rtrial_H = 0, rtrial_P = 0;              // k_bwd_trial: adjoint rows in LDS, pieces of a row (0: not used)
   bool rtrial_always = false;                  // whatever spikes (ADSEQ_REVERSE_TRIALS = 1)
@@ -2022,7 +2023,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
   d.syn_cells = (int*)(ws + L.syn_cells); d.syn_mask = (unsigned long long*)(ws + L.syn_mask);
   d.syn_flagged = (unsigned long long*)(ws + L.syn_flagged);
   d.syn_mw = L.syn_mw; d.syn_R2 = L.syn_R2;
-  if (d.kind == ADSEQ_RING) h->trial_near = trial_near(cfg, &h->trial_H, &h->trial_P);
+  if (d.kind == ADSEQ_RING) {
+    h->trial_near = trial_near(cfg, &h->trial_H, &h->trial_P);
+    if (env_pow2("ADSEQ_RING_TRIALS", 2, 0, 2) != 1) h->trial_least = trial_steps_least(h->trial_P, d.B);
+  }
 #if defined(ADSEQ_PHASE_CLOCK) || defined(ADSEQ_ABLATE)
   d.dbg = getenv("ADSEQ_DBG") ? atoi(getenv("ADSEQ_DBG")) : 0;
 #endif
@@ -2466,7 +2470,7 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   if (step0 != h->next_step)
     return fail(h, ADSEQ_E_ORDER, "adseq_run: got step %lld, expected %lld", (long long)step0, h->next_step);
   // (not while kernels are timed class by class)
-  if (h->dev.kind == ADSEQ_RING && h->trial_near >= 0 && n_steps >= kTrialSteps && !h->prof) {
+  if (h->dev.kind == ADSEQ_RING && h->trial_near >= 0 && n_steps >= h->trial_least && !h->prof) {
     ring_run_trials(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
     WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);

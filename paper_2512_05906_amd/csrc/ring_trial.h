@@ -40,9 +40,16 @@ constexpr long long kTrialSteps = 64;            // steps of a call at least: a 
 //   1,000 x 262, 50 (2), 64 trials 3.8 9.6 52 167 282 / 1.39 2.95 9.1 24 39, 4 2.39 3.77 9.1 21.8 34.5 / 1.39 2.95 9.1 24.1 39.1
 //   700 x 300, 120 (3), 16 trials 2.39 4.1 8.6 16.3 24.6 / 1.38 2.95 8.9 22.9 37.0;  1,000 x 20, 100 (4), 16 trials 2.05 2.32 4.2 9.2 14.0 / 1.35 3.62 9.9 24.6 39.2
 // (16 x 1,000 x 100 at 0.2 spikes per step and trial: 2.06 / 0.83.)  A piece is a trip to the L2 whatever it holds, and one compute unit has
-// only so many under way: two pieces of 24 entries and more, and long rows or single trials only where that was no slower with a
-// third of the neurons firing in every step (trial_pieces_pay).
+// only so many under way: two pieces of 24 entries and more, and long rows or single trials only where that was no slower, or hardly,
+// with a third of the neurons firing in every step (trial_pieces_pay).  At 0.2, 2, 10, 30 and 60 % of them, other sizes: 500 x 100, 100 (2), one trial 1.7 3.1 5.6 11.7 20.4 / 1.0 2.1 4.4 9.8
+// 17.7, 16 1.8 2.5 5.9 13.9 25.4 / 1.0 2.1 4.5 9.8 17.8; 500 x 400, 100 (2), 32 trials 2.4 5.3 20.5 62.5 127 / 1.2 2.5 6.4 15.4 28.8; 250 x 1,000, 200 (2), 32 2.4 7.8 19.8 61 124 / 1.3 3.0 5.3
+// 12.8 23.8; 300 x 50, 200 (2), 32 1.9 2.5 4.2 9.7 17.7 / 1.0 1.9 2.7 5.2 8.8; 1,000 x 100, 50 (2), 256 3.2 7.7 84 267 542 / 1.2 2.1 7.8 19.6 36.5, 512 3.8 13.7 174 543 1,095 / 2.1 3.9 15.5 38.5 72.9.
 inline bool trial_pieces_pay(int P, double row, int batch) { return P == 2 && row >= 48.0 && (batch >= 32 || (row <= 128.0 && (batch >= 16 || row >= 90.0))); }
+// Fewer than 16 trials only in calls of so many steps: the other kernels have few blocks then, and taking in the state and adding what is under way is most of a
+// short call.  us per step by launches per window / so, 1 x 1,000 x 100 in calls of 64, 128, 256 steps: 5 spikes per step 3.1 3.0 3.0 / 2.1 1.8 1.7, 100 6.9 6.9 6.8 / 8.3 7.0 6.4, 400 19.2
+// 19.1 19.1 / 26.1 21.8 19.6 (in one call of 300: 300 16.0 / 17.0, 600 28.2 / 31.7); 16 trials in calls of 64: 100 8.2 / 8.5, 400 26.5 / 26.6.
+// (From 256 steps on would cost calls of 128 to 255 more at loads up to a twentieth of the neurons than it gives at a third.)
+inline long long trial_steps_least(int P, int batch) { return P > 1 && batch < 16 ? 128 : kTrialSteps; }
 constexpr int kTrialPieces = 4;
 
 template <int kMost>

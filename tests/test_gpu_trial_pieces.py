@@ -48,3 +48,27 @@ def test_trial_pieces(n, b, fan, d_max, T, rate, tau_syn, tau_rise, continuous, 
         for got, want in ((g_w, gw), (g_d, gd)):   # (bound of the absolute part: see test_gpu_trial_reverse.py)
             grad_close(got.cpu().numpy(), want, atol=1e-6 + 5e-7 * float(np.abs(want).max(initial=0.0)))
     sim.close()
+
+
+@pytest.mark.parametrize("b,least", [(1, 128), (16, 64)])
+def test_calls_that_are_too_short(b, least):
+    """At the default line calls below the least number of steps go by the other kernels, and each takes over from the other."""
+    n, d_max, pieces = 1000, 50, (least - 1, least, 3, least + 5)
+    T = sum(pieces)
+    wl = synth.ragged_network(n, 200, d_max, seed=b, rate_hz=40.0, t=T, b=b, w_mean=0.004, w_std=0.004)
+    ref = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=b, n_threads=8)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=b, record_tape=True, max_steps=T)
+    from torch.profiler import ProfilerActivity, profile
+    ran, at = [], 0
+    for p in pieces:
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            sim.run(at, p)
+            torch.cuda.synchronize()
+        ran.append("k_trial_run" in " ".join(e.name for e in prof.events()))
+        at += p
+    assert ran == [p >= least for p in pieces]
+    np.testing.assert_array_equal(sim.tape()["U"].cpu().numpy().view(np.uint32), ref.U.view(np.uint32))
+    c, rc = sim.counters(), ref.counters()
+    for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
+        assert c[key] == rc[key], key
+    sim.close()
