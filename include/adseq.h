@@ -179,7 +179,11 @@ size_t adseq_workspace_bytes(const adseq_config *cfg);
  * are those of Section 4.3), for the whole network at once.
  * Builds a handle: validates cfg (host), then on cfg->stream converts the synapses into the
  * packed internal form, validates delays and the CSR on the device, clears all state, and
- * synchronises that stream once.  *out is written only on success. */
+ * synchronises that stream once.  *out is written only on success.
+ * A ring of 2^21 synapses and more, and of up to 2^25 synapses x trials, also gets every target's incoming synapses
+ * listed, for windows in which much of the network spikes: 8 bytes of workspace a synapse, and a quarter of the
+ * time of the whole preparation (10,000 x 1,000: 5.1 ms, 1.1 of them), whether or not adseq_run, which alone
+ * reads the lists, is called. */
 int adseq_create(const adseq_config *cfg, adseq_t **out);
 
 /* For callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses
@@ -223,7 +227,8 @@ int adseq_enqueue(adseq_t *h, int64_t step, const int32_t *spike_ids, const int3
  * of the paper's Poisson benchmark (Section 5.1: externally generated spike trains through the
  * queues).  Same results as those calls, in fewer launches: the ring takes the steps of a window in two,
  * FIFO and SORTED up to 64 steps unless many events per step are to be expected (from the distances
- * of spike_offsets).  Stops at the first error. */
+ * of spike_offsets), and with rows of up to 128 entries and no more events in a step than targets as many
+ * steps as the handle has buffers for (at most 512: step_event_capacity).  Stops at the first error. */
 int adseq_run_open(adseq_t *h, int64_t step0, int64_t n_steps, const int32_t *spike_ids,
                    const int64_t *spike_offsets /*host*/, const int32_t *n_spikes, float *I_out,
                    int64_t I_stride, void *stream);
@@ -236,7 +241,8 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
 /* n_steps closed-loop steps starting at `step0` (same results as calling adseq_step in a loop with
  * i_ext = spikes_out = NULL).  ADSEQ_RING runs the steps between two window boundaries, and
  * ADSEQ_FIFO / ADSEQ_SORTED up to 1,024 steps (of at most 2^20 targets, where half the overflow list has
- * room for every synapse of every trial, and kernels are not being timed: adseq_profile), and the per-synapse
+ * room for every synapse of every trial, and kernels are not being timed: adseq_profile; with many trials, or few
+ * neurons, one block per trial, up to 256 steps, and a second launch that makes the spike list), and the per-synapse
  * kinds up to 128 steps (calls of three steps or more while every step since the reset has been recorded by such calls: one
  * shorter call or single step, and the steps to the next reset go by three launches each), in ONE kernel
  * whose blocks (at most one per compute unit) wait for one another at a barrier per step; such a
@@ -246,8 +252,10 @@ int adseq_step(adseq_t *h, int64_t step, const float *i_ext, uint8_t *spikes_out
  * the bounded kinds keep to launches whose blocks wait for nobody, one to three per step (the per-synapse kinds in
  * every later call of a handle of which a call has been captured, too); a captured ring's launches stay what they are, and
  * the program keeps the graph's replays apart from other such launches (same stream, or events of
- * its own).  A small ring network whose delay line fits a compute unit's LDS runs by one workgroup per
- * trial that waits for nobody (calls of 64 steps or more).  adseq_create
+ * its own).  A small ring network whose delay line, or with rows long enough half of it, fits a compute unit's
+ * LDS runs by one workgroup per trial that waits for nobody (calls of 64 steps or more; half a line and fewer than
+ * 16 trials: 128).  FIFO and SORTED with a block per trial wait for nobody either, but take their turn and
+ * keep out of captured calls like the others.  adseq_create
  * asks the runtime how many such blocks the device holds at once and, below 256, keeps to one
  * launch per step (same results).  Every wait is
  * bounded (tens of ms, with the bounded kinds a second and more): if one runs out, the kernels still run to their end, the run is void, and the error
@@ -276,7 +284,8 @@ int adseq_run(adseq_t *h, int64_t step0, int64_t n_steps, void *stream);
  * (for the adjoint cells they gather; every wait bounded, see adseq_run) -- with every queue kind, unless
  * the synapse is double-exponential, the state array has more than 2^20 cells (or more than 2^17 and a number
  * of them that no 4 divides), the handle is a static one of a bounded kind, or a very small ring
- * is swept window by window.  Should such a wait run out --
+ * is swept window by window.  Networks of up to 1,024 neurons with few spikes on the tape are swept by one
+ * workgroup per trial instead, which waits for nobody.  Should such a wait run out --
  * the blocks of a launch were not running together -- the kernels still run to their end, the gradients are
  * void, and the error word carries bit 32 afterwards: read it with adseq_counters once the stream is done
  * (adseq_drop_count and the next adseq_backward refuse the run with ADSEQ_E_HIP).  (A cell that is not

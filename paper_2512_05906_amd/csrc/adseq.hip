@@ -577,7 +577,7 @@ struct adseq {
   unsigned chain_turn = 0;       // chained launches so far: the parity picks the stream
   int chain_tpb = 256;           // threads per block of the chained launches (256 or 1024)
   bool range_warn = false;    // some target's incoming |amplitudes| add up to 128 or more (ERR_RANGE, reported with the counters)
-  unsigned long long* open_steps = nullptr;   // FIFO / SORTED, qsteps > 64: [qsteps / 64][BN] steps of a long open-loop stretch in which a target has contenders
+  unsigned long long* open_steps = nullptr;   // FIFO / SORTED, qsteps > 2: [(qsteps + 63) / 64][BN] steps of an open-loop stretch of k_queue_events in which a target has contenders
   Pull pull = {};             // RING: ring_pull.h
   long long pull_at = 0;      // RING: from how many spikes in a window's history on the next is pulled (ring_pull.h)
   long long hist_from = 0, hist_upto = 0;   // RING: steps whose window words (Pull::hist) are in place
@@ -2067,7 +2067,10 @@ int create_in(const adseq_config* cfg, const Layout& L, void* workspace, size_t 
     h->pull.K = best;
     if (d.dense_K == 0) d.dense_K = -1;
     // from half as many events in a window as the lists have entries on (10,000 x 1,000, 2,000 steps, ms with few / 166 / 341 / 491 / 741 Hz:
-    // by the spikes 5.6 / 9.03 / 14.6 / 24.3 / 40.8; pulled 8.3 / 8.5 / 8.9 / 9.0 / 9.4)
+    // by the spikes 5.6 / 9.03 / 14.6 / 24.3 / 40.8; pulled 8.3 / 8.5 / 8.9 / 9.0 / 9.4).  us per step by the spikes / with this line, at 1, 4, 15 and 60 % of the
+    // neurons firing, 640 steps: 10,000 x 1,000, d_max 200 3.7 8.2 14.0 34.8 / 3.7 4.6 5.2 8.9, d_max 50 6.6 14.9 35.7 109 / 6.7 11.9 13.6 19.8; 2,100 x 1,000, 100 4.3 8.5 24.8 72 / 4.4 6.7 7.7 11.4;
+    // several trials, whose near events go by the spikes: 4 of 4,000 x 1,000, 200 5.2 18.0 18.5 50 / 5.2 6.8 13.0 38, 50 7.2 17 59 188 / 7.3 13.3 26 74; 8 of 2,500 x 1,000, 100 5.5 20.0 50 160 / 5.5 9.2 17.1 46;
+    // 8 of 5,000 x 500, 250 4.2 7.7 18.2 55 / 4.3 6.3 13.5 39; 2 of 5,000 x 1,000, 100 4.9 10.4 24 74 / 4.9 7.3 15.2 47.  With hardly a spike 1 to 2 % slower: the larger k_fwd_chip.
     h->pull_at = (long long)d.BN * d.d_max / (2 * d.W);
     if (env_pow2("ADSEQ_RING_DENSE", 1, 0, 2) == 2) h->pull_at = -1;
   }
