@@ -2473,7 +2473,10 @@ int adseq_run(adseq_t* h, int64_t step0, int64_t n_steps, void* stream) {
   if (step0 != h->next_step)
     return fail(h, ADSEQ_E_ORDER, "adseq_run: got step %lld, expected %lld", (long long)step0, h->next_step);
   // (not while kernels are timed class by class)
-  if (h->dev.kind == ADSEQ_RING && h->trial_near >= 0 && n_steps >= h->trial_least && !h->prof) {
+  unsigned long long capture = 0;
+  // (under capture any call that k_trial_run can take: what it records waits for nobody, whatever else runs when it is replayed)
+  if (h->dev.kind == ADSEQ_RING && h->trial_near >= 0 && !h->prof &&
+      (n_steps >= h->trial_least || (n_steps >= kTrialSteps && capturing((hipStream_t)stream, &capture)))) {
     ring_run_trials(h, (hipStream_t)stream, step0, n_steps);
   } else if (h->dev.kind == ADSEQ_RING && h->fwd_P > 0) {
     WholeChipCall turn(h, (hipStream_t)stream, n_steps > 0);

@@ -72,3 +72,28 @@ def test_calls_that_are_too_short(b, least):
     for key in ("enqueued", "dropped", "delivered", "sum_enqueued", "sum_dropped", "sum_delivered"):
         assert c[key] == rc[key], key
     sim.close()
+
+
+def test_short_calls_under_capture():
+    """A captured call of 64 steps and more is recorded as the kernel whose workgroups wait for nobody; its replays leave what eager calls leave."""
+    n, T = 1000, 70
+    wl = synth.ragged_network(n, 200, 50, seed=2, rate_hz=60.0, t=T, b=1, w_mean=0.004, w_std=0.004)
+    ref = oracle.Run(wl, oracle.RING, 0, n_steps=T, batch=1, n_threads=8)
+    sim = adseq.Adseq(wl, adseq.RING, 0, batch=1, record_tape=True, max_steps=T)
+    sim.reset(); sim.run(0, T)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sim.reset()
+        sim.run(0, T)
+    U = sim.membrane_tape(T)
+    from torch.profiler import ProfilerActivity, profile
+    for _ in range(3):
+        U.zero_()
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            graph.replay()
+            torch.cuda.synchronize()
+        names = " ".join(e.name for e in prof.events())
+        assert "k_trial_run" in names and "k_fwd_chip" not in names and "k_run_xcd" not in names
+        np.testing.assert_array_equal(U.cpu().numpy().view(np.uint32), ref.U.view(np.uint32).reshape(U.shape))
+    sim.close()
